@@ -130,7 +130,7 @@ hipError_t alloc_iteration_buffers(pixelsne_ctx* c) {
         return e;
     c->side_blocks = (int64_t)c->prm.attract_blocks_per_cu * (cus > 0 ? cus : 1);
     c->help_blocks = (int64_t)c->prm.attract_help_blocks_per_cu * (cus > 0 ? cus : 1);
-    c->zpart_n = ceil_div(n, 256);
+    c->zpart_n = ceil_div(n, kWave);   // one per wavefront of points at most
     if ((e = dalloc(c, &c->zpart, sizeof(double) * c->zpart_n)) != hipSuccess) return e;
     c->mm_n = attract_block_count(n);
     if ((e = dalloc(c, &c->mm_part, sizeof(double) * 4 * c->mm_n)) != hipSuccess) return e;

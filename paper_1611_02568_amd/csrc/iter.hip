@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "ctx.h"
@@ -624,65 +625,63 @@ struct WaveStack {
 struct alignas(16) CellF4 { CellF c[4]; };
 struct alignas(32) Node4 { Node n[4]; };
 
-// F32T (FP32 path only): the opening test and the distances in FP32 on the
-// cells' FP32 copies (cells32), whose coordinates are scaled by cell_scale so
-// that the beta-weighted squared distance is dx*dx + dy*dy of the scaled
-// differences, every operation rounded separately; the force sums run on the
-// scaled axes and are scaled back at the end.  Otherwise in FP64 on nodes.
-template <typename T, bool COUNT, bool F32T, bool DEEP>
-__global__ __launch_bounds__(kBlock) void k_traverse(
-    const Node* __restrict__ nodes, const CellF* __restrict__ cells32,
-    const double2* __restrict__ nsum, const T* __restrict__ zs,
-    const uint32_t* __restrict__ perm, const uint32_t* __restrict__ leaf_of,
-    const DevScalars* __restrict__ sc, int64_t n, int L, double th2, int com_mode,
-    T* __restrict__ R, double* __restrict__ zpart, const uint32_t* __restrict__ orig,
-    double* __restrict__ Zi_out, uint32_t* __restrict__ visits_out,
-    uint32_t* __restrict__ used_out) {
-    using V = v2_t<T>;
+// One point per lane and its running sums.  F32T (FP32 path only): the opening
+// test and the distances in FP32 on the cells' FP32 copies (cells32), whose
+// coordinates are scaled by cell_scale so that the beta-weighted squared
+// distance is dx*dx + dy*dy of the scaled differences, every operation rounded
+// separately; the force sums run on the scaled axes and are scaled back at the
+// end.  Otherwise in FP64 on nodes.
+template <typename T, bool COUNT, bool F32T>
+struct Walker {
+    using Group = std::conditional_t<F32T, CellF4, Node4>;
     static_assert(!F32T || sizeof(T) == 4, "the FP32 opening test belongs to the FP32 path");
-    __shared__ double wz[4];
-    const int lane = lane_id(), w = threadIdx.x >> 6;
-    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool valid = s < n;
-    const V zp = valid ? reinterpret_cast<const V*>(zs)[s] : V{T(0), T(0)};
-    const double zx = (double)zp.x, zy = (double)zp.y;
-    const uint32_t own = valid ? leaf_of[s] : 0xFFFFFFFFu;
-    const double s0 = sc->s[0], s1 = sc->s[1];
-    const double b1 = mul_nc(s0, s0), b2 = mul_nc(s1, s1), bsum = add_nc(b1, b2);
-    // single-precision operands of the FP32 test: beta and theta^2 rounded,
-    // the point on the cells' scaled axes
-    const float b1f = (float)b1, b2f = (float)b2, th2f = (float)th2;
-    const float bsumf = b1f + b2f;
-    const float rs0 = cell_scale(s0), rs1 = cell_scale(s1);
-    const float xs = (float)zp.x * rs0, ys = (float)zp.y * rs1;
-
+    const Node* __restrict__ nodes;
+    const CellF* __restrict__ cells32;
+    const double2* __restrict__ nsum;
+    int L, com_mode;
+    double th2, zx, zy, b1, b2, bsum;
+    float th2f, bsumf, rs0, rs1, xs, ys;
+    uint32_t own;
     double zacc = 0.0;
     T rx = T(0), ry = T(0);
     uint32_t nvis = 0, nuse = 0;
 
-    // stack entries: first cell of a sibling group, (group size | level << 8),
-    // lane mask (lo, hi)
-    WaveStack<DEEP> st;
-    int sp = 0;
-    const uint64_t m0 = ballot64(valid);
-    if (m0) {
-        st.push(0, 0, 1, (int)(uint32_t)m0, (int)(uint32_t)(m0 >> 32));
-        sp = 1;
+    __device__ __forceinline__ Walker(const Node* nd, const CellF* c32, const double2* sums,
+                                      const DevScalars* __restrict__ sc, int levels, double theta2,
+                                      int mode, v2_t<T> zp, uint32_t leaf)
+        : nodes(nd), cells32(c32), nsum(sums), L(levels), com_mode(mode), th2(theta2), own(leaf) {
+        zx = (double)zp.x;
+        zy = (double)zp.y;
+        const double s0 = sc->s[0], s1 = sc->s[1];
+        b1 = mul_nc(s0, s0);
+        b2 = mul_nc(s1, s1);
+        bsum = add_nc(b1, b2);
+        // single-precision operands of the FP32 test: beta and theta^2 rounded,
+        // the point on the cells' scaled axes
+        th2f = (float)th2;
+        bsumf = (float)b1 + (float)b2;
+        rs0 = cell_scale(s0);
+        rs1 = cell_scale(s1);
+        xs = (float)zp.x * rs0;
+        ys = (float)zp.y * rs1;
     }
-    while (sp > 0) {
-        sp--;
-        uint32_t first, info;
-        uint64_t mask;
-        st.read(sp, first, info, mask);
-        const uint32_t nsib = info & 0xFFu;
-        const int level = (int)(info >> 8);
+
+    // a sibling group's four records (children are consecutive; the arrays
+    // have three records of slack at their end) in one batch of scalar loads
+    __device__ __forceinline__ Group load(uint32_t first) const {
+        if constexpr (F32T) return *reinterpret_cast<const CellF4*>(cells32 + first);
+        else return *reinterpret_cast<const Node4*>(nodes + first);
+    }
+
+    // The lanes of MASK meet the NSIB cells of a sibling group; cells that any
+    // of them opens go to push(child word, level, lanes).
+    template <typename Push>
+    __device__ __forceinline__ void meet(const Group& g4, uint32_t first, uint32_t nsib, int level,
+                                         uint64_t mask, Push&& push) {
         const bool act = __builtin_amdgcn_inverse_ballot_w64(mask);   // lane in mask
         if constexpr (F32T) {
             // (w w)(b1 + b2) with w = 2^(L - level): a power-of-two scaling, exact in FP32
             const float diag2f = ldexpf(bsumf, 2 * (L - level));
-            // the group's four records (children are consecutive; the array
-            // has three records of slack at its end) in one 64-byte scalar load
-            const CellF4 g4 = *reinterpret_cast<const CellF4*>(cells32 + first);
             const CellF* grp = g4.c;
             float zg = 0.f;
 #pragma unroll
@@ -741,95 +740,290 @@ __global__ __launch_bounds__(kBlock) void k_traverse(
                 const float f = mq * qq;
                 rx = fmaf(f, dx, rx);
                 ry = fmaf(f, dy, ry);
-                if (om) {
-                    st.push(sp, (int)(nd.child & 0x3FFFFFFFu),
-                            (int)(((nd.child >> 30) + 1u) | ((uint32_t)(level + 1) << 8)),
-                            (int)(uint32_t)om, (int)(uint32_t)(om >> 32));
-                    sp++;
-                }
+                if (om) push(nd.child, level + 1, om);
             }
             zacc += (double)zg;
         } else {
-        const double diag2 = ldexp(bsum, 2 * (L - level));
-        // the group's records (children are consecutive) in one batch of scalar loads
-        const Node4 g4 = *reinterpret_cast<const Node4*>(nodes + first);
-        const Node* grp = g4.n;
+            const double diag2 = ldexp(bsum, 2 * (L - level));
+            const Node* grp = g4.n;
 #pragma unroll
-        for (uint32_t q = 0; q < 4; q++) {
-            if (q >= nsib) break;
-            const uint32_t c = first + q;
-            const Node nd = grp[q];
-            uint64_t om = 0;   // lanes that open the cell
-            // Every lane evaluates the term; lanes that do not take the cell
-            // add it with mass 0, which leaves their sums bit for bit as they
-            // were and keeps the loop free of divergent branches.
-            double dx, dy, d2;
-            T m;
-            bool use;
-            uint64_t take = mask;   // lanes that take the cell
-            if (nd.child != 0u) {
-                // inner cell: the opening test and, for lanes that accept, the
-                // force term share one distance
-                dx = zx - nd.cx;
-                dy = zy - nd.cy;
-                d2 = dist2(b1, b2, dx, dy);
-                const uint64_t near = ballot64(!(diag2 < mul_nc(th2, d2)));
-                om = near & mask;   // every lane runs this loop
-                take = mask & ~near;
-                use = __builtin_amdgcn_inverse_ballot_w64(take);
-                m = (T)nd.count;
-            } else {
-                // leaf (one pixel): always used; at its own leaf a point counts
-                // the others only, at their centre of mass in mass mode
-                double cx = nd.cx, cy = nd.cy;
-                m = (T)nd.count;
-                use = act;
-                if (c == own) {
-                    const uint32_t others = nd.count - 1u;
-                    m = (T)others;
-                    if (others > 0u && com_mode != PSNE_COM_CELL_CENTER) {
-                        const double2 sm = nsum[c];
-                        cx = (sm.x - zx) / (double)others;
-                        cy = (sm.y - zy) / (double)others;
+            for (uint32_t q = 0; q < 4; q++) {
+                if (q >= nsib) break;
+                const uint32_t c = first + q;
+                const Node nd = grp[q];
+                uint64_t om = 0;   // lanes that open the cell
+                // Every lane evaluates the term; lanes that do not take the cell
+                // add it with mass 0, which leaves their sums bit for bit as they
+                // were and keeps the loop free of divergent branches.
+                double dx, dy, d2;
+                T m;
+                bool use;
+                uint64_t take = mask;   // lanes that take the cell
+                if (nd.child != 0u) {
+                    // inner cell: the opening test and, for lanes that accept, the
+                    // force term share one distance
+                    dx = zx - nd.cx;
+                    dy = zy - nd.cy;
+                    d2 = dist2(b1, b2, dx, dy);
+                    const uint64_t near = ballot64(!(diag2 < mul_nc(th2, d2)));
+                    om = near & mask;   // every lane runs this loop
+                    take = mask & ~near;
+                    use = __builtin_amdgcn_inverse_ballot_w64(take);
+                    m = (T)nd.count;
+                } else {
+                    // leaf (one pixel): always used; at its own leaf a point counts
+                    // the others only, at their centre of mass in mass mode
+                    double cx = nd.cx, cy = nd.cy;
+                    m = (T)nd.count;
+                    use = act;
+                    if (c == own) {
+                        const uint32_t others = nd.count - 1u;
+                        m = (T)others;
+                        if (others > 0u && com_mode != PSNE_COM_CELL_CENTER) {
+                            const double2 sm = nsum[c];
+                            cx = (sm.x - zx) / (double)others;
+                            cy = (sm.y - zy) / (double)others;
+                        }
+                        use = act && others > 0u;
                     }
-                    use = act && others > 0u;
+                    dx = zx - cx;
+                    dy = zy - cy;
+                    d2 = dist2(b1, b2, dx, dy);
                 }
-                dx = zx - cx;
-                dy = zy - cy;
-                d2 = dist2(b1, b2, dx, dy);
-            }
-            // skipped when every lane opens the cell (the FP64 reciprocal is
-            // a long sequence; the FP32 path gains nothing from the branch)
-            if (take) bh_term<T>(d2, dx, dy, use ? m : T(0), zacc, rx, ry);
-            if (COUNT) {
-                nuse += use ? 1u : 0u;
-                nvis += act ? 1u : 0u;
-            }
-            if (om) {
-                st.push(sp, (int)(nd.child & 0x3FFFFFFFu),
-                        (int)(((nd.child >> 30) + 1u) | ((uint32_t)(level + 1) << 8)),
-                        (int)(uint32_t)om, (int)(uint32_t)(om >> 32));
-                sp++;
+                // skipped when every lane opens the cell (the FP64 reciprocal is
+                // a long sequence; the FP32 path gains nothing from the branch)
+                if (take) bh_term<T>(d2, dx, dy, use ? m : T(0), zacc, rx, ry);
+                if (COUNT) {
+                    nuse += use ? 1u : 0u;
+                    nvis += act ? 1u : 0u;
+                }
+                if (om) push(nd.child, level + 1, om);
             }
         }
+    }
+
+    // the point's repulsion in pixel units (the F32T sums ran on the scaled axes)
+    __device__ __forceinline__ v2_t<T> force() const {
+        if constexpr (F32T) return v2_t<T>{rx / rs0, ry / rs1};
+        else return v2_t<T>{rx, ry};
+    }
+};
+
+// A child word of a cell (Node::child) as a sibling group: first cell and size.
+__device__ __forceinline__ uint32_t child_first(uint32_t c) { return c & 0x3FFFFFFFu; }
+__device__ __forceinline__ uint32_t child_num(uint32_t c) { return (c >> 30) + 1u; }
+
+template <typename T, bool COUNT, bool F32T, bool DEEP>
+__global__ __launch_bounds__(kBlock) void k_traverse(
+    const Node* __restrict__ nodes, const CellF* __restrict__ cells32,
+    const double2* __restrict__ nsum, const T* __restrict__ zs,
+    const uint32_t* __restrict__ perm, const uint32_t* __restrict__ leaf_of,
+    const DevScalars* __restrict__ sc, int64_t n, int L, double th2, int com_mode,
+    T* __restrict__ R, double* __restrict__ zpart, const uint32_t* __restrict__ orig,
+    double* __restrict__ Zi_out, uint32_t* __restrict__ visits_out,
+    uint32_t* __restrict__ used_out) {
+    using V = v2_t<T>;
+    __shared__ double wz[4];
+    const int lane = lane_id(), w = threadIdx.x >> 6;
+    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool valid = s < n;
+    const V zp = valid ? reinterpret_cast<const V*>(zs)[s] : V{T(0), T(0)};
+    Walker<T, COUNT, F32T> wk(nodes, cells32, nsum, sc, L, th2, com_mode, zp,
+                              valid ? leaf_of[s] : 0xFFFFFFFFu);
+
+    // stack entries: first cell of a sibling group, (group size | level << 8),
+    // lane mask (lo, hi)
+    WaveStack<DEEP> st;
+    int sp = 0;
+    const uint64_t m0 = ballot64(valid);
+    if (m0) {
+        st.push(0, 0, 1, (int)(uint32_t)m0, (int)(uint32_t)(m0 >> 32));
+        sp = 1;
+    }
+    auto push = [&](uint32_t child, int level, uint64_t om) {
+        st.push(sp, (int)child_first(child), (int)(child_num(child) | ((uint32_t)level << 8)),
+                (int)(uint32_t)om, (int)(uint32_t)(om >> 32));
+        sp++;
+    };
+    while (sp > 0) {
+        sp--;
+        uint32_t first, info;
+        uint64_t mask;
+        st.read(sp, first, info, mask);
+        wk.meet(wk.load(first), first, info & 0xFFu, (int)(info >> 8), mask, push);
+    }
+    if (valid) {
+        const uint32_t i = perm[s];
+        reinterpret_cast<V*>(R)[i] = wk.force();
+        if (Zi_out) Zi_out[orig[i]] = wk.zacc;
+        if (visits_out) visits_out[orig[i]] = wk.nvis;
+        if (used_out) used_out[orig[i]] = wk.nuse;
+    }
+    const double zw = wave_sum(wk.zacc);
+    if (lane == 0) wz[w] = zw;
+    __syncthreads();
+    if (threadIdx.x == 0) zpart[blockIdx.x] = ((wz[0] + wz[1]) + wz[2]) + wz[3];
+}
+
+// The same walk shared by the G wavefronts of a block, for point counts that
+// leave the chip short of wavefronts: one block per 64 points, and every
+// wavefront holds all 64 of them.  The union list is walked level by level:
+// the sibling groups of a level lie in LDS, wavefront w takes the groups w,
+// w + G, ..., and appends the groups that its lanes open to its own segment
+// of the next level, so which wavefront meets a cell, and the order of every
+// lane's partial sums, depend on the tree alone.  The partial sums of the
+// wavefronts are added in wavefront order at the end.  A segment that is full
+// sends its wavefront down depth first instead (theta near 0 opens whole
+// levels).  Known groups are also loaded one ahead of their use, where the
+// depth-first walk waits for each group's records.  Bound by that latency
+// below one wavefront per SIMD: the kernel takes 39 us where the walk alone
+// took 194 (2,000 points, FP32), 93 where it took 220 (70,000).
+constexpr int kShareCap = 96;      // groups per wavefront and level
+constexpr int kShareFlush = 8;     // groups gathered in registers before they go to LDS
+template <typename T> struct ShareSum { T x, y; double z; };
+
+template <typename T, bool COUNT, bool F32T, int G>
+__global__ __launch_bounds__(kWave * G) void k_traverse_shared(
+    const Node* __restrict__ nodes, const CellF* __restrict__ cells32,
+    const double2* __restrict__ nsum, const T* __restrict__ zs,
+    const uint32_t* __restrict__ perm, const uint32_t* __restrict__ leaf_of,
+    const DevScalars* __restrict__ sc, int64_t n, int L, double th2, int com_mode,
+    T* __restrict__ R, double* __restrict__ zpart, const uint32_t* __restrict__ orig,
+    double* __restrict__ Zi_out, uint32_t* __restrict__ visits_out,
+    uint32_t* __restrict__ used_out) {
+    using V = v2_t<T>;
+    // the groups of two levels; after the walk the partial sums take the room
+    struct Lists {
+        uint64_t mask[2][G][kShareCap];
+        uint32_t child[2][G][kShareCap];
+    };
+    union Room {
+        Lists l;
+        ShareSum<T> sum[G][kWave];
+        __device__ Room() {}
+    };
+    __shared__ Room room;
+    __shared__ uint32_t num[2][G];
+    __shared__ uint32_t counts[COUNT ? 2 : 1][COUNT ? G : 1][COUNT ? kWave : 1];
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t s = (int64_t)blockIdx.x * kWave + lane;
+    const bool valid = s < n;
+    const V zp = valid ? reinterpret_cast<const V*>(zs)[s] : V{T(0), T(0)};
+    Walker<T, COUNT, F32T> wk(nodes, cells32, nsum, sc, L, th2, com_mode, zp,
+                              valid ? leaf_of[s] : 0xFFFFFFFFu);
+    const uint64_t all = ballot64(valid);            // at least one point per block
+    if (threadIdx.x < G) num[0][threadIdx.x] = threadIdx.x == 0 ? 1u : 0u;
+    if (threadIdx.x == 0) {
+        room.l.mask[0][0][0] = all;
+        room.l.child[0][0][0] = 0u;                  // the root: cell 0, one cell
+    }
+    __syncthreads();
+    for (int level = 0;; level++) {
+        const int b = level & 1;
+        // the level's groups in wavefront order: segment starts
+        uint32_t start[G + 1];
+        start[0] = 0;
+        const uint32_t nl = lane < G ? num[b][lane < G ? lane : 0] : 0u;
+#pragma unroll
+        for (int q = 0; q < G; q++)
+            start[q + 1] = start[q] + (uint32_t)__builtin_amdgcn_readlane((int)nl, q);
+        const uint32_t total = start[G];
+        if (total == 0) break;
+        WaveStack<false> st;     // groups opened by this wavefront, not yet in LDS
+        int sp = 0;
+        uint32_t put = 0;        // groups of the next level in this wavefront's segment
+        auto push = [&](uint32_t child, int lv, uint64_t om) {
+            st.push(sp, (int)child, lv, (int)(uint32_t)om, (int)(uint32_t)(om >> 32));
+            sp++;
+        };
+        auto flush = [&]() {
+            if (put + (uint32_t)sp <= (uint32_t)kShareCap) {
+                if (lane < sp) {
+                    room.l.child[b ^ 1][w][put + lane] = (uint32_t)st.f0;
+                    room.l.mask[b ^ 1][w][put + lane] =
+                        ((uint64_t)(uint32_t)st.hi0 << 32) | (uint64_t)(uint32_t)st.lo0;
+                }
+                put += (uint32_t)sp;
+                sp = 0;
+                return;
+            }
+            // no room: the pending groups depth first (at most kShareFlush + 3
+            // of them, each level adds at most three: 11 + 3 * 17 entries)
+            while (sp > 0) {
+                sp--;
+                uint32_t child, lv;
+                uint64_t mask;
+                st.read(sp, child, lv, mask);
+                const uint32_t first = child_first(child);
+                wk.meet(wk.load(first), first, child_num(child), (int)lv, mask, push);
+            }
+        };
+        // this wavefront's groups, 64 at a time into lanes
+        for (uint32_t e0 = (uint32_t)w; e0 < total; e0 += (uint32_t)(G * kWave)) {
+            const uint32_t e = e0 + (uint32_t)(G * lane);
+            uint32_t child = 0;
+            uint64_t mask = 0;
+            if (e < total) {
+                int seg = 0;
+#pragma unroll
+                for (int q = 1; q < G; q++) seg += e >= start[q] ? 1 : 0;
+                uint32_t at = e;
+#pragma unroll
+                for (int q = 1; q < G; q++) at = seg == q ? e - start[q] : at;
+                child = room.l.child[b][seg][at];
+                mask = room.l.mask[b][seg][at];
+            }
+            const int mlo = (int)(uint32_t)mask, mhi = (int)(uint32_t)(mask >> 32);
+            const uint32_t left = (total - e0 + (uint32_t)G - 1) / (uint32_t)G;
+            const int m = left < (uint32_t)kWave ? (int)left : kWave;
+            uint32_t ch = (uint32_t)__builtin_amdgcn_readlane((int)child, 0);
+            typename Walker<T, COUNT, F32T>::Group cur = wk.load(child_first(ch));
+            for (int k = 0; k < m; k++) {
+                const int k1 = k + 1 < m ? k + 1 : k;
+                const uint32_t ch1 = (uint32_t)__builtin_amdgcn_readlane((int)child, k1);
+                const typename Walker<T, COUNT, F32T>::Group nxt = wk.load(child_first(ch1));
+                const uint64_t gm =
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(mhi, k) << 32) |
+                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane(mlo, k);
+                wk.meet(cur, child_first(ch), child_num(ch), level, gm, push);
+                if (sp >= kShareFlush) flush();
+                cur = nxt;
+                ch = ch1;
+            }
+        }
+        if (sp > 0) flush();
+        if (lane == 0) num[b ^ 1][w] = put;
+        __syncthreads();
+    }
+    __syncthreads();             // the lists are done with: the sums take their room
+    room.sum[w][lane] = ShareSum<T>{wk.rx, wk.ry, wk.zacc};
+    if constexpr (COUNT) {
+        counts[0][w][lane] = wk.nvis;
+        counts[1][w][lane] = wk.nuse;
+    }
+    __syncthreads();
+    if (w != 0) return;
+#pragma unroll
+    for (int q = 1; q < G; q++) {
+        const ShareSum<T> p = room.sum[q][lane];
+        wk.rx += p.x;
+        wk.ry += p.y;
+        wk.zacc += p.z;
+        if constexpr (COUNT) {
+            wk.nvis += counts[0][q][lane];
+            wk.nuse += counts[1][q][lane];
         }
     }
     if (valid) {
         const uint32_t i = perm[s];
-        if constexpr (F32T) {
-            // the FP32 sums ran on the scaled axes: back to pixel units
-            reinterpret_cast<V*>(R)[i] = V{rx / rs0, ry / rs1};
-        } else {
-            reinterpret_cast<V*>(R)[i] = V{rx, ry};
-        }
-        if (Zi_out) Zi_out[orig[i]] = zacc;
-        if (visits_out) visits_out[orig[i]] = nvis;
-        if (used_out) used_out[orig[i]] = nuse;
+        reinterpret_cast<V*>(R)[i] = wk.force();
+        if (Zi_out) Zi_out[orig[i]] = wk.zacc;
+        if (visits_out) visits_out[orig[i]] = wk.nvis;
+        if (used_out) used_out[orig[i]] = wk.nuse;
     }
-    const double zw = wave_sum(zacc);
-    if (lane == 0) wz[w] = zw;
-    __syncthreads();
-    if (threadIdx.x == 0) zpart[blockIdx.x] = ((wz[0] + wz[1]) + wz[2]) + wz[3];
+    const double zw = wave_sum(wk.zacc);
+    if (lane == 0) zpart[blockIdx.x] = zw;
 }
 
 __global__ __launch_bounds__(kBlock) void k_zsum(const double* __restrict__ zpart, int64_t m,
@@ -1033,7 +1227,13 @@ __global__ __launch_bounds__(kBlock) void k_attract(
     constexpr uint32_t kColMask = (1u << kColBits) - 1u;
     int64_t ch = blockIdx.x;
     if (kQueue) {
-        if (t == 0) s_next = atomicAdd(&sc->att_next, 1u);
+        // a block that finds the queue empty leaves without a ticket: the
+        // helper's 768 tickets on one address took 11 us
+        if (t == 0) {
+            const uint32_t taken =
+                __hip_atomic_load(&sc->att_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_next = (int64_t)taken < nch ? atomicAdd(&sc->att_next, 1u) : taken;
+        }
         __syncthreads();
         ch = s_next;
     }
@@ -1613,10 +1813,38 @@ hipError_t run_tree(pixelsne_ctx* c) {
     return hipGetLastError();
 }
 
+template <typename T, bool COUNT, bool F32T, int G>
+void launch_traverse_shared(pixelsne_ctx* c, double th2, uint32_t* visits, uint32_t* used,
+                            double* Zi) {
+    TreeBufs& tb = c->tb;
+    k_traverse_shared<T, COUNT, F32T, G>
+        <<<dim3((unsigned)ceil_div(c->n, kWave)), kWave * G, 0, c->stream>>>(
+            tb.nodes, tb.cells32, tb.nsum, (const T*)tb.zs, tb.idx[tb.sorted], tb.leaf_of, c->sc,
+            c->n, c->L, th2, c->prm.com_mode, (T*)c->R, c->zpart, c->orig, Zi, visits, used);
+}
+
+// Wavefronts that share the walk of 64 points (0: one wavefront walks alone).
+// Alone, 64 points take a serial walk of some 200 us whatever n is, and the
+// chip holds n / 64 of them: below about 6 wavefronts per SIMD it waits for
+// their loads.  Sharing costs a barrier and a list per level and a tail per
+// wavefront, which only free SIMDs pay for.  Measured, us per iteration, late
+// layout, FP32 alone / 4 / 8 / 16: n = 6,000: 363 / 220 / 200 / 193; 30,000:
+// 383 / 238 / 220 / 233; 50,000: 392 / 245 / 256 / 276; 200,000: 489 / 434 /
+// 470 / 608; 300,000: 553 / 533 / 573 / 809; 1,000,000: 1,208 / 1,374 / 1,619 /
+// 2,333; FP64 30,000: 489 / 282 / 238 / 254; 200,000: 642 / 543 / 579 / 743.
+// The data-driven tree's 33 levels do not fit the shared walk's stack.
+static int traverse_share(const pixelsne_ctx* c) {
+    if (c->prm.tree == PSNE_TREE_DATA) return 0;
+    return c->n <= 40000 ? 8 : c->n <= 400000 ? 4 : 0;
+}
+
 template <typename T, bool COUNT, bool F32T>
 void launch_traverse(pixelsne_ctx* c, double th2, uint32_t* visits, uint32_t* used, double* Zi) {
     TreeBufs& tb = c->tb;
-    if (c->prm.tree == PSNE_TREE_DATA)
+    const int share = traverse_share(c);
+    if (share == 8) launch_traverse_shared<T, COUNT, F32T, 8>(c, th2, visits, used, Zi);
+    else if (share == 4) launch_traverse_shared<T, COUNT, F32T, 4>(c, th2, visits, used, Zi);
+    else if (c->prm.tree == PSNE_TREE_DATA)
         k_traverse<T, COUNT, F32T, true><<<grid_for(c->n), kBlock, 0, c->stream>>>(
             tb.nodes, tb.cells32, tb.nsum, (const T*)tb.zs, tb.idx[tb.sorted], tb.leaf_of, c->sc,
             c->n, c->L, th2, c->prm.com_mode, (T*)c->R, c->zpart, c->orig, Zi, visits, used);
@@ -1645,7 +1873,8 @@ hipError_t run_traverse(pixelsne_ctx* c, uint32_t* visits, uint32_t* used, doubl
 }
 
 hipError_t run_zsum(pixelsne_ctx* c) {
-    k_zsum<<<1, kBlock, 0, c->stream>>>(c->zpart, ceil_div(c->n, kBlock), c->sc);
+    k_zsum<<<1, kBlock, 0, c->stream>>>(
+        c->zpart, ceil_div(c->n, traverse_share(c) ? kWave : kBlock), c->sc);
     return hipGetLastError();
 }
 
@@ -1683,7 +1912,10 @@ static hipError_t launch_attract_sums(pixelsne_ctx* c, const dim3 grid, hipStrea
 }
 
 static hipError_t run_attract_sums(pixelsne_ctx* c, bool help, bool early = false) {
-    const int64_t blocks = help ? c->help_blocks : c->side_blocks;
+    // a chunk holds up to kChunkRows rows: blocks past that many chunks would
+    // find the queue empty
+    const int64_t most = ceil_div(c->n, kChunkRows);
+    const int64_t blocks = std::min(help ? c->help_blocks : c->side_blocks, most);
     // the early launch always runs: it stamps the tuner's clock
     if (early && blocks == 0) return launch_attract_sums<0>(c, dim3(1), c->side, 2);
     if (blocks == 0) return hipSuccess;

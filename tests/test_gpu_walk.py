@@ -1,0 +1,46 @@
+"""The Barnes-Hut walk at the point counts where its work split changes.
+
+Up to 40,000 points eight wavefronts share the walk of 64 points, up to
+400,000 four do, above that one walks alone; theta = 0 opens every cell, which
+overflows the shared walk's lists.  Against the CPU oracle: visits exact; R and
+Z within the bars of the gradient parity tests.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1611_02568_amd import datagen
+
+pytestmark = pytest.mark.gpu
+
+TOL_R = {0: 1e-4, 1: 1e-10}
+TOL_Z = {0: 1e-6, 1: 1e-12}
+
+
+def _ring_P(n):
+    rp = np.arange(0, 2 * n + 1, 2, dtype=np.int64)
+    col = np.stack([(np.arange(n) - 1) % n, (np.arange(n) + 1) % n], 1)
+    return rp, np.sort(col, 1).ravel().astype(np.int32), np.full(2 * n, 1.0 / (2 * n))
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,r,theta", [(3, 4, 0.5), (65, 32, 0.5), (4001, 128, 0.0),
+                                       (40000, 512, 0.5), (40001, 512, 0.5), (50003, 256, 0.05),
+                                       (400000, 1024, 0.5), (400001, 1024, 0.5)])
+def test_walk_at_the_split_points(n, r, theta, prec):
+    from paper_1611_02568_amd import pixelsne
+    dt = np.float64 if prec else np.float32
+    z = datagen.clustered_pixels(n, r, seed=n, spread=0.05, dtype=dt)
+    s = np.array([0.05, 0.06])
+    P = _ring_P(n)
+    ctx = pixelsne.Context.from_P(*P, screen=r, precision=prec, theta=theta)
+    ctx.set_state(torch.as_tensor(z), s)
+    g = ctx.gradient(1.0)
+    og = oracle.gradient(z.astype(np.float64), r, s, P, theta=theta, predicate=0 if prec else 1)
+    assert np.array_equal(g["visits"].cpu().numpy(), og["visits"])
+    R = g["R"].double().cpu().numpy()
+    assert np.linalg.norm(R - og["R"]) <= TOL_R[prec] * np.linalg.norm(og["R"])
+    assert abs(g["Z"] - og["Z"]) <= TOL_Z[prec] * og["Z"]
+    again = ctx.gradient(1.0)
+    assert torch.equal(g["R"], again["R"]) and torch.equal(g["Zi"], again["Zi"])
