@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "walk.h"
 
 namespace psne {
 
@@ -574,53 +575,6 @@ __device__ __forceinline__ float mulf_nc(float a, float b) {
     return a * b;
 }
 
-// Write a stack entry (four wave-uniform words, in scalar registers) into
-// lane `sel` of the four per-lane stack registers.  With one scalar operand
-// per vector instruction the lane select goes through m0 (an input operand:
-// the compiler writes it with a scalar move); the s_nop adds two wait states
-// before it is read.
-__device__ __forceinline__ void push_entry(int& a, int& b, int& c, int& d, int va, int vb,
-                                           int vc, int vd, int sel) {
-    asm("s_nop 1\n\t"
-        "v_writelane_b32 %0, %4, m0\n\t"
-        "v_writelane_b32 %1, %5, m0\n\t"
-        "v_writelane_b32 %2, %6, m0\n\t"
-        "v_writelane_b32 %3, %7, m0"
-        : "+v"(a), "+v"(b), "+v"(c), "+v"(d)
-        : "s"(va), "s"(vb), "s"(vc), "s"(vd), "{m0}"(sel));
-}
-
-// The traversal's stack: entry k (a sibling group: its first cell, size and
-// level, and the 64-bit mask of lanes that descend into it) lives in lane k of
-// four registers.  A walk pushes at most three pending groups per level plus
-// the one it expands next, so 3 (levels) + 1 entries suffice: 52 for the pixel
-// tree (at most 17 levels), 100 for the data-driven tree (33 levels), which
-// takes a second set of four registers for entries 64..127 (DEEP).
-template <bool DEEP>
-struct WaveStack {
-    int f0 = 0, i0 = 0, lo0 = 0, hi0 = 0;
-    int f1 = 0, i1 = 0, lo1 = 0, hi1 = 0;
-    __device__ __forceinline__ void push(int sp, int f, int info, int lo, int hi) {
-        if (!DEEP || sp < kWave) push_entry(f0, i0, lo0, hi0, f, info, lo, hi, sp);
-        else push_entry(f1, i1, lo1, hi1, f, info, lo, hi, sp - kWave);
-    }
-    __device__ __forceinline__ void read(int sp, uint32_t& first, uint32_t& info,
-                                         uint64_t& mask) const {
-        if (!DEEP || sp < kWave) {
-            first = (uint32_t)__builtin_amdgcn_readlane(f0, sp);
-            info = (uint32_t)__builtin_amdgcn_readlane(i0, sp);
-            mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi0, sp) << 32) |
-                   (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo0, sp);
-        } else {
-            const int k = sp - kWave;
-            first = (uint32_t)__builtin_amdgcn_readlane(f1, k);
-            info = (uint32_t)__builtin_amdgcn_readlane(i1, k);
-            mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi1, k) << 32) |
-                   (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo1, k);
-        }
-    }
-};
-
 // a sibling group's records, read together
 struct alignas(16) CellF4 { CellF c[4]; };
 struct alignas(32) Node4 { Node n[4]; };
@@ -674,7 +628,7 @@ struct Walker {
     }
 
     // The lanes of MASK meet the NSIB cells of a sibling group; cells that any
-    // of them opens go to push(child word, level, lanes).
+    // of them opens go to push(group of their children, level, lanes).
     template <typename Push>
     __device__ __forceinline__ void meet(const Group& g4, uint32_t first, uint32_t nsib, int level,
                                          uint64_t mask, Push&& push) {
@@ -809,10 +763,6 @@ struct Walker {
     }
 };
 
-// A child word of a cell (Node::child) as a sibling group: first cell and size.
-__device__ __forceinline__ uint32_t child_first(uint32_t c) { return c & 0x3FFFFFFFu; }
-__device__ __forceinline__ uint32_t child_num(uint32_t c) { return (c >> 30) + 1u; }
-
 template <typename T, bool COUNT, bool F32T, bool DEEP>
 __global__ __launch_bounds__(kBlock) void k_traverse(
     const Node* __restrict__ nodes, const CellF* __restrict__ cells32,
@@ -841,7 +791,7 @@ __global__ __launch_bounds__(kBlock) void k_traverse(
         sp = 1;
     }
     auto push = [&](uint32_t child, int level, uint64_t om) {
-        st.push(sp, (int)child_first(child), (int)(child_num(child) | ((uint32_t)level << 8)),
+        st.push(sp, (int)group_first(child), (int)(group_num(child) | ((uint32_t)level << 8)),
                 (int)(uint32_t)om, (int)(uint32_t)(om >> 32));
         sp++;
     };
@@ -865,21 +815,12 @@ __global__ __launch_bounds__(kBlock) void k_traverse(
     if (threadIdx.x == 0) zpart[blockIdx.x] = ((wz[0] + wz[1]) + wz[2]) + wz[3];
 }
 
-// The same walk shared by the G wavefronts of a block, for point counts that
-// leave the chip short of wavefronts: one block per 64 points, and every
-// wavefront holds all 64 of them.  The union list is walked level by level:
-// the sibling groups of a level lie in LDS, wavefront w takes the groups w,
-// w + G, ..., and appends the groups that its lanes open to its own segment
-// of the next level, so which wavefront meets a cell, and the order of every
-// lane's partial sums, depend on the tree alone.  The partial sums of the
-// wavefronts are added in wavefront order at the end.  A segment that is full
-// sends its wavefront down depth first instead (theta near 0 opens whole
-// levels).  Known groups are also loaded one ahead of their use, where the
-// depth-first walk waits for each group's records.  Bound by that latency
-// below one wavefront per SIMD: the kernel takes 39 us where the walk alone
-// took 194 (2,000 points, FP32), 93 where it took 220 (70,000).
+// The same walk shared by the G wavefronts of a block (walk.h), one block per
+// 64 points, for point counts that leave the chip short of wavefronts.
+// Bound by the latency of a lone walk's loads below one wavefront per SIMD:
+// it takes 39 us where the walk alone took 194 (2,000 points, FP32), 93 where
+// it took 220 (70,000).
 constexpr int kShareCap = 96;      // groups per wavefront and level
-constexpr int kShareFlush = 8;     // groups gathered in registers before they go to LDS
 template <typename T> struct ShareSum { T x, y; double z; };
 
 template <typename T, bool COUNT, bool F32T, int G>
@@ -892,18 +833,13 @@ __global__ __launch_bounds__(kWave * G) void k_traverse_shared(
     double* __restrict__ Zi_out, uint32_t* __restrict__ visits_out,
     uint32_t* __restrict__ used_out) {
     using V = v2_t<T>;
-    // the groups of two levels; after the walk the partial sums take the room
-    struct Lists {
-        uint64_t mask[2][G][kShareCap];
-        uint32_t child[2][G][kShareCap];
-    };
+    // the lists; after the walk the partial sums take their room
     union Room {
-        Lists l;
+        WalkLists<G, kShareCap> l;
         ShareSum<T> sum[G][kWave];
         __device__ Room() {}
     };
     __shared__ Room room;
-    __shared__ uint32_t num[2][G];
     __shared__ uint32_t counts[COUNT ? 2 : 1][COUNT ? G : 1][COUNT ? kWave : 1];
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -912,90 +848,7 @@ __global__ __launch_bounds__(kWave * G) void k_traverse_shared(
     const V zp = valid ? reinterpret_cast<const V*>(zs)[s] : V{T(0), T(0)};
     Walker<T, COUNT, F32T> wk(nodes, cells32, nsum, sc, L, th2, com_mode, zp,
                               valid ? leaf_of[s] : 0xFFFFFFFFu);
-    const uint64_t all = ballot64(valid);            // at least one point per block
-    if (threadIdx.x < G) num[0][threadIdx.x] = threadIdx.x == 0 ? 1u : 0u;
-    if (threadIdx.x == 0) {
-        room.l.mask[0][0][0] = all;
-        room.l.child[0][0][0] = 0u;                  // the root: cell 0, one cell
-    }
-    __syncthreads();
-    for (int level = 0;; level++) {
-        const int b = level & 1;
-        // the level's groups in wavefront order: segment starts
-        uint32_t start[G + 1];
-        start[0] = 0;
-        const uint32_t nl = lane < G ? num[b][lane < G ? lane : 0] : 0u;
-#pragma unroll
-        for (int q = 0; q < G; q++)
-            start[q + 1] = start[q] + (uint32_t)__builtin_amdgcn_readlane((int)nl, q);
-        const uint32_t total = start[G];
-        if (total == 0) break;
-        WaveStack<false> st;     // groups opened by this wavefront, not yet in LDS
-        int sp = 0;
-        uint32_t put = 0;        // groups of the next level in this wavefront's segment
-        auto push = [&](uint32_t child, int lv, uint64_t om) {
-            st.push(sp, (int)child, lv, (int)(uint32_t)om, (int)(uint32_t)(om >> 32));
-            sp++;
-        };
-        auto flush = [&]() {
-            if (put + (uint32_t)sp <= (uint32_t)kShareCap) {
-                if (lane < sp) {
-                    room.l.child[b ^ 1][w][put + lane] = (uint32_t)st.f0;
-                    room.l.mask[b ^ 1][w][put + lane] =
-                        ((uint64_t)(uint32_t)st.hi0 << 32) | (uint64_t)(uint32_t)st.lo0;
-                }
-                put += (uint32_t)sp;
-                sp = 0;
-                return;
-            }
-            // no room: the pending groups depth first (at most kShareFlush + 3
-            // of them, each level adds at most three: 11 + 3 * 17 entries)
-            while (sp > 0) {
-                sp--;
-                uint32_t child, lv;
-                uint64_t mask;
-                st.read(sp, child, lv, mask);
-                const uint32_t first = child_first(child);
-                wk.meet(wk.load(first), first, child_num(child), (int)lv, mask, push);
-            }
-        };
-        // this wavefront's groups, 64 at a time into lanes
-        for (uint32_t e0 = (uint32_t)w; e0 < total; e0 += (uint32_t)(G * kWave)) {
-            const uint32_t e = e0 + (uint32_t)(G * lane);
-            uint32_t child = 0;
-            uint64_t mask = 0;
-            if (e < total) {
-                int seg = 0;
-#pragma unroll
-                for (int q = 1; q < G; q++) seg += e >= start[q] ? 1 : 0;
-                uint32_t at = e;
-#pragma unroll
-                for (int q = 1; q < G; q++) at = seg == q ? e - start[q] : at;
-                child = room.l.child[b][seg][at];
-                mask = room.l.mask[b][seg][at];
-            }
-            const int mlo = (int)(uint32_t)mask, mhi = (int)(uint32_t)(mask >> 32);
-            const uint32_t left = (total - e0 + (uint32_t)G - 1) / (uint32_t)G;
-            const int m = left < (uint32_t)kWave ? (int)left : kWave;
-            uint32_t ch = (uint32_t)__builtin_amdgcn_readlane((int)child, 0);
-            typename Walker<T, COUNT, F32T>::Group cur = wk.load(child_first(ch));
-            for (int k = 0; k < m; k++) {
-                const int k1 = k + 1 < m ? k + 1 : k;
-                const uint32_t ch1 = (uint32_t)__builtin_amdgcn_readlane((int)child, k1);
-                const typename Walker<T, COUNT, F32T>::Group nxt = wk.load(child_first(ch1));
-                const uint64_t gm =
-                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(mhi, k) << 32) |
-                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane(mlo, k);
-                wk.meet(cur, child_first(ch), child_num(ch), level, gm, push);
-                if (sp >= kShareFlush) flush();
-                cur = nxt;
-                ch = ch1;
-            }
-        }
-        if (sp > 0) flush();
-        if (lane == 0) num[b ^ 1][w] = put;
-        __syncthreads();
-    }
+    walk_shared<G, kShareCap, false>(wk, room.l, w, ballot64(valid));
     __syncthreads();             // the lists are done with: the sums take their room
     room.sum[w][lane] = ShareSum<T>{wk.rx, wk.ry, wk.zacc};
     if constexpr (COUNT) {

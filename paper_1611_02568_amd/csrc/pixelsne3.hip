@@ -15,10 +15,8 @@
 //             level l = a run of equal key >> 3(L - l)); leaf sums by a
 //             segmented scan per wavefront and the pieces of each leaf, inner
 //             sums from the <= 8 children, one launch per level
-//   traverse  the 64 points of a wavefront walk the union of their paths
-//             depth first without a stack: children are consecutive cells,
-//             so after a cell the wave moves to the next sibling or climbs
-//             to the parent
+//   traverse  64 points walk the union of their paths together, shared by the
+//             wavefronts of a block, level by level
 //   zsum      Z = sum of the per-point terms (fixed order)
 //   attract   one wavefront per row of P
 //   update    gains / momentum step and per-block min / max of z + u
@@ -31,6 +29,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "walk.h"
 
 namespace psne {
 
@@ -101,7 +100,6 @@ struct pixelsne3_ctx {
     double* nsum = nullptr;                 // [max_nodes][3] coordinate sums
     uint32_t* nstart = nullptr;             // first sorted position of each cell
     uint32_t* fchild = nullptr;             // first child of each inner cell
-    uint32_t* parent = nullptr;
     uint32_t* leaf_of = nullptr;            // [n] leaf of each sorted position
     double* zs = nullptr;                   // [n][3] positions in sorted order
     double* zscan = nullptr;                // [n][3] per-wave segmented leaf scan
@@ -197,12 +195,11 @@ __global__ __launch_bounds__(kBlock) void k3_tree_count(const uint32_t* __restri
 }
 
 // For every level, the rank of the cell holding sorted position s; positions
-// that open a cell record its start, first child and parent.
+// that open a cell record its start and first child.
 __global__ __launch_bounds__(kBlock) void k3_tree_nodes(
     const uint32_t* __restrict__ keys, int64_t n, int L, const uint32_t* __restrict__ off,
     int64_t nb, const uint32_t* __restrict__ ltot, Scalars3* __restrict__ sc,
-    uint32_t* __restrict__ nstart, uint32_t* __restrict__ fchild, uint32_t* __restrict__ parent,
-    uint32_t* __restrict__ leaf_of) {
+    uint32_t* __restrict__ nstart, uint32_t* __restrict__ fchild, uint32_t* __restrict__ leaf_of) {
     __shared__ uint32_t wc[4][kLevels3];
     __shared__ uint32_t lbase[kLevels3 + 1];
     const int t = threadIdx.x, w = t >> 6;
@@ -251,7 +248,6 @@ __global__ __launch_bounds__(kBlock) void k3_tree_nodes(
             const uint32_t g = cell[l];
             nstart[g] = (uint32_t)s;
             fchild[g] = l < L ? cell[l < L ? l + 1 : L] : 0u;
-            parent[g] = l > 0 ? cell[l > 0 ? l - 1 : 0] : 0u;
         }
     }
 }
@@ -352,44 +348,54 @@ __global__ __launch_bounds__(kBlock) void k3_inner(int l, const Scalars3* __rest
 // w^2 (b1 + b2 + b3) < theta^2 d^2, else its children are visited in order.
 //
 // The 64 points of a wavefront (neighbours in Morton order) walk the union of
-// their walks together: the wave steps through cells in depth-first order
-// and enters a cell's children when any of its lanes opens the cell.  A lane
-// takes part in a cell only if it opened every ancestor: `mark` holds the
-// level of the last cell the lane used (or skipped), and the lane sits out
-// every cell deeper than that until the wave returns to that level.  The
-// cell address is the same for the whole wave, so cells arrive through
-// scalar loads, and each lane's sums run in the order of its own walk.
-__global__ __launch_bounds__(kBlock) void k3_traverse(
-    const uint32_t* __restrict__ perm, const uint32_t* __restrict__ leaf_of,
-    const double* __restrict__ zs, const Node3* __restrict__ nodes,
-    const double* __restrict__ nsum, const uint32_t* __restrict__ parent,
-    const Scalars3* __restrict__ sc, int64_t n, int L, double th2, double* __restrict__ R,
-    double* __restrict__ Zi, uint32_t* __restrict__ visits) {
-    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool valid = s < n;
-    const int64_t i = valid ? (int64_t)perm[s] : 0;
-    const uint32_t own = valid ? leaf_of[s] : 0xFFFFFFFFu;
-    const double b0 = sc->s[0] * sc->s[0], b1 = sc->s[1] * sc->s[1], b2 = sc->s[2] * sc->s[2];
-    double bs;
-    {
-#pragma clang fp contract(off)
-        bs = (b0 + b1) + b2;
-    }
-    const double x = valid ? zs[3 * s] : 0.0, y = valid ? zs[3 * s + 1] : 0.0,
-                 w3 = valid ? zs[3 * s + 2] : 0.0;
+// their walks together (walk.h), shared by the wavefronts of a block.  A cell's up to eight
+// children are met as two sibling groups of at most four records, each read by
+// one batch of scalar loads.
+struct alignas(32) Node3x4 { Node3 n[4]; };
+
+template <bool COUNT>
+struct Walker3 {
+    using Group = Node3x4;
+    const Node3* __restrict__ nodes;
+    const double* __restrict__ nsum;
+    int L;
+    double th2, b0, b1, b2, bs, x, y, w3;
+    uint32_t own;
     double rx = 0.0, ry = 0.0, rz = 0.0, zacc = 0.0;
     uint32_t nv = 0;
-    int mark = valid ? 0x7FFFFFFF : -1;
-    uint32_t g = 0;
-    int lvl = 0;
-    for (;;) {
-        const Node3 nd = nodes[g];
-        bool open = false;
-        if (lvl <= mark) {
-            nv++;
-            bool use = true;
-            double m = (double)nd.count, cx = nd.cx, cy = nd.cy, cz = nd.cz;
-            if (nd.child == 0u) {
+
+    // four records (the array has three of slack at its end)
+    __device__ __forceinline__ Group load(uint32_t first) const {
+        return *reinterpret_cast<const Node3x4*>(nodes + first);
+    }
+
+    // the lanes of MASK meet the NSIB cells of a group; cells that any of them
+    // opens go to push(group of children, level, lanes)
+    template <typename Push>
+    __device__ __forceinline__ void meet(const Group& g4, uint32_t first, uint32_t nsib, int level,
+                                         uint64_t mask, Push&& push) {
+        const bool act = __builtin_amdgcn_inverse_ballot_w64(mask);
+        const double wc = (double)(1u << (L - level));
+        const double diag2 = mul_nc3(mul_nc3(wc, wc), bs);
+#pragma unroll
+        for (uint32_t q = 0; q < 4; q++) {
+            if (q >= nsib) break;
+            const uint32_t g = first + q;
+            const Node3 nd = g4.n[q];
+            uint64_t om = 0;                 // lanes that open the cell
+            double m = (double)nd.count, dx, dy, dz, d2;
+            bool use;
+            if (nd.child != 0u) {
+                dx = x - nd.cx;
+                dy = y - nd.cy;
+                dz = w3 - nd.cz;
+                d2 = dist3(b0, b1, b2, dx, dy, dz);
+                const uint64_t near = ballot64(!(diag2 < mul_nc3(th2, d2)));
+                om = near & mask;
+                use = __builtin_amdgcn_inverse_ballot_w64(mask & ~near);
+            } else {
+                double cx = nd.cx, cy = nd.cy, cz = nd.cz;
+                use = act;
                 if (g == own) {
                     m -= 1.0;
                     if (m > 0.0) {
@@ -400,65 +406,104 @@ __global__ __launch_bounds__(kBlock) void k3_traverse(
                         use = false;
                     }
                 }
-            } else {
-                const double d2 = dist3(b0, b1, b2, x - cx, y - cy, w3 - cz);
-                const double wc = (double)(1u << (L - lvl));
-                if (!(mul_nc3(mul_nc3(wc, wc), bs) < mul_nc3(th2, d2))) {
-                    use = false;
-                    open = true;
-                }
+                dx = x - cx;
+                dy = y - cy;
+                dz = w3 - cz;
+                d2 = dist3(b0, b1, b2, dx, dy, dz);
             }
+            if constexpr (COUNT) nv += act ? 1u : 0u;
             if (use) {
-                const double dx = x - cx, dy = y - cy, dz = w3 - cz;
-                const double q = rcp_nr(1.0 + dist3(b0, b1, b2, dx, dy, dz));
-                const double mq = m * q;
+                const double qq = rcp_nr(1.0 + d2);
+                const double mq = m * qq;
                 zacc += mq;
-                const double f = mq * q;
+                const double f = mq * qq;
                 rx += f * dx;
                 ry += f * dy;
                 rz += f * dz;
             }
-            mark = open ? 0x7FFFFFFF : lvl;
-        }
-        if (ballot64(open)) {
-            g = nd.child & kChildMask3;
-            lvl++;
-            continue;
-        }
-        // the next sibling, climbing while the cell is the last of its parent
-        bool done = true;
-        while (g != 0u) {
-            const uint32_t p = parent[g];
-            const uint32_t pc = nodes[p].child;
-            if (g < (pc & kChildMask3) + (pc >> kChildBits3)) {
-                g++;
-                done = false;
-                break;
+            if (om) {
+                const uint32_t c0 = nd.child & kChildMask3, nc = (nd.child >> kChildBits3) + 1u;
+                push(c0 | ((nc < 4u ? nc : 4u) - 1u) << 30, level + 1, om);
+                if (nc > 4u) push((c0 + 4u) | (nc - 5u) << 30, level + 1, om);
             }
-            g = p;
-            lvl--;
         }
-        if (done) break;
     }
-    if (!valid) return;
-    R[3 * i] = rx;
-    R[3 * i + 1] = ry;
-    R[3 * i + 2] = rz;
-    Zi[i] = zacc;
-    if (visits) visits[i] = nv;
-}
+};
 
-__global__ __launch_bounds__(kBlock) void k3_zpart(const double* __restrict__ Zi, int64_t n,
-                                                   double* __restrict__ part) {
-    __shared__ double red[kBlock];
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    red[threadIdx.x] = i < n ? Zi[i] : 0.0;
-    __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+// One block of kShare3 wavefronts per 64 points, at every n: FP64 issue bounds
+// the walk once the SIMDs are full (3,766 cells in the union list of 64 points
+// against 2,100 visits per point at 100,000 points), the latency of its loads
+// before that.  Measured, us per iteration, late layout on a 256 cube, with 1 /
+// 2 / 4 / 8 wavefronts: 2,000 points 684 / 364 / 248 / 190; 100,000: 1,978 /
+// 1,230 / 928 / 866; 1,000,000: 11,106 / 9,167 / 8,877 / 9,247 (the walk by one
+// wavefront through parent links that this replaces: 3,550 at 100,000).  Six
+// wavefronts per SIMD (80 registers, a few spilled) and no load ahead, whose
+// 32 more scalar registers spill in the loop: 734 at 100,000 and 7,619 at
+// 1,000,000; five per SIMD 800 and 8,565, seven 757 and 7,733.
+constexpr int kShare3 = 8;
+constexpr int kShareCap3 = 128;
+constexpr int kWaves3 = 6;
+struct Sum3 { double x, y, z, q; };
+
+template <bool COUNT>
+__global__ __launch_bounds__(kWave * kShare3, kWaves3) void k3_traverse(
+    const uint32_t* __restrict__ perm, const uint32_t* __restrict__ leaf_of,
+    const double* __restrict__ zs, const Node3* __restrict__ nodes,
+    const double* __restrict__ nsum, const Scalars3* __restrict__ sc, int64_t n, int L,
+    double th2, double* __restrict__ R, double* __restrict__ Zi, double* __restrict__ zpart,
+    uint32_t* __restrict__ visits) {
+    union Room {
+        WalkLists<kShare3, kShareCap3> l;
+        Sum3 sum[kShare3][kWave];
+        __device__ Room() {}
+    };
+    __shared__ Room room;
+    __shared__ uint32_t nvs[COUNT ? kShare3 : 1][kWave];
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t s = (int64_t)blockIdx.x * kWave + lane;
+    const bool valid = s < n;
+    Walker3<COUNT> wk;
+    wk.nodes = nodes;
+    wk.nsum = nsum;
+    wk.L = L;
+    wk.th2 = th2;
+    wk.b0 = sc->s[0] * sc->s[0];
+    wk.b1 = sc->s[1] * sc->s[1];
+    wk.b2 = sc->s[2] * sc->s[2];
+    {
+#pragma clang fp contract(off)
+        wk.bs = (wk.b0 + wk.b1) + wk.b2;
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+    wk.own = valid ? leaf_of[s] : 0xFFFFFFFFu;
+    wk.x = valid ? zs[3 * s] : 0.0;
+    wk.y = valid ? zs[3 * s + 1] : 0.0;
+    wk.w3 = valid ? zs[3 * s + 2] : 0.0;
+    walk_shared<kShare3, kShareCap3, true, false>(wk, room.l, w, ballot64(valid));
+    __syncthreads();             // the lists are done with: the sums take their room
+    room.sum[w][lane] = Sum3{wk.rx, wk.ry, wk.rz, wk.zacc};
+    if constexpr (COUNT) nvs[w][lane] = wk.nv;
+    __syncthreads();
+    if (w != 0) return;
+#pragma unroll
+    for (int q = 1; q < kShare3; q++) {
+        const Sum3 p = room.sum[q][lane];
+        wk.rx += p.x;
+        wk.ry += p.y;
+        wk.rz += p.z;
+        wk.zacc += p.q;
+        if constexpr (COUNT) wk.nv += nvs[q][lane];
+    }
+    if (valid) {
+        const int64_t i = perm[s];
+        R[3 * i] = wk.rx;
+        R[3 * i + 1] = wk.ry;
+        R[3 * i + 2] = wk.rz;
+        Zi[i] = wk.zacc;
+        if constexpr (COUNT) visits[i] = wk.nv;
+    }
+    const double zw = wave_sum(wk.zacc);
+    if (lane == 0) zpart[blockIdx.x] = zw;
 }
 
 __global__ __launch_bounds__(kBlock) void k3_zfinal(const double* __restrict__ part, int64_t m,
@@ -879,7 +924,7 @@ hipError_t alloc3(pixelsne3_ctx* c) {
     for (double** v : vecs)
         if ((e = dalloc3(c, v, v3)) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->Zi, 8 * (size_t)n)) != hipSuccess) return e;
-    c->zpart_n = ceil_div(n, kBlock);
+    c->zpart_n = ceil_div(n, kWave);
     if ((e = dalloc3(c, &c->zpart, 8 * (size_t)c->zpart_n)) != hipSuccess) return e;
     c->mm_n = update_blocks(n);
     if ((e = dalloc3(c, &c->mm_part, 6 * 8 * (size_t)c->mm_n)) != hipSuccess) return e;
@@ -900,11 +945,10 @@ hipError_t alloc3(pixelsne3_ctx* c) {
         mx += cap < n ? cap : n;
     }
     c->max_nodes = mx;
-    if ((e = dalloc3(c, &c->nodes, sizeof(Node3) * (size_t)mx)) != hipSuccess) return e;
+    if ((e = dalloc3(c, &c->nodes, sizeof(Node3) * (size_t)(mx + 3))) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->nsum, 3 * 8 * (size_t)mx)) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->nstart, 4 * (size_t)mx)) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->fchild, 4 * (size_t)mx)) != hipSuccess) return e;
-    if ((e = dalloc3(c, &c->parent, 4 * (size_t)mx)) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->leaf_of, 4 * (size_t)n)) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->zs, v3)) != hipSuccess) return e;
     if ((e = dalloc3(c, &c->zscan, v3)) != hipSuccess) return e;
@@ -931,6 +975,14 @@ hipError_t run_init3(pixelsne3_ctx* c) {
     return run_scale3(c);
 }
 
+// Visits are counted only when they are asked for.
+template <bool COUNT>
+void launch_traverse3(pixelsne3_ctx* c, uint32_t* visits) {
+    k3_traverse<COUNT><<<dim3((unsigned)ceil_div(c->n, kWave)), kWave * kShare3, 0, c->stream>>>(
+        c->idx[c->sorted], c->leaf_of, c->zs, c->nodes, c->nsum, c->sc, c->n, c->L,
+        c->prm.theta * c->prm.theta, c->R, c->Zi, c->zpart, visits);
+}
+
 // keys, sort, octree, traversal, Z and attraction at the current state
 hipError_t run_forces3(pixelsne3_ctx* c, uint32_t* visits) {
     const int64_t n = c->n;
@@ -946,7 +998,7 @@ hipError_t run_forces3(pixelsne3_ctx* c, uint32_t* visits) {
     if (e != hipSuccess) return e;
     k3_tree_nodes<<<dim3((unsigned)c->tree_blocks), kBlock, 0, c->stream>>>(
         keys, n, c->L, c->lvl_cnt, c->tree_blocks, c->ltot, c->sc, c->nstart, c->fchild,
-        c->parent, c->leaf_of);
+        c->leaf_of);
     k3_leaf_scan<<<grid_for(n), kBlock, 0, c->stream>>>(perm, c->leaf_of, c->z, n, c->zs,
                                                         c->zscan);
     k3_leaves<<<grid_for(n), kBlock, 0, c->stream>>>(c->zscan, n, c->L, c->sc, c->nstart,
@@ -956,10 +1008,8 @@ hipError_t run_forces3(pixelsne3_ctx* c, uint32_t* visits) {
         k3_inner<<<grid_for(cap < n ? cap : n), kBlock, 0, c->stream>>>(l, c->sc, c->fchild,
                                                                          c->nodes, c->nsum);
     }
-    k3_traverse<<<grid_for(n), kBlock, 0, c->stream>>>(
-        perm, c->leaf_of, c->zs, c->nodes, c->nsum, c->parent, c->sc, n, c->L,
-        c->prm.theta * c->prm.theta, c->R, c->Zi, visits);
-    k3_zpart<<<dim3((unsigned)c->zpart_n), kBlock, 0, c->stream>>>(c->Zi, n, c->zpart);
+    if (visits) launch_traverse3<true>(c, visits);
+    else launch_traverse3<false>(c, nullptr);
     k3_zfinal<<<1, kBlock, 0, c->stream>>>(c->zpart, c->zpart_n, c->sc);
     k3_attract<<<dim3((unsigned)ceil_div(n, kBlock / kWave)), kBlock, 0, c->stream>>>(
         c->row_ptr, c->col, c->val, c->z, perm, c->sc, n, c->A);

@@ -2,8 +2,9 @@
 
 Up to 40,000 points eight wavefronts share the walk of 64 points, up to
 400,000 four do, above that one walks alone; theta = 0 opens every cell, which
-overflows the shared walk's lists.  Against the CPU oracle: visits exact; R and
-Z within the bars of the gradient parity tests.
+overflows the shared walk's lists.  The octree's walk is shared by eight at
+every size.  Against the CPU oracle: visits exact; R and Z within the bars of
+the gradient parity tests.
 """
 import numpy as np
 import pytest
@@ -44,3 +45,20 @@ def test_walk_at_the_split_points(n, r, theta, prec):
     assert abs(g["Z"] - og["Z"]) <= TOL_Z[prec] * og["Z"]
     again = ctx.gradient(1.0)
     assert torch.equal(g["R"], again["R"]) and torch.equal(g["Zi"], again["Zi"])
+
+
+@pytest.mark.parametrize("n,r,theta", [(3, 2, 0.5), (65, 16, 0.5), (4001, 64, 0.0),
+                                       (5003, 128, 0.05), (30011, 256, 0.5)])
+def test_octree_walk(n, r, theta):
+    from paper_1611_02568_amd import pixelsne
+    z = datagen.clustered_pixels(n, r, seed=n, spread=0.05, dim=3)
+    s = np.array([0.05, 0.06, 0.055])
+    P = _ring_P(n)
+    ctx = pixelsne.Context3.from_P(*P, screen=r, theta=theta)
+    ctx.set_state(torch.as_tensor(z), s)
+    g = ctx.gradient(1.0)
+    og = oracle.gradient3(z, r, s, P, theta=theta)
+    assert np.array_equal(g["visits"].cpu().numpy(), og["visits"])
+    R = g["R"].cpu().numpy()
+    assert np.linalg.norm(R - og["R"]) <= TOL_R[1] * np.linalg.norm(og["R"])
+    assert abs(g["Z"] - og["Z"]) <= TOL_Z[1] * og["Z"]
