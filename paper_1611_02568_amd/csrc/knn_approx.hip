@@ -22,6 +22,7 @@
 // is a deterministic function of the data and the seed (the CPU reference
 // takes the same steps).
 #include "ctx.h"
+#include "nearest.h"
 
 namespace psne {
 
@@ -57,11 +58,6 @@ __device__ __forceinline__ double sqdist(const X* __restrict__ Xm, int32_t D, in
     }
     return s;
 }
-
-__device__ __forceinline__ bool knn_less(double da, int32_t ja, double db, int32_t jb) {
-    return da < db || (da == db && ja < jb);
-}
-
 
 __global__ __launch_bounds__(kBlock) void k_rp_init(uint32_t* __restrict__ perm,
                                                     uint32_t* __restrict__ sa,
@@ -188,28 +184,6 @@ struct ListLds {
     TT rows[kWaveBlock][kSlice + 1];
     int32_t m, npend;
 };
-
-// bitonic sort of one (d, j) pair per lane across the wave, ascending
-__device__ __forceinline__ void wave_sort(double& d, int32_t& j) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int size = 2; size <= kWave; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const double od = __shfl_xor(d, stride, kWave);
-            const int32_t oj = __shfl_xor(j, stride, kWave);
-            const bool up = (lane & size) == 0;          // this block sorts ascending
-            const bool low = (lane & stride) == 0;       // this lane holds the lower slot
-            const bool other_less = knn_less(od, oj, d, j);
-            // the lower slot of an ascending block keeps the smaller pair
-            const bool take = (low == up) ? other_less : knn_less(d, j, od, oj);
-            if (take) {
-                d = od;
-                j = oj;
-            }
-        }
-    }
-}
 
 // number of entries of a sorted list (ascending (d, j)) below (d, j)
 __device__ __forceinline__ int rank_in(const double* ld, const int32_t* lj, int m, double d,
