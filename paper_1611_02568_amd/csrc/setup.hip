@@ -432,7 +432,6 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
                                                     const uint32_t* __restrict__ cand_cnt,
                                                     const uint32_t* __restrict__ cand_thr,
                                                     const float* __restrict__ nrm, float nrm_max,
-                                                    int exact_keys,
                                                     int32_t* __restrict__ idx,
                                                     double* __restrict__ d2,
                                                     uint32_t* __restrict__ flag) {
@@ -481,9 +480,6 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
         const uint32_t tb = cand_thr[i];
         if (tb == kNoThr) {
             flag[i] = 0u;                        // every candidate was kept
-        } else if (exact_keys) {
-            // exact integer distances: only a tie at the threshold is unproven
-            flag[i] = dv[k - 1] < (double)tb ? 0u : 1u;
         } else {
             // |fp32(d) - d| <= (D + 4) 2^-24 (|x| + |y|)^2  (conservative)
             const double tau = (double)__uint_as_float(tb);
@@ -492,6 +488,20 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
             flag[i] = dv[k - 1] < tau - err ? 0u : 1u;
         }
     }
+}
+
+// uint8 rows: the kept keys are exact integer distances, a candidate equal to
+// the threshold is always kept, and the last compaction left the list sorted
+// by (distance, index), so its first k entries are the answer.
+__global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ cand, int64_t n,
+                                                  int k, int32_t* __restrict__ idx,
+                                                  double* __restrict__ d2) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= n * (int64_t)k) return;
+    const int64_t i = e / k;
+    const uint64_t c = cand[i * kCap + (e - i * k)];
+    idx[e] = (int32_t)(uint32_t)c;
+    d2[e] = (double)(uint32_t)(c >> 32);
 }
 
 // Exact fallback for rows the bound could not certify: block per row,
@@ -813,8 +823,13 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
             k_knn_candidates<X, false><<<dim3((unsigned)ceil_div(n, kQB)), 256, 0, s>>>(
                 Xm, n, D, nrm, kp, cand, ccnt, cthr);
     }
-    k_knn_rerank<X><<<dim3((unsigned)n), 256, 0, s>>>(Xm, D, k, cand, ccnt, cthr, nrm, nmax,
-                                                      kExact ? 1 : 0, idx, d2, flag);
+    if (kExact) {
+        k_knn_emit<<<dim3((unsigned)ceil_div(n * k, 256)), 256, 0, s>>>(cand, n, k, idx, d2);
+        if ((e = hipGetLastError()) != hipSuccess) return fail(e);
+        return fail(hipStreamSynchronize(s));
+    }
+    k_knn_rerank<X><<<dim3((unsigned)n), 256, 0, s>>>(Xm, D, k, cand, ccnt, cthr, nrm, nmax, idx,
+                                                      d2, flag);
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     std::vector<uint32_t> hf(n);
     if ((e = hipMemcpyAsync(hf.data(), flag, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s)) != hipSuccess)
