@@ -552,30 +552,64 @@ __global__ __launch_bounds__(256) void k_knn_exact_row(const X* __restrict__ Xm,
 }
 
 // ---------------------------------------------------------------------------
-// perplexity calibration, one thread per row (FP64)
+// perplexity calibration, one wavefront per row (FP64)
 // ---------------------------------------------------------------------------
+// Lane l holds the row's entries l, l + 64, ...: in registers up to 64 * HELD
+// entries, read again for every evaluation beyond (HELD = 0).  Bound by the
+// FP64 exponentials, about 20 evaluations of k of them per row; a thread per
+// row also read and wrote its row, 8 k bytes from its neighbour's, at every
+// evaluation.  70,000 rows of 150: 1.1 ms where that took 4.8.
+template <int HELD>
 __global__ __launch_bounds__(256) void k_perplexity(const double* __restrict__ d2, int64_t n,
                                                     int k, double target, double tol,
                                                     int max_iter, double* __restrict__ P,
                                                     double* __restrict__ beta_out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int lane = lane_id();
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= n) return;
     const double* d = d2 + i * k;
     double* p = P + i * k;
-    double dmin = d[0];
-    for (int j = 1; j < k; j++) dmin = fmin(dmin, d[j]);
+    constexpr int kH = HELD > 0 ? HELD : 1;
+    double dh[kH], eh[kH];
+    double dmin = INFINITY;
+    if constexpr (HELD > 0) {
+#pragma unroll
+        for (int q = 0; q < HELD; q++) {
+            const int j = lane + q * kWave;
+            dh[q] = j < k ? d[j] : INFINITY;
+            dmin = fmin(dmin, dh[q]);
+        }
+    } else {
+        for (int j = lane; j < k; j += kWave) dmin = fmin(dmin, d[j]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) dmin = fmin(dmin, __shfl_xor(dmin, o, kWave));
     double b = 1.0, lo = 0.0, hi = 0.0, S = 0.0;
     bool have_lo = false, have_hi = false;
     for (int it = 0; it < max_iter; it++) {
         S = 0.0;
         double SD = 0.0;
-        for (int j = 0; j < k; j++) {
-            const double dj = d[j] - dmin;
-            const double e = exp(-b * dj);
-            p[j] = e;
-            S += e;
-            SD += dj * e;
+        if constexpr (HELD > 0) {
+#pragma unroll
+            for (int q = 0; q < HELD; q++) {
+                eh[q] = 0.0;
+                if (lane + q * kWave < k) {
+                    const double dj = dh[q] - dmin;
+                    eh[q] = exp(-b * dj);
+                    S += eh[q];
+                    SD += dj * eh[q];
+                }
+            }
+        } else {
+            for (int j = lane; j < k; j += kWave) {
+                const double dj = d[j] - dmin;
+                const double e = exp(-b * dj);
+                S += e;
+                SD += dj * e;
+            }
         }
+        S = wave_sum(S);
+        SD = wave_sum(SD);
         const double H = log(S) + b * SD / S;
         if (fabs(H - target) < tol || it == max_iter - 1) break;
         if (H > target) {
@@ -586,26 +620,19 @@ __global__ __launch_bounds__(256) void k_perplexity(const double* __restrict__ d
             b = have_lo ? 0.5 * (b + lo) : 0.5 * b;
         }
     }
-    for (int j = 0; j < k; j++) p[j] /= S;
-    if (beta_out) beta_out[i] = b;
+    if constexpr (HELD > 0) {
+#pragma unroll
+        for (int q = 0; q < HELD; q++)
+            if (lane + q * kWave < k) p[lane + q * kWave] = eh[q] / S;
+    } else {
+        for (int j = lane; j < k; j += kWave) p[j] = exp(-b * (d[j] - dmin)) / S;
+    }
+    if (beta_out && lane == 0) beta_out[i] = b;
 }
 
 // ---------------------------------------------------------------------------
 // symmetrisation
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_indeg(const int32_t* __restrict__ idx, int64_t m,
-                                               uint32_t* __restrict__ indeg) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e < m) atomicAdd(&indeg[idx[e]], 1u);
-}
-
-__global__ __launch_bounds__(256) void k_row_caps(const uint32_t* __restrict__ indeg, int64_t n,
-                                                  int k, int64_t* __restrict__ cap) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) cap[i] = (int64_t)k + indeg[i];
-    if (i == n) cap[n] = 0;
-}
-
 // exclusive scan of int64, three phases (block size 1024 elements)
 __global__ __launch_bounds__(256) void k_scan64_reduce(const int64_t* __restrict__ a, int64_t m,
                                                        int64_t* __restrict__ bsum) {
@@ -649,117 +676,157 @@ __global__ __launch_bounds__(1024) void k_scan64_top(int64_t* __restrict__ bsum,
 __global__ __launch_bounds__(256) void k_scan64_apply(const int64_t* __restrict__ a, int64_t m,
                                                       const int64_t* __restrict__ bsum,
                                                       int64_t* __restrict__ out) {
-    __shared__ int64_t s[1024];
-    const int64_t base = (int64_t)blockIdx.x * 1024;
-    for (int e = threadIdx.x; e < 1024; e += 256) s[e] = base + e < m ? a[base + e] : 0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = bsum[blockIdx.x];
-        for (int e = 0; e < 1024; e++) {
-            const int64_t v = s[e];
-            s[e] = run;
-            run += v;
-        }
+    __shared__ int64_t ws[4];
+    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const int64_t base = (int64_t)blockIdx.x * 1024 + 4 * t;
+    int64_t v[4], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        v[q] = base + q < m ? a[base + q] : 0;
+        sum += v[q];
     }
+    int64_t x = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) ws[w] = x;
     __syncthreads();
-    for (int e = threadIdx.x; e < 1024; e += 256)
-        if (base + e < m) out[base + e] = s[e];
+    int64_t run = bsum[blockIdx.x] + x - sum;
+    for (int q = 0; q < w; q++) run += ws[q];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        if (base + q < m) out[base + q] = run;
+        run += v[q];
+    }
 }
 
-__global__ __launch_bounds__(256) void k_sym_fill(const int32_t* __restrict__ idx,
-                                                  const double* __restrict__ Pc, int64_t n, int k,
-                                                  const int64_t* __restrict__ off,
-                                                  uint32_t* __restrict__ fill,
-                                                  uint32_t* __restrict__ tcol,
-                                                  double* __restrict__ tval) {
+// Row i of P joins the k out-edges i -> j with the in-edges i' -> i.  A stable
+// sort of the edges by their target leaves each target's in-edges together
+// and, as edge e = i k + t comes before the edges of later rows, ordered by
+// their source; the out-edges are sorted by their target in LDS, and the two
+// ordered lists are merged by rank.  A pair that is in both is one entry.
+// (In-edges placed by atomic counters and then ranked against each other cost
+// the square of a row's length: 31.9 ms for the one or two hub rows of 70,000
+// byte images, where this takes 0.4.)
+
+// first sorted position of each target's in-edges; start[n] = m
+__global__ __launch_bounds__(256) void k_in_start(const uint32_t* __restrict__ target, int64_t m,
+                                                  int64_t n, int64_t* __restrict__ start) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= n * (int64_t)k) return;
-    const int64_t i = e / k;
-    const int t = (int)(e - i * k);
-    const int32_t j = idx[e];
-    const double v = Pc[e];
-    tcol[off[i] + t] = (uint32_t)j;
-    tval[off[i] + t] = v;
-    const uint32_t slot = atomicAdd(&fill[j], 1u);
-    tcol[off[j] + k + slot] = (uint32_t)i;
-    tval[off[j] + k + slot] = v;
+    if (e > m) return;
+    const int64_t a = e > 0 ? (int64_t)target[e - 1] + 1 : 0;      // rows without in-edges too
+    const int64_t b = e < m ? (int64_t)target[e] : n;
+    for (int64_t j = a; j <= b; j++) start[j] = e;
 }
 
-constexpr int kRowMax = 4096;
+// position of source j among the in-edges [a, b) (edge numbers, ascending):
+// the first whose source is not below j
+__device__ __forceinline__ int64_t in_lower(const uint32_t* __restrict__ edge, int64_t a, int64_t b,
+                                            uint32_t j, uint32_t k) {
+    const uint64_t e0 = (uint64_t)j * k;           // the first edge of row j
+    while (a < b) {
+        const int64_t mid = (a + b) >> 1;
+        if ((uint64_t)edge[mid] < e0) a = mid + 1;
+        else b = mid;
+    }
+    return a;
+}
+__device__ __forceinline__ bool in_has(const uint32_t* __restrict__ edge, int64_t a, int64_t b,
+                                       uint32_t j, uint32_t k) {
+    return a < b && edge[a] / k == j;
+}
 
-// Sort one row by column (rank by counting, ties by position) into scol/sval
-// at the same offsets, merge the (at most two) summands of each column, write
-// the unique entries at the row start of tcol/tval and their number.  Rows
-// up to kRowMax entries are ranked from LDS, longer rows from global memory.
-__global__ __launch_bounds__(256) void k_sym_row(const int64_t* __restrict__ off,
-                                                 uint32_t* __restrict__ tcol,
-                                                 double* __restrict__ tval,
-                                                 uint32_t* __restrict__ scol,
-                                                 double* __restrict__ sval,
-                                                 int64_t* __restrict__ ucnt) {
-    __shared__ uint32_t c_in[kRowMax];
+// entries of each row: out-edges and in-edges less the pairs in both (one
+// wavefront per row; entry n is 0 for the scan)
+__global__ __launch_bounds__(256) void k_sym_count(const int32_t* __restrict__ idx,
+                                                   const int64_t* __restrict__ start,
+                                                   const uint32_t* __restrict__ edge, int64_t n,
+                                                   int k, int64_t* __restrict__ ucnt) {
+    const int lane = lane_id();
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i > n) return;
+    if (i == n) {
+        if (lane == 0) ucnt[n] = 0;
+        return;
+    }
+    const int64_t a = start[i], b = start[i + 1];
+    int both = 0;
+    for (int t = lane; t < k; t += kWave) {
+        const uint32_t j = (uint32_t)idx[i * k + t];
+        both += in_has(edge, in_lower(edge, a, b, j, (uint32_t)k), b, j, (uint32_t)k) ? 1 : 0;
+    }
+    both = wave_sum(both);
+    if (lane == 0) ucnt[i] = (int64_t)k + (b - a) - both;
+}
+
+// One row per block: k <= 256 out-edges, any number of in-edges.
+__global__ __launch_bounds__(256) void k_sym_row(const int32_t* __restrict__ idx,
+                                                 const double* __restrict__ Pc,
+                                                 const int64_t* __restrict__ start,
+                                                 const uint32_t* __restrict__ edge, int k,
+                                                 const int64_t* __restrict__ rp, double inv2n,
+                                                 uint32_t* __restrict__ col,
+                                                 double* __restrict__ val) {
+    __shared__ uint32_t own[256];           // out-edges' targets, then sorted
+    __shared__ uint32_t sorted[256];
+    __shared__ uint32_t both[257];          // sorted targets that are in-edges too, before each
     __shared__ uint32_t wsum[4];
     const int64_t i = blockIdx.x;
-    const int t = threadIdx.x;
-    const int64_t b = off[i];
-    const int64_t len = off[i + 1] - b;
-    const bool in_lds = len <= kRowMax;
-    if (in_lds)
-        for (int64_t e = t; e < len; e += 256) c_in[e] = tcol[b + e];
-    __syncthreads();
-    for (int64_t e = t; e < len; e += 256) {
-        const uint32_t ce = in_lds ? c_in[e] : tcol[b + e];
-        int64_t r = 0;
-        if (in_lds) {
-            for (int64_t f = 0; f < len; f++) {
-                const uint32_t cf = c_in[f];
-                r += (cf < ce || (cf == ce && f < e)) ? 1 : 0;
-            }
-        } else {
-            for (int64_t f = 0; f < len; f++) {
-                const uint32_t cf = tcol[b + f];
-                r += (cf < ce || (cf == ce && f < e)) ? 1 : 0;
-            }
-        }
-        scol[b + r] = ce;
-        sval[b + r] = tval[b + e];
+    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const int64_t a = start[i], b = start[i + 1], o = rp[i];
+    const uint32_t uk = (uint32_t)k;
+    uint32_t j = 0xFFFFFFFFu;
+    double v = 0.0;
+    if (t < k) {
+        j = (uint32_t)idx[i * k + t];
+        v = Pc[i * k + t];
+        own[t] = j;
     }
-    __threadfence_block();
     __syncthreads();
-    // unique flags and their exclusive prefix, 256 entries at a time
-    int64_t base = 0;
-    for (int64_t c0 = 0; c0 < len; c0 += 256) {
-        const int64_t e = c0 + t;
-        const bool u = e < len && (e == 0 || scol[b + e] != scol[b + e - 1]);
-        const uint64_t bal = ballot64(u);
-        if (lane_id() == 0) wsum[t >> 6] = (uint32_t)__popcll(bal);
-        __syncthreads();
-        int64_t pre = base + (int64_t)__popcll(bal & lanemask_lt());
-        for (int q = 0; q < (t >> 6); q++) pre += wsum[q];
-        if (u) {
-            double v = sval[b + e];
-            if (e + 1 < len && scol[b + e + 1] == scol[b + e]) v = v + sval[b + e + 1];
-            tcol[b + pre] = scol[b + e];
-            tval[b + pre] = v;
-        }
-        const int64_t tot = (int64_t)wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        __syncthreads();
-        base += tot;
+    int r = 0;                              // rank among the out-edges (targets are distinct)
+    if (t < k) {
+        for (int q = 0; q < k; q++) r += own[q] < j ? 1 : 0;
+        sorted[r] = j;
     }
-    if (t == 0) ucnt[i] = base;
-}
-
-__global__ __launch_bounds__(256) void k_sym_write(const int64_t* __restrict__ off,
-                                                   const int64_t* __restrict__ rp,
-                                                   const uint32_t* __restrict__ tcol,
-                                                   const double* __restrict__ tval,
-                                                   uint32_t* __restrict__ col,
-                                                   double* __restrict__ val, double inv2n) {
-    const int64_t i = blockIdx.x;
-    const int64_t b = off[i], o = rp[i], m = rp[i + 1] - rp[i];
-    for (int64_t e = threadIdx.x; e < m; e += 256) {
-        col[o + e] = tcol[b + e];
-        val[o + e] = tval[b + e] * inv2n;
+    // where the target stands among the in-edges, and whether it is one
+    const int64_t at = t < k ? in_lower(edge, a, b, j, uk) : b;
+    const bool dup = t < k && in_has(edge, at, b, j, uk);
+    if (t < 256) both[t] = 0;
+    __syncthreads();
+    if (t < k) both[r] = dup ? 1u : 0u;
+    __syncthreads();
+    // exclusive prefix of the flags over the sorted targets
+    uint32_t f = both[t], x = f;
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) {
+        const uint32_t y = __shfl_up(x, s, kWave);
+        if (lane >= s) x += y;
+    }
+    if (lane == kWave - 1) wsum[w] = x;
+    __syncthreads();
+    for (int q = 0; q < w; q++) x += wsum[q];
+    both[t] = x - f;
+    if (t == 255) both[256] = x;
+    __syncthreads();
+    if (t < k) {
+        const int64_t pos = o + r + (at - a) - both[r];
+        col[pos] = j;
+        val[pos] = (dup ? v + Pc[edge[at]] : v) * inv2n;
+    }
+    for (int64_t e = a + t; e < b; e += 256) {
+        const uint32_t src = edge[e] / uk;
+        int lo = 0, hi = k;                 // out-edges' targets below src
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (sorted[mid] < src) lo = mid + 1;
+            else hi = mid;
+        }
+        if (lo < k && sorted[lo] == src) continue;      // written with the out-edge
+        const int64_t pos = o + (e - a) + lo - both[lo];
+        col[pos] = src;
+        val[pos] = Pc[edge[e]] * inv2n;
     }
 }
 
@@ -987,8 +1054,12 @@ hipError_t knn(const void* X, int64_t n, int32_t D, int32_t x_dtype, int32_t k, 
 
 hipError_t perplexity(const double* d2, int64_t n, int32_t k, double u, double* P, double* beta,
                       hipStream_t s) {
-    k_perplexity<<<dim3((unsigned)ceil_div(n, 256)), 256, 0, s>>>(d2, n, k, log(u), 1e-5, 200, P,
-                                                                  beta);
+    const dim3 g((unsigned)ceil_div(n, 4));
+    const double target = log(u);
+    if (k <= 64) k_perplexity<1><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
+    else if (k <= 128) k_perplexity<2><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
+    else if (k <= 256) k_perplexity<4><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
+    else k_perplexity<0><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
     return hipGetLastError();
 }
 
@@ -996,15 +1067,17 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
                       int64_t** row_ptr_out, uint32_t** col_out, double** val_out, int64_t* nnz_out,
                       hipStream_t s) {
     const int64_t m = n * (int64_t)k;
-    uint32_t *indeg = nullptr, *fill = nullptr, *tcol = nullptr, *scol = nullptr;
-    int64_t *cap = nullptr, *off = nullptr, *tmp = nullptr, *ucnt = nullptr, *rp = nullptr;
-    double *tval = nullptr, *sval = nullptr;
-    uint32_t* col = nullptr;
+    // edge numbers are 32 bits: 2^32 edges need 155 GB here and 86 GB for the
+    // lists they come from
+    if (m >= ((int64_t)1 << 32)) return hipErrorOutOfMemory;
+    uint32_t *key[2] = {nullptr, nullptr}, *edge[2] = {nullptr, nullptr};
+    uint32_t *hist = nullptr, *dtot = nullptr, *col = nullptr;
+    int64_t *start = nullptr, *tmp = nullptr, *ucnt = nullptr, *rp = nullptr;
     double* val = nullptr;
     hipError_t e = hipSuccess;
     auto cleanup = [&]() {
-        for (void* q : {(void*)indeg, (void*)fill, (void*)tcol, (void*)scol, (void*)cap,
-                        (void*)off, (void*)tmp, (void*)ucnt, (void*)tval, (void*)sval})
+        for (void* q : {(void*)key[0], (void*)key[1], (void*)edge[0], (void*)edge[1], (void*)hist,
+                        (void*)dtot, (void*)start, (void*)tmp, (void*)ucnt})
             (void)hipFree(q);
     };
     auto fail = [&](hipError_t x) {
@@ -1012,34 +1085,31 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
         (void)hipFree(rp); (void)hipFree(col); (void)hipFree(val);
         return x;
     };
-    const int64_t nb = ceil_div(n + 1, 1024);
-    if ((e = hipMalloc(&indeg, 4 * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&fill, 4 * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&cap, 8 * (n + 1))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&off, 8 * (n + 1))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&tmp, 8 * (nb + 1))) != hipSuccess) return fail(e);
+    for (int h = 0; h < 2; h++) {
+        if ((e = hipMalloc(&key[h], 4 * m)) != hipSuccess) return fail(e);
+        if ((e = hipMalloc(&edge[h], 4 * m)) != hipSuccess) return fail(e);
+    }
+    if ((e = hipMalloc(&hist, 4 * 256 * (size_t)sort_blocks_for(m))) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&dtot, 4 * 256)) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&start, 8 * (n + 1))) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&tmp, 8 * (size_t)scan_i64_tmp_len(n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&ucnt, 8 * (n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&rp, 8 * (n + 1))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&tcol, 4 * 2 * m)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&tval, 8 * 2 * m)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&scol, 4 * 2 * m)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&sval, 8 * 2 * m)) != hipSuccess) return fail(e);
-    if ((e = hipMemsetAsync(indeg, 0, 4 * n, s)) != hipSuccess) return fail(e);
-    if ((e = hipMemsetAsync(fill, 0, 4 * n, s)) != hipSuccess) return fail(e);
-    k_indeg<<<dim3((unsigned)ceil_div(m, 256)), 256, 0, s>>>(idx, m, indeg);
-    k_row_caps<<<dim3((unsigned)ceil_div(n + 1, 256)), 256, 0, s>>>(indeg, n, k, cap);
-    if ((e = scan_i64_local(cap, n + 1, off, tmp, s)) != hipSuccess) return fail(e);
-    k_sym_fill<<<dim3((unsigned)ceil_div(m, 256)), 256, 0, s>>>(idx, Pc, n, k, off, fill, tcol, tval);
-    k_sym_row<<<dim3((unsigned)n), 256, 0, s>>>(off, tcol, tval, scol, sval, ucnt);
-    if ((e = hipMemsetAsync(ucnt + n, 0, 8, s)) != hipSuccess) return fail(e);
+    if ((e = hipMemcpyAsync(key[0], idx, 4 * m, hipMemcpyDeviceToDevice, s)) != hipSuccess)
+        return fail(e);
+    int bits = 1, at = 0;
+    while (((int64_t)1 << bits) < n) bits++;
+    if ((e = sort_pairs32(key, edge, m, bits, hist, dtot, s, &at)) != hipSuccess) return fail(e);
+    k_in_start<<<dim3((unsigned)ceil_div(m + 1, 256)), 256, 0, s>>>(key[at], m, n, start);
+    k_sym_count<<<dim3((unsigned)ceil_div(n + 1, 4)), 256, 0, s>>>(idx, start, edge[at], n, k, ucnt);
     if ((e = scan_i64_local(ucnt, n + 1, rp, tmp, s)) != hipSuccess) return fail(e);
     int64_t nnz = 0;
     if ((e = hipMemcpyAsync(&nnz, rp + n, 8, hipMemcpyDeviceToHost, s)) != hipSuccess) return fail(e);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&col, 4 * (nnz > 0 ? nnz : 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&val, 8 * (nnz > 0 ? nnz : 1))) != hipSuccess) return fail(e);
-    k_sym_write<<<dim3((unsigned)n), 256, 0, s>>>(off, rp, tcol, tval, col, val,
-                                                  1.0 / (2.0 * (double)n));
+    k_sym_row<<<dim3((unsigned)n), 256, 0, s>>>(idx, Pc, start, edge[at], k, rp,
+                                                1.0 / (2.0 * (double)n), col, val);
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
     cleanup();
