@@ -1,16 +1,17 @@
 // One-time setup on gfx950: the sparse affinity matrix P (paper Section 3.2-3.3).
 //
-//   knn          brute-force k nearest neighbours.  Distance tiles come from
-//                FP32 MFMA (v_mfma_f32_32x32x2f32): d = |x|^2 + |y|^2 - 2 x.y,
-//                or, for uint8 rows, exactly from INT8 MFMA on x - 128;
-//                each row keeps a candidate list (global memory, per-row
-//                threshold in LDS) that is compacted to the K' = k + 32 best
-//                by a block-wide bitonic sort whenever it fills up.  The K'
-//                survivors are re-ranked with exact FP64 distances and ties go
-//                to the smaller index.
+//   knn          brute-force k nearest neighbours.  Distance tiles
+//                d = |x|^2 + |y|^2 - 2 x.y come from the matrix units: FP16
+//                MFMA on rows split into two halves of 11 bits each (three
+//                products), or, for uint8 rows, exactly from INT8 MFMA on
+//                x - 128; each row keeps a candidate list (global memory,
+//                threshold in LDS) that a wavefront cuts to the K' = k + 32
+//                best whenever it fills up.  The K' survivors are re-ranked
+//                with exact FP64 distances and ties go to the smaller index.
 //   perplexity   per-row bisection on the Gaussian precision (FP64)
 //   symmetrize   p_ij = (p_{j|i} + p_{i|j}) / 2n on the union pattern -> CSR
 #include <math.h>
+#include <string.h>
 
 #include <string>
 #include <type_traits>
@@ -23,29 +24,57 @@ namespace {
 
 
 constexpr int kQB = 128;       // query rows per block
-constexpr int kCB = 128;       // candidate columns per tile
-constexpr int kKC = 32;        // reduction chunk staged in LDS (2 threads x 16 per row)
-constexpr int kCap = 512;      // candidate list capacity per row
+constexpr int kCB = 256;       // candidate columns per tile
+constexpr int kCap = 1024;     // candidate list capacity per row
 constexpr int kMargin = 32;    // extra candidates kept for the exact re-rank
+constexpr int kCutAt = 512;    // a list longer than this is cut before the next tile, and
+constexpr int kCutLow = 320;   // with it every list longer than this
+constexpr int kHits = 256;     // passing elements a wavefront gathers per tile
+constexpr int kCutSlack = 32;  // entries beyond the kp best that a cut may leave
+constexpr int kBatch = 1 << 19;   // query rows whose lists exist at a time (4 GB)
+static_assert(kBatch % kQB == 0, "batches are whole blocks");
+static_assert(kCutLow >= 256 + kMargin + kCutSlack && kCutAt + kCB <= kCap,
+              "a cut list is shorter than kCutLow, and a tile's columns fit");
 
 template <typename X> __device__ __forceinline__ float to_f32(X v) { return (float)v; }
 
 template <typename X>
 __device__ __forceinline__ double to_f64(X v) { return (double)v; }
 
+// What the host needs of X: the largest row norm and entry (as float bits,
+// ordered like the floats), and whether a norm is not finite.
+struct RowStats { uint32_t norm, entry, bad; };
+
 template <typename X>
 __global__ __launch_bounds__(256) void k_row_norms(const X* __restrict__ Xm, int64_t n, int D,
-                                                   float* __restrict__ nrm) {
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = lane_id();
-    if (i >= n) return;
-    double a = 0.0;
-    for (int d = lane; d < D; d += 64) {
-        const float v = to_f32(Xm[i * D + d]);
-        a += (double)v * (double)v;
+                                                   float* __restrict__ nrm,
+                                                   RowStats* __restrict__ st) {
+    __shared__ float red[4][3];
+    const int lane = lane_id(), w = threadIdx.x >> 6;
+    float big = 0.f, top = 0.f, bad = 0.f;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + w; i < n; i += (int64_t)gridDim.x * 4) {
+        double a = 0.0;
+        for (int d = lane; d < D; d += 64) {
+            const float v = to_f32(Xm[i * D + d]);
+            a += (double)v * (double)v;
+            top = fmaxf(top, fabsf(v));
+        }
+        a = wave_sum(a);
+        const float f = (float)a;
+        if (lane == 0) nrm[i] = f;
+        if (isfinite(f)) big = fmaxf(big, f);
+        else bad = 1.f;
     }
-    a = wave_sum(a);
-    if (lane == 0) nrm[i] = (float)a;
+    top = wave_max(top);
+    if (lane == 0) { red[w][0] = big; red[w][1] = top; red[w][2] = bad; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < 4; q++)
+            for (int c = 0; c < 3; c++) red[0][c] = fmaxf(red[0][c], red[q][c]);
+        atomicMax(&st->norm, __float_as_uint(red[0][0]));
+        atomicMax(&st->entry, __float_as_uint(red[0][1]));
+        if (red[0][2] > 0.f) atomicOr(&st->bad, 1u);
+    }
 }
 
 // block-wide bitonic sort of 512 uint64 keys in LDS (256 threads)
@@ -67,219 +96,189 @@ __device__ void bitonic512(uint64_t* s) {
     }
 }
 
-__device__ __forceinline__ uint64_t cand_key(float d, uint32_t j) {
-    const float c = d > 0.0f ? d : 0.0f;
-    return ((uint64_t)__float_as_uint(c) << 32) | (uint64_t)j;
-}
-
 // A candidate key is (distance bits << 32 | column): the bits of a
 // non-negative float, or an exact integer distance, both ordered as unsigned
 // integers.  A row's threshold is the distance bits of its kp-th best key
 // (kNoThr while the list is not full).
 constexpr uint32_t kNoThr = 0xFFFFFFFFu;
 
-// Compact the candidate list of local row q to its kp best (sorted).
-__device__ void compact_row(int q, int64_t grow, uint32_t* cnt, uint32_t* thr, uint64_t* cand,
-                            uint64_t* sbuf, int kp) {
-    const int t = threadIdx.x;
-    const int m = (int)cnt[q];
-    uint64_t* lst = cand + grow * kCap;
-    for (int e = t; e < 512; e += 256) sbuf[e] = e < m ? lst[e] : ~0ull;
-    __syncthreads();
-    bitonic512(sbuf);
-    const int keep = m < kp ? m : kp;
-    for (int e = t; e < keep; e += 256) lst[e] = sbuf[e];
-    __syncthreads();
-    if (t == 0) {
-        cnt[q] = (uint32_t)keep;
-        thr[q] = keep == kp ? (uint32_t)(sbuf[kp - 1] >> 32) : kNoThr;
+// One wavefront cuts a list of m keys, kp <= m <= kCap, to its smallest, kp of
+// them or up to `slack` more (in no order), and returns their number;
+// thr: distance bits that none of the kp best exceeds.  The bits of the
+// kp-th distance are found from the top by counts over the wave, until a count
+// within the slack ends the search (about ten of the 32 for a slack of 32);
+// among equal distances at the kp-th place the smallest columns are kept.
+__device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int kp, int slack, uint32_t& thr) {
+    constexpr int kPer = kCap / kWave;
+    const int lane = lane_id();
+    uint32_t d[kPer], j[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; q++) {
+        const int e = lane + q * kWave;
+        const uint64_t c = e < m ? lst[e] : ~0ull;
+        d[q] = (uint32_t)(c >> 32);
+        j[q] = (uint32_t)c;
     }
-    __syncthreads();
-}
-
-// After a tile: compact the rows whose lists could overflow during the next
-// one.  Threads 0..kQB-1 test their row and the waves' ballots go through LDS,
-// so the block walks only the rows that need it (usually none).
-__device__ void compact_full_rows(int64_t q0, uint32_t* cnt, uint32_t* thr, uint64_t* cand,
-                                  uint64_t* sbuf, uint64_t* need, int kp) {
-    static_assert(kQB == 2 * 64, "two waves test the rows");
-    const int t = threadIdx.x;
-    if (t < kQB) {
-        const uint64_t b = ballot64(cnt[t] > (uint32_t)(kCap - kCB));
-        if (lane_id() == 0) need[t >> 6] = b;
-    }
-    __syncthreads();
-    // need[] is next written after the next tile's barriers
-    const uint64_t m0 = need[0], m1 = need[1];
-    for (int h = 0; h < 2; h++) {
-        uint64_t m = h ? m1 : m0;
-        while (m) {
-            const int q = 64 * h + __ffsll((long long)m) - 1;
-            m &= m - 1;
-            compact_row(q, q0 + q, cnt, thr, cand, sbuf, kp);
+    auto count = [&](auto&& in) {
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; q++) c += __popcll(ballot64(in(q)));
+        return c;
+    };
+    // the kept are d < end, or d == end and j <= last
+    uint32_t end = 0, last = 0xFFFFFFFEu;
+    bool found = false;
+    for (int b = 31; b >= 0; b--) {
+        const uint32_t u = end | (1u << b);
+        const int c = count([&](int q) { return d[q] < u; });
+        if (c < kp) {
+            end = u;                // the largest value with fewer than kp below it
+        } else if (c <= kp + slack) {
+            end = u - 1;
+            found = true;
+            break;
         }
     }
-}
-
-// Candidate generation.  One block (four waves) per kQB query rows sweeps all
-// candidate columns in tiles of kCB; the 128 x 128 distance tile comes from
-// FP32 MFMA (v_mfma_f32_32x32x2f32), each wave owning a 64 x 64 quarter as
-// 2 x 2 MFMA tiles.  X is staged through LDS in chunks of kKC dimensions,
-// k-major so that a fragment read is 32 consecutive words, with the next
-// chunk's global loads in flight while the current one is multiplied.
-typedef float v16f __attribute__((ext_vector_type(16)));
-
-template <typename X, bool VEC>
-__global__ __launch_bounds__(256) void k_knn_candidates(const X* __restrict__ Xm, int64_t n,
-                                                        int D, const float* __restrict__ nrm,
-                                                        int kp, uint64_t* __restrict__ cand,
-                                                        uint32_t* __restrict__ cand_cnt,
-                                                        uint32_t* __restrict__ cand_thr) {
-    static_assert(!VEC || std::is_same<X, float>::value, "16-byte loads of FP32 rows");
-    // [buffer][k][row]: rows 0..127 queries, 128..255 candidates
-    __shared__ float S[2][kKC][2 * kQB + 4];
-    __shared__ uint32_t cnt[kQB];
-    __shared__ uint32_t thr[kQB];
-    __shared__ float nq[kQB];
-    __shared__ float nc[kCB];
-    __shared__ uint64_t sbuf[512];
-    __shared__ uint64_t need[2];
-
-    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
-    const int wr = 64 * (w >> 1), wc = 64 * (w & 1);
-    const int64_t q0 = (int64_t)blockIdx.x * kQB;
-    if (t < kQB) {
-        cnt[t] = 0;
-        thr[t] = kNoThr;
-        nq[t] = q0 + t < n ? nrm[q0 + t] : 0.0f;
-    }
-    const int nk = (D + kKC - 1) / kKC;
-
-    for (int64_t c0 = 0; c0 < n; c0 += kCB) {
-        v16f acc[2][2];
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-            for (int b = 0; b < 2; b++)
-#pragma unroll
-                for (int v = 0; v < 16; v++) acc[a][b][v] = 0.0f;
-        if (t < kCB) nc[t] = c0 + t < n ? nrm[c0 + t] : 0.0f;
-        // query rows q0.. as staging rows 0..127, candidates c0.. as 128..255:
-        // thread t loads row t / 2 of the queries (h = 0) and of the candidates (h = 1)
-        float g[kKC];                           // kKC / 2 query and kKC / 2 candidate values
-        const int64_t rq = q0 + (t >> 1), rc = c0 + (t >> 1);
-        const bool okq = rq < n, okc = rc < n;
-        constexpr int kH = kKC / 2;                     // dimensions per thread and row
-        const X* pq = Xm + (okq ? rq : 0) * (int64_t)D + kH * (t & 1);
-        const X* pc = Xm + (okc ? rc : 0) * (int64_t)D + kH * (t & 1);
-        auto fetch = [&](int k0) {
-            if constexpr (VEC) {
-                // FP32 rows, D a multiple of 4, 16-byte aligned: 16-byte loads;
-                // a group of four past the row's end reads the row's first four
-                // (D >= 4), a row past n reads row 0, and both are zeroed
-                const int lim = D - k0 - kH * (t & 1);          // elements left in the row
-#pragma unroll
-                for (int u = 0; u < kH; u += 4) {
-                    const bool in = u < lim;                    // lim is a multiple of 4
-                    const int off = in ? k0 + u : -kH * (t & 1);   // else the row's start
-                    const float4 a = *reinterpret_cast<const float4*>(pq + off);
-                    const float4 c = *reinterpret_cast<const float4*>(pc + off);
-                    const bool iq = okq && in, ic = okc && in;
-                    g[u] = iq ? a.x : 0.0f;
-                    g[u + 1] = iq ? a.y : 0.0f;
-                    g[u + 2] = iq ? a.z : 0.0f;
-                    g[u + 3] = iq ? a.w : 0.0f;
-                    g[kH + u] = ic ? c.x : 0.0f;
-                    g[kH + u + 1] = ic ? c.y : 0.0f;
-                    g[kH + u + 2] = ic ? c.z : 0.0f;
-                    g[kH + u + 3] = ic ? c.w : 0.0f;
-                }
-            } else {
-                const int lim = D - k0 - kH * (t & 1);          // elements left in the row
-#pragma unroll
-                for (int e = 0; e < kH; e++) {
-                    g[e] = (okq && e < lim) ? to_f32(pq[k0 + e]) : 0.0f;
-                    g[kH + e] = (okc && e < lim) ? to_f32(pc[k0 + e]) : 0.0f;
-                }
+    if (!found) {
+        const int below = count([&](int q) { return d[q] < end; });
+        const int equal = count([&](int q) { return d[q] == end && j[q] != 0xFFFFFFFFu; });
+        if (equal > kp - below + slack) {
+            last = 0;
+            for (int b = 30; b >= 0; b--) {
+                const uint32_t u = last | (1u << b);
+                if (count([&](int q) { return d[q] == end && j[q] < u; }) < kp - below) last = u;
             }
-        };
-        auto store = [&](int buf) {
-            const int row = t >> 1, kb = kH * (t & 1);
-#pragma unroll
-            for (int e = 0; e < kH; e++) {
-                S[buf][kb + e][row] = g[e];
-                S[buf][kb + e][kQB + row] = g[kH + e];
-            }
-        };
-        __syncthreads();                       // previous tile's readers are done
-        fetch(0);
-        store(0);
-        __syncthreads();
-        for (int kc = 0; kc < nk; kc++) {
-            const int buf = kc & 1;
-            if (kc + 1 < nk) fetch((kc + 1) * kKC);
-#pragma unroll
-            for (int kk = 0; kk < kKC; kk += 2) {
-                const int k = kk + (lane >> 5);
-                const float a0 = S[buf][k][wr + (lane & 31)];
-                const float a1 = S[buf][k][wr + 32 + (lane & 31)];
-                const float b0 = S[buf][k][kQB + wc + (lane & 31)];
-                const float b1 = S[buf][k][kQB + wc + 32 + (lane & 31)];
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-            }
-            if (kc + 1 < nk) store(buf ^ 1);
-            __syncthreads();
         }
-        // filter, one 32 x 32 MFMA tile at a time through a wave-private LDS
-        // tile (the staging buffer is free after the last chunk): element v of
-        // tile (a, b) is row 8(v / 4) + 4(lane / 32) + v % 4, column lane % 32
-        float* T = &S[0][0][0] + w * (32 * 33);
-        const int cj = lane & 31;
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-            for (int b = 0; b < 2; b++) {
-#pragma unroll
-                for (int v = 0; v < 16; v++)
-                    T[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 33 + cj] = acc[a][b][v];
-                const int cl = wc + 32 * b + cj;
-                const int64_t gc = c0 + cl;
-                const float ncv = nc[cl];
-#pragma unroll 2
-                for (int m = 0; m < 16; m++) {
-                    const int i = 2 * m + (lane >> 5);
-                    const int rl = wr + 32 * a + i;
-                    const int64_t gr = q0 + rl;
-                    const float d = nq[rl] + ncv - 2.0f * T[i * 33 + cj];
-                    const uint64_t key = cand_key(d, (uint32_t)gc);
-                    if (gr < n && gc < n && gc != gr && (uint32_t)(key >> 32) <= thr[rl]) {
-                        const uint32_t pos = atomicAdd(&cnt[rl], 1u);
-                        cand[gr * kCap + pos] = key;
-                    }
-                }
-            }
-        __syncthreads();
-        compact_full_rows(q0, cnt, thr, cand, sbuf, need, kp);
     }
-    for (int q = 0; q < kQB; q++) {
-        if (q0 + q < n) compact_row(q, q0 + q, cnt, thr, cand, sbuf, kp);
+    int at = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; q++) {
+        const bool keep = d[q] < end || (d[q] == end && j[q] <= last);
+        const uint64_t b = ballot64(keep);
+        if (keep)
+            lst[at + __popcll(b & lanemask_lt())] = ((uint64_t)d[q] << 32) | (uint64_t)j[q];
+        at += __popcll(b);
     }
-    if (t < kQB && q0 + t < n) {
-        cand_cnt[q0 + t] = cnt[t];
-        cand_thr[q0 + t] = thr[t];
-    }
+    thr = end;
+    return at;
 }
 
-// Exact candidates for uint8 rows: x' = x - 128 as int8 through
-// v_mfma_i32_32x32x16_i8, so that every distance |x'|^2 + |y'|^2 - 2 x'.y'
-// is an exact int32 (|x'| <= 128, D <= 32768).  Same blocking as the FP32
-// kernel: 128 x 128 tile per block, a 64 x 64 quarter per wave; X staged in
-// LDS row-major, kKB bytes of each row per chunk.
-typedef int v16i __attribute__((ext_vector_type(16)));
-constexpr int kKB = 64;
+// The matrix operands of a run of rows, as the MFMA units take them: a
+// fragment is 32 rows times one instruction's depth, 16 bytes per lane (lane l:
+// row l % 32, half l / 32 of the depth), 1 KB in lane order.  Fragments lie by
+// [32 rows][depth step][part], so a fragment moves to LDS and to registers in
+// whole cache lines and without bank conflicts.  Rows and depth are padded
+// with zeros.
+//
+// FP16: a row times the power of two `scale` is split into two halves of 11
+// bits each, x = hi + lo, and x.y = hi.hi + hi.lo + lo.hi up to 2^-22 per
+// product.
+struct PartsF16 {
+    using Vec = _Float16 __attribute__((ext_vector_type(8)));
+    using Acc = float __attribute__((ext_vector_type(16)));
+    using Num = float;
+    static constexpr int kDepth = 16, kParts = 2, kSteps = 2;
+    static __device__ __forceinline__ void product(const Vec* a, const Vec* b, Acc& c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[1], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], b[0], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[0], c, 0, 0, 0);
+    }
+    // |y|^2 - 2 x.y, with f = -2 / scale^2
+    static __device__ __forceinline__ float part_dist(float dot, float f, float ny) {
+        return fmaf(dot, f, ny);
+    }
+    // the bound on it that keeps a candidate, from a threshold and |x|^2
+    static __device__ __forceinline__ float bound(uint32_t thr, float nx) {
+        return thr == kNoThr ? INFINITY : __uint_as_float(thr) - nx;
+    }
+    static __device__ __forceinline__ uint32_t bits(float part, float nx) {
+        const float d = nx + part;
+        return __float_as_uint(d > 0.0f ? d : 0.0f);
+    }
+    static __device__ __forceinline__ float none() { return -INFINITY; }
+    static __device__ __forceinline__ float far() { return INFINITY; }
+};
+
+// INT8: x - 128 for uint8 rows, every distance an exact int32 (D <= 32768).
+struct PartsI8 {
+    using Vec = int __attribute__((ext_vector_type(4)));
+    using Acc = int __attribute__((ext_vector_type(16)));
+    using Num = int32_t;
+    static constexpr int kDepth = 32, kParts = 1, kSteps = 4;
+    static __device__ __forceinline__ void product(const Vec* a, const Vec* b, Acc& c) {
+        c = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[0], b[0], c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int32_t part_dist(int32_t dot, float, int32_t ny) {
+        return ny - 2 * dot;
+    }
+    static __device__ __forceinline__ int32_t bound(uint32_t thr, int32_t nx) {
+        return thr == kNoThr ? 0x7FFFFFFF : (int32_t)thr - nx;
+    }
+    static __device__ __forceinline__ uint32_t bits(int32_t part, int32_t nx) {
+        return (uint32_t)(nx + part);
+    }
+    static __device__ __forceinline__ int32_t none() { return -0x7FFFFFFF - 1; }
+    static __device__ __forceinline__ int32_t far() { return 0x7FFFFFFF; }   // a padding row's dot is 0
+};
+
+inline int64_t pad_rows(int64_t n) { return ceil_div(n, kCB) * kCB; }
+template <typename F> inline int pad_steps(int D) {
+    return (int)(ceil_div(D, F::kDepth * F::kSteps) * F::kSteps);
+}
+template <typename F> inline size_t packed_bytes(int64_t n, int D) {
+    return (size_t)(pad_rows(n) / 32) * pad_steps<F>(D) * F::kParts * 1024;
+}
+
+// One thread per 16-byte piece of the hi (and lo) fragments.
+template <typename X>
+__global__ __launch_bounds__(256) void k_pack_f16(const X* __restrict__ Xm, int64_t n, int64_t np,
+                                                  int D, int steps, float scale,
+                                                  _Float16* __restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= np * steps * 2) return;
+    const int lane = (int)(e & 63);
+    const int64_t f = e >> 6;                               // [32 rows][step]
+    const int64_t row = (f / steps) * 32 + (lane & 31);
+    const int d0 = (int)(f % steps) * 16 + 8 * (lane >> 5);
+    PartsF16::Vec hi, lo;
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        const float v = row < n && d0 + q < D ? to_f32(Xm[row * D + d0 + q]) * scale : 0.f;
+        hi[q] = (_Float16)v;
+        lo[q] = (_Float16)(v - (float)hi[q]);
+    }
+    PartsF16::Vec* o = reinterpret_cast<PartsF16::Vec*>(out) + f * 128 + lane;
+    o[0] = hi;
+    o[64] = lo;
+}
+
+__global__ __launch_bounds__(256) void k_pack_i8(const uint8_t* __restrict__ Xm, int64_t n,
+                                                 int64_t np, int D, int steps,
+                                                 uint4* __restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= np * steps * 2) return;
+    const int lane = (int)(e & 63);
+    const int64_t f = e >> 6;
+    const int64_t row = (f / steps) * 32 + (lane & 31);
+    const int d0 = (int)(f % steps) * 32 + 16 * (lane >> 5);
+    union {
+        uint4 q;
+        uint8_t b[16];
+    } v;
+    const uint8_t* src = Xm + row * D + d0;
+    if (row < n && d0 + 16 <= D && (reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
+        v.q = *reinterpret_cast<const uint4*>(src);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 16; q++) v.b[q] = row < n && d0 + q < D ? src[q] : (uint8_t)128;
+    }
+    // x - 128 as int8 is the byte with its top bit flipped; padding becomes 0
+    v.q.x ^= 0x80808080u;
+    v.q.y ^= 0x80808080u;
+    v.q.z ^= 0x80808080u;
+    v.q.w ^= 0x80808080u;
+    out[e] = v.q;
+}
 
 __global__ __launch_bounds__(256) void k_row_norms_i8(const uint8_t* __restrict__ Xm, int64_t n,
                                                       int D, int32_t* __restrict__ nrm) {
@@ -295,166 +294,313 @@ __global__ __launch_bounds__(256) void k_row_norms_i8(const uint8_t* __restrict_
     if (lane == 0) nrm[i] = a;
 }
 
-__global__ __launch_bounds__(256) void k_knn_candidates_i8(const uint8_t* __restrict__ Xm,
-                                                           int64_t n, int D,
-                                                           const int32_t* __restrict__ nrm,
-                                                           int kp, uint64_t* __restrict__ cand,
-                                                           uint32_t* __restrict__ cand_cnt,
-                                                           uint32_t* __restrict__ cand_thr) {
-    // [buffer][row][k]: rows 0..127 queries, 128..255 candidates; 16 bytes pad
-    __shared__ __attribute__((aligned(16))) int8_t S[2][2 * kQB][kKB + 16];
-    __shared__ int32_t T[4][32][33];
-    __shared__ uint32_t cnt[kQB];
-    __shared__ uint32_t thr[kQB];
-    __shared__ int32_t nq[kQB];
-    __shared__ int32_t nc[kCB];
-    __shared__ uint64_t sbuf[512];
-    __shared__ uint64_t need[2];
+// Candidate generation.  A block of eight wavefronts owns kQB query rows and
+// sweeps all candidates in tiles of kCB; each wavefront computes a 64 x 64
+// part as 2 x 2 MFMA tiles.  The depth runs in stages of F::kSteps
+// instructions, staged by loads straight into LDS, the next stage (of this
+// tile or of the next) in flight while one is multiplied; with HOLD the
+// queries' fragments stay in LDS (depth up to 128 for FP16), else they are
+// staged too.  The distances are filtered from the accumulators: per element
+// one multiply-add and one comparison with the row's bound, and only elements
+// that pass take the way to the lists.
+//
+// Three FP16 products at 400,000 x 128 are 123 TFLOP, 50 ms of the matrix
+// units; the kernel takes 150: 100 with the loads and the lists taken away
+// (barriers of the stages, LDS latency, the filter), 25 more for loads that
+// come late, 25 for the lists (3,000 entries a row on the way to the last
+// 182).  Tried: stages half as deep, three in flight, 165; lists cut only at
+// 768 entries, 153.  The FP32 MFMA kernel of 128 x 128 tiles, filtered
+// through LDS, that this replaces took 605; at 70,000 x 784 bytes 6.7 ms where
+// the INT8 one took 46.6.
+typedef __attribute__((address_space(1))) const void GlobalPtr;
+typedef __attribute__((address_space(3))) void LdsPtr;
 
-    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
-    const int wr = 64 * (w >> 1), wc = 64 * (w & 1);
-    const int64_t q0 = (int64_t)blockIdx.x * kQB;
+template <typename F, bool HOLD>
+__global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__ packed,
+                                                        int64_t n, int steps,
+                                                        const typename F::Num* __restrict__ nrm,
+                                                        float f, int64_t q_first, int kp,
+                                                        uint64_t* __restrict__ cand,
+                                                        uint32_t* __restrict__ cand_cnt,
+                                                        uint32_t* __restrict__ cand_thr) {
+    using Vec = typename F::Vec;
+    using Num = typename F::Num;
+    constexpr int kFrag = 1024;
+    constexpr int kQF = kQB / 32, kCF = kCB / 32;          // fragments of 32 rows
+    constexpr int kStageC = kCF * F::kSteps * F::kParts;   // fragments of a stage
+    constexpr int kStageQ = kQF * F::kSteps * F::kParts;
+    constexpr int kHoldQ = kQF * 8 * F::kParts;            // up to 8 steps held
+    __shared__ __attribute__((aligned(16))) char C[2][kStageC * kFrag];
+    __shared__ __attribute__((aligned(16))) char Q[(HOLD ? kHoldQ : 2 * kStageQ) * kFrag];
+    __shared__ uint32_t cnt[kQB];
+    __shared__ __attribute__((aligned(16))) Num bnd[kQB];
+    __shared__ Num nq[kQB];
+    __shared__ uint32_t thr[kQB];          // every column left out so far is further
+    struct Hit { Num part; uint32_t at; };                  // row << 8 | column, in the tile
+    __shared__ Hit hits[8][kHits];
+
+    const int t = threadIdx.x, lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wr = w >> 2, wc = w & 3;                      // 64 query rows, 64 columns
+    const int64_t q0 = q_first + (int64_t)blockIdx.x * kQB; // q0 - q_first indexes the lists
+    const int nst = steps / F::kSteps;
+    const int64_t tiles = (n + kCB - 1) / kCB;
     if (t < kQB) {
         cnt[t] = 0;
         thr[t] = kNoThr;
-        nq[t] = q0 + t < n ? nrm[q0 + t] : 0;
+        nq[t] = q0 + t < n ? nrm[q0 + t] : Num(0);
+        bnd[t] = q0 + t < n ? F::bound(kNoThr, Num(0)) : F::none();
     }
-    const int nk = (D + kKB - 1) / kKB;
-    const int seg = 16 * (t & 3);                  // this thread's 16 bytes of a row
+    // A stage takes kPer = 4 fragments of each 32 rows.  Wavefront w loads the
+    // fragments w, w + 8, ... of a stage: fragment w % 4 of the rows w / 4,
+    // w / 4 + 2, ...
+    constexpr int kPer = F::kSteps * F::kParts;
+    static_assert(kPer == 4 && kStageC % 8 == 0 && kStageQ % 8 == 0, "whole rounds of loads");
+    const int64_t frag_row = (int64_t)steps * F::kParts * kFrag;   // bytes of 32 rows
+    const char* const mine = packed + (w >> 2) * frag_row + (w & 3) * kFrag + lane * 16;
+    auto to_lds = [&](const char* src, char* dst) {
+        __builtin_amdgcn_global_load_lds((GlobalPtr*)src, (LdsPtr*)dst, 16, 0, 0);
+    };
+    auto fetch = [&](int64_t tile, int s, int buf) {
+        const char* c = mine + tile * (kCF * frag_row) + s * (kPer * kFrag);
+#pragma unroll
+        for (int y = 0; y < kStageC / 8; y++)
+            to_lds(c + y * (2 * frag_row), C[buf] + (w + 8 * y) * kFrag);
+        if constexpr (!HOLD) {
+            const char* q = mine + (q0 / 32) * frag_row + s * (kPer * kFrag);
+#pragma unroll
+            for (int y = 0; y < kStageQ / 8; y++)
+                to_lds(q + y * (2 * frag_row), Q + (buf * kStageQ + w + 8 * y) * kFrag);
+        }
+    };
+    // every load and store of the block is done, in LDS and in the lists
+    auto settle = [&]() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    auto cut = [&]() {
+        // Lists that could overflow during the next tile are cut, 16 rows per
+        // wavefront.  The block waits for a wavefront that cuts, so once any
+        // list is that long every long one is cut.
+        const uint64_t full =
+            ballot64(cnt[lane] > (uint32_t)kCutAt || cnt[lane + kWave] > (uint32_t)kCutAt);
+        if (full == 0) return;
+        uint64_t todo = ballot64(lane < 16 && cnt[w * 16 + (lane & 15)] > (uint32_t)kCutLow);
+        while (todo) {
+            const int q = w * 16 + __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            uint32_t end;
+            const int m = cut_list(cand + (q0 - q_first + q) * (int64_t)kCap, (int)cnt[q], kp,
+                                   kCutSlack, end);
+            if (lane == 0) {
+                end = end < thr[q] ? end : thr[q];
+                cnt[q] = (uint32_t)m;
+                thr[q] = end;
+                bnd[q] = F::bound(end, nq[q]);
+            }
+        }
+    };
 
-    for (int64_t c0 = 0; c0 < n; c0 += kCB) {
-        v16i acc[2][2];
+    if constexpr (HOLD) {
+        // all steps of the queries, by [32 rows][8 steps][part]
+        for (int x = w; x < kQF * steps * F::kParts; x += 8) {
+            const int rb = x / (steps * F::kParts), rest = x % (steps * F::kParts);
+            to_lds(packed + (q0 / 32 + rb) * frag_row + rest * kFrag + lane * 16,
+                   Q + (rb * 8 * F::kParts + rest) * kFrag);
+        }
+    }
+    fetch(0, 0, 0);
+    settle();
+    int buf = 0;
+    for (int64_t tile = 0; tile < tiles; tile++) {
+        typename F::Acc acc[2][2];
 #pragma unroll
         for (int a = 0; a < 2; a++)
 #pragma unroll
             for (int b = 0; b < 2; b++)
 #pragma unroll
                 for (int v = 0; v < 16; v++) acc[a][b][v] = 0;
-        if (t < kCB) nc[t] = c0 + t < n ? nrm[c0 + t] : 0;
-        // thread t stages staging rows t / 4 + 64 h (h = 0..3), bytes seg..seg+15
-        uint4 g[4];
-        auto fetch = [&](int k0) {
+        const int64_t c0 = tile * kCB + 64 * wc + (lane & 31);
+        const Num nc0 = c0 < n ? nrm[c0] : F::far(), nc1 = c0 + 32 < n ? nrm[c0 + 32] : F::far();
+        auto stage = [&](int s) {
+            if (s + 1 < nst) fetch(tile, s + 1, buf ^ 1);
+            else if (tile + 1 < tiles) fetch(tile + 1, 0, buf ^ 1);
+            const char* cs = C[buf] + 2 * wc * kPer * kFrag + lane * 16;
+            const char* qs = HOLD ? Q + (2 * wr * 8 * F::kParts + s * kPer) * kFrag + lane * 16
+                                  : Q + (buf * kStageQ + 2 * wr * kPer) * kFrag + lane * 16;
+            constexpr int kQRow = HOLD ? 8 * F::kParts : kPer;     // fragments of 32 queries
 #pragma unroll
-            for (int h = 0; h < 4; h++) {
-                const int row = (t >> 2) + 64 * h;
-                const int64_t gr = row < kQB ? q0 + row : c0 + (row - kQB);
-                const int kb = k0 + seg;
-                union {
-                    uint4 q;
-                    uint8_t b[16];
-                } v;
-                const uint8_t* src = Xm + (gr < n ? gr : 0) * (int64_t)D + kb;
-                if (gr < n && kb + 16 <= D && ((reinterpret_cast<uintptr_t>(src) & 15u) == 0)) {
-                    v.q = *reinterpret_cast<const uint4*>(src);
-                } else {
+            for (int k = 0; k < F::kSteps; k++) {
+                Vec av[2][F::kParts], bv[2][F::kParts];
 #pragma unroll
-                    for (int e = 0; e < 16; e++)
-                        v.b[e] = (gr < n && kb + e < D) ? src[e] : (uint8_t)128;   // x' = 0
-                }
-                // centre: x - 128 as int8 is the byte with its top bit flipped
-                v.q.x ^= 0x80808080u;
-                v.q.y ^= 0x80808080u;
-                v.q.z ^= 0x80808080u;
-                v.q.w ^= 0x80808080u;
-                g[h] = v.q;
+                for (int p = 0; p < F::kParts; p++)
+#pragma unroll
+                    for (int h = 0; h < 2; h++) {
+                        const int x = k * F::kParts + p;
+                        av[h][p] = *reinterpret_cast<const Vec*>(qs + (h * kQRow + x) * kFrag);
+                        bv[h][p] = *reinterpret_cast<const Vec*>(cs + (h * kPer + x) * kFrag);
+                    }
+#pragma unroll
+                for (int a = 0; a < 2; a++)
+#pragma unroll
+                    for (int b = 0; b < 2; b++) F::product(av[a], bv[b], acc[a][b]);
             }
+            settle();
+            buf ^= 1;
         };
-        auto store = [&](int buf) {
-#pragma unroll
-            for (int h = 0; h < 4; h++)
-                *reinterpret_cast<uint4*>(&S[buf][(t >> 2) + 64 * h][seg]) = g[h];
-        };
-        __syncthreads();                       // previous tile's readers are done
-        fetch(0);
-        store(0);
-        __syncthreads();
-        for (int kc = 0; kc < nk; kc++) {
-            const int buf = kc & 1;
-            if (kc + 1 < nk) fetch((kc + 1) * kKB);
-#pragma unroll
-            for (int kk = 0; kk < kKB; kk += 16) {
-                const int kb = kk + 8 * (lane >> 5);
-                const long a0 = *reinterpret_cast<const long*>(&S[buf][wr + (lane & 31)][kb]);
-                const long a1 = *reinterpret_cast<const long*>(&S[buf][wr + 32 + (lane & 31)][kb]);
-                const long b0 = *reinterpret_cast<const long*>(&S[buf][kQB + wc + (lane & 31)][kb]);
-                const long b1 =
-                    *reinterpret_cast<const long*>(&S[buf][kQB + wc + 32 + (lane & 31)][kb]);
-                acc[0][0] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a0, b0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a0, b1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a1, b0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_i32_32x32x16_i8(a1, b1, acc[1][1], 0, 0, 0);
-            }
-            if (kc + 1 < nk) store(buf ^ 1);
-            __syncthreads();
+        stage(0);
+        // the previous tile's candidates are all in the lists now; the next
+        // stage's barrier, or one more, shows the new bounds to everybody
+        if (tile > 0) {
+            cut();
+            if (nst == 1) __syncthreads();
         }
-        // filter through a wave-private LDS tile, as in the FP32 kernel
-        const int cj = lane & 31;
+        for (int s = 1; s < nst; s++) stage(s);
+        // filter: element v of tile (a, b) is row 8 (v / 4) + 4 (lane / 32) + v % 4,
+        // column lane % 32.  Each lane collects a bit per element that passes;
+        // those few are picked out lane by lane, gather in LDS and go to the
+        // lists together.
+        int qn = 0;
+        auto drain = [&]() {
+            __builtin_amdgcn_wave_barrier();
+            for (int x = lane; x < qn; x += kWave) {
+                const Hit h = hits[w][x];
+                const uint32_t rl = h.at >> 8;
+                const int64_t gc = tile * kCB + (h.at & 255u);
+                if (gc < n && gc != q0 + rl) {
+                    const uint32_t pos = atomicAdd(&cnt[rl], 1u);
+                    cand[(q0 - q_first + rl) * kCap + pos] =
+                        ((uint64_t)F::bits(h.part, nq[rl]) << 32) | (uint64_t)gc;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            qn = 0;
+        };
 #pragma unroll
-        for (int a = 0; a < 2; a++)
+        for (int a = 0; a < 2; a++) {
+            Num g[16];
+#pragma unroll
+            for (int v = 0; v < 16; v++)
+                g[v] = bnd[64 * wr + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)];
 #pragma unroll
             for (int b = 0; b < 2; b++) {
+                const Num ncv = b ? nc1 : nc0;
+                uint32_t pass = 0;
 #pragma unroll
-                for (int v = 0; v < 16; v++)
-                    T[w][8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)][cj] = acc[a][b][v];
-                const int cl = wc + 32 * b + cj;
-                const int64_t gc = c0 + cl;
-                const int32_t ncv = nc[cl];
-#pragma unroll 2
-                for (int m = 0; m < 16; m++) {
-                    const int i = 2 * m + (lane >> 5);
-                    const int rl = wr + 32 * a + i;
-                    const int64_t gr = q0 + rl;
-                    const int32_t d = nq[rl] + ncv - 2 * T[w][i][cj];
-                    if (gr < n && gc < n && gc != gr && (uint32_t)d <= thr[rl]) {
-                        const uint32_t pos = atomicAdd(&cnt[rl], 1u);
-                        cand[gr * kCap + pos] = ((uint64_t)(uint32_t)d << 32) | (uint64_t)gc;
+                for (int v = 15; v >= 0; v--)
+                    pass = pass + pass + (F::part_dist(acc[a][b][v], f, ncv) <= g[v] ? 1u : 0u);
+                uint64_t m;
+                while ((m = ballot64(pass != 0u)) != 0) {
+                    const int c = __popcll(m);
+                    if (qn + c > kHits) drain();
+                    const uint32_t v = (uint32_t)__ffs((int)pass) - 1u;
+                    // acc[a][b][v], by a tree of selects between values
+                    auto pick = [](bool c, Num hi, Num lo) { return c ? hi : lo; };
+                    const bool v0 = (v & 1u) != 0, v1 = (v & 2u) != 0, v2 = (v & 4u) != 0,
+                               v3 = (v & 8u) != 0;
+                    auto of4 = [&](int q) {
+                        return pick(v1, pick(v0, acc[a][b][q + 3], acc[a][b][q + 2]),
+                                    pick(v0, acc[a][b][q + 1], acc[a][b][q]));
+                    };
+                    const Num x = pick(v3, pick(v2, of4(12), of4(8)), pick(v2, of4(4), of4(0)));
+                    if (pass != 0u) {
+                        const uint32_t rl = (uint32_t)(64 * wr + 32 * a + 4 * (lane >> 5)) +
+                                            8u * (v >> 2) + (v & 3u);
+                        const uint32_t cl = (uint32_t)(64 * wc + 32 * b + (lane & 31));
+                        hits[w][qn + __builtin_amdgcn_mbcnt_hi(
+                                         (uint32_t)(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
+                            Hit{F::part_dist(x, f, ncv), rl << 8 | cl};
+                        pass &= pass - 1u;
                     }
+                    qn += c;
                 }
             }
-        __syncthreads();
-        compact_full_rows(q0, cnt, thr, cand, sbuf, need, kp);
+        }
+        if (qn > 0) drain();
     }
-    for (int q = 0; q < kQB; q++) {
-        if (q0 + q < n) compact_row(q, q0 + q, cnt, thr, cand, sbuf, kp);
-    }
+    __syncthreads();
     if (t < kQB && q0 + t < n) {
-        cand_cnt[q0 + t] = cnt[t];
-        cand_thr[q0 + t] = thr[t];
+        cand_cnt[q0 - q_first + t] = cnt[t];
+        cand_thr[q0 - q_first + t] = thr[t];
+    }
+}
+
+// Cuts every list to its kp best (one wavefront per row).
+__global__ __launch_bounds__(256) void k_knn_cut(uint64_t* __restrict__ cand, int64_t rows,
+                                                 int64_t n, int kp,
+                                                 uint32_t* __restrict__ cand_cnt,
+                                                 uint32_t* __restrict__ cand_thr) {
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= rows) return;
+    const int m = __builtin_amdgcn_readfirstlane((int)cand_cnt[i]);
+    if (m < kp) return;
+    uint32_t end;
+    const int kept = cut_list(cand + i * kCap, m, kp, 0, end);
+    if (lane_id() == 0) {
+        end = end < cand_thr[i] ? end : cand_thr[i];
+        cand_cnt[i] = (uint32_t)kept;
+        cand_thr[i] = kp == n - 1 ? kNoThr : end;      // all of them are in the list
     }
 }
 
 // Exact re-rank: FP64 distances of the candidates, sorted by (d, j); emits
-// the first k.  flag[i] = 1 when the error bound of the FP32 pre-selection
-// does not prove that the k best are among the candidates.
+// the first k.  flag[i] = 1 when the error bound of the pre-selection does not
+// prove that the k best are among the candidates.
+//
+// A wavefront takes 64 candidates at a time: their rows pass through LDS in
+// slices of kSlice dimensions, read along the rows, and each lane sums its
+// candidate's terms in order of the dimension.  (A lane reading its own row
+// touched 64 cache lines per load: 44 ms at 400,000 x 128.)
+constexpr int kSlice = 32;
+
 template <typename X>
-__global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, int D,
-                                                    int k, const uint64_t* __restrict__ cand,
+__global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, int64_t q_first,
+                                                    int D, int k,
+                                                    const uint64_t* __restrict__ cand,
                                                     const uint32_t* __restrict__ cand_cnt,
                                                     const uint32_t* __restrict__ cand_thr,
                                                     const float* __restrict__ nrm, float nrm_max,
-                                                    int32_t* __restrict__ idx,
+                                                    float scale, int32_t* __restrict__ idx,
                                                     double* __restrict__ d2,
                                                     uint32_t* __restrict__ flag) {
     __shared__ double dv[512];
     __shared__ uint32_t jv[512];
-    const int64_t i = blockIdx.x;
-    const int t = threadIdx.x;
-    const int m = (int)cand_cnt[i];
-    const uint64_t* lst = cand + i * kCap;
+    __shared__ X rows[4][kWave][kSlice + 1];
+    __shared__ X own[4][kSlice];
+    const int64_t l = blockIdx.x, i = q_first + l;
+    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const int m = (int)cand_cnt[l];                 // at most 256 + kMargin
+    const uint64_t* lst = cand + l * kCap;
     for (int e = t; e < 512; e += 256) {
-        if (e < m) {
-            const uint32_t j = (uint32_t)(lst[e] & 0xFFFFFFFFu);
-            double a = 0.0;
-            for (int d = 0; d < D; d++) {
-                const double v = to_f64(Xm[i * D + d]) - to_f64(Xm[(int64_t)j * D + d]);
-                a += v * v;
+        dv[e] = INFINITY;
+        jv[e] = e < m ? (uint32_t)lst[e] : 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    constexpr int kPass = kWave / kSlice;
+    const int col = lane % kSlice, r0 = lane / kSlice;
+    for (int g = w * kWave; g < m; g += 256) {      // wavefronts go their own ways here
+        double a = 0.0;
+        for (int d0 = 0; d0 < D; d0 += kSlice) {
+            const int wd = D - d0 < kSlice ? D - d0 : kSlice;
+            X v[kWave / kPass];
+            const X vx = lane < wd ? Xm[i * D + d0 + lane] : X(0);
+#pragma unroll
+            for (int q = 0; q < kWave / kPass; q++) {
+                const uint32_t c = jv[g + r0 + kPass * q];
+                v[q] = c != 0xFFFFFFFFu && col < wd ? Xm[(int64_t)c * D + d0 + col] : X(0);
             }
-            dv[e] = a;
-            jv[e] = j;
-        } else {
-            dv[e] = INFINITY;
-            jv[e] = 0xFFFFFFFFu;
+            __builtin_amdgcn_wave_barrier();
+            if (lane < kSlice) own[w][lane] = vx;
+#pragma unroll
+            for (int q = 0; q < kWave / kPass; q++) rows[w][r0 + kPass * q][col] = v[q];
+            __builtin_amdgcn_wave_barrier();
+            for (int d = 0; d < wd; d++) {
+                const double e = to_f64(own[w][d]) - to_f64(rows[w][lane][d]);
+                a += e * e;
+            }
         }
+        if (g + lane < m) dv[g + lane] = a;
     }
     __syncthreads();
     for (int kk = 2; kk <= 512; kk <<= 1) {
@@ -477,31 +623,44 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
         d2[i * k + e] = dv[e];
     }
     if (t == 0) {
-        const uint32_t tb = cand_thr[i];
+        const uint32_t tb = cand_thr[l];
         if (tb == kNoThr) {
             flag[i] = 0u;                        // every candidate was kept
         } else {
-            // |fp32(d) - d| <= (D + 4) 2^-24 (|x| + |y|)^2  (conservative)
+            // Error of a pre-selected distance: 3 D products of the two
+            // halves rounded on the way into |x.y| (2 * 3 D 2^-24 |x||y|, and
+            // |x||y| <= (|x| + |y|)^2 / 4), the parts left out and the norms
+            // (16 2^-24 (|x| + |y|)^2), and half-precision numbers below the
+            // normal range, 2^-14 / scale per entry.  A row closer than the
+            // k-th has |y| <= |x| + its distance.
             const double tau = (double)__uint_as_float(tb);
-            const double sx = sqrt((double)nrm[i]), sy = sqrt((double)nrm_max);
-            const double err = (double)(D + 4) * 0x1.0p-24 * (sx + sy) * (sx + sy) * 1.01;
+            const double sx = sqrt((double)nrm[i]);
+            const double sy = fmin(sqrt((double)nrm_max), sx + sqrt(dv[k - 1])), s = sx + sy;
+            const double err = 1.01 * ((1.5 * D + 16.0) * 0x1.0p-24 * s * s +
+                                       2.0 * sqrt((double)D) * s * (0x1.0p-14 / (double)scale));
             flag[i] = dv[k - 1] < tau - err ? 0u : 1u;
         }
     }
 }
 
-// uint8 rows: the kept keys are exact integer distances, a candidate equal to
-// the threshold is always kept, and the last compaction left the list sorted
-// by (distance, index), so its first k entries are the answer.
-__global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ cand, int64_t n,
-                                                  int k, int32_t* __restrict__ idx,
+// uint8 rows: the kept keys are exact integer distances and a candidate equal
+// to the threshold is always kept, so the first k of the sorted list are the
+// answer.
+__global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ cand,
+                                                  const uint32_t* __restrict__ cand_cnt,
+                                                  int64_t q_first, int k,
+                                                  int32_t* __restrict__ idx,
                                                   double* __restrict__ d2) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= n * (int64_t)k) return;
-    const int64_t i = e / k;
-    const uint64_t c = cand[i * kCap + (e - i * k)];
-    idx[e] = (int32_t)(uint32_t)c;
-    d2[e] = (double)(uint32_t)(c >> 32);
+    __shared__ uint64_t key[512];
+    const int64_t l = blockIdx.x, i = q_first + l;
+    const int t = threadIdx.x, m = (int)cand_cnt[l];
+    for (int e = t; e < 512; e += 256) key[e] = e < m ? cand[l * kCap + e] : ~0ull;
+    __syncthreads();
+    bitonic512(key);
+    for (int e = t; e < k; e += 256) {
+        idx[i * k + e] = (int32_t)(uint32_t)key[e];
+        d2[i * k + e] = (double)(uint32_t)(key[e] >> 32);
+    }
 }
 
 // Exact fallback for rows the bound could not certify: block per row,
@@ -838,83 +997,112 @@ hipError_t scan_i64_local(const int64_t* a, int64_t m, int64_t* out, int64_t* tm
     return hipGetLastError();
 }
 
+template <typename F>
+void launch_candidates(const char* packed, int64_t n, int steps, const typename F::Num* nrm,
+                       float f, int64_t first, int64_t rows, int kp, uint64_t* cand,
+                       uint32_t* ccnt, uint32_t* cthr, hipStream_t s) {
+    const dim3 g((unsigned)ceil_div(rows, kQB));
+    // the queries' fragments stay in LDS while 8 steps of them fit beside two
+    // stages (FP16: depth 128)
+    if (steps <= 8)
+        k_knn_candidates<F, true><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, cand,
+                                                    ccnt, cthr);
+    else
+        k_knn_candidates<F, false><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, cand,
+                                                     ccnt, cthr);
+    k_knn_cut<<<dim3((unsigned)ceil_div(rows, 4)), 256, 0, s>>>(cand, rows, n, kp, ccnt, cthr);
+}
+
 template <typename X>
 hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx, double* d2,
                      hipStream_t s, std::string* err) {
     const int kp = (int)((int64_t)(k + kMargin) < n - 1 ? (k + kMargin) : (n - 1));
+    // exact while 256^2 D fits an int32
+    const bool exact = std::is_same<X, uint8_t>::value && D <= 32768;
+    const int64_t rows = n < kBatch ? n : kBatch;
+    const int steps = exact ? pad_steps<PartsI8>(D) : pad_steps<PartsF16>(D);
     float* nrm = nullptr;
-    uint64_t* cand = nullptr;
-    uint32_t *ccnt = nullptr, *flag = nullptr, *cthr = nullptr;
     int32_t* nrm_i = nullptr;
+    char* packed = nullptr;
+    uint64_t* cand = nullptr;
+    uint32_t *ccnt = nullptr, *cthr = nullptr, *flag = nullptr;
+    RowStats* st = nullptr;
     hipError_t e = hipSuccess;
     auto fail = [&](hipError_t x) {
-        (void)hipFree(nrm); (void)hipFree(cand); (void)hipFree(ccnt); (void)hipFree(flag);
-        (void)hipFree(cthr); (void)hipFree(nrm_i);
+        for (void* q : {(void*)nrm, (void*)nrm_i, (void*)packed, (void*)cand, (void*)ccnt,
+                        (void*)cthr, (void*)flag, (void*)st})
+            (void)hipFree(q);
         return x;
     };
-    if ((e = hipMalloc(&nrm, sizeof(float) * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&cand, sizeof(uint64_t) * kCap * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&ccnt, sizeof(uint32_t) * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&cthr, sizeof(uint32_t) * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&flag, sizeof(uint32_t) * n)) != hipSuccess) return fail(e);
-    k_row_norms<X><<<dim3((unsigned)ceil_div(n, 4)), 256, 0, s>>>(Xm, n, D, nrm);
-    std::vector<float> hn(n);
-    if ((e = hipMemcpyAsync(hn.data(), nrm, sizeof(float) * n, hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return fail(e);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
-    float nmax = 0.0f;
-    for (float v : hn) {
-        if (!isfinite(v)) {
-            if (err) *err = "X contains non-finite values";
-            return fail(hipErrorInvalidValue);
-        }
-        nmax = v > nmax ? v : nmax;
-    }
-    // exact while 256^2 D fits an int32
-    const bool kExact = std::is_same<X, uint8_t>::value && D <= 32768;
-    if (kExact) {
+    if ((e = hipMalloc(&cand, sizeof(uint64_t) * kCap * rows)) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&ccnt, sizeof(uint32_t) * rows)) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&cthr, sizeof(uint32_t) * rows)) != hipSuccess) return fail(e);
+    const size_t bytes = exact ? packed_bytes<PartsI8>(n, D) : packed_bytes<PartsF16>(n, D);
+    if ((e = hipMalloc(&packed, bytes)) != hipSuccess) return fail(e);
+    const int64_t np = pad_rows(n);
+    const dim3 gpack((unsigned)ceil_div(np * steps * 2, 256));
+    if (exact) {
         // uint8 rows: exact integer distances from INT8 MFMA
         if ((e = hipMalloc(&nrm_i, sizeof(int32_t) * n)) != hipSuccess) return fail(e);
-        k_row_norms_i8<<<dim3((unsigned)ceil_div(n, 4)), 256, 0, s>>>(
-            (const uint8_t*)Xm, n, D, nrm_i);
-        k_knn_candidates_i8<<<dim3((unsigned)ceil_div(n, kQB)), 256, 0, s>>>(
-            (const uint8_t*)Xm, n, D, nrm_i, kp, cand, ccnt, cthr);
-    } else {
-        bool vec = false;
-        if constexpr (std::is_same<X, float>::value)
-            vec = D % 4 == 0 && ((uintptr_t)Xm & 15) == 0;
-        if (vec)
-            k_knn_candidates<float, true><<<dim3((unsigned)ceil_div(n, kQB)), 256, 0, s>>>(
-                (const float*)Xm, n, D, nrm, kp, cand, ccnt, cthr);
-        else
-            k_knn_candidates<X, false><<<dim3((unsigned)ceil_div(n, kQB)), 256, 0, s>>>(
-                Xm, n, D, nrm, kp, cand, ccnt, cthr);
-    }
-    if (kExact) {
-        k_knn_emit<<<dim3((unsigned)ceil_div(n * k, 256)), 256, 0, s>>>(cand, n, k, idx, d2);
+        k_row_norms_i8<<<dim3((unsigned)ceil_div(n, 4)), 256, 0, s>>>((const uint8_t*)Xm, n, D,
+                                                                     nrm_i);
+        k_pack_i8<<<gpack, 256, 0, s>>>((const uint8_t*)Xm, n, np, D, steps, (uint4*)packed);
+        for (int64_t first = 0; first < n; first += kBatch) {
+            const int64_t m = n - first < kBatch ? n - first : kBatch;
+            launch_candidates<PartsI8>(packed, n, steps, nrm_i, 0.f, first, m, kp, cand, ccnt,
+                                       cthr, s);
+            k_knn_emit<<<dim3((unsigned)m), 256, 0, s>>>(cand, ccnt, first, k, idx, d2);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);
         return fail(hipStreamSynchronize(s));
     }
-    k_knn_rerank<X><<<dim3((unsigned)n), 256, 0, s>>>(Xm, D, k, cand, ccnt, cthr, nrm, nmax, idx,
-                                                      d2, flag);
+    if ((e = hipMalloc(&nrm, sizeof(float) * n)) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&flag, sizeof(uint32_t) * n)) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&st, sizeof(RowStats))) != hipSuccess) return fail(e);
+    if ((e = hipMemsetAsync(st, 0, sizeof(RowStats), s)) != hipSuccess) return fail(e);
+    const int64_t nblk = ceil_div(n, 4) < 2048 ? ceil_div(n, 4) : 2048;
+    k_row_norms<X><<<dim3((unsigned)nblk), 256, 0, s>>>(Xm, n, D, nrm, st);
+    RowStats h;
+    if ((e = hipMemcpyAsync(&h, st, sizeof(h), hipMemcpyDeviceToHost, s)) != hipSuccess)
+        return fail(e);
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
+    if (h.bad) {
+        if (err) *err = "X contains non-finite values";
+        return fail(hipErrorInvalidValue);
+    }
+    float norm_max, entry_max;
+    memcpy(&norm_max, &h.norm, 4);
+    memcpy(&entry_max, &h.entry, 4);
+    // the largest entry just below FP16's range, 2^14 <= |x| < 2^15 (and 1 /
+    // scale^2 in range)
+    int ex = 0;
+    if (entry_max > 0.f) (void)frexpf(entry_max, &ex);
+    const int sh = 15 - ex < -60 ? -60 : (15 - ex > 60 ? 60 : 15 - ex);
+    const float scale = ldexpf(1.f, sh), f = ldexpf(-2.f, -2 * sh);
+    k_pack_f16<X><<<gpack, 256, 0, s>>>(Xm, n, np, D, steps, scale, (_Float16*)packed);
+    for (int64_t first = 0; first < n; first += kBatch) {
+        const int64_t m = n - first < kBatch ? n - first : kBatch;
+        launch_candidates<PartsF16>(packed, n, steps, nrm, f, first, m, kp, cand, ccnt, cthr, s);
+        k_knn_rerank<X><<<dim3((unsigned)m), 256, 0, s>>>(Xm, first, D, k, cand, ccnt, cthr, nrm,
+                                                          norm_max, scale, idx, d2, flag);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     std::vector<uint32_t> hf(n);
     if ((e = hipMemcpyAsync(hf.data(), flag, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s)) != hipSuccess)
         return fail(e);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
-    std::vector<uint32_t> rows;
+    std::vector<uint32_t> miss;
     for (int64_t i = 0; i < n; i++)
-        if (hf[i]) rows.push_back((uint32_t)i);
-    if (!rows.empty()) {
-        // exact FP64 fallback for rows the FP32 bound did not certify
-        if ((e = hipMemcpyAsync(flag, rows.data(), sizeof(uint32_t) * rows.size(),
+        if (hf[i]) miss.push_back((uint32_t)i);
+    if (!miss.empty()) {
+        // exact FP64 fallback for rows the bound did not certify
+        if ((e = hipMemcpyAsync(flag, miss.data(), sizeof(uint32_t) * miss.size(),
                                 hipMemcpyHostToDevice, s)) != hipSuccess)
             return fail(e);
-        k_knn_exact_row<X><<<dim3((unsigned)rows.size()), 256, 0, s>>>(Xm, n, D, k, flag, idx, d2);
+        k_knn_exact_row<X><<<dim3((unsigned)miss.size()), 256, 0, s>>>(Xm, n, D, k, flag, idx, d2);
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
     }
-    (void)err;
     return fail(hipSuccess);
 }
 
