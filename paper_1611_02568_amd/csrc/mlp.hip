@@ -7,6 +7,14 @@
 // Cast points (operands rounded to bfloat16, round to nearest even):
 //   forward   X^, W1 | H1, W2 | H2, W3
 //   backward  dA2, H1, W2 (dW2, dH1) and dA1, X^ (dW1); the head uses H2, W3.
+//
+// Every operand of a matrix product lies in memory as the MFMA units take it,
+// in fragments of 16 rows by 32 of the reduction (512 elements, 16 bytes per
+// lane, in lane order): an operand's fragments move to LDS by loads straight
+// into it and are read without bank conflicts.  The kernel that computes a
+// matrix writes it in the order of each product that reads it: X^, H1, dA2
+// by rows (reduction along the columns) and by columns (reduction along the
+// batch), dA1 by columns, the weights after each step.
 #include <math.h>
 #include <string.h>
 
@@ -27,31 +35,35 @@ struct pixelsne_mlp {
     int64_t step = 0;                   // Adam step count
     int64_t cap_batch = 0;              // rows the work buffers hold
     float* theta = nullptr;             // FP32 master parameters (flat)
-    float* grad = nullptr;              // FP32 gradient (flat, same layout)
     float* m1 = nullptr;                // Adam first moment
     float* m2 = nullptr;                // Adam second moment
-    uint16_t* w1b = nullptr;            // bfloat16 copies of W1, W2, W3
-    uint16_t* w2b = nullptr;
-    uint16_t* w3b = nullptr;
+    uint16_t* w1p = nullptr;            // W1: fragments of rows h1, reduction d
+    uint16_t* w2p = nullptr;            // W2: rows h2, reduction h1 (forward)
+    uint16_t* w2q = nullptr;            // W2: rows h1, reduction h2 (backward)
+    uint16_t* w3b = nullptr;            // W3 [h2][2]
     float* mean = nullptr;              // input standardisation
     float* inv_std = nullptr;
-    // per-batch work buffers
-    uint16_t* xb = nullptr;             // X^ [B][d] bf16
+    // work buffers of a forward pass (rows padded to whole tiles)
+    uint16_t* xp = nullptr;             // X^: rows batch, reduction d
+    uint16_t* h1p = nullptr;            // H1: rows batch, reduction h1
+    uint16_t* h2b = nullptr;            // H2 [B][h2]
+    int64_t cap_train = 0;              // rows the training buffers hold
+    int64_t train_steps = 0;            // depth steps of the batch they are laid out for
+    uint16_t* xq = nullptr;             // X^: rows d, reduction batch
+    uint16_t* h1q = nullptr;            // H1: rows h1, reduction batch
+    uint16_t* da2p = nullptr;           // dA2: rows batch, reduction h2
+    uint16_t* da2q = nullptr;           // dA2: rows h2, reduction batch
+    uint16_t* da1q = nullptr;           // dA1: rows h1, reduction batch
     float* yb = nullptr;                // targets [B][2]
     float* a1 = nullptr;                // pre-activations [B][h1], [B][h2]
     float* a2 = nullptr;
-    uint16_t* h1b = nullptr;            // activations (bf16) [B][h1], [B][h2]
-    uint16_t* h2b = nullptr;
-    float* out = nullptr;               // [B][2]
     float* dout = nullptr;              // [B][2]
     float* da2 = nullptr;               // [B][h2]
-    uint16_t* da2b = nullptr;
     float* da1 = nullptr;               // [B][h1]
-    uint16_t* da1b = nullptr;
     float* splitk = nullptr;            // split-K partials
     int64_t splitk_len = 0;
     float* part = nullptr;              // row-slice partial sums of the batch reductions
-    double* lossbuf = nullptr;          // per-block loss partials
+    double* lossbuf = nullptr;          // loss partials, one per four rows
     int64_t lossbuf_len = 0;
     uint32_t* order = nullptr;          // batch row order (device)
     int64_t order_len = 0;
@@ -62,6 +74,7 @@ namespace psne {
 namespace {
 
 constexpr int kT = 256;
+constexpr int64_t kForwardRows = 32768;
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
     uint32_t u = __float_as_uint(f);
@@ -76,182 +89,414 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
            x * expf(-0.5f * x * x) * 0.39894228040143268f;
 }
 
-enum { EPI_F32 = 0, EPI_BIAS_GELU = 1, EPI_GELU_GRAD = 2 };
+constexpr int kXcds = 8;
+constexpr int kFrag = 512;                     // elements of a fragment
+constexpr int kTileRows = 128;                 // rows of an operand are padded to this
 
-// Stage rows r0..r0+63, k0..k0+31 of an operand into S[row][k] (k < ke, row
-// < R zero-filled beyond).  kmaj: stored [row][ld] with k contiguous;
-// otherwise stored [k][ld] with rows contiguous.  Thread t moves 8 elements,
-// with one 16-byte load when the run is inside the matrix and aligned.
-__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ G, int ld, int kmaj,
-                                          int r0, int R, int k0, int ke, int t,
-                                          uint16_t (*S)[40]) {
+// depth steps (of 32) of a reduction, padded to whole stages of two
+__host__ __device__ inline int depth_steps(int64_t k) { return 2 * (int)((k + 63) / 64); }
+inline int64_t pad_tile(int64_t r) { return ceil_div(r, kTileRows) * kTileRows; }
+inline int64_t frag_elems(int64_t rows, int64_t k) { return pad_tile(rows) * depth_steps(k) * 32; }
+
+// element (r, k) of an operand with `steps` depth steps
+__device__ __forceinline__ int64_t frag_at(int64_t r, int k, int steps) {
+    return ((r >> 4) * steps + (k >> 5)) * kFrag + (((r & 15) + 16 * ((k & 31) >> 3)) << 3) +
+           (k & 7);
+}
+
+// rows of an operand that exist in memory
+__device__ __forceinline__ int pad_cols(int r) { return (r + kTileRows - 1) / kTileRows * kTileRows; }
+
+// C[n][m] = sum_k B[n][k] A[m][k] over the depth steps step0 .. step0 + n_steps of
+// the operands' sa and sb, for a TM x TN tile at row fragments ma and nb, by
+// WM x WN wavefronts.  Stages of KS steps, the next one in flight while one is
+// multiplied.  Lane l ends with the elements m = l % 16, n = 4 (l / 16) + 0..3
+// of each 16 x 16 tile, so four consecutive columns of one row.  The depth runs
+// in instructions of 32 in ascending order, whatever the tile.
+template <int TM, int TN, int WM, int WN, int KS>
+struct Tile {
+    static constexpr int kWaves = WM * WN;
+    static constexpr int kA = TM / 16, kB = TN / 16;        // fragments per step
+    static constexpr int kLds = 2 * KS * (kA + kB) * kFrag; // elements, two stages
+    static constexpr int kMi = TM / WM / 16, kNj = TN / WN / 16;   // a wavefront's
+    static_assert(KS * (kA + kB) % kWaves == 0, "every wavefront loads as many fragments");
+    v4f acc[kNj][kMi];
+
+    __device__ __forceinline__ void run(const uint16_t* __restrict__ A, int sa, int64_t ma,
+                                        const uint16_t* __restrict__ B, int sb, int64_t nb,
+                                        int step0, int n_steps, uint16_t* lds) {
+        const int t = threadIdx.x, lane = t & 63;
+        const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+        const int wm = w / WN, wn = w % WN;
+#pragma unroll
+        for (int j = 0; j < kNj; j++)
+#pragma unroll
+            for (int i = 0; i < kMi; i++) acc[j][i] = v4f{0.f, 0.f, 0.f, 0.f};
+        const int stages = (n_steps + KS - 1) / KS, end = step0 + n_steps;
+        // a stage holds [A fragments][KS steps], then B's; wavefront w loads
+        // fragments w, w + kWaves, ...
+        auto fetch = [&](int st, int buf) {
+            uint16_t* to = lds + buf * (kLds / 2);
+            const int s = step0 + KS * st;
+#pragma unroll
+            for (int y = 0; y < KS * (kA + kB) / kWaves; y++) {
+                const int x = w + kWaves * y, f = x / KS;
+                const int q = s + x % KS < end ? s + x % KS : end - 1;     // an odd last stage
+                const uint16_t* src = f < kA ? A + ((ma + f) * sa + q) * kFrag
+                                             : B + ((nb + (f - kA)) * sb + q) * kFrag;
+                __builtin_amdgcn_global_load_lds(
+                    (__attribute__((address_space(1))) const void*)(src + 8 * lane),
+                    (__attribute__((address_space(3))) void*)(to + x * kFrag), 16, 0, 0);
+            }
+        };
+        auto settle = [&]() {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        };
+        auto step = [&](const uint16_t* from, int h) {
+            v8bf a[kMi], b[kNj];
+#pragma unroll
+            for (int i = 0; i < kMi; i++)
+                a[i] = *reinterpret_cast<const v8bf*>(from + ((wm * kMi + i) * KS + h) * kFrag +
+                                                      8 * lane);
+#pragma unroll
+            for (int j = 0; j < kNj; j++)
+                b[j] = *reinterpret_cast<const v8bf*>(from + ((kA + wn * kNj + j) * KS + h) * kFrag +
+                                                      8 * lane);
+#pragma unroll
+            for (int j = 0; j < kNj; j++)
+#pragma unroll
+                for (int i = 0; i < kMi; i++)
+                    acc[j][i] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[j][i], 0, 0, 0);
+        };
+        fetch(0, 0);
+        settle();
+        for (int st = 0; st < stages; st++) {
+            const int buf = st & 1;
+            if (st + 1 < stages) fetch(st + 1, buf ^ 1);
+            const uint16_t* from = lds + buf * (kLds / 2);
+            step(from, 0);
+            if (KS == 2 && 2 * st + 1 < n_steps) step(from, 1);
+            settle();
+        }
+    }
+
+    // fn(mf, nf, values) for every 16 x 16 tile, mf and nf its (uniform) place in
+    // units of 16; the lane's four elements are row 16 mf + lane_m(), columns
+    // 16 nf + lane_n() + 0..3
+    template <typename Fn>
+    __device__ __forceinline__ void each(int64_t m0, int n0, Fn&& fn) const {
+        const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int wm = w / WN, wn = w % WN;
+#pragma unroll
+        for (int j = 0; j < kNj; j++)
+#pragma unroll
+            for (int i = 0; i < kMi; i++)
+                fn(m0 / 16 + wm * kMi + i, n0 / 16 + wn * kNj + j, acc[j][i]);
+    }
+};
+__device__ __forceinline__ int lane_m() { return threadIdx.x & 15; }
+__device__ __forceinline__ int lane_n() { return 4 * ((threadIdx.x & 63) >> 4); }
+
+// A lane's four elements of tile (mf, nf): to fragments by rows (one 8-byte
+// store), and by columns (a 2-byte store each; 16 lanes fill two 16-byte
+// pieces).
+__device__ __forceinline__ void put_rows(uint16_t* __restrict__ P, int steps, int64_t mf, int nf,
+                                         const uint16_t* h) {
+    const int n = 16 * (nf & 1) + lane_n();
+    uint16_t* base = P + (mf * steps + (nf >> 1)) * kFrag;
+    *reinterpret_cast<uint2*>(base + ((lane_m() + 16 * (n >> 3)) << 3) + (n & 7)) =
+        uint2{(uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16};
+}
+__device__ __forceinline__ void put_cols(uint16_t* __restrict__ Q, int steps, int64_t mf, int nf,
+                                         const uint16_t* h) {
+    const int k = 16 * (int)(mf & 1) + lane_m();
+    uint16_t* base = Q + ((int64_t)nf * steps + (mf >> 1)) * kFrag + ((16 * (k >> 3)) << 3) + (k & 7);
+#pragma unroll
+    for (int e = 0; e < 4; e++) base[(lane_n() + e) << 3] = h[e];
+}
+
+// and to a row-major matrix of N columns
+template <typename V, typename E>
+__device__ __forceinline__ void put_flat(E* __restrict__ C, int64_t m, int n, int M, int N,
+                                         const E* v) {
+    E* p = C + m * N + n;
+    if (N % 4 == 0) {
+        if (m < M && n < N) *reinterpret_cast<V*>(p) = *reinterpret_cast<const V*>(v);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            if (m < M && n + e < N) p[e] = v[e];
+    }
+}
+
+// Blocks b, b + 8, ... share an L2 (blocks go round the XCDs): those of one XCD
+// take all column tiles of one row tile before the next row tile, so that a row
+// tile of A is read once per chip and B stays in each L2.
+
+// A layer: H = gelu(A B^T + bias) for M rows and N columns.  pre (training):
+// the pre-activations [M][N]; rowsP / colsQ / flat: where H goes.  Rows past M
+// and columns past N become zeros in the fragments.  What bounds it is GELU
+// (erff is 40 vector instructions per element, on both sides of a branch) and
+// the latency of the short depth loop, so wavefronts per CU count for more than
+// LDS traffic.  A million rows of two 1,024-wide layers, all kernels: tiles of
+// 128 x 128 with four wavefronts and stages of two steps 9.4 ms, with eight 7.2,
+// with stages of one step (half the LDS) 6.4, in the order above 5.8.  One layer
+// of 32,768 rows takes 77 us; all layers together 4.8 ms, where products of
+// row-major operands took 17.3.
+template <int TM, int TN, int WM, int WN, int KS>
+__global__ __launch_bounds__(64 * WM * WN) void k_layer(const uint16_t* __restrict__ A,
+                                                        const uint16_t* __restrict__ B, int steps,
+                                                        int M, int N,
+                                                        const float* __restrict__ bias,
+                                                        float* __restrict__ pre,
+                                                        uint16_t* __restrict__ rowsP,
+                                                        uint16_t* __restrict__ colsQ, int sq,
+                                                        uint16_t* __restrict__ flat) {
+    using T = Tile<TM, TN, WM, WN, KS>;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[T::kLds];
+    const int nt = (N + TN - 1) / TN, q = (int)blockIdx.x / kXcds;
+    const int64_t m0 = ((int64_t)(q / nt) * kXcds + blockIdx.x % kXcds) * TM;
+    const int n0 = q % nt * TN, sp = depth_steps(N);
+    if (m0 >= 32 * (int64_t)depth_steps(M)) return;
+    T c;
+    c.run(A, steps, m0 / 16, B, steps, n0 / 16, 0, steps, lds);
+    c.each(m0, n0, [&](int64_t mf, int nf, const v4f& v) {
+        const int64_t m = 16 * mf + lane_m();
+        const int n = 16 * nf + lane_n();
+        __attribute__((aligned(16))) float a[4];
+        __attribute__((aligned(8))) uint16_t h[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const bool in = m < M && n + e < N;
+            a[e] = v[e] + (in ? bias[n + e] : 0.f);
+            h[e] = in ? f2bf(gelu_f(a[e])) : (uint16_t)0;
+        }
+        if (pre) put_flat<float4>(pre, m, n, M, N, a);
+        if (flat) put_flat<uint2>(flat, m, n, M, N, h);
+        if (nf < 2 * sp) {
+            if (rowsP) put_rows(rowsP, sp, mf, nf, h);
+            if (colsQ && mf < 2 * sq) put_cols(colsQ, sq, mf, nf, h);
+        }
+    });
+}
+
+// dA = (A B^T) * gelu'(pre): M rows, N columns; FP32 [M][N] and by columns
+template <int TM, int TN, int WM, int WN, int KS>
+__global__ __launch_bounds__(64 * WM * WN) void k_layer_back(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int steps, int M, int N,
+    const float* __restrict__ pre, float* __restrict__ da, uint16_t* __restrict__ colsQ, int sq) {
+    using T = Tile<TM, TN, WM, WN, KS>;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[T::kLds];
+    const int nt = (N + TN - 1) / TN, q = (int)blockIdx.x / kXcds;
+    const int64_t m0 = ((int64_t)(q / nt) * kXcds + blockIdx.x % kXcds) * TM;
+    const int n0 = q % nt * TN;
+    if (m0 >= 32 * (int64_t)sq) return;
+    T c;
+    c.run(A, steps, m0 / 16, B, steps, n0 / 16, 0, steps, lds);
+    c.each(m0, n0, [&](int64_t mf, int nf, const v4f& v) {
+        const int64_t m = 16 * mf + lane_m();
+        const int n = 16 * nf + lane_n();
+        __attribute__((aligned(16))) float d[4];
+        uint16_t h[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const bool in = m < M && n + e < N;
+            d[e] = in ? v[e] * gelu_grad_f(pre[m * N + n + e]) : 0.f;
+            h[e] = f2bf(d[e]);
+        }
+        put_flat<float4>(da, m, n, M, N, d);
+        if (mf < 2 * sq && 16 * nf < pad_cols(N)) put_cols(colsQ, sq, mf, nf, h);
+    });
+}
+
+// X^ rows of a batch: standardise, round to bfloat16.  A wavefront writes one
+// fragment, a lane eight consecutive features of one row (16 bytes), so that
+// reads are 128-byte runs of 16 rows and writes 1 KiB in a row.  wide: the
+// rows of X begin on 16 bytes.  32,768 rows of 100 take 7 us; with a row's
+// pieces in consecutive lanes, whose writes lie 256 bytes apart, 20.
+__global__ __launch_bounds__(kT) void k_stage_x(const float* __restrict__ X, int d, int steps,
+                                                int64_t b0, int Bn, int64_t rows, bool wide,
+                                                const float* __restrict__ mean,
+                                                const float* __restrict__ inv_std,
+                                                uint16_t* __restrict__ xp) {
+    const int64_t f = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
+    if (f >= rows / 16 * steps) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t r = 16 * (f / steps) + (lane & 15);
+    const int c0 = 32 * (int)(f % steps) + 8 * (lane >> 4);
     union {
         uint4 q;
         uint16_t h[8];
     } v;
-    if (kmaj) {
-        const int r = t >> 2, c = (t & 3) * 8;                 // row r, k c..c+7
-        const int gr = r0 + r, gk = k0 + c;
-        const uint16_t* p = G + (int64_t)gr * ld + gk;
-        if (gr < R && gk + 8 <= ke && ((reinterpret_cast<uintptr_t>(p) & 15u) == 0)) {
-            v.q = *reinterpret_cast<const uint4*>(p);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; e++) v.h[e] = (gr < R && gk + e < ke) ? p[e] : (uint16_t)0;
-        }
-        *reinterpret_cast<uint4*>(&S[r][c]) = v.q;
+    __attribute__((aligned(16))) float x[8];
+    const float* row = X + (b0 + r) * d + c0;
+    if (wide && r < Bn && c0 + 8 <= d) {
+        *reinterpret_cast<float4*>(x) = *reinterpret_cast<const float4*>(row);
+        *reinterpret_cast<float4*>(x + 4) = *reinterpret_cast<const float4*>(row + 4);
     } else {
-        const int k = t >> 3, c = (t & 7) * 8;                 // k, rows c..c+7
-        const int gk = k0 + k, gr = r0 + c;
-        const uint16_t* p = G + (int64_t)gk * ld + gr;
-        if (gk < ke && gr + 8 <= R && ((reinterpret_cast<uintptr_t>(p) & 15u) == 0)) {
-            v.q = *reinterpret_cast<const uint4*>(p);
-        } else {
 #pragma unroll
-            for (int e = 0; e < 8; e++) v.h[e] = (gk < ke && gr + e < R) ? p[e] : (uint16_t)0;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; e++) S[c + e][k] = v.h[e];
+        for (int e = 0; e < 8; e++) x[e] = r < Bn && c0 + e < d ? row[e] : 0.f;
     }
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const int c = c0 + e;
+        v.h[e] = r < Bn && c < d ? f2bf((x[e] - mean[c]) * inv_std[c]) : (uint16_t)0;
+    }
+    *reinterpret_cast<uint4*>(xp + f * kFrag + 8 * lane) = v.q;
 }
 
-// C[M,N] = op(A)[M,K] * op(B)[K,N], bfloat16 operands, FP32 accumulate.
-// ta: A stored [K][lda] (transposed); tb: B stored [N][ldb] (transposed).
-// 64 x 64 tile per block, four wavefronts of 32 x 32 (2 x 2 MFMA tiles),
-// K in steps of 32 staged through LDS as [row][k].  With gridDim.z > 1 each
-// z-slice reduces its own K range into C + z*M*N (split-K, FP32 only).
-template <int EPI>
-__global__ __launch_bounds__(kT) void k_gemm_bf16(const uint16_t* __restrict__ A, int lda, int ta,
-                                                  const uint16_t* __restrict__ B, int ldb, int tb,
-                                                  int M, int N, int K, int kchunk,
-                                                  float* __restrict__ C, int ldc,
-                                                  const float* __restrict__ bias,
-                                                  const float* __restrict__ pre,
-                                                  uint16_t* __restrict__ Cb) {
-    __shared__ uint16_t As[64][40];
-    __shared__ uint16_t Bs[64][40];
+// The same for training, in both orders, and the targets: a thread takes one
+// feature of eight rows (a 16-byte piece of the order by columns).
+__global__ __launch_bounds__(kT) void k_stage_train(const float* __restrict__ X, int d, int steps,
+                                                    const uint32_t* __restrict__ order, int64_t b0,
+                                                    int Bn, int sq, const float* __restrict__ mean,
+                                                    const float* __restrict__ inv_std,
+                                                    uint16_t* __restrict__ xp,
+                                                    uint16_t* __restrict__ xq,
+                                                    const float* __restrict__ Y,
+                                                    float* __restrict__ yb) {
+    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
+    const int cols = 32 * steps;
+    if (i >= (int64_t)4 * sq * cols) return;
+    const int64_t r0 = 8 * (i / cols);
+    const int c = (int)(i % cols);
+    const float mu = c < d ? mean[c] : 0.f, is = c < d ? inv_std[c] : 0.f;
+    union {
+        uint4 q;
+        uint16_t h[8];
+    } v;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const int64_t r = r0 + e;
+        uint16_t h = 0;
+        if (r < Bn) {
+            const int64_t src = order ? order[b0 + r] : b0 + r;
+            if (c < d) h = f2bf((X[src * d + c] - mu) * is);
+            if (c == 0) {
+                yb[r * 2] = Y[src * 2];
+                yb[r * 2 + 1] = Y[src * 2 + 1];
+            }
+        }
+        v.h[e] = h;
+        xp[frag_at(r, c, steps)] = h;
+    }
+    if (c < pad_cols(d)) *reinterpret_cast<uint4*>(xq + frag_at(c, (int)r0, sq)) = v.q;
+}
+
+// R rows of the head, out = H2 W3 + b3, by one wavefront: lane l adds columns
+// l, l + 64, ... of each.  Rows from Bn on repeat the last.
+template <int R>
+__device__ __forceinline__ void head_rows(const uint16_t* __restrict__ h2b, int64_t r0, int Bn,
+                                          int h2, const uint16_t* __restrict__ w3b,
+                                          const float* __restrict__ b3, float2* out) {
+    float s0[R], s1[R];
+    const uint16_t* row[R];
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+        s0[q] = s1[q] = 0.f;
+        row[q] = h2b + (r0 + q < Bn ? r0 + q : Bn - 1) * h2;
+    }
+#pragma unroll 4
+    for (int j = threadIdx.x & 63; j < h2; j += 64) {
+        const float w0 = bf2f(w3b[2 * j]), w1 = bf2f(w3b[2 * j + 1]);
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            const float h = bf2f(row[q][j]);
+            s0[q] += h * w0;
+            s1[q] += h * w1;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < R; q++)
+        out[q] = float2{psne::wave_sum(s0[q]) + b3[0], psne::wave_sum(s1[q]) + b3[1]};
+}
+
+// Bound by the rate of its 2-byte loads, so four rows per wavefront share those
+// of W3: 32,768 rows of 1,024 in 12 us, 26 with a row per wavefront.
+constexpr int kPlaceRows = 4;
+__global__ __launch_bounds__(kT) void k_head(const uint16_t* __restrict__ h2b, int h2,
+                                             const uint16_t* __restrict__ w3b,
+                                             const float* __restrict__ b3, int Bn,
+                                             float* __restrict__ out) {
+    const int64_t r = ((int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6)) * kPlaceRows;
+    if (r >= Bn) return;
+    float2 o[kPlaceRows];
+    head_rows<kPlaceRows>(h2b, r, Bn, h2, w3b, b3, o);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int q = 0; q < kPlaceRows; q++)
+            if (r + q < Bn) reinterpret_cast<float2*>(out)[r + q] = o[q];
+}
+
+// The head in training, 16 rows per block: out and the loss partials of every
+// four rows, dout, then dA2 = (dout W3^T) * GELU'(A2) in FP32 and in both
+// orders of the products that read it (zeros past the batch).  A wavefront per
+// row, then a thread per eight elements of a column: 4,096 rows of 512 leave
+// one block per CU, so its sixteen wavefronts are all there is to hide the
+// latency (29 us with four wavefronts, 11 with sixteen).
+constexpr int kHeadRows = 16, kHeadT = 64 * kHeadRows;
+
+__global__ __launch_bounds__(kHeadT) void k_head_train(const uint16_t* __restrict__ h2b, int h2,
+                                                   const uint16_t* __restrict__ w3b,
+                                                   const float* __restrict__ b3, int Bn,
+                                                   const float* __restrict__ yb,
+                                                   const float* __restrict__ a2,
+                                                   float* __restrict__ dout,
+                                                   double* __restrict__ lossp,
+                                                   float* __restrict__ da2, int sp,
+                                                   uint16_t* __restrict__ da2p, int sq,
+                                                   uint16_t* __restrict__ da2q) {
+    __shared__ double red[kHeadRows];
+    __shared__ float dl[kHeadRows][2];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int kb = blockIdx.z * kchunk;
-    const int ke = kb + kchunk < K ? kb + kchunk : K;
-    v4f acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = kb; k0 < ke; k0 += 32) {
-        __syncthreads();
-        // 64 x 32 elements per operand and step: one run of 8 consecutive
-        // elements (16 bytes) per thread, along k for an operand stored with k
-        // contiguous and along m (n) for a transposed one
-        load_tile(A, lda, !ta, m0, M, k0, ke, t, As);
-        load_tile(B, ldb, tb, n0, N, k0, ke, t, Bs);
-        __syncthreads();
-        v8bf af[2], bfr[2];
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-            af[i] = *reinterpret_cast<const v8bf*>(&As[32 * wm + 16 * i + (lane & 15)][8 * (lane >> 4)]);
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-            bfr[j] = *reinterpret_cast<const v8bf*>(&Bs[32 * wn + 16 * j + (lane & 15)][8 * (lane >> 4)]);
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-#pragma unroll
-            for (int j = 0; j < 2; j++)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-    float* Cz = C + (int64_t)blockIdx.z * M * ldc;
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const int row = m0 + 32 * wm + 16 * i + 4 * (lane >> 4) + e;
-                const int col = n0 + 32 * wn + 16 * j + (lane & 15);
-                if (row >= M || col >= N) continue;
-                const float v = acc[i][j][e];
-                const int64_t o = (int64_t)row * ldc + col;
-                if (EPI == EPI_F32) {
-                    Cz[o] = v;
-                } else if (EPI == EPI_BIAS_GELU) {
-                    const float a = v + bias[col];
-                    C[o] = a;
-                    Cb[o] = f2bf(gelu_f(a));
-                } else {
-                    const float d = v * gelu_grad_f(pre[o]);
-                    C[o] = d;
-                    Cb[o] = f2bf(d);
-                }
-            }
-}
-
-// sum the split-K slices in slice order
-__global__ __launch_bounds__(kT) void k_splitk_sum(const float* __restrict__ part, int64_t mn,
-                                                   int S, float* __restrict__ C) {
-    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (i >= mn) return;
-    float a = 0.f;
-    for (int z = 0; z < S; z++) a += part[(int64_t)z * mn + i];
-    C[i] = a;
-}
-
-// X^ rows of a batch: gather by order, standardise, round to bfloat16
-__global__ __launch_bounds__(kT) void k_stage_x(const float* __restrict__ X, int d,
-                                                const uint32_t* __restrict__ order, int64_t b0,
-                                                int Bn, const float* __restrict__ mean,
-                                                const float* __restrict__ inv_std,
-                                                uint16_t* __restrict__ xb,
-                                                const float* __restrict__ Y, float* __restrict__ yb) {
-    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (i >= (int64_t)Bn * d) return;
-    const int64_t r = i / d;
-    const int c = (int)(i - r * d);
-    const int64_t src = order ? order[b0 + r] : b0 + r;
-    xb[i] = f2bf((X[src * d + c] - mean[c]) * inv_std[c]);
-    if (Y && c == 0) {
-        yb[r * 2] = Y[src * 2];
-        yb[r * 2 + 1] = Y[src * 2 + 1];
-    }
-}
-
-// head: out = H2 W3 + b3 (one wavefront per row), then dout and the loss
-__global__ __launch_bounds__(kT) void k_head_fwd(const uint16_t* __restrict__ h2b, int h2,
-                                                 const uint16_t* __restrict__ w3b,
-                                                 const float* __restrict__ b3, int Bn,
-                                                 float* __restrict__ out,
-                                                 const float* __restrict__ yb,
-                                                 float* __restrict__ dout,
-                                                 double* __restrict__ lossp) {
-    __shared__ double red[4];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int r = blockIdx.x * 4 + w;
+    const int64_t r0 = (int64_t)blockIdx.x * kHeadRows;
+    const int64_t r = r0 + w;
     double l = 0.0;
+    float d0 = 0.f, d1 = 0.f;
     if (r < Bn) {
-        float s0 = 0.f, s1 = 0.f;
-        for (int j = lane; j < h2; j += 64) {
-            const float h = bf2f(h2b[(int64_t)r * h2 + j]);
-            s0 += h * bf2f(w3b[2 * j]);
-            s1 += h * bf2f(w3b[2 * j + 1]);
-        }
-        s0 = psne::wave_sum(s0);
-        s1 = psne::wave_sum(s1);
-        if (lane == 0) {
-            const float o0 = s0 + b3[0], o1 = s1 + b3[1];
-            out[2 * r] = o0;
-            out[2 * r + 1] = o1;
-            if (yb) {
-                const float e0 = o0 - yb[2 * r], e1 = o1 - yb[2 * r + 1];
-                dout[2 * r] = 2.f * e0 / (float)Bn;
-                dout[2 * r + 1] = 2.f * e1 / (float)Bn;
-                l = (double)e0 * e0 + (double)e1 * e1;
-            }
+        float2 o;
+        head_rows<1>(h2b, r, Bn, h2, w3b, b3, &o);
+        const float e0 = o.x - yb[2 * r], e1 = o.y - yb[2 * r + 1];
+        d0 = 2.f * e0 / (float)Bn;
+        d1 = 2.f * e1 / (float)Bn;
+        l = (double)e0 * e0 + (double)e1 * e1;
+    }
+    if (lane == 0) {
+        red[w] = l;
+        dl[w][0] = d0;
+        dl[w][1] = d1;
+        if (r < Bn) {
+            dout[2 * r] = d0;
+            dout[2 * r + 1] = d1;
         }
     }
-    if (lane == 0) red[w] = l;
     __syncthreads();
-    if (threadIdx.x == 0 && lossp) lossp[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+    if (t < kHeadRows / 4 && r0 + 4 * t < Bn)
+        lossp[r0 / 4 + t] = ((red[4 * t] + red[4 * t + 1]) + red[4 * t + 2]) + red[4 * t + 3];
+    const int cols = pad_cols(h2);
+    for (int x = t; x < 2 * cols; x += kHeadT) {
+        const int j = x % cols, m0 = 8 * (x / cols);        // eight rows of one column
+        const float w0 = j < h2 ? bf2f(w3b[2 * j]) : 0.f, w1 = j < h2 ? bf2f(w3b[2 * j + 1]) : 0.f;
+        union {
+            uint4 q;
+            uint16_t h[8];
+        } v;
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const int64_t r = r0 + m0 + e;
+            float d = 0.f;
+            if (r < Bn && j < h2) {
+                const float g = dl[m0 + e][0] * w0 + dl[m0 + e][1] * w1;
+                d = g * gelu_grad_f(a2[r * h2 + j]);
+                da2[r * h2 + j] = d;
+            }
+            v.h[e] = f2bf(d);
+            if (j < 32 * sp) da2p[frag_at(r, j, sp)] = v.h[e];
+        }
+        *reinterpret_cast<uint4*>(da2q + frag_at(j, (int)(r0 + m0), sq)) = v.q;
+    }
 }
 
 // dW3[j][d] = sum_b H2[b][j] dout[b][d];  db3[d] = sum_b dout[b][d]
@@ -262,14 +507,13 @@ constexpr int kSlices = 32;
 
 // dW3[j][c] = sum_b H2[b][j] dout[b][c]; columns j < h2 give 2 outputs each,
 // and block x == 0 also sums dout itself (db3) into part[z][2 h2 + c]
-__global__ __launch_bounds__(kT) void k_head_wgrad_part(const uint16_t* __restrict__ h2b, int h2,
-                                                        const float* __restrict__ dout, int Bn,
-                                                        float* __restrict__ part) {
-    __shared__ float red[4][64][3];
-    const int t = threadIdx.x, cj = t & 63, ph = t >> 6;
-    const int j = blockIdx.x * 64 + cj;
+__device__ __forceinline__ void head_wgrad(const uint16_t* __restrict__ h2b, int h2,
+                                           const float* __restrict__ dout, int Bn, int bx, int bz,
+                                           float* __restrict__ part, float (*red)[64][3]) {
+    const int t = threadIdx.x, cj = t & 63, ph = (t >> 6) & 3;
+    const int j = bx * 64 + cj;
     const int per = (Bn + kSlices - 1) / kSlices;
-    const int b0 = blockIdx.z * per, b1 = b0 + per < Bn ? b0 + per : Bn;
+    const int b0 = bz * per, b1 = b0 + per < Bn ? b0 + per : Bn;
     float s0 = 0.f, s1 = 0.f, d0 = 0.f, d1 = 0.f;
     for (int b = b0 + ph; b < b1; b += 4) {
         const float o0 = dout[2 * b], o1 = dout[2 * b + 1];
@@ -288,76 +532,151 @@ __global__ __launch_bounds__(kT) void k_head_wgrad_part(const uint16_t* __restri
     if (ph == 0) {
         const float a0 = ((red[0][cj][0] + red[1][cj][0]) + red[2][cj][0]) + red[3][cj][0];
         const float a1 = ((red[0][cj][1] + red[1][cj][1]) + red[2][cj][1]) + red[3][cj][1];
-        float* p = part + (int64_t)blockIdx.z * (2 * h2 + 2);
+        float* p = part + (int64_t)bz * (2 * h2 + 2);
         if (j < h2) {
             p[2 * j] = a0;
             p[2 * j + 1] = a1;
         }
-        if (blockIdx.x == 0 && cj < 2)
+        if (bx == 0 && cj < 2)
             p[2 * h2 + cj] = ((red[0][cj][2] + red[1][cj][2]) + red[2][cj][2]) + red[3][cj][2];
     }
 }
 
-// dA2 = (dout W3^T) * GELU'(A2)
-__global__ __launch_bounds__(kT) void k_head_bgrad(const float* __restrict__ dout,
-                                                   const uint16_t* __restrict__ w3b,
-                                                   const float* __restrict__ a2, int h2, int Bn,
-                                                   float* __restrict__ da2,
-                                                   uint16_t* __restrict__ da2b) {
-    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (i >= (int64_t)Bn * h2) return;
-    const int64_t b = i / h2;
-    const int j = (int)(i - b * h2);
-    const float g = dout[2 * b] * bf2f(w3b[2 * j]) + dout[2 * b + 1] * bf2f(w3b[2 * j + 1]);
-    const float d = g * gelu_grad_f(a2[i]);
-    da2[i] = d;
-    da2b[i] = f2bf(d);
-}
-
 // column sums over the batch (bias gradients), per row slice
-__global__ __launch_bounds__(kT) void k_colsum_part(const float* __restrict__ a, int rows, int cols,
-                                                    float* __restrict__ part) {
-    __shared__ float red[4][64];
-    const int t = threadIdx.x, cj = t & 63, ph = t >> 6;
-    const int j = blockIdx.x * 64 + cj;
+__device__ __forceinline__ void column_sums(const float* __restrict__ a, int rows, int cols,
+                                            int bx, int bz, float* __restrict__ part,
+                                            float (*red)[64][3]) {
+    const int t = threadIdx.x, cj = t & 63, ph = (t >> 6) & 3;
+    const int j = bx * 64 + cj;
     const int per = (rows + kSlices - 1) / kSlices;
-    const int b0 = blockIdx.z * per, b1 = b0 + per < rows ? b0 + per : rows;
+    const int b0 = bz * per, b1 = b0 + per < rows ? b0 + per : rows;
     float s = 0.f;
     if (j < cols)
         for (int b = b0 + ph; b < b1; b += 4) s += a[(int64_t)b * cols + j];
-    red[ph][cj] = s;
+    red[ph][cj][0] = s;
     __syncthreads();
     if (ph == 0 && j < cols)
-        part[(int64_t)blockIdx.z * cols + j] = ((red[0][cj] + red[1][cj]) + red[2][cj]) + red[3][cj];
+        part[(int64_t)bz * cols + j] =
+            ((red[0][cj][0] + red[1][cj][0]) + red[2][cj][0]) + red[3][cj][0];
 }
 
-__global__ __launch_bounds__(kT) void k_sum_slices(const float* __restrict__ part, int m,
-                                                   float* __restrict__ out) {
-    const int i = blockIdx.x * kT + threadIdx.x;
-    if (i >= m) return;
+// All gradients of a batch that need nothing but dA1 and dA2, in one launch:
+// the split-K partials of dW2 = H1^T dA2 and dW1 = X^T dA1, the column sums of
+// dA1 and dA2 and the head's.  No part fills the chip alone, side by side they
+// do: 22 us for 4,096 rows of 128-512-512.  Blocks of one batch slice share an
+// L2 (every eighth block with 8 slices; its operands are 1.7 MB), and the tiles
+// take sixteen wavefronts, as in the small layers.
+constexpr int kGradT = 1024, kGradSlices = kGradT / 256;   // row slices of a block of sums
+constexpr int kSliceBlocks = kSlices / kGradSlices;
+struct GradArgs {
+    const uint16_t *h1q, *da2q, *xq, *da1q, *h2b;
+    const float *da1, *da2, *dout;
+    float *pw2, *pw1;                       // [slices][h1][h2], [slices][d][h1]
+    float *pb1, *pb2, *ph;                  // [kSlices][...]
+    int d, h1, h2, Bn, sq;                  // sq: depth steps of the batch
+    int slice_steps, slices;                // split-K
+    int g2, g1;                             // blocks of dW2 and dW1
+    int c1, c2;                             // groups of 64 columns of the sums (the head's last)
+};
+
+__global__ __launch_bounds__(kGradT) void k_grads(GradArgs g) {
+    using T = Tile<64, 64, 4, 4, 2>;
+    union Room {
+        uint16_t lds[T::kLds];
+        float red[kGradSlices][4][64][3];
+        __device__ Room() {}
+    };
+    __shared__ __attribute__((aligned(16))) Room room;
+    int b = blockIdx.x;
+    if (b < g.g2 + g.g1) {
+        const bool two = b < g.g2;
+        if (!two) b -= g.g2;
+        const int M = two ? g.h1 : g.d, N = two ? g.h2 : g.h1;
+        const int nt = (N + 63) / 64;
+        const int z = b % g.slices, x = b / g.slices;
+        const int n0 = 64 * (x % nt), m0 = 64 * (x / nt);
+        const int s0 = z * g.slice_steps, total = (g.Bn + 31) / 32;
+        const int ns = s0 + g.slice_steps < total ? g.slice_steps : total - s0;
+        T c;
+        c.run(two ? g.h1q : g.xq, g.sq, m0 / 16, two ? g.da2q : g.da1q, g.sq, n0 / 16, s0, ns,
+              room.lds);
+        float* p = (two ? g.pw2 : g.pw1) + (int64_t)z * M * N;
+        c.each(m0, n0, [&](int64_t mf, int nf, const v4f& v) {
+            const int64_t m = 16 * mf + lane_m();
+            const int n = 16 * nf + lane_n();
+            __attribute__((aligned(16))) const float a[4] = {v[0], v[1], v[2], v[3]};
+            put_flat<float4>(p, m, n, M, N, a);
+        });
+        return;
+    }
+    b -= g.g2 + g.g1;
+    const int ws = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    const int bx = b / kSliceBlocks, bz = (b % kSliceBlocks) * kGradSlices + ws;
+    if (bx < g.c1) column_sums(g.da1, g.Bn, g.h1, bx, bz, g.pb1, room.red[ws]);
+    else if (bx < g.c1 + g.c2)
+        column_sums(g.da2, g.Bn, g.h2, bx - g.c1, bz, g.pb2, room.red[ws]);
+    else head_wgrad(g.h2b, g.h2, g.dout, g.Bn, bx - g.c1 - g.c2, bz, g.ph, room.red[ws]);
+}
+
+// One parameter per thread: its gradient (the partials summed in their order,
+// or a caller's), one Adam step on it, and the bfloat16 copies of a weight in
+// the orders of the products that read it.
+struct FinishArgs {
+    float *th, *m1, *m2, *grad_out;         // grad_out may be null
+    const float* grad_in;                   // a caller's gradient, or null: the partials
+    const float *pw2, *pw1, *pb1, *pb2, *ph;
+    uint16_t *w1p, *w2p, *w2q, *w3b;
+    int64_t np, o_b1, o_w2, o_b2, o_w3;
+    int d, h1, h2, slices;
+    int adam;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ float sum_parts(const float* __restrict__ p, int64_t stride, int n) {
     float s = 0.f;
-    for (int z = 0; z < kSlices; z++) s += part[(int64_t)z * m + i];
-    out[i] = s;
+    for (int z = 0; z < n; z++) s += p[z * stride];
+    return s;
 }
 
-__global__ __launch_bounds__(kT) void k_adam(float* __restrict__ th, const float* __restrict__ g,
-                                             float* __restrict__ m1, float* __restrict__ m2,
-                                             int64_t np, float lr, float b1, float b2, float eps,
-                                             float c1, float c2) {
-    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (i >= np) return;
-    const float gi = g[i];
-    const float a = b1 * m1[i] + (1.f - b1) * gi;
-    const float v = b2 * m2[i] + (1.f - b2) * gi * gi;
-    m1[i] = a;
-    m2[i] = v;
-    th[i] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
+// the bfloat16 copies of parameter i (biases have none)
+__device__ __forceinline__ void put_weight(const FinishArgs& a, int64_t i, float v) {
+    const uint16_t h = f2bf(v);
+    if (i < a.o_b1) {
+        a.w1p[frag_at(i % a.h1, (int)(i / a.h1), depth_steps(a.d))] = h;
+    } else if (i >= a.o_w2 && i < a.o_b2) {
+        const int64_t q = i - a.o_w2;
+        const int k = (int)(q / a.h2), n = (int)(q % a.h2);
+        a.w2p[frag_at(n, k, depth_steps(a.h1))] = h;
+        a.w2q[frag_at(k, n, depth_steps(a.h2))] = h;
+    } else if (i >= a.o_w3 && i < a.o_w3 + 2 * (int64_t)a.h2) {
+        a.w3b[i - a.o_w3] = h;
+    }
 }
 
-__global__ __launch_bounds__(kT) void k_to_bf16(const float* __restrict__ a, int64_t m,
-                                                uint16_t* __restrict__ b) {
+__global__ __launch_bounds__(kT) void k_finish(FinishArgs a) {
     const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (i < m) b[i] = f2bf(a[i]);
+    if (i >= a.np) return;
+    float gi;
+    if (a.grad_in) gi = a.grad_in[i];
+    else if (i < a.o_b1) gi = sum_parts(a.pw1 + i, (int64_t)a.d * a.h1, a.slices);
+    else if (i < a.o_w2) gi = sum_parts(a.pb1 + (i - a.o_b1), a.h1, kSlices);
+    else if (i < a.o_b2) gi = sum_parts(a.pw2 + (i - a.o_w2), (int64_t)a.h1 * a.h2, a.slices);
+    else if (i < a.o_w3) gi = sum_parts(a.pb2 + (i - a.o_b2), a.h2, kSlices);
+    else gi = sum_parts(a.ph + (i - a.o_w3), 2 * a.h2 + 2, kSlices);
+    if (a.grad_out) a.grad_out[i] = gi;
+    if (!a.adam) return;
+    const float m = a.b1 * a.m1[i] + (1.f - a.b1) * gi;
+    const float v = a.b2 * a.m2[i] + (1.f - a.b2) * gi * gi;
+    a.m1[i] = m;
+    a.m2[i] = v;
+    const float th = a.th[i] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+    a.th[i] = th;
+    put_weight(a, i, th);
+}
+
+__global__ __launch_bounds__(kT) void k_weights(FinishArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (i < a.np) put_weight(a, i, a.th[i]);
 }
 
 // per-feature mean and 1/std over n rows, FP64 accumulation (one block per feature)
@@ -423,25 +742,20 @@ int64_t off_b2(const pixelsne_mlp* m) { return off_W2(m) + (int64_t)m->h1 * m->h
 int64_t off_W3(const pixelsne_mlp* m) { return off_b2(m) + m->h2; }
 int64_t off_b3(const pixelsne_mlp* m) { return off_W3(m) + (int64_t)m->h2 * 2; }
 
-hipError_t ensure_batch(pixelsne_mlp* m, int64_t B) {
+// a zeroed buffer of fragments (the padding of rows and depth stays zero)
+hipError_t mal_frags(pixelsne_mlp* m, uint16_t** p, int64_t rows, int64_t k) {
+    const size_t bytes = 2 * (size_t)frag_elems(rows, k);
+    hipError_t e = mal(m, p, bytes);
+    return e == hipSuccess ? hipMemsetAsync(*p, 0, bytes, m->stream) : e;
+}
+
+// buffers of a forward pass over B rows
+hipError_t ensure_forward(pixelsne_mlp* m, int64_t B) {
     if (B <= m->cap_batch) return hipSuccess;
     hipError_t e;
-    const int64_t h = m->h1 > m->h2 ? m->h1 : m->h2;
-    if ((e = mal(m, &m->xb, 2 * B * m->d)) != hipSuccess) return e;
-    if ((e = mal(m, &m->yb, 4 * B * 2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->a1, 4 * B * m->h1)) != hipSuccess) return e;
-    if ((e = mal(m, &m->a2, 4 * B * m->h2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->h1b, 2 * B * m->h1)) != hipSuccess) return e;
-    if ((e = mal(m, &m->h2b, 2 * B * m->h2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->out, 4 * B * 2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->dout, 4 * B * 2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->da2, 4 * B * m->h2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->da2b, 2 * B * m->h2)) != hipSuccess) return e;
-    if ((e = mal(m, &m->da1, 4 * B * m->h1)) != hipSuccess) return e;
-    if ((e = mal(m, &m->da1b, 2 * B * m->h1)) != hipSuccess) return e;
-    m->lossbuf_len = ceil_div(B, 4);
-    if ((e = mal(m, &m->lossbuf, 8 * m->lossbuf_len)) != hipSuccess) return e;
-    if (!m->part && (e = mal(m, &m->part, 4 * (size_t)kSlices * (2 * h + 2))) != hipSuccess) return e;
+    if ((e = mal_frags(m, &m->xp, B, m->d)) != hipSuccess) return e;
+    if ((e = mal_frags(m, &m->h1p, B, m->h1)) != hipSuccess) return e;
+    if ((e = mal(m, &m->h2b, 2 * (size_t)B * m->h2)) != hipSuccess) return e;
     m->cap_batch = B;
     return hipSuccess;
 }
@@ -451,103 +765,191 @@ int splits_for(int64_t K) {
     return s < 1 ? 1 : (s > 16 ? 16 : s);
 }
 
-hipError_t gemm(pixelsne_mlp* m, int epi, const uint16_t* A, int lda, int ta, const uint16_t* B,
-                int ldb, int tb, int M, int N, int K, float* C, const float* bias,
-                const float* pre, uint16_t* Cb) {
-    dim3 grid((unsigned)ceil_div(N, 64), (unsigned)ceil_div(M, 64), 1);
-    if (epi == EPI_F32) {
-        const int S = splits_for(K);
-        if (S > 1) {
-            const int64_t need = (int64_t)S * M * N;
-            if (need > m->splitk_len) {
-                hipError_t e = mal(m, &m->splitk, 4 * need);
-                if (e != hipSuccess) return e;
-                m->splitk_len = need;
-            }
-            const int kc = (int)ceil_div(ceil_div(K, S), 32) * 32;
-            grid.z = (unsigned)ceil_div(K, kc);
-            k_gemm_bf16<EPI_F32><<<grid, kT, 0, m->stream>>>(A, lda, ta, B, ldb, tb, M, N, K, kc,
-                                                             m->splitk, N, nullptr, nullptr,
-                                                             nullptr);
-            k_splitk_sum<<<g1((int64_t)M * N), kT, 0, m->stream>>>(m->splitk, (int64_t)M * N,
-                                                                  (int)grid.z, C);
-            return hipGetLastError();
-        }
-        k_gemm_bf16<EPI_F32><<<grid, kT, 0, m->stream>>>(A, lda, ta, B, ldb, tb, M, N, K, K, C, N,
-                                                         nullptr, nullptr, nullptr);
-    } else if (epi == EPI_BIAS_GELU) {
-        k_gemm_bf16<EPI_BIAS_GELU><<<grid, kT, 0, m->stream>>>(A, lda, ta, B, ldb, tb, M, N, K, K,
-                                                               C, N, bias, nullptr, Cb);
-    } else {
-        k_gemm_bf16<EPI_GELU_GRAD><<<grid, kT, 0, m->stream>>>(A, lda, ta, B, ldb, tb, M, N, K, K,
-                                                               C, N, nullptr, pre, Cb);
+// and of a training batch of B rows; the orders by columns are laid out for
+// their batch, so another size starts from zeroed ones
+hipError_t ensure_train(pixelsne_mlp* m, int64_t B) {
+    hipError_t e = ensure_forward(m, B);
+    if (e != hipSuccess) return e;
+    if (B > m->cap_train) {
+        if ((e = mal_frags(m, &m->xq, m->d, B)) != hipSuccess) return e;
+        if ((e = mal_frags(m, &m->h1q, m->h1, B)) != hipSuccess) return e;
+        if ((e = mal_frags(m, &m->da2p, B, m->h2)) != hipSuccess) return e;
+        if ((e = mal_frags(m, &m->da2q, m->h2, B)) != hipSuccess) return e;
+        if ((e = mal_frags(m, &m->da1q, m->h1, B)) != hipSuccess) return e;
+        if ((e = mal(m, &m->yb, 8 * (size_t)B)) != hipSuccess) return e;
+        if ((e = mal(m, &m->a1, 4 * (size_t)B * m->h1)) != hipSuccess) return e;
+        if ((e = mal(m, &m->a2, 4 * (size_t)B * m->h2)) != hipSuccess) return e;
+        if ((e = mal(m, &m->dout, 8 * (size_t)B)) != hipSuccess) return e;
+        if ((e = mal(m, &m->da2, 4 * (size_t)B * m->h2)) != hipSuccess) return e;
+        if ((e = mal(m, &m->da1, 4 * (size_t)B * m->h1)) != hipSuccess) return e;
+        m->cap_train = B;
+        m->train_steps = depth_steps(B);
     }
+    if (m->train_steps != depth_steps(B)) {
+        const int64_t rows[4] = {m->d, m->h1, m->h2, m->h1};
+        uint16_t* q[4] = {m->xq, m->h1q, m->da2q, m->da1q};
+        for (int x = 0; x < 4; x++)
+            if ((e = hipMemsetAsync(q[x], 0, 2 * (size_t)frag_elems(rows[x], B), m->stream)) !=
+                hipSuccess)
+                return e;
+        m->train_steps = depth_steps(B);
+    }
+    const int64_t need = splits_for(B) * ((int64_t)m->h1 * m->h2 + (int64_t)m->d * m->h1);
+    if (need > m->splitk_len) {
+        if ((e = mal(m, &m->splitk, 4 * (size_t)need)) != hipSuccess) return e;
+        m->splitk_len = need;
+    }
+    if (!m->part &&
+        (e = mal(m, &m->part, 4 * (size_t)kSlices * (m->h1 + 3 * (int64_t)m->h2 + 2))) != hipSuccess)
+        return e;
+    return hipSuccess;
+}
+
+hipError_t ensure_loss(pixelsne_mlp* m, int64_t partials) {
+    if (partials <= m->lossbuf_len) return hipSuccess;
+    hipError_t e = mal(m, &m->lossbuf, 8 * (size_t)partials);
+    if (e == hipSuccess) m->lossbuf_len = partials;
+    return e;
+}
+
+// 128 x 128 tiles of eight wavefronts when they give every CU two blocks (LDS
+// and L2 traffic per product halves), else 64 x 64 tiles of sixteen.  A
+// million rows through 1,024-wide layers take 4.98 ms with the large tiles and
+// 7.88 with the small, an epoch of 100,000 rows at 512 wide in batches of 4,096
+// (256 large tiles per layer) 3.07 with the large and 2.34 with the small.
+bool large_tiles(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, 128) >= 512; }
+
+dim3 layer_grid(int64_t M, int TM, int64_t N, int TN) {
+    return dim3((unsigned)(ceil_div(ceil_div(M, TM), kXcds) * kXcds * ceil_div(N, TN)));
+}
+
+hipError_t layer(pixelsne_mlp* m, const uint16_t* A, const uint16_t* B, int64_t K, int M, int N,
+                 const float* bias, float* pre, uint16_t* rowsP, uint16_t* colsQ, int sq,
+                 uint16_t* flat) {
+    const int steps = depth_steps(K);
+    if (large_tiles(M, N))
+        k_layer<128, 128, 2, 4, 1><<<layer_grid(M, 128, N, 128), 512, 0, m->stream>>>(
+            A, B, steps, M, N, bias, pre, rowsP, colsQ, sq, flat);
+    else
+        k_layer<64, 64, 4, 4, 2><<<layer_grid(M, 64, N, 64), 1024, 0, m->stream>>>(
+            A, B, steps, M, N, bias, pre, rowsP, colsQ, sq, flat);
     return hipGetLastError();
 }
 
-// forward of staged rows xb[0..Bn) -> out (and, with targets, dout + loss partials)
-hipError_t forward_batch(pixelsne_mlp* m, int Bn, bool with_targets) {
-    hipError_t e;
-    if ((e = gemm(m, EPI_BIAS_GELU, m->xb, m->d, 0, m->w1b, m->h1, 0, Bn, m->h1, m->d, m->a1,
-                  m->theta + off_b1(m), nullptr, m->h1b)) != hipSuccess)
-        return e;
-    if ((e = gemm(m, EPI_BIAS_GELU, m->h1b, m->h1, 0, m->w2b, m->h2, 0, Bn, m->h2, m->h1, m->a2,
-                  m->theta + off_b2(m), nullptr, m->h2b)) != hipSuccess)
-        return e;
-    k_head_fwd<<<dim3((unsigned)ceil_div(Bn, 4)), kT, 0, m->stream>>>(
-        m->h2b, m->h2, m->w3b, m->theta + off_b3(m), Bn, m->out, with_targets ? m->yb : nullptr,
-        m->dout, with_targets ? m->lossbuf : nullptr);
+// staged rows xp[0..Bn) through both layers; training keeps the
+// pre-activations and H1 by columns
+hipError_t forward_layers(pixelsne_mlp* m, int Bn, bool train) {
+    const int sq = depth_steps(Bn);
+    hipError_t e = layer(m, m->xp, m->w1p, m->d, Bn, m->h1, m->theta + off_b1(m),
+                         train ? m->a1 : nullptr, m->h1p, train ? m->h1q : nullptr, sq, nullptr);
+    if (e != hipSuccess) return e;
+    return layer(m, m->h1p, m->w2p, m->h1, Bn, m->h2, m->theta + off_b2(m),
+                 train ? m->a2 : nullptr, nullptr, nullptr, 0, m->h2b);
+}
+
+FinishArgs finish_args(pixelsne_mlp* m) {
+    FinishArgs a{};
+    a.th = m->theta;
+    a.m1 = m->m1;
+    a.m2 = m->m2;
+    a.w1p = m->w1p;
+    a.w2p = m->w2p;
+    a.w2q = m->w2q;
+    a.w3b = m->w3b;
+    a.np = m->n_params;
+    a.o_b1 = off_b1(m);
+    a.o_w2 = off_W2(m);
+    a.o_b2 = off_b2(m);
+    a.o_w3 = off_W3(m);
+    a.d = m->d;
+    a.h1 = m->h1;
+    a.h2 = m->h2;
+    return a;
+}
+
+// Gradient partials of a staged batch: seven launches with the staging and
+// k_finish.  lossp: the batch's loss partials, one per four rows.
+hipError_t grad_batch(pixelsne_mlp* m, int Bn, double* lossp, FinishArgs& fin) {
+    hipError_t e = forward_layers(m, Bn, true);
+    if (e != hipSuccess) return e;
+    const int sq = depth_steps(Bn);
+    k_head_train<<<dim3((unsigned)(32 * sq / kHeadRows)), kHeadT, 0, m->stream>>>(
+        m->h2b, m->h2, m->w3b, m->theta + off_b3(m), Bn, m->yb, m->a2, m->dout, lossp, m->da2,
+        depth_steps(m->h2), m->da2p, sq, m->da2q);
+    // dA1 = (dA2 W2^T) * GELU'(A1)
+    const int steps = depth_steps(m->h2);
+    if (large_tiles(Bn, m->h1))
+        k_layer_back<128, 128, 2, 4, 1><<<layer_grid(Bn, 128, m->h1, 128), 512, 0, m->stream>>>(
+            m->da2p, m->w2q, steps, Bn, m->h1, m->a1, m->da1, m->da1q, sq);
+    else
+        k_layer_back<64, 64, 4, 4, 2><<<layer_grid(Bn, 64, m->h1, 64), 1024, 0, m->stream>>>(
+            m->da2p, m->w2q, steps, Bn, m->h1, m->a1, m->da1, m->da1q, sq);
+    GradArgs g{};
+    g.h1q = m->h1q;
+    g.da2q = m->da2q;
+    g.xq = m->xq;
+    g.da1q = m->da1q;
+    g.h2b = m->h2b;
+    g.da1 = m->da1;
+    g.da2 = m->da2;
+    g.dout = m->dout;
+    g.d = m->d;
+    g.h1 = m->h1;
+    g.h2 = m->h2;
+    g.Bn = Bn;
+    g.sq = sq;
+    g.slice_steps = (int)ceil_div(ceil_div(Bn, splits_for(Bn)), 32);
+    g.slices = (int)ceil_div(Bn, 32 * (int64_t)g.slice_steps);
+    g.pw2 = m->splitk;
+    g.pw1 = m->splitk + (int64_t)g.slices * m->h1 * m->h2;
+    g.pb1 = m->part;
+    g.pb2 = g.pb1 + (int64_t)kSlices * m->h1;
+    g.ph = g.pb2 + (int64_t)kSlices * m->h2;
+    const int64_t t1 = ceil_div(m->h1, 64), t2 = ceil_div(m->h2, 64);
+    const int64_t g2 = t1 * t2 * g.slices, g1 = ceil_div(m->d, 64) * t1 * g.slices;
+    const int64_t total = g2 + g1 + (t1 + 2 * t2) * kSliceBlocks;
+    if (total >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    g.g2 = (int)g2;
+    g.g1 = (int)g1;
+    g.c1 = (int)t1;
+    g.c2 = (int)t2;
+    k_grads<<<dim3((unsigned)total), kGradT, 0, m->stream>>>(g);
+    fin = finish_args(m);
+    fin.pw2 = g.pw2;
+    fin.pw1 = g.pw1;
+    fin.pb1 = g.pb1;
+    fin.pb2 = g.pb2;
+    fin.ph = g.ph;
+    fin.slices = g.slices;
     return hipGetLastError();
 }
 
-hipError_t backward_batch(pixelsne_mlp* m, int Bn) {
-    hipError_t e;
-    float* g = m->grad;
-    // dW3 and db3 are adjacent in the flat gradient: 2 h2 + 2 values
-    k_head_wgrad_part<<<dim3((unsigned)ceil_div(m->h2, 64), 1, kSlices), kT, 0, m->stream>>>(
-        m->h2b, m->h2, m->dout, Bn, m->part);
-    k_sum_slices<<<g1(2 * m->h2 + 2), kT, 0, m->stream>>>(m->part, 2 * m->h2 + 2, g + off_W3(m));
-    k_head_bgrad<<<g1((int64_t)Bn * m->h2), kT, 0, m->stream>>>(m->dout, m->w3b, m->a2, m->h2, Bn,
-                                                               m->da2, m->da2b);
-    k_colsum_part<<<dim3((unsigned)ceil_div(m->h2, 64), 1, kSlices), kT, 0, m->stream>>>(
-        m->da2, Bn, m->h2, m->part);
-    k_sum_slices<<<g1(m->h2), kT, 0, m->stream>>>(m->part, m->h2, g + off_b2(m));
-    // dW2 = H1^T dA2 : A = H1 stored [B][h1] (transposed), B = dA2 [B][h2]
-    if ((e = gemm(m, EPI_F32, m->h1b, m->h1, 1, m->da2b, m->h2, 0, m->h1, m->h2, Bn,
-                  g + off_W2(m), nullptr, nullptr, nullptr)) != hipSuccess)
-        return e;
-    // dA1 = (dA2 W2^T) * GELU'(A1) : B = W2 stored [h1][h2] = [N][K] (transposed)
-    if ((e = gemm(m, EPI_GELU_GRAD, m->da2b, m->h2, 0, m->w2b, m->h2, 1, Bn, m->h1, m->h2, m->da1,
-                  nullptr, m->a1, m->da1b)) != hipSuccess)
-        return e;
-    k_colsum_part<<<dim3((unsigned)ceil_div(m->h1, 64), 1, kSlices), kT, 0, m->stream>>>(
-        m->da1, Bn, m->h1, m->part);
-    k_sum_slices<<<g1(m->h1), kT, 0, m->stream>>>(m->part, m->h1, g + off_b1(m));
-    // dW1 = X^T dA1
-    return gemm(m, EPI_F32, m->xb, m->d, 1, m->da1b, m->h1, 0, m->d, m->h1, Bn, g + off_W1(m),
-                nullptr, nullptr, nullptr);
+hipError_t stage_train(pixelsne_mlp* m, const float* X, const float* Y, const uint32_t* order,
+                       int64_t b0, int Bn) {
+    const int steps = depth_steps(m->d), sq = depth_steps(Bn);
+    k_stage_train<<<g1((int64_t)4 * sq * 32 * steps), kT, 0, m->stream>>>(
+        X, m->d, steps, order, b0, Bn, sq, m->mean, m->inv_std, m->xp, m->xq, Y, m->yb);
+    return hipGetLastError();
 }
 
 hipError_t refresh_bf16(pixelsne_mlp* m) {
-    k_to_bf16<<<g1((int64_t)m->d * m->h1), kT, 0, m->stream>>>(m->theta + off_W1(m),
-                                                              (int64_t)m->d * m->h1, m->w1b);
-    k_to_bf16<<<g1((int64_t)m->h1 * m->h2), kT, 0, m->stream>>>(m->theta + off_W2(m),
-                                                               (int64_t)m->h1 * m->h2, m->w2b);
-    k_to_bf16<<<g1((int64_t)m->h2 * 2), kT, 0, m->stream>>>(m->theta + off_W3(m),
-                                                           (int64_t)m->h2 * 2, m->w3b);
+    k_weights<<<g1(m->n_params), kT, 0, m->stream>>>(finish_args(m));
     return hipGetLastError();
 }
 
 // One Adam step (Kingma & Ba, 2015; beta 0.9 / 0.999, eps 1e-8, bias-corrected)
-// on the master weights with gradient g, then the bfloat16 weight copies.
-hipError_t adam_update(pixelsne_mlp* m, const float* g, float lr) {
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+// on the master weights, with the bfloat16 weight copies.
+hipError_t adam_update(pixelsne_mlp* m, FinishArgs a, float lr) {
+    a.adam = 1;
+    a.b1 = 0.9f;
+    a.b2 = 0.999f;
+    a.eps = 1e-8f;
+    a.lr = lr;
     m->step++;
-    const float c1 = 1.f - powf(b1, (float)m->step), c2 = 1.f - powf(b2, (float)m->step);
-    k_adam<<<g1(m->n_params), kT, 0, m->stream>>>(m->theta, g, m->m1, m->m2, m->n_params, lr, b1,
-                                                 b2, eps, c1, c2);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? refresh_bf16(m) : e;
+    a.c1 = 1.f - powf(a.b1, (float)m->step);
+    a.c2 = 1.f - powf(a.b2, (float)m->step);
+    k_finish<<<g1(m->n_params), kT, 0, m->stream>>>(a);
+    return hipGetLastError();
 }
 
 psne_status mlp_error(hipError_t e, const char* where) {
@@ -588,11 +990,11 @@ pixelsne_mlp* pixelsne_mlp_create(int32_t d_in, int32_t h1, int32_t h2, uint64_t
     m->stream = (hipStream_t)stream;
     m->n_params = (int64_t)d_in * h1 + h1 + (int64_t)h1 * h2 + h2 + (int64_t)h2 * 2 + 2;
     hipError_t e = mal(m, &m->theta, 4 * m->n_params);
-    if (e == hipSuccess) e = mal(m, &m->grad, 4 * m->n_params);
     if (e == hipSuccess) e = mal(m, &m->m1, 4 * m->n_params);
     if (e == hipSuccess) e = mal(m, &m->m2, 4 * m->n_params);
-    if (e == hipSuccess) e = mal(m, &m->w1b, 2 * (size_t)d_in * h1);
-    if (e == hipSuccess) e = mal(m, &m->w2b, 2 * (size_t)h1 * h2);
+    if (e == hipSuccess) e = mal_frags(m, &m->w1p, h1, d_in);
+    if (e == hipSuccess) e = mal_frags(m, &m->w2p, h2, h1);
+    if (e == hipSuccess) e = mal_frags(m, &m->w2q, h1, h2);
     if (e == hipSuccess) e = mal(m, &m->w3b, 2 * (size_t)h2 * 2);
     if (e == hipSuccess) e = mal(m, &m->mean, 4 * (size_t)d_in);
     if (e == hipSuccess) e = mal(m, &m->inv_std, 4 * (size_t)d_in);
@@ -678,14 +1080,18 @@ psne_status pixelsne_mlp_grad(pixelsne_mlp* m, const float* X, const float* Y01,
         return PSNE_E_INVAL;
     }
     if (grads_out && !dev_ptr(grads_out)) { set_error("mlp_grad: grads_out must be a device pointer"); return PSNE_E_INVAL; }
-    hipError_t e = ensure_batch(m, n);
+    hipError_t e = ensure_train(m, n);
+    if (e == hipSuccess) e = ensure_loss(m, ceil_div(n, 4));
     if (e != hipSuccess) return mlp_error(e, "mlp_grad");
-    k_stage_x<<<g1(n * m->d), kT, 0, m->stream>>>(X, m->d, nullptr, 0, (int)n, m->mean, m->inv_std,
-                                                  m->xb, Y01, m->yb);
-    if ((e = forward_batch(m, (int)n, true)) == hipSuccess) e = backward_batch(m, (int)n);
+    FinishArgs fin;
+    e = stage_train(m, X, Y01, nullptr, 0, (int)n);
+    if (e == hipSuccess) e = grad_batch(m, (int)n, m->lossbuf, fin);
+    if (e == hipSuccess && grads_out) {
+        fin.grad_out = grads_out;
+        k_finish<<<g1(m->n_params), kT, 0, m->stream>>>(fin);
+        e = hipGetLastError();
+    }
     std::vector<double> lp(m->lossbuf_len);
-    if (e == hipSuccess && grads_out)
-        e = hipMemcpyAsync(grads_out, m->grad, 4 * m->n_params, hipMemcpyDeviceToDevice, m->stream);
     const int64_t nb = ceil_div(n, 4);
     if (e == hipSuccess)
         e = hipMemcpyAsync(lp.data(), m->lossbuf, 8 * nb, hipMemcpyDeviceToHost, m->stream);
@@ -707,7 +1113,10 @@ psne_status pixelsne_mlp_train(pixelsne_mlp* m, const float* X, const float* Y01
         return PSNE_E_INVAL;
     }
     const int64_t B = batch < n ? batch : n;
-    hipError_t e = ensure_batch(m, B);
+    const int64_t nbatch = n / B;                // full batches only
+    const int64_t nl = ceil_div(B, 4);           // loss partials per batch
+    hipError_t e = ensure_train(m, B);
+    if (e == hipSuccess) e = ensure_loss(m, nbatch * nl);
     if (e == hipSuccess && m->order_len < n) {
         e = mal(m, &m->order, 4 * (size_t)n);
         m->order_len = n;
@@ -721,24 +1130,21 @@ psne_status pixelsne_mlp_train(pixelsne_mlp* m, const float* X, const float* Y01
         std::shuffle(ord.begin(), ord.end(), rng);
         e = hipMemcpyAsync(m->order, ord.data(), 4 * (size_t)n, hipMemcpyHostToDevice, m->stream);
         if (e != hipSuccess) return mlp_error(e, "mlp_train");
-        std::vector<double> lsum;
-        const int64_t nbatch = n / B;            // full batches only
-        std::vector<double> lp(m->lossbuf_len);
-        double acc = 0.0;
         for (int64_t bi = 0; bi < nbatch && e == hipSuccess; bi++) {
-            k_stage_x<<<g1(B * m->d), kT, 0, m->stream>>>(X, m->d, m->order, bi * B, (int)B,
-                                                          m->mean, m->inv_std, m->xb, Y01, m->yb);
-            e = forward_batch(m, (int)B, true);
-            if (e == hipSuccess) e = backward_batch(m, (int)B);
-            if (e == hipSuccess) e = adam_update(m, m->grad, lr);
-            if (e == hipSuccess && ep == epochs - 1) {
-                e = hipMemcpyAsync(lp.data(), m->lossbuf, 8 * ceil_div(B, 4), hipMemcpyDeviceToHost,
-                                   m->stream);
-                if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
-                for (int64_t i = 0; i < ceil_div(B, 4); i++) acc += lp[i];
-            }
+            FinishArgs fin;
+            e = stage_train(m, X, Y01, m->order, bi * B, (int)B);
+            if (e == hipSuccess) e = grad_batch(m, (int)B, m->lossbuf + bi * nl, fin);
+            if (e == hipSuccess) e = adam_update(m, fin, lr);
         }
-        if (ep == epochs - 1 && nbatch > 0) epoch_loss = acc / (double)(nbatch * B);
+    }
+    if (e == hipSuccess && epochs > 0 && nbatch > 0) {
+        // the last epoch's partials, added in their order
+        std::vector<double> lp((size_t)(nbatch * nl));
+        e = hipMemcpyAsync(lp.data(), m->lossbuf, 8 * lp.size(), hipMemcpyDeviceToHost, m->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
+        double acc = 0.0;
+        for (double v : lp) acc += v;
+        epoch_loss = acc / (double)(nbatch * B);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     if (e != hipSuccess) return mlp_error(e, "mlp_train");
@@ -751,7 +1157,9 @@ psne_status pixelsne_mlp_adam_step(pixelsne_mlp* m, const float* grad, float lr)
         set_error("mlp_adam_step: bad arguments");
         return PSNE_E_INVAL;
     }
-    hipError_t e = adam_update(m, grad, lr);
+    FinishArgs fin = finish_args(m);
+    fin.grad_in = grad;
+    hipError_t e = adam_update(m, fin, lr);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     return e == hipSuccess ? PSNE_OK : mlp_error(e, "mlp_adam_step");
 }
@@ -782,16 +1190,23 @@ psne_status pixelsne_mlp_forward(pixelsne_mlp* m, const float* X, int64_t n, flo
         set_error("mlp_forward: bad arguments");
         return PSNE_E_INVAL;
     }
-    const int64_t B = n < 8192 ? n : 8192;
-    hipError_t e = ensure_batch(m, B);
+    // rows per pass: whole rounds of 128 x 128 tiles, 140 MB of activations at
+    // 1,024 wide
+    const int64_t B = n < kForwardRows ? n : kForwardRows;
+    hipError_t e = ensure_forward(m, B);
+    const int steps = depth_steps(m->d);
     for (int64_t b0 = 0; b0 < n && e == hipSuccess; b0 += B) {
         const int Bn = (int)(n - b0 < B ? n - b0 : B);
-        k_stage_x<<<g1((int64_t)Bn * m->d), kT, 0, m->stream>>>(X, m->d, nullptr, b0, Bn, m->mean,
-                                                                m->inv_std, m->xb, nullptr, nullptr);
-        e = forward_batch(m, Bn, false);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(Y01_out + 2 * b0, m->out, 8 * (size_t)Bn, hipMemcpyDeviceToDevice,
-                               m->stream);
+        const int64_t rows = pad_tile(Bn);
+        k_stage_x<<<g1(rows * 4 * steps), kT, 0, m->stream>>>(
+            X, m->d, steps, b0, Bn, rows, m->d % 4 == 0 && (uintptr_t)X % 16 == 0, m->mean,
+            m->inv_std, m->xp);
+        e = forward_layers(m, Bn, false);
+        if (e == hipSuccess) {
+            k_head<<<dim3((unsigned)ceil_div(Bn, kPlaceRows * (kT / 64))), kT, 0, m->stream>>>(
+                m->h2b, m->h2, m->w3b, m->theta + off_b3(m), Bn, Y01_out + 2 * b0);
+            e = hipGetLastError();
+        }
     }
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     return e == hipSuccess ? PSNE_OK : mlp_error(e, "mlp_forward");
