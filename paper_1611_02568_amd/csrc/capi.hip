@@ -154,8 +154,12 @@ hipError_t alloc_iteration_buffers(pixelsne_ctx* c) {
         if ((e = dalloc(c, &tb.key[h], 4 * (size_t)n)) != hipSuccess) return e;
         if ((e = dalloc(c, &tb.idx[h], 4 * (size_t)n)) != hipSuccess) return e;
     }
-    if ((e = dalloc(c, &tb.hist, 4 * 256 * (size_t)tb.sort_blocks)) != hipSuccess) return e;
-    if ((e = dalloc(c, &tb.dtot, 4 * 256)) != hipSuccess) return e;
+    // for the sorts of the iteration, the renumbering, the embedding's
+    // neighbours and the data tree
+    int64_t hist = 256 * tb.sort_blocks;
+    for (int bits : {2 * c->L, 30, 32}) hist = std::max(hist, psne::sort_hist_words(n, bits));
+    if ((e = dalloc(c, &tb.hist, 4 * (size_t)hist)) != hipSuccess) return e;
+    if ((e = dalloc(c, &tb.dtot, 4 * (size_t)psne::sort_digit_words())) != hipSuccess) return e;
     if ((e = dalloc(c, &tb.lvl_cnt, 4 * (size_t)(lmax + 1) * tb.tree_blocks)) != hipSuccess) return e;
     if ((e = dalloc(c, &tb.ltot, 4 * (size_t)(lmax + 1))) != hipSuccess) return e;
     if (dtree) {

@@ -15,9 +15,9 @@ struct TreeBufs {
     uint32_t* key[2] = {nullptr, nullptr};   // radix-sort ping-pong: Morton keys
     uint32_t* idx[2] = {nullptr, nullptr};   // ... and point indices
     int sorted = 0;                          // which half holds the sorted result
-    uint32_t* hist = nullptr;                // [256][sort blocks]
-    uint32_t* dtot = nullptr;                // [256] digit totals of one pass
-    int64_t sort_blocks = 0;
+    uint32_t* hist = nullptr;                // digit counts of the sort's tiles
+    uint32_t* dtot = nullptr;                // digit totals of one pass
+    int64_t sort_blocks = 0;                 // of the data tree's sort
     uint32_t* lvl_cnt = nullptr;             // [levels][tree blocks], scanned in place
     uint32_t* ltot = nullptr;                // [levels] cells per level
     int64_t tree_blocks = 0;
@@ -136,10 +136,11 @@ hipError_t run_export_dtree(const pixelsne_ctx* c, uint64_t* keys, uint32_t* per
 hipError_t run_rows_scan(uint32_t* a, int64_t rows, int64_t len, uint32_t* tot, hipStream_t s);
 // stable sort of (tb.key[0], index) on the low `bits` key bits
 hipError_t run_sort_bits(pixelsne_ctx* c, int bits);
-// stable LSD radix sort (8-bit digits) of the pairs (key[0][i], i) on the low
-// `bits` key bits; the result lands in key[*sorted], idx[*sorted].  hist holds
-// 256 * sort_blocks_for(n) words, dtot 256.
-int64_t sort_blocks_for(int64_t n);
+// stable LSD radix sort of the pairs (key[0][i], i) on the low `bits` key bits;
+// the result lands in key[*sorted], idx[*sorted].  hist holds
+// sort_hist_words(n, bits) words, dtot sort_digit_words().
+int64_t sort_hist_words(int64_t n, int bits);
+int64_t sort_digit_words();
 hipError_t sort_pairs32(uint32_t* const key[2], uint32_t* const idx[2], int64_t n, int bits,
                         uint32_t* hist, uint32_t* dtot, hipStream_t s, int* sorted);
 hipError_t run_tree(pixelsne_ctx* c);

@@ -31,52 +31,77 @@ namespace psne {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kRsItems = 8;
-constexpr int kRsTile = kBlock * kRsItems;
+constexpr int kRsItems = 4;
 constexpr int kAttractBlocksMax = 8192;
+constexpr int kRsMaxBits = 11;               // of a sort digit
 
 
 // ---------------------------------------------------------------------------
-// snap: z = clamp((zh - zmin) * scale, 0, r^-), key = Morton(floor(z))
+// radix sort (stable, LSD): per pass the tiles' digit counts ([digit][tile]),
+// their scan, and the scatter; a tile of TH kRsItems keys per block.
+//
+// Bound by launches and latency, not bytes, so digits are wide: the 22 key bits
+// of a 2,048 screen take two passes of 11 bits, the 20 of a 1,024 screen two of
+// 10, and the snap pass makes the first counts.  With three passes of 8 bits
+// and a separate snap an iteration of 70,000 points takes 255 us, with two 235,
+// one of 2,000 points 161 and 141.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_snap(const T* __restrict__ zh, T* __restrict__ z,
-                                                 uint32_t* __restrict__ key,
-                                                 uint32_t* __restrict__ idx,
-                                                 const DevScalars* __restrict__ sc, int64_t n,
-                                                 int r) {
-    using V = v2_t<T>;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const T top = top_below<T>(r);
-    const V p = reinterpret_cast<const V*>(zh)[i];
-    T zx = (p.x - (T)sc->zmin[0]) * (T)sc->scale[0];
-    T zy = (p.y - (T)sc->zmin[1]) * (T)sc->scale[1];
-    zx = zx < T(0) ? T(0) : (zx > top ? top : zx);
-    zy = zy < T(0) ? T(0) : (zy > top ? top : zy);
-    reinterpret_cast<V*>(z)[i] = V{zx, zy};
-    const uint32_t px = (uint32_t)zx, py = (uint32_t)zy;
-    key[i] = spread_bits16(px) | (spread_bits16(py) << 1);
-    idx[i] = (uint32_t)i;
-}
+struct SortPlan {
+    int passes, bits;                        // digits of `bits` bits
+    int threads;
+    int64_t tiles;
+};
 
-// ---------------------------------------------------------------------------
-// radix sort (stable, LSD, 8-bit digits)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t* __restrict__ keys, int64_t n,
-                                                    int shift, uint32_t* __restrict__ hist,
-                                                    int64_t nblocks) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
+template <int TH>
+__global__ __launch_bounds__(TH) void k_rs_hist(const uint32_t* __restrict__ keys, int64_t n,
+                                                int shift, int bits, uint32_t* __restrict__ hist) {
+    __shared__ uint32_t h[1 << kRsMaxBits];
+    for (int d = threadIdx.x; d < 1 << bits; d += TH) h[d] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
+    const int64_t base = (int64_t)blockIdx.x * (TH * kRsItems);
+    const uint32_t mask = (1u << bits) - 1u;
 #pragma unroll
     for (int j = 0; j < kRsItems; j++) {
-        const int64_t p = base + j * kBlock + threadIdx.x;
-        if (p < n) atomicAdd(&h[(keys[p] >> shift) & 255u], 1u);
+        const int64_t p = base + j * TH + threadIdx.x;
+        if (p < n) atomicAdd(&h[(keys[p] >> shift) & mask], 1u);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    for (int d = threadIdx.x; d < 1 << bits; d += TH)
+        hist[(int64_t)d * gridDim.x + blockIdx.x] = h[d];
+}
+
+// Snap: z = clamp((zh - zmin) * scale, 0, r^-), key = Morton(floor(z)), and the
+// first pass's digit counts.
+template <typename T, int TH>
+__global__ __launch_bounds__(TH) void k_snap(const T* __restrict__ zh, T* __restrict__ z,
+                                             uint32_t* __restrict__ key,
+                                             const DevScalars* __restrict__ sc, int64_t n, int r,
+                                             int bits, uint32_t* __restrict__ hist) {
+    using V = v2_t<T>;
+    __shared__ uint32_t h[1 << kRsMaxBits];
+    for (int d = threadIdx.x; d < 1 << bits; d += TH) h[d] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * (TH * kRsItems);
+    const uint32_t mask = (1u << bits) - 1u;
+    const T top = top_below<T>(r);
+    const T m0 = (T)sc->zmin[0], m1 = (T)sc->zmin[1], s0 = (T)sc->scale[0], s1 = (T)sc->scale[1];
+#pragma unroll
+    for (int j = 0; j < kRsItems; j++) {
+        const int64_t i = base + j * TH + threadIdx.x;
+        if (i >= n) continue;
+        const V p = reinterpret_cast<const V*>(zh)[i];
+        T zx = (p.x - m0) * s0;
+        T zy = (p.y - m1) * s1;
+        zx = zx < T(0) ? T(0) : (zx > top ? top : zx);
+        zy = zy < T(0) ? T(0) : (zy > top ? top : zy);
+        reinterpret_cast<V*>(z)[i] = V{zx, zy};
+        const uint32_t k = spread_bits16((uint32_t)zx) | (spread_bits16((uint32_t)zy) << 1);
+        key[i] = k;
+        atomicAdd(&h[k & mask], 1u);
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < 1 << bits; d += TH)
+        hist[(int64_t)d * gridDim.x + blockIdx.x] = h[d];
 }
 
 // Exclusive scan of each row of a [rows][len] uint32 array in place (one block
@@ -120,70 +145,104 @@ __global__ __launch_bounds__(kBlock) void k_rows_scan(uint32_t* __restrict__ a, 
     if (t == 0) tot[blockIdx.x] = carry;
 }
 
-__global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t* __restrict__ kin,
-                                                       const uint32_t* __restrict__ vin,
-                                                       uint32_t* __restrict__ kout,
-                                                       uint32_t* __restrict__ vout, int64_t n,
-                                                       int shift,
-                                                       const uint32_t* __restrict__ hist,
-                                                       const uint32_t* __restrict__ dtot,
-                                                       int64_t nblocks) {
-    __shared__ uint32_t run[256];
-    __shared__ uint32_t wcnt[4][256];
+// One tile: wavefront w holds the keys 256 w + 64 j + lane, so that wavefront,
+// j and lane are their order.  A key's place in its digit is its rank among the
+// lanes (ballots per digit bit), behind the wavefront's earlier rounds (a
+// counter per wavefront and digit, touched by that wavefront alone), behind
+// the wavefronts before it.
+template <int TH>
+__global__ __launch_bounds__(TH) void k_rs_scatter(
+    const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
+    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift, int bits,
+    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ dtot) {
+    extern __shared__ uint32_t rs_lds[];
+    const int bins = 1 << bits;
+    uint32_t* at = rs_lds;                                   // [bins] first place of a digit
+    uint16_t* cnt = reinterpret_cast<uint16_t*>(rs_lds + bins);   // [wavefronts][bins]
+    __shared__ uint32_t ws[(TH / kWave)];
     const int t = threadIdx.x, w = t >> 6, lane = lane_id();
-    {
-        // digit bases: exclusive scan of the 256 digit totals
-        const uint32_t v = dtot[t];
-        uint32_t x = v;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t y = __shfl_up(x, o, kWave);
-            if (lane >= o) x += y;
-        }
-        if (lane == kWave - 1) wcnt[0][w] = x;
-        __syncthreads();
-        uint32_t pre = x - v;
-        for (int q = 0; q < w; q++) pre += wcnt[0][q];
-        run[t] = pre + hist[(int64_t)t * nblocks + blockIdx.x];
-        __syncthreads();
-    }
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    // every item's key and value loaded up front, so that the loads overlap
-    // instead of waiting behind each round's barriers
+    const int64_t base = (int64_t)blockIdx.x * (TH * kRsItems) + w * (kWave * kRsItems) + lane;
     uint32_t keys[kRsItems], vals[kRsItems];
 #pragma unroll
     for (int j = 0; j < kRsItems; j++) {
-        const int64_t p = base + j * kBlock + t;
+        const int64_t p = base + j * kWave;
         keys[j] = p < n ? kin[p] : 0u;
         vals[j] = p < n ? (vin ? vin[p] : (uint32_t)p) : 0u;
     }
+    for (int x = t; x < bins * (TH / kWave) / 2; x += TH) rs_lds[bins + x] = 0;
+    // the digit's keys in the tiles before this one, and in all
+    uint32_t mine[(1 << kRsMaxBits) / TH];
+#pragma unroll
+    for (int q = 0; q < (1 << kRsMaxBits) / TH; q++) {
+        const int d = q * TH + t;
+        if (d >= bins) continue;
+        mine[q] = hist[(int64_t)d * gridDim.x + blockIdx.x];
+        at[d] = dtot[d];
+    }
+    __syncthreads();
+    // exclusive scan of the totals, `per` consecutive digits per thread
+    const int per = bins > TH ? bins / TH : 1;
+    uint32_t sum = 0;
+    if (t * per < bins)
+        for (int q = 0; q < per; q++) sum += at[t * per + q];
+    uint32_t x = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) ws[w] = x;
+    // places within the wavefront meanwhile
+    uint32_t loc[kRsItems];
+    uint16_t* own = cnt + w * bins;
 #pragma unroll
     for (int j = 0; j < kRsItems; j++) {
-        const int64_t p = base + j * kBlock + t;
-        const bool valid = p < n;
-        const uint32_t key = keys[j];
-        const uint32_t val = vals[j];
-        const uint32_t d = (key >> shift) & 255u;
-        wcnt[0][t] = 0; wcnt[1][t] = 0; wcnt[2][t] = 0; wcnt[3][t] = 0;
-        __syncthreads();
+        const bool valid = base + j * kWave < n;
+        const uint32_t d = (keys[j] >> shift) & (uint32_t)(bins - 1);
         uint64_t peers = ballot64(valid);
-#pragma unroll
-        for (int b = 0; b < 8; b++) {
+        for (int b = 0; b < bits; b++) {
             const bool bit = (d >> b) & 1u;
             const uint64_t m = ballot64(bit);
             peers &= bit ? m : ~m;
         }
         const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
-        if (valid && rank == 0) wcnt[w][d] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t off = run[d] + rank;
-            for (int q = 0; q < w; q++) off += wcnt[q][d];
-            kout[off] = key;
-            vout[off] = val;
+        const uint32_t before = own[d];
+        __builtin_amdgcn_wave_barrier();
+        if (valid && rank == 0) own[d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+        __builtin_amdgcn_wave_barrier();
+        loc[j] = before + rank;
+    }
+    __syncthreads();
+    uint32_t run = x - sum;
+    for (int q = 0; q < w; q++) run += ws[q];
+    if (t * per < bins)
+        for (int q = 0; q < per; q++) {
+            const uint32_t v = at[t * per + q];
+            at[t * per + q] = run;
+            run += v;
         }
-        __syncthreads();
-        run[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < (1 << kRsMaxBits) / TH; q++) {
+        const int d = q * TH + t;
+        if (d >= bins) continue;
+        at[d] += mine[q];
+        uint32_t before = 0;
+#pragma unroll
+        for (int v = 0; v < (TH / kWave); v++) {
+            const uint32_t c = cnt[v * bins + d];
+            cnt[v * bins + d] = (uint16_t)before;
+            before += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRsItems; j++) {
+        if (base + j * kWave >= n) continue;
+        const uint32_t d = (keys[j] >> shift) & (uint32_t)(bins - 1);
+        const uint32_t off = at[d] + own[d] + loc[j];
+        kout[off] = keys[j];
+        vout[off] = vals[j];
     }
 }
 
@@ -1601,20 +1660,44 @@ StepParams step_params(const pixelsne_ctx* c, double alpha) {
 
 int64_t attract_block_count(int64_t n) { return attract_blocks(n); }
 
-hipError_t run_snap(pixelsne_ctx* c) {
-    if (c->prm.tree == PSNE_TREE_DATA) return run_snap_dtree(c);
-    if (fp64(c))
-        k_snap<double><<<grid_for(c->n), kBlock, 0, c->stream>>>(
-            (const double*)c->zh, (double*)c->z, c->tb.key[0], c->tb.idx[0], c->sc, c->n, c->r);
-    else
-        k_snap<float><<<grid_for(c->n), kBlock, 0, c->stream>>>(
-            (const float*)c->zh, (float*)c->z, c->tb.key[0], c->tb.idx[0], c->sc, c->n, c->r);
-    return hipGetLastError();
+// Blocks of 512 threads give 70,000 points 35 tiles, of 1,024 only 18: an
+// iteration takes 235 us with the former and 242 with the latter.  At a million
+// points the halves of a larger tile's scan rows count for more: 1,207 us with
+// 1,024 threads, 1,224 with 512.
+static SortPlan sort_plan(int64_t n, int bits) {
+    SortPlan p;
+    p.passes = (int)ceil_div(bits, kRsMaxBits);
+    p.bits = p.passes ? (int)ceil_div(bits, p.passes) : 0;
+    p.threads = n <= (1 << 18) ? 512 : 1024;
+    p.tiles = ceil_div(n, p.threads * kRsItems);
+    return p;
 }
 
-hipError_t run_sort(pixelsne_ctx* c) {
-    if (c->prm.tree == PSNE_TREE_DATA) return run_sort_dtree(c);
-    return run_sort_bits(c, 2 * c->L);
+int64_t sort_hist_words(int64_t n, int bits) {
+    const SortPlan p = sort_plan(n, bits);
+    return p.tiles << p.bits;
+}
+
+int64_t sort_digit_words() { return 1 << kRsMaxBits; }
+
+hipError_t run_snap(pixelsne_ctx* c) {
+    if (c->prm.tree == PSNE_TREE_DATA) return run_snap_dtree(c);
+    const SortPlan p = sort_plan(c->n, 2 * c->L);
+    const dim3 grid((unsigned)p.tiles);
+    auto snap = [&](auto th) {
+        constexpr int TH = decltype(th)::value;
+        if (fp64(c))
+            k_snap<double, TH><<<grid, TH, 0, c->stream>>>((const double*)c->zh, (double*)c->z,
+                                                           c->tb.key[0], c->sc, c->n, c->r, p.bits,
+                                                           c->tb.hist);
+        else
+            k_snap<float, TH><<<grid, TH, 0, c->stream>>>((const float*)c->zh, (float*)c->z,
+                                                          c->tb.key[0], c->sc, c->n, c->r, p.bits,
+                                                          c->tb.hist);
+    };
+    if (p.threads == 512) snap(std::integral_constant<int, 512>());
+    else snap(std::integral_constant<int, 1024>());
+    return hipGetLastError();
 }
 
 hipError_t run_rows_scan(uint32_t* a, int64_t rows, int64_t len, uint32_t* tot, hipStream_t s) {
@@ -1622,30 +1705,49 @@ hipError_t run_rows_scan(uint32_t* a, int64_t rows, int64_t len, uint32_t* tot, 
     return hipGetLastError();
 }
 
-int64_t sort_blocks_for(int64_t n) { return ceil_div(n, kRsTile); }
-
-hipError_t sort_pairs32(uint32_t* const key[2], uint32_t* const idx[2], int64_t n, int bits,
-                        uint32_t* hist, uint32_t* dtot, hipStream_t s, int* sorted) {
-    const int64_t nb = sort_blocks_for(n);
-    const int passes = (bits + 7) / 8;
+// `counted`: hist holds the first pass's digit counts already
+static hipError_t sort_passes(uint32_t* const key[2], uint32_t* const idx[2], int64_t n, int bits,
+                              uint32_t* hist, uint32_t* dtot, hipStream_t s, bool counted,
+                              int* sorted) {
+    const SortPlan pl = sort_plan(n, bits);
+    const dim3 grid((unsigned)pl.tiles);
+    const int bins = 1 << pl.bits;
+    const size_t lds = (size_t)bins * (4 + 2 * (pl.threads / kWave));
     int cur = 0;
-    for (int p = 0; p < passes; p++) {
-        const int shift = 8 * p;
-        k_rs_hist<<<dim3((unsigned)nb), kBlock, 0, s>>>(key[cur], n, shift, hist, nb);
-        k_rows_scan<<<256, kBlock, 0, s>>>(hist, nb, dtot);
+    auto pass = [&](auto th, int p) {
+        constexpr int TH = decltype(th)::value;
+        const int shift = pl.bits * p;
+        if (p > 0 || !counted)
+            k_rs_hist<TH><<<grid, TH, 0, s>>>(key[cur], n, shift, pl.bits, hist);
+        k_rows_scan<<<dim3((unsigned)bins), kBlock, 0, s>>>(hist, pl.tiles, dtot);
         // the first pass generates the identity permutation itself
-        k_rs_scatter<<<dim3((unsigned)nb), kBlock, 0, s>>>(
-            key[cur], p == 0 ? nullptr : idx[cur], key[cur ^ 1], idx[cur ^ 1], n, shift, hist,
-            dtot, nb);
+        k_rs_scatter<TH><<<grid, TH, lds, s>>>(key[cur], p == 0 ? nullptr : idx[cur], key[cur ^ 1],
+                                               idx[cur ^ 1], n, shift, pl.bits, hist, dtot);
         cur ^= 1;
+    };
+    for (int p = 0; p < pl.passes; p++) {
+        if (pl.threads == 512) pass(std::integral_constant<int, 512>(), p);
+        else pass(std::integral_constant<int, 1024>(), p);
     }
     *sorted = cur;
     return hipGetLastError();
 }
 
+hipError_t sort_pairs32(uint32_t* const key[2], uint32_t* const idx[2], int64_t n, int bits,
+                        uint32_t* hist, uint32_t* dtot, hipStream_t s, int* sorted) {
+    return sort_passes(key, idx, n, bits, hist, dtot, s, false, sorted);
+}
+
+hipError_t run_sort(pixelsne_ctx* c) {
+    if (c->prm.tree == PSNE_TREE_DATA) return run_sort_dtree(c);
+    TreeBufs& tb = c->tb;
+    return sort_passes(tb.key, tb.idx, c->n, 2 * c->L, tb.hist, tb.dtot, c->stream, true,
+                       &tb.sorted);
+}
+
 hipError_t run_sort_bits(pixelsne_ctx* c, int bits) {
     TreeBufs& tb = c->tb;
-    return sort_pairs32(tb.key, tb.idx, c->n, bits, tb.hist, tb.dtot, c->stream, &tb.sorted);
+    return sort_passes(tb.key, tb.idx, c->n, bits, tb.hist, tb.dtot, c->stream, false, &tb.sorted);
 }
 
 hipError_t run_tree(pixelsne_ctx* c) {

@@ -933,8 +933,8 @@ hipError_t alloc3(pixelsne3_ctx* c) {
         if ((e = dalloc3(c, &c->key[h], 4 * (size_t)n)) != hipSuccess) return e;
         if ((e = dalloc3(c, &c->idx[h], 4 * (size_t)n)) != hipSuccess) return e;
     }
-    if ((e = dalloc3(c, &c->hist, 4 * 256 * (size_t)sort_blocks_for(n))) != hipSuccess) return e;
-    if ((e = dalloc3(c, &c->dtot, 4 * 256)) != hipSuccess) return e;
+    if ((e = dalloc3(c, &c->hist, 4 * (size_t)sort_hist_words(n, 3 * c->L))) != hipSuccess) return e;
+    if ((e = dalloc3(c, &c->dtot, 4 * (size_t)sort_digit_words())) != hipSuccess) return e;
     c->tree_blocks = ceil_div(n, kBlock);
     if ((e = dalloc3(c, &c->lvl_cnt, 4 * (size_t)(c->L + 1) * c->tree_blocks)) != hipSuccess)
         return e;

@@ -1277,16 +1277,16 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
         if ((e = hipMalloc(&key[h], 4 * m)) != hipSuccess) return fail(e);
         if ((e = hipMalloc(&edge[h], 4 * m)) != hipSuccess) return fail(e);
     }
-    if ((e = hipMalloc(&hist, 4 * 256 * (size_t)sort_blocks_for(m))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&dtot, 4 * 256)) != hipSuccess) return fail(e);
+    int bits = 1, at = 0;
+    while (((int64_t)1 << bits) < n) bits++;
+    if ((e = hipMalloc(&hist, 4 * (size_t)sort_hist_words(m, bits))) != hipSuccess) return fail(e);
+    if ((e = hipMalloc(&dtot, 4 * (size_t)sort_digit_words())) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&start, 8 * (n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&tmp, 8 * (size_t)scan_i64_tmp_len(n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&ucnt, 8 * (n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&rp, 8 * (n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMemcpyAsync(key[0], idx, 4 * m, hipMemcpyDeviceToDevice, s)) != hipSuccess)
         return fail(e);
-    int bits = 1, at = 0;
-    while (((int64_t)1 << bits) < n) bits++;
     if ((e = sort_pairs32(key, edge, m, bits, hist, dtot, s, &at)) != hipSuccess) return fail(e);
     k_in_start<<<dim3((unsigned)ceil_div(m + 1, 256)), 256, 0, s>>>(key[at], m, n, start);
     k_sym_count<<<dim3((unsigned)ceil_div(n + 1, 4)), 256, 0, s>>>(idx, start, edge[at], n, k, ucnt);
