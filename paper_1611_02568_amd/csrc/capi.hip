@@ -9,7 +9,7 @@
 
 namespace psne {
 
-int64_t attract_block_count(int64_t n);
+int64_t point_block_count(int64_t n);
 
 namespace {
 thread_local std::string g_err;
@@ -132,7 +132,7 @@ hipError_t alloc_iteration_buffers(pixelsne_ctx* c) {
     c->help_blocks = (int64_t)c->prm.attract_help_blocks_per_cu * (cus > 0 ? cus : 1);
     c->zpart_n = ceil_div(n, kWave);   // one per wavefront of points at most
     if ((e = dalloc(c, &c->zpart, sizeof(double) * c->zpart_n)) != hipSuccess) return e;
-    c->mm_n = attract_block_count(n);
+    c->mm_n = point_block_count(n);
     if ((e = dalloc(c, &c->mm_part, sizeof(double) * 4 * c->mm_n)) != hipSuccess) return e;
     if ((e = dalloc(c, &c->sc, sizeof(DevScalars))) != hipSuccess) return e;
     TreeBufs& tb = c->tb;

@@ -33,6 +33,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kRsItems = 4;
 constexpr int kAttractBlocksMax = 8192;
+constexpr int kPointBlocksMax = 2048;
 constexpr int kRsMaxBits = 11;               // of a sort digit
 
 
@@ -296,22 +297,22 @@ __global__ __launch_bounds__(kBlock) void k_tree_nodes(
     double2* __restrict__ wlast) {
     using V = v2_t<T>;
     __shared__ uint32_t wc[4][kMaxLevels];
-    __shared__ uint32_t lbase[kMaxLevels + 1];
+    __shared__ uint32_t lbase[kMaxLevels + 1], loff[kMaxLevels];
     const int t = threadIdx.x, w = t >> 6, lane = lane_id();
-    if (t == 0) {
-        uint32_t b = 0;
-        for (int l = 0; l <= L; l++) {
-            lbase[l] = b;
-            b += ltot[l];
+    if (w == 0) {
+        const uint32_t size = lane <= L ? ltot[lane] : 0u;
+        if (lane <= L) loff[lane] = off[(int64_t)lane * nb + blockIdx.x];
+        uint32_t x = size;
+#pragma unroll
+        for (int o = 1; o < 32; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, kWave);
+            if (lane >= o) x += y;
         }
-        lbase[L + 1] = b;
+        if (lane <= L + 1) lbase[lane] = x - size;
         if (blockIdx.x == 0) {
-            for (int l = 0; l <= L; l++) {
-                sc->level_size[l] = ltot[l];
-                sc->level_base[l] = lbase[l];
-            }
-            sc->level_base[L + 1] = b;
-            sc->n_nodes = b;
+            if (lane <= L) sc->level_size[lane] = size;
+            if (lane <= L + 1) sc->level_base[lane] = x - size;
+            if (lane == L) sc->n_nodes = x;
         }
     }
     const int64_t s = (int64_t)blockIdx.x * kBlock + t;
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_nodes(
     for (int l = 0; l < kMaxLevels; l++) {
         if (l <= L) {
             const uint64_t b = ballot64(l0 <= l);
-            uint32_t r = off[(int64_t)l * nb + blockIdx.x] + (uint32_t)__popcll(b & le);
+            uint32_t r = loff[l] + (uint32_t)__popcll(b & le);
             for (int q = 0; q < w; q++) r += wc[q][l];
             rank[l] = r - 1;
         } else {
@@ -474,28 +475,50 @@ __global__ __launch_bounds__(kBlock) void k_tree_leaves(
                cell_scale(sc->s[0]), cell_scale(sc->s[1]));
 }
 
+// First cell and size of the levels, read once per block.
+struct LevelInfo {
+    uint32_t base[kMaxLevels + 1], size[kMaxLevels];
+};
+__device__ __forceinline__ void read_levels(LevelInfo& lv, const DevScalars* __restrict__ sc,
+                                            int L) {
+    const int t = threadIdx.x;
+    if (t <= L + 1) lv.base[t] = sc->level_base[t];
+    if (t <= L) lv.size[t] = sc->level_size[t];
+    __syncthreads();
+}
+
 // One inner cell: count and sums of its children (consecutive in the next
-// level) added in child order.
+// level) added in child order.  The at most four children are read at once.
 __device__ __forceinline__ void inner_cell(const uint32_t* __restrict__ keys, int l, int L,
-                                           int com_mode, const DevScalars* __restrict__ sc,
+                                           int com_mode, const LevelInfo& lv,
                                            const uint32_t* __restrict__ first_child,
                                            const uint32_t* __restrict__ cell_start,
                                            Node* __restrict__ nodes, CellF* __restrict__ c32,
                                            double2* __restrict__ nsum, uint32_t t, uint32_t m,
                                            float rs0, float rs1) {
-    const uint32_t g = sc->level_base[l] + t;
+    const uint32_t g = lv.base[l] + t;
+    const uint32_t st = cell_start[g];
     const uint32_t fc = first_child[g];
-    const uint32_t lc = (t + 1 < m) ? first_child[g + 1] : sc->level_base[l + 1] + sc->level_size[l + 1];
+    const uint32_t lc = (t + 1 < m) ? first_child[g + 1] : lv.base[l + 1] + lv.size[l + 1];
+    const uint32_t key0 = keys[st];
+    double2 v[4];
+    uint32_t cnt[4];
+#pragma unroll
+    for (uint32_t q = 0; q < 4; q++) {
+        const uint32_t at = fc + q < lc ? fc + q : fc;
+        v[q] = nsum[at];
+        cnt[q] = nodes[at].count;
+    }
     double ax = 0.0, ay = 0.0;
     uint32_t c = 0;
-    for (uint32_t q = fc; q < lc; q++) {
-        const double2 v = nsum[q];
-        ax += v.x;
-        ay += v.y;
-        c += nodes[q].count;
-    }
-    const uint32_t st = cell_start[g];
-    write_node(nodes, c32, nsum, g, l, L, ax, ay, c, fc | ((lc - fc - 1) << 30), st, keys[st],
+#pragma unroll
+    for (uint32_t q = 0; q < 4; q++)
+        if (fc + q < lc) {
+            ax += v[q].x;
+            ay += v[q].y;
+            c += cnt[q];
+        }
+    write_node(nodes, c32, nsum, g, l, L, ax, ay, c, fc | ((lc - fc - 1) << 30), st, key0,
                com_mode, rs0, rs1);
 }
 
@@ -519,9 +542,11 @@ __global__ __launch_bounds__(kBlock) void k_tree_group(const uint32_t* __restric
                                                        CellF* __restrict__ c32,
                                                        double2* __restrict__ nsum) {
     __shared__ uint32_t lo[kGroupLevels], hi[kGroupLevels];
+    __shared__ LevelInfo lv;
     const int t = threadIdx.x;
     const float rs0 = cell_scale(sc->s[0]), rs1 = cell_scale(sc->s[1]);
-    const uint32_t mtop = sc->level_size[ltop];
+    read_levels(lv, sc, L);
+    const uint32_t mtop = lv.size[ltop];
     const uint32_t a0 = blockIdx.x * K;
     if (a0 >= mtop) return;
     if (t == 0) {
@@ -530,19 +555,19 @@ __global__ __launch_bounds__(kBlock) void k_tree_group(const uint32_t* __restric
         hi[0] = e;
         for (int l = ltop; l < lbot; l++) {
             // children of the level-l cells [a, e) at level l + 1
-            const uint32_t base = sc->level_base[l], nbase = sc->level_base[l + 1];
-            const uint32_t m = sc->level_size[l];
+            const uint32_t base = lv.base[l], nbase = lv.base[l + 1];
+            const uint32_t m = lv.size[l];
             a = first_child[base + a] - nbase;
-            e = e < m ? first_child[base + e] - nbase : sc->level_size[l + 1];
+            e = e < m ? first_child[base + e] - nbase : lv.size[l + 1];
             lo[l + 1 - ltop] = a;
             hi[l + 1 - ltop] = e;
         }
     }
     __syncthreads();
     for (int l = lbot; l >= ltop; l--) {
-        const uint32_t m = sc->level_size[l];
+        const uint32_t m = lv.size[l];
         for (uint32_t x = lo[l - ltop] + t; x < hi[l - ltop]; x += kBlock)
-            inner_cell(keys, l, L, com_mode, sc, first_child, cell_start, nodes, c32, nsum, x, m,
+            inner_cell(keys, l, L, com_mode, lv, first_child, cell_start, nodes, c32, nsum, x, m,
                        rs0, rs1);
         __syncthreads();
     }
@@ -562,11 +587,13 @@ __global__ __launch_bounds__(kTopThreads) void k_tree_top(const uint32_t* __rest
                                                           Node* __restrict__ nodes,
                                                           CellF* __restrict__ c32,
                                                           double2* __restrict__ nsum) {
+    __shared__ LevelInfo lv;
     const float rs0 = cell_scale(sc->s[0]), rs1 = cell_scale(sc->s[1]);
+    read_levels(lv, sc, L);
     for (int l = top; l >= 0; l--) {
-        const uint32_t m = sc->level_size[l];
+        const uint32_t m = lv.size[l];
         for (uint32_t t = threadIdx.x; t < m; t += kTopThreads)
-            inner_cell(keys, l, L, com_mode, sc, first_child, cell_start, nodes, c32, nsum, t, m,
+            inner_cell(keys, l, L, com_mode, lv, first_child, cell_start, nodes, c32, nsum, t, m,
                        rs0, rs1);
         __syncthreads();
     }
@@ -938,18 +965,21 @@ __global__ __launch_bounds__(kWave * G) void k_traverse_shared(
     if (lane == 0) zpart[blockIdx.x] = zw;
 }
 
-__global__ __launch_bounds__(kBlock) void k_zsum(const double* __restrict__ zpart, int64_t m,
-                                                 DevScalars* __restrict__ sc) {
-    __shared__ double red[kBlock];
+constexpr int kZsumThreads = 1024;
+
+__global__ __launch_bounds__(kZsumThreads) void k_zsum(const double* __restrict__ zpart, int64_t m,
+                                                       DevScalars* __restrict__ sc) {
+    __shared__ double red[kZsumThreads / kWave];
     double a = 0.0;
-    for (int64_t i = threadIdx.x; i < m; i += kBlock) a += zpart[i];
-    red[threadIdx.x] = a;
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < m; i += kZsumThreads) a += zpart[i];
+    a = wave_sum(a);
+    if (lane_id() == 0) red[threadIdx.x / kWave] = a;
     __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    if (threadIdx.x < kWave) {
+        a = wave_sum(threadIdx.x < kZsumThreads / kWave ? red[threadIdx.x] : 0.0);
+        if (threadIdx.x == 0) sc->Z = a;
     }
-    if (threadIdx.x == 0) sc->Z = red[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -1323,27 +1353,30 @@ __global__ __launch_bounds__(kBlock) void k_minmax(const T* __restrict__ zh, int
 __global__ __launch_bounds__(kBlock) void k_finalize(const double* __restrict__ mm_part,
                                                      int64_t m, DevScalars* __restrict__ sc,
                                                      int r, double eps, int advance, int fork) {
-    __shared__ double red[4][kBlock];
+    __shared__ double red[4][kBlock / kWave];
     double mn0 = INFINITY, mn1 = INFINITY, mx0 = -INFINITY, mx1 = -INFINITY;
+#pragma unroll 4
     for (int64_t i = threadIdx.x; i < m; i += kBlock) {
-        mn0 = fmin(mn0, mm_part[4 * i + 0]);
-        mn1 = fmin(mn1, mm_part[4 * i + 1]);
-        mx0 = fmax(mx0, mm_part[4 * i + 2]);
-        mx1 = fmax(mx1, mm_part[4 * i + 3]);
+        const double2 lo = reinterpret_cast<const double2*>(mm_part)[2 * i];
+        const double2 hi = reinterpret_cast<const double2*>(mm_part)[2 * i + 1];
+        mn0 = fmin(mn0, lo.x);
+        mn1 = fmin(mn1, lo.y);
+        mx0 = fmax(mx0, hi.x);
+        mx1 = fmax(mx1, hi.y);
     }
-    red[0][threadIdx.x] = mn0; red[1][threadIdx.x] = mn1;
-    red[2][threadIdx.x] = mx0; red[3][threadIdx.x] = mx1;
+    mn0 = wave_min(mn0); mn1 = wave_min(mn1); mx0 = wave_max(mx0); mx1 = wave_max(mx1);
+    if (lane_id() == 0) {
+        const int w = threadIdx.x / kWave;
+        red[0][w] = mn0; red[1][w] = mn1; red[2][w] = mx0; red[3][w] = mx1;
+    }
     __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            const int a = threadIdx.x, b = threadIdx.x + o;
-            red[0][a] = fmin(red[0][a], red[0][b]);
-            red[1][a] = fmin(red[1][a], red[1][b]);
-            red[2][a] = fmax(red[2][a], red[2][b]);
-            red[3][a] = fmax(red[3][a], red[3][b]);
-        }
-        __syncthreads();
+    if (threadIdx.x < 4) {
+        const int k = threadIdx.x;
+        double v = red[k][0];
+        for (int q = 1; q < kBlock / kWave; q++) v = k < 2 ? fmin(v, red[k][q]) : fmax(v, red[k][q]);
+        red[k][0] = v;
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
         for (int d = 0; d < 2; d++) {
             const double lo = red[d][0], hi = red[2 + d][0];
@@ -1641,6 +1674,16 @@ inline int64_t attract_blocks(int64_t n) {
     return b < kAttractBlocksMax ? b : kAttractBlocksMax;
 }
 
+// Blocks of the passes that leave a minimum and maximum per block: one per 256
+// points, at most as many as the chip holds at once.  (As many as the attraction
+// may take, one per 16 points, they took 13 us at 70,000 points and 23 at a
+// million, and the scaling that reads their parts 7 and 11; now 5 and 14, 4 and
+// 4.5.)
+inline int64_t point_blocks(int64_t n) {
+    const int64_t b = ceil_div(n, kBlock);
+    return b < kPointBlocksMax ? b : kPointBlocksMax;
+}
+
 inline bool fp64(const pixelsne_ctx* c) { return c->prm.precision == PSNE_FP64; }
 
 StepParams step_params(const pixelsne_ctx* c, double alpha) {
@@ -1658,7 +1701,7 @@ StepParams step_params(const pixelsne_ctx* c, double alpha) {
 
 }  // namespace
 
-int64_t attract_block_count(int64_t n) { return attract_blocks(n); }
+int64_t point_block_count(int64_t n) { return point_blocks(n); }
 
 // Blocks of 512 threads give 70,000 points 35 tiles, of 1,024 only 18: an
 // iteration takes 235 us with the former and 242 with the latter.  At a million
@@ -1853,7 +1896,7 @@ hipError_t run_traverse(pixelsne_ctx* c, uint32_t* visits, uint32_t* used, doubl
 }
 
 hipError_t run_zsum(pixelsne_ctx* c) {
-    k_zsum<<<1, kBlock, 0, c->stream>>>(
+    k_zsum<<<1, kZsumThreads, 0, c->stream>>>(
         c->zpart, ceil_div(c->n, traverse_share(c) ? kWave : kBlock), c->sc);
     return hipGetLastError();
 }
@@ -1905,7 +1948,7 @@ static hipError_t run_attract_sums(pixelsne_ctx* c, bool help, bool early = fals
 
 static hipError_t run_update(pixelsne_ctx* c) {
     const StepParams p = step_params(c, 0.0);
-    const dim3 grid((unsigned)attract_blocks(c->n));
+    const dim3 grid((unsigned)point_blocks(c->n));
     if (fp64(c))
         k_update<double><<<grid, kBlock, 0, c->stream>>>(
             (const double*)c->A, (const double*)c->z, (const double*)c->R, (double*)c->u,
@@ -1918,7 +1961,7 @@ static hipError_t run_update(pixelsne_ctx* c) {
 }
 
 hipError_t run_finalize(pixelsne_ctx* c, int advance) {
-    k_finalize<<<1, kBlock, 0, c->stream>>>(c->mm_part, attract_blocks(c->n), c->sc, c->r,
+    k_finalize<<<1, kBlock, 0, c->stream>>>(c->mm_part, point_blocks(c->n), c->sc, c->r,
                                             c->prm.eps, advance, c->prm.attract_fork);
     return hipGetLastError();
 }
@@ -1988,7 +2031,7 @@ hipError_t run_init_state(pixelsne_ctx* c, const double* Y, uint64_t seed, doubl
     reset_fork_tuner(h, c->prm.attract_fork);
     hipError_t e = hipMemcpyAsync(c->sc, &h, sizeof(h), hipMemcpyHostToDevice, c->stream);
     if (e != hipSuccess) return e;
-    const int64_t nb = attract_blocks(c->n);
+    const int64_t nb = point_blocks(c->n);
     if (fp64(c)) {
         k_init_state<double><<<grid_for(c->n), kBlock, 0, c->stream>>>(
             Y, (double*)c->zh, (double*)c->u, (double*)c->g, c->n, seed, sigma);
