@@ -14,11 +14,12 @@
 //   tree      cells of every level numbered from the sorted keys (a cell of
 //             level l = a run of equal key >> 3(L - l)); leaf sums by a
 //             segmented scan per wavefront and the pieces of each leaf, inner
-//             sums from the <= 8 children, one launch per level
+//             sums from the <= 8 children, one launch per level and one for
+//             levels 3 to 0
 //   traverse  64 points walk the union of their paths together, shared by the
-//             wavefronts of a block, level by level
+//             wavefronts of a block, level by level; and, in further blocks of
+//             the same launch, the attraction, one wavefront per row of P
 //   zsum      Z = sum of the per-point terms (fixed order)
-//   attract   one wavefront per row of P
 //   update    gains / momentum step and per-block min / max of z + u
 //   finalize  gamma_d = max - min + eps per axis, s_d *= gamma_d / r
 //   rescale   z = r (zh - min) / gamma, u *= r / gamma
@@ -319,13 +320,10 @@ __global__ __launch_bounds__(kBlock) void k3_leaves(const double* __restrict__ z
     write_cell3(nodes, nsum, g, sm[0], sm[1], sm[2], (uint32_t)(e - a), 0u);
 }
 
-// inner cells of level l: the sums of their (consecutive) children
-__global__ __launch_bounds__(kBlock) void k3_inner(int l, const Scalars3* __restrict__ sc,
-                                                   const uint32_t* __restrict__ fchild,
-                                                   Node3* __restrict__ nodes,
-                                                   double* __restrict__ nsum) {
-    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (q >= (int64_t)sc->level_size[l]) return;
+// one inner cell of level l: the sums of its (consecutive) children
+__device__ __forceinline__ void inner3(int l, int64_t q, const Scalars3* __restrict__ sc,
+                                       const uint32_t* __restrict__ fchild,
+                                       Node3* __restrict__ nodes, double* __restrict__ nsum) {
     const uint32_t g = sc->level_base[l] + (uint32_t)q;
     const uint32_t c0 = fchild[g];
     const uint32_t c1 = g + 1 < sc->level_base[l + 1] ? fchild[g + 1] : sc->level_base[l + 2];
@@ -338,6 +336,29 @@ __global__ __launch_bounds__(kBlock) void k3_inner(int l, const Scalars3* __rest
         cnt += nodes[c].count;
     }
     write_cell3(nodes, nsum, g, sx, sy, sz, cnt, c0 | ((c1 - c0 - 1u) << kChildBits3));
+}
+
+__global__ __launch_bounds__(kBlock) void k3_inner(int l, const Scalars3* __restrict__ sc,
+                                                   const uint32_t* __restrict__ fchild,
+                                                   Node3* __restrict__ nodes,
+                                                   double* __restrict__ nsum) {
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (q < (int64_t)sc->level_size[l]) inner3(l, q, sc, fchild, nodes, nsum);
+}
+
+// Levels top..0 in one block, one after another (8^3 cells at most): 9.5 us
+// where their four launches took 16.
+constexpr int kTopLevel3 = 3;
+constexpr int kTopThreads3 = 512;
+
+__global__ __launch_bounds__(kTopThreads3) void k3_top(int top, const Scalars3* __restrict__ sc,
+                                                       const uint32_t* __restrict__ fchild,
+                                                       Node3* __restrict__ nodes,
+                                                       double* __restrict__ nsum) {
+    for (int l = top; l >= 0; l--) {
+        if (threadIdx.x < sc->level_size[l]) inner3(l, threadIdx.x, sc, fchild, nodes, nsum);
+        __syncthreads();
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -445,13 +466,51 @@ constexpr int kShareCap3 = 128;
 constexpr int kWaves3 = 6;
 struct Sum3 { double x, y, z, q; };
 
+// ---------------------------------------------------------------------------
+// attraction A_i = sum_j p_ij w_ij (z_i - z_j) (Eq. 5 first term, Eq. 12)
+// ---------------------------------------------------------------------------
+// Rows are taken in the Morton order of their points (perm), so that waves
+// running at the same time gather the positions of nearby points, whose
+// neighbours largely coincide.  The rows are blocks behind the walk's in its
+// launch: bound by the latency of their gathers where the walk is bound by FP64
+// issue, they run in what it leaves and in its tail.  100,000 points: 538 us
+// together, 504 and 103 one after the other.
+__device__ __forceinline__ void attract3(const int64_t* __restrict__ rp,
+                                         const uint32_t* __restrict__ col,
+                                         const double* __restrict__ val,
+                                         const double* __restrict__ z,
+                                         int64_t row, const Scalars3* __restrict__ sc,
+                                         double* __restrict__ A) {
+    const int lane = lane_id();
+    const double b0 = sc->s[0] * sc->s[0], b1 = sc->s[1] * sc->s[1], b2 = sc->s[2] * sc->s[2];
+    const double x = z[3 * row], y = z[3 * row + 1], w3 = z[3 * row + 2];
+    double ax = 0.0, ay = 0.0, az = 0.0;
+    for (int64_t e = rp[row] + lane; e < rp[row + 1]; e += kWave) {
+        const int64_t j = col[e];
+        const double dx = x - z[3 * j], dy = y - z[3 * j + 1], dz = w3 - z[3 * j + 2];
+        const double pq = val[e] * rcp_nr(1.0 + dist3(b0, b1, b2, dx, dy, dz));
+        ax += pq * dx;
+        ay += pq * dy;
+        az += pq * dz;
+    }
+    ax = wave_sum(ax);
+    ay = wave_sum(ay);
+    az = wave_sum(az);
+    if (lane == 0) {
+        A[3 * row] = ax;
+        A[3 * row + 1] = ay;
+        A[3 * row + 2] = az;
+    }
+}
+
 template <bool COUNT>
 __global__ __launch_bounds__(kWave * kShare3, kWaves3) void k3_traverse(
     const uint32_t* __restrict__ perm, const uint32_t* __restrict__ leaf_of,
     const double* __restrict__ zs, const Node3* __restrict__ nodes,
     const double* __restrict__ nsum, const Scalars3* __restrict__ sc, int64_t n, int L,
     double th2, double* __restrict__ R, double* __restrict__ Zi, double* __restrict__ zpart,
-    uint32_t* __restrict__ visits) {
+    uint32_t* __restrict__ visits, const int64_t* __restrict__ rp, const uint32_t* __restrict__ col,
+    const double* __restrict__ val, const double* __restrict__ z, double* __restrict__ A) {
     union Room {
         WalkLists<kShare3, kShareCap3> l;
         Sum3 sum[kShare3][kWave];
@@ -461,6 +520,13 @@ __global__ __launch_bounds__(kWave * kShare3, kWaves3) void k3_traverse(
     __shared__ uint32_t nvs[COUNT ? kShare3 : 1][kWave];
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t walks = (n + kWave - 1) / kWave;
+    if (blockIdx.x >= walks) {
+        for (int64_t i = (blockIdx.x - walks) * kShare3 + w; i < n;
+             i += (gridDim.x - walks) * kShare3)
+            attract3(rp, col, val, z, perm[i], sc, A);
+        return;
+    }
     const int64_t s = (int64_t)blockIdx.x * kWave + lane;
     const bool valid = s < n;
     Walker3<COUNT> wk;
@@ -518,44 +584,6 @@ __global__ __launch_bounds__(kBlock) void k3_zfinal(const double* __restrict__ p
         __syncthreads();
     }
     if (threadIdx.x == 0) sc->Z = red[0];
-}
-
-// ---------------------------------------------------------------------------
-// attraction A_i = sum_j p_ij w_ij (z_i - z_j) (Eq. 5 first term, Eq. 12)
-// ---------------------------------------------------------------------------
-// Rows are taken in the Morton order of their points (perm), so that waves
-// running at the same time gather the positions of nearby points, whose
-// neighbours largely coincide.
-__global__ __launch_bounds__(kBlock) void k3_attract(const int64_t* __restrict__ rp,
-                                                     const uint32_t* __restrict__ col,
-                                                     const double* __restrict__ val,
-                                                     const double* __restrict__ z,
-                                                     const uint32_t* __restrict__ perm,
-                                                     const Scalars3* __restrict__ sc, int64_t n,
-                                                     double* __restrict__ A) {
-    const int lane = lane_id();
-    const int64_t wv = (int64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
-    if (wv >= n) return;
-    const int64_t row = perm[wv];
-    const double b0 = sc->s[0] * sc->s[0], b1 = sc->s[1] * sc->s[1], b2 = sc->s[2] * sc->s[2];
-    const double x = z[3 * row], y = z[3 * row + 1], w3 = z[3 * row + 2];
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    for (int64_t e = rp[row] + lane; e < rp[row + 1]; e += kWave) {
-        const int64_t j = col[e];
-        const double dx = x - z[3 * j], dy = y - z[3 * j + 1], dz = w3 - z[3 * j + 2];
-        const double pq = val[e] * rcp_nr(1.0 + dist3(b0, b1, b2, dx, dy, dz));
-        ax += pq * dx;
-        ay += pq * dy;
-        az += pq * dz;
-    }
-    ax = wave_sum(ax);
-    ay = wave_sum(ay);
-    az = wave_sum(az);
-    if (lane == 0) {
-        A[3 * row] = ax;
-        A[3 * row + 1] = ay;
-        A[3 * row + 2] = az;
-    }
 }
 
 // B = alpha A - R / Z
@@ -978,9 +1006,12 @@ hipError_t run_init3(pixelsne3_ctx* c) {
 // Visits are counted only when they are asked for.
 template <bool COUNT>
 void launch_traverse3(pixelsne3_ctx* c, uint32_t* visits) {
-    k3_traverse<COUNT><<<dim3((unsigned)ceil_div(c->n, kWave)), kWave * kShare3, 0, c->stream>>>(
+    const int64_t rows = std::min(ceil_div(c->n, kShare3), (int64_t)1 << 20);
+    k3_traverse<COUNT><<<dim3((unsigned)(ceil_div(c->n, kWave) + rows)), kWave * kShare3, 0,
+                         c->stream>>>(
         c->idx[c->sorted], c->leaf_of, c->zs, c->nodes, c->nsum, c->sc, c->n, c->L,
-        c->prm.theta * c->prm.theta, c->R, c->Zi, c->zpart, visits);
+        c->prm.theta * c->prm.theta, c->R, c->Zi, c->zpart, visits, c->row_ptr, c->col, c->val, c->z,
+        c->A);
 }
 
 // keys, sort, octree, traversal, Z and attraction at the current state
@@ -1003,16 +1034,16 @@ hipError_t run_forces3(pixelsne3_ctx* c, uint32_t* visits) {
                                                         c->zscan);
     k3_leaves<<<grid_for(n), kBlock, 0, c->stream>>>(c->zscan, n, c->L, c->sc, c->nstart,
                                                      c->nodes, c->nsum);
-    for (int l = c->L - 1; l >= 0; l--) {
+    const int top = c->L - 1 < kTopLevel3 ? c->L - 1 : kTopLevel3;
+    for (int l = c->L - 1; l > top; l--) {
         const int64_t cap = (int64_t)1 << (3 * l);
         k3_inner<<<grid_for(cap < n ? cap : n), kBlock, 0, c->stream>>>(l, c->sc, c->fchild,
                                                                          c->nodes, c->nsum);
     }
+    if (top >= 0) k3_top<<<1, kTopThreads3, 0, c->stream>>>(top, c->sc, c->fchild, c->nodes, c->nsum);
     if (visits) launch_traverse3<true>(c, visits);
     else launch_traverse3<false>(c, nullptr);
     k3_zfinal<<<1, kBlock, 0, c->stream>>>(c->zpart, c->zpart_n, c->sc);
-    k3_attract<<<dim3((unsigned)ceil_div(n, kBlock / kWave)), kBlock, 0, c->stream>>>(
-        c->row_ptr, c->col, c->val, c->z, perm, c->sc, n, c->A);
     c->have_tree = true;
     return hipGetLastError();
 }
