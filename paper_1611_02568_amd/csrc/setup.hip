@@ -6,7 +6,8 @@
 //                products), or, for uint8 rows, exactly from INT8 MFMA on
 //                x - 128; each row keeps a candidate list (global memory,
 //                threshold in LDS) that a wavefront cuts to the K' = k + 32
-//                best whenever it fills up.  The K' survivors are re-ranked
+//                best whenever it fills up.  Rows that fall into clusters are
+//                put in an order by which whole tiles can be left out.  The K' survivors are re-ranked
 //                with exact FP64 distances and ties go to the smaller index.
 //   perplexity   per-row bisection on the Gaussian precision (FP64)
 //   symmetrize   p_ij = (p_{j|i} + p_{i|j}) / 2n on the union pattern -> CSR
@@ -15,6 +16,7 @@
 
 #include <string>
 #include <type_traits>
+#include <vector>
 
 #include "ctx.h"
 
@@ -31,6 +33,9 @@ constexpr int kCutAt = 512;    // a list longer than this is cut before the next
 constexpr int kCutLow = 320;   // with it every list longer than this
 constexpr int kHits = 256;     // passing elements a wavefront gathers per tile
 constexpr int kCutSlack = 32;  // entries beyond the kp best that a cut may leave
+// Rows from which on an order is looked for: at 17,000 x 50 in 30 clusters the
+// search takes 1.5 ms without and 1.8 with it, at 33,000 3.3 and 2.1.
+constexpr int64_t kOrderFrom = 1 << 15;
 constexpr int kBatch = 1 << 19;   // query rows whose lists exist at a time (4 GB)
 static_assert(kBatch % kQB == 0, "batches are whole blocks");
 static_assert(kCutLow >= 256 + kMargin + kCutSlack && kCutAt + kCB <= kCap,
@@ -108,7 +113,8 @@ constexpr uint32_t kNoThr = 0xFFFFFFFFu;
 // kp-th distance are found from the top by counts over the wave, until a count
 // within the slack ends the search (about ten of the 32 for a slack of 32);
 // among equal distances at the kp-th place the smallest columns are kept.
-__device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int kp, int slack, uint32_t& thr) {
+__device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int kp, int slack,
+                                        uint32_t& thr) {
     constexpr int kPer = kCap / kWave;
     const int lane = lane_id();
     uint32_t d[kPer], j[kPer];
@@ -183,6 +189,10 @@ struct PartsF16 {
         c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], b[0], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[0], c, 0, 0, 0);
     }
+    static __device__ __forceinline__ void center_product(const Vec* a, const Vec& y, Acc& c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], y, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], y, c, 0, 0, 0);
+    }
     // |y|^2 - 2 x.y, with f = -2 / scale^2
     static __device__ __forceinline__ float part_dist(float dot, float f, float ny) {
         return fmaf(dot, f, ny);
@@ -194,6 +204,10 @@ struct PartsF16 {
     static __device__ __forceinline__ uint32_t bits(float part, float nx) {
         const float d = nx + part;
         return __float_as_uint(d > 0.0f ? d : 0.0f);
+    }
+    // no distance of FP32 bits thr or less reaches low2 - err
+    static __device__ __forceinline__ bool beyond(float low2, float err, uint32_t thr) {
+        return low2 - err > __uint_as_float(thr);
     }
     static __device__ __forceinline__ float none() { return -INFINITY; }
     static __device__ __forceinline__ float far() { return INFINITY; }
@@ -208,6 +222,9 @@ struct PartsI8 {
     static __device__ __forceinline__ void product(const Vec* a, const Vec* b, Acc& c) {
         c = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[0], b[0], c, 0, 0, 0);
     }
+    static __device__ __forceinline__ void center_product(const Vec* a, const Vec& y, Acc& c) {
+        c = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[0], y, c, 0, 0, 0);
+    }
     static __device__ __forceinline__ int32_t part_dist(int32_t dot, float, int32_t ny) {
         return ny - 2 * dot;
     }
@@ -216,6 +233,9 @@ struct PartsI8 {
     }
     static __device__ __forceinline__ uint32_t bits(int32_t part, int32_t nx) {
         return (uint32_t)(nx + part);
+    }
+    static __device__ __forceinline__ bool beyond(float low2, float, uint32_t thr) {
+        return low2 > (float)thr * (1.f + 0x1p-20f);
     }
     static __device__ __forceinline__ int32_t none() { return -0x7FFFFFFF - 1; }
     static __device__ __forceinline__ int32_t far() { return 0x7FFFFFFF; }   // a padding row's dot is 0
@@ -233,6 +253,7 @@ template <typename F> inline size_t packed_bytes(int64_t n, int D) {
 template <typename X>
 __global__ __launch_bounds__(256) void k_pack_f16(const X* __restrict__ Xm, int64_t n, int64_t np,
                                                   int D, int steps, float scale,
+                                                  const uint32_t* __restrict__ perm,
                                                   _Float16* __restrict__ out) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= np * steps * 2) return;
@@ -240,10 +261,11 @@ __global__ __launch_bounds__(256) void k_pack_f16(const X* __restrict__ Xm, int6
     const int64_t f = e >> 6;                               // [32 rows][step]
     const int64_t row = (f / steps) * 32 + (lane & 31);
     const int d0 = (int)(f % steps) * 16 + 8 * (lane >> 5);
+    const int64_t src = row < n && perm ? perm[row] : row;
     PartsF16::Vec hi, lo;
 #pragma unroll
     for (int q = 0; q < 8; q++) {
-        const float v = row < n && d0 + q < D ? to_f32(Xm[row * D + d0 + q]) * scale : 0.f;
+        const float v = row < n && d0 + q < D ? to_f32(Xm[src * D + d0 + q]) * scale : 0.f;
         hi[q] = (_Float16)v;
         lo[q] = (_Float16)(v - (float)hi[q]);
     }
@@ -254,6 +276,7 @@ __global__ __launch_bounds__(256) void k_pack_f16(const X* __restrict__ Xm, int6
 
 __global__ __launch_bounds__(256) void k_pack_i8(const uint8_t* __restrict__ Xm, int64_t n,
                                                  int64_t np, int D, int steps,
+                                                 const uint32_t* __restrict__ perm,
                                                  uint4* __restrict__ out) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= np * steps * 2) return;
@@ -265,7 +288,7 @@ __global__ __launch_bounds__(256) void k_pack_i8(const uint8_t* __restrict__ Xm,
         uint4 q;
         uint8_t b[16];
     } v;
-    const uint8_t* src = Xm + row * D + d0;
+    const uint8_t* src = Xm + (row < n && perm ? (int64_t)perm[row] : row) * D + d0;
     if (row < n && d0 + 16 <= D && (reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
         v.q = *reinterpret_cast<const uint4*>(src);
     } else {
@@ -294,6 +317,365 @@ __global__ __launch_bounds__(256) void k_row_norms_i8(const uint8_t* __restrict_
     if (lane == 0) nrm[i] = a;
 }
 
+// ---------------------------------------------------------------------------
+// An order of the rows that lets the exact search leave tiles out
+//
+// Rows are sorted by their nearest of kPivots sample rows.  The sample is taken
+// in kRounds rounds, the first evenly, the others with probability proportional
+// to the squared distance from the nearest pivot so far (as in the seeding of
+// Bahmani et al., 2012), so that small clusters get pivots too; a cluster
+// without one would be spread over all others'.  The pivots are numbered along a
+// chain from each to its nearest not yet taken.  The rows are then cut into groups of G
+// consecutive rows, G a multiple of a tile's columns and large enough that at
+// most kMaxGroups remain.  Every group has a centre c, its mean rounded to what
+// the matrix units take (any point would do).  For x in group q and y in group
+// t, with D = |c_q - c_t|,
+//
+//   |x - y| >= (x - y).(c_q - c_t) / D = (m_t(x) + m_q(y)) / 2D,
+//   m_t(x) = |x - c_t|^2 - |x - c_q|^2 and m_q(y) = |y - c_q|^2 - |y - c_t|^2,
+//
+// so the smallest m of every group against every centre, one product of all
+// rows with all centres (n^2 / G against n^2 of the search), bounds the distance
+// of any two rows of two groups from below.  Each group sweeps the groups in the
+// order of that bound and stops where it exceeds the block's largest threshold.
+// Every row that is left out is further than the threshold, which is what the
+// selection asserts of it; rows without structure meet every tile as before.
+// ---------------------------------------------------------------------------
+constexpr int kPivots = 256, kRounds = 4, kRoundPivots = kPivots / kRounds;
+constexpr int kMaxGroups = 4096;
+constexpr double kNearShare = 0.35;     // of the pivots' mean squared distance: the rows' at most
+constexpr double kApartShare = 0.05;    // of the pairs of groups: apart at least
+
+// centres in fragments of the matrix units, one part
+struct CenterF16 {
+    static __device__ __forceinline__ float put(void* out, int64_t e, float v, float scale) {
+        const _Float16 h = (_Float16)(v * scale);
+        reinterpret_cast<_Float16*>(out)[e] = h;
+        return (float)h / scale;
+    }
+};
+struct CenterI8 {
+    static __device__ __forceinline__ float put(void* out, int64_t e, float v, float) {
+        const float c = fminf(fmaxf(rintf(v - 128.f), -128.f), 127.f);
+        reinterpret_cast<int8_t*>(out)[e] = (int8_t)c;
+        return c;
+    }
+};
+
+// Centre t (block): the mean of rows first[t] .. first[t] + count - 1 of the
+// order; its fragment entries, its coordinates by dimension (ct [D][T]) and |c|^2.
+template <typename X, typename F, typename P>
+__global__ __launch_bounds__(256) void k_centers(const X* __restrict__ Xm, int64_t n, int D,
+                                                 const uint32_t* __restrict__ perm, int64_t stride,
+                                                 int64_t count, int steps, float scale,
+                                                 void* __restrict__ frag, float* __restrict__ ct,
+                                                 typename F::Num* __restrict__ cn) {
+    __shared__ double red[4];
+    const int t = blockIdx.x, T = gridDim.x, lane = lane_id();
+    const int64_t r0 = t * stride < n ? t * stride : n - 1;
+    const int64_t r1 = r0 + count < n ? r0 + count : n;
+    constexpr int kD = F::kDepth, kHalf = kD / 2;
+    double a = 0.0;
+    for (int d = threadIdx.x; d < steps * kD; d += 256) {
+        float v = 0.f;
+        if (d < D) {
+            for (int64_t r = r0; r < r1; r++) v += to_f32(Xm[(perm ? (int64_t)perm[r] : r) * D + d]);
+            v /= (float)(r1 - r0);
+        }
+        // entry d of row t: [32 rows][step], lane 32 half + row, kHalf entries each
+        const int64_t e = (((int64_t)(t / 32) * steps + d / kD) * 64 + 32 * (d % kD / kHalf) + t % 32) *
+                              kHalf + d % kHalf;
+        if (d < D) {
+            const float c = P::put(frag, e, v, scale);
+            ct[(int64_t)d * T + t] = c;
+            a += (double)c * c;
+        }
+    }
+    a = wave_sum(a);
+    if (lane == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    if (threadIdx.x == 0) cn[t] = (typename F::Num)(((red[0] + red[1]) + red[2]) + red[3]);
+}
+
+// squared distances of all centres, row q (block) of [T][T]
+__global__ __launch_bounds__(256) void k_center_d2(const float* __restrict__ ct, int D, int T,
+                                                   float* __restrict__ d2) {
+    const int q = blockIdx.x;
+    for (int t = threadIdx.x; t < T; t += 256) {
+        double a = 0.0;
+#pragma unroll 8
+        for (int d = 0; d < D; d++) {
+            const double v = (double)ct[(int64_t)d * T + q] - (double)ct[(int64_t)d * T + t];
+            a += v * v;
+        }
+        d2[(int64_t)q * T + t] = (float)a;
+    }
+}
+
+// The chain of the pivots, by one wavefront: rank[t] is t's place in it.
+__global__ __launch_bounds__(64) void k_chain(const float* __restrict__ d2,
+                                              uint32_t* __restrict__ rank) {
+    const int lane = lane_id();
+    constexpr int kPer = kPivots / kWave;
+    bool taken[kPer] = {};
+    int at = 0;
+    for (int r = 0; r < kPivots; r++) {
+        float best = INFINITY;
+        int who = kPivots;
+#pragma unroll
+        for (int q = 0; q < kPer; q++) {
+            const int t = q * kWave + lane;
+            if (t == at) {
+                taken[q] = true;
+                rank[t] = (uint32_t)r;
+            }
+            const float v = d2[(int64_t)at * kPivots + t];
+            if (!taken[q] && (v < best || who == kPivots)) {
+                best = v;
+                who = t;
+            }
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const float b = __shfl_xor(best, o, kWave);
+            const int j = __shfl_xor(who, o, kWave);
+            if (j < kPivots && (who == kPivots || b < best || (b == best && j < who))) {
+                best = b;
+                who = j;
+            }
+        }
+        at = __builtin_amdgcn_readfirstlane(who < kPivots ? who : 0);
+    }
+}
+
+// All rows against all T centres: a wavefront takes 32 rows, a block one run of
+// 256, and four tiles of 32 centres at a time.  ASSIGN: key[row] = rank of the
+// nearest centre, or weight[row] its squared distance in units of 1 / unit.  Else m[group][t] (infinity to begin with) gets the smallest
+// |x - c_t|^2 - |x - c_group|^2 of the group's rows, and radius2[group] (bits,
+// zero to begin with) the largest |x - c_group|^2.
+__device__ __forceinline__ void atomic_min_float(float* at, float v) {
+    if (v >= 0.f) atomicMin(reinterpret_cast<int*>(at), __float_as_int(v));
+    else atomicMax(reinterpret_cast<unsigned int*>(at), __float_as_uint(v));
+}
+
+template <typename F> using Num_t = typename F::Num;
+
+template <typename F, bool ASSIGN>
+__global__ __launch_bounds__(512) void k_center_dots(const char* __restrict__ packed, int64_t n,
+                                                     int steps, const char* __restrict__ centers,
+                                                     const typename F::Num* __restrict__ cn, int T,
+                                                     float f, int64_t G,
+                                                     const uint32_t* __restrict__ rank,
+                                                     uint32_t* __restrict__ key,
+                                                     const Num_t<F>* __restrict__ nrm, float unit,
+                                                     int64_t* __restrict__ weight,
+                                                     float* __restrict__ m,
+                                                     uint32_t* __restrict__ radius2) {
+    using Vec = typename F::Vec;
+    using Num = typename F::Num;
+    constexpr int kTiles = 4;
+    __shared__ float low[8][32 * kTiles];
+    const int t = threadIdx.x, lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t r0 = ((int64_t)blockIdx.x * 8 + w) * 32, group = r0 / G;
+    const char* rows = packed + (r0 / 32) * ((int64_t)steps * F::kParts * 1024) + lane * 16;
+    const int ctiles = (T + 31) / 32;
+    typename F::Acc acc[kTiles];
+    auto dots = [&](int c0) {
+#pragma unroll
+        for (int b = 0; b < kTiles; b++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[b][v] = 0;
+        for (int x = 0; x < steps; x++) {
+            Vec a[F::kParts];
+#pragma unroll
+            for (int p = 0; p < F::kParts; p++)
+                a[p] = *reinterpret_cast<const Vec*>(rows + ((int64_t)x * F::kParts + p) * 1024);
+#pragma unroll
+            for (int b = 0; b < kTiles; b++) {
+                const int c = c0 + b < ctiles ? c0 + b : ctiles - 1;
+                const Vec y = *reinterpret_cast<const Vec*>(
+                    centers + ((int64_t)c * steps + x) * 1024 + lane * 16);
+                F::center_product(a, y, acc[b]);
+            }
+        }
+    };
+    // element v: row r0 + 8 (v / 4) + 4 (lane / 32) + v % 4, centre lane % 32
+    auto row_of = [&](int v) { return r0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); };
+    if constexpr (ASSIGN) {
+        Num best[16];
+        int id[16];
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            best[v] = F::far();
+            id[v] = 0;
+        }
+        for (int c0 = 0; c0 < ctiles; c0 += kTiles) {
+            dots(c0);
+#pragma unroll
+            for (int b = 0; b < kTiles; b++) {
+                const int col = 32 * (c0 + b) + (lane & 31);
+                if (col >= T) continue;
+                const Num c2 = cn[col];
+#pragma unroll
+                for (int v = 0; v < 16; v++) {
+                    const Num d = F::part_dist(acc[b][v], f, c2);
+                    if (d < best[v]) {
+                        best[v] = d;
+                        id[v] = col;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            for (int o = 16; o > 0; o >>= 1) {
+                const Num d = __shfl_xor(best[v], o, kWave);
+                const int j = __shfl_xor(id[v], o, kWave);
+                if (d < best[v] || (d == best[v] && j < id[v])) {
+                    best[v] = d;
+                    id[v] = j;
+                }
+            }
+            const int64_t row = row_of(v);
+            if ((lane & 31) == 0 && row < n) {
+                if (weight) {
+                    const float d = fmaxf((float)nrm[row] + (float)best[v], 0.f) * unit;
+                    weight[row] = 1 + (int64_t)fminf(d, 0x1p30f);
+                } else {
+                    key[row] = rank[id[v]];
+                }
+            }
+        }
+    } else {
+        float own[16], far2 = 0.f;
+        {
+            const int c = (int)(group / 32) / kTiles * kTiles, b = (int)(group / 32) - c;
+            dots(c);
+            const Num c2 = cn[group];
+#pragma unroll
+            for (int v = 0; v < 16; v++) {
+                Num d = acc[0][v];
+#pragma unroll
+                for (int q = 1; q < kTiles; q++) d = b == q ? acc[q][v] : d;
+                own[v] = (float)F::part_dist(__shfl(d, (int)(group & 31) | (lane & 32), kWave), f, c2);
+                if (row_of(v) < n) far2 = fmaxf(far2, (float)nrm[row_of(v)] + own[v]);
+                else own[v] = -INFINITY;
+            }
+            far2 = wave_max(far2);
+            if (lane == 0) atomicMax(&radius2[group], __float_as_uint(far2));
+        }
+        for (int c0 = 0; c0 < ctiles; c0 += kTiles) {
+            dots(c0);
+#pragma unroll
+            for (int b = 0; b < kTiles; b++) {
+                const int col = 32 * (c0 + b) + (lane & 31);
+                const Num c2 = col < T ? cn[col] : Num(0);
+                float s = INFINITY;
+#pragma unroll
+                for (int v = 0; v < 16; v++)
+                    s = fminf(s, (float)F::part_dist(acc[b][v], f, c2) - own[v]);
+                s = fminf(s, __shfl_xor(s, 32, kWave));
+                if (lane < 32) low[w][32 * b + lane] = s;
+            }
+            __syncthreads();
+            const int col = 32 * c0 + t;
+            if (t < 32 * kTiles && col < T) {
+                float s = low[0][t];
+#pragma unroll
+                for (int q = 1; q < 8; q++) s = fminf(s, low[q][t]);
+                atomic_min_float(&m[group * T + col], s);
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Group q's (block) list of the groups by their bound on the squared distance,
+// rounded down; err: what a value of m may be off by.  apart counts the pairs of
+// groups further apart than the rows of the first typically are (for rows at r
+// from their mean 2 r^2, squared).
+struct GroupAt { float low2; uint32_t group; };
+
+__global__ __launch_bounds__(256) void k_group_order(const float* __restrict__ m,
+                                                     const float* __restrict__ d2, int T,
+                                                     float err,
+                                                     const uint32_t* __restrict__ radius2,
+                                                     GroupAt* __restrict__ order,
+                                                     unsigned long long* __restrict__ apart) {
+    __shared__ uint64_t key[kMaxGroups];
+    const int q = blockIdx.x, t = threadIdx.x;
+    const float reach2 = 2.f * __uint_as_float(radius2[q]);
+    unsigned int far = 0;
+    int P = 1;
+    while (P < T) P <<= 1;
+    for (int g = t; g < P; g += 256) {
+        uint64_t k = ~0ull;
+        if (g < T) {
+            float low2 = 0.f;
+            const float D = sqrtf(d2[(int64_t)q * T + g]) * (1.f + 0x1p-20f);
+            const float a = m[(int64_t)q * T + g], b = m[(int64_t)g * T + q];
+            const float num = (a + b) - 2.f * err - (fabsf(a) + fabsf(b)) * 0x1p-20f;
+            if (g != q && num > 0.f && D > 0.f && isfinite(num)) {
+                const float low = num / (2.f * D);
+                low2 = low * low * (1.f - 0x1p-18f);
+            }
+            far += low2 > reach2 ? 1u : 0u;
+            k = (uint64_t)__float_as_uint(low2) << 32 | (uint32_t)(g == q ? 0 : g + 1);
+        }
+        key[g] = k;
+    }
+    for (int o = 32; o > 0; o >>= 1) far += __shfl_xor(far, o, kWave);
+    if (lane_id() == 0 && far) atomicAdd(apart, (unsigned long long)far);
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int x = t; x < P / 2; x += 256) {
+                const int a = ((x & ~(j - 1)) << 1) | (x & (j - 1)), b = a | j;
+                const uint64_t u = key[a], v = key[b];
+                if ((u > v) == ((a & k) == 0)) {
+                    key[a] = v;
+                    key[b] = u;
+                }
+            }
+            __syncthreads();
+        }
+    for (int x = t; x < T; x += 256) {
+        const uint32_t g = (uint32_t)key[x];
+        order[(int64_t)q * T + x] =
+            GroupAt{__uint_as_float((uint32_t)(key[x] >> 32)), g == 0 ? (uint32_t)q : g - 1};
+    }
+}
+
+// The rows at even steps of the weights' running sum: the next pivots.
+__global__ __launch_bounds__(kRoundPivots) void k_pick(const int64_t* __restrict__ sum, int64_t n,
+                                                       uint32_t* __restrict__ row) {
+    const double at = (double)sum[n] * ((threadIdx.x + 0.5) / kRoundPivots);
+    int64_t lo = 0, hi = n;                     // sum[lo] <= at < sum[hi]
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((double)sum[mid] <= at) lo = mid;
+        else hi = mid;
+    }
+    row[threadIdx.x] = (uint32_t)lo;
+}
+
+__global__ __launch_bounds__(kRoundPivots) void k_even_rows(int64_t n, uint32_t* __restrict__ row) {
+    row[threadIdx.x] = (uint32_t)(n / kRoundPivots * threadIdx.x);
+}
+
+template <typename V>
+__global__ __launch_bounds__(256) void k_permuted(const V* __restrict__ a,
+                                                  const uint32_t* __restrict__ perm, int64_t n,
+                                                  V* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) out[i] = a[perm[i]];
+}
+
+__global__ __launch_bounds__(256) void k_fill_inf(float* __restrict__ a, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) a[i] = INFINITY;
+}
+
 // Candidate generation.  A block of eight wavefronts owns kQB query rows and
 // sweeps all candidates in tiles of kCB; each wavefront computes a 64 x 64
 // part as 2 x 2 MFMA tiles.  The depth runs in stages of F::kSteps
@@ -304,14 +686,28 @@ __global__ __launch_bounds__(256) void k_row_norms_i8(const uint8_t* __restrict_
 // one multiply-add and one comparison with the row's bound, and only elements
 // that pass take the way to the lists.
 //
-// Three FP16 products at 400,000 x 128 are 123 TFLOP, 50 ms of the matrix
-// units; the kernel takes 150: 100 with the loads and the lists taken away
-// (barriers of the stages, LDS latency, the filter), 25 more for loads that
-// come late, 25 for the lists (3,000 entries a row on the way to the last
-// 182).  Tried: stages half as deep, three in flight, 165; lists cut only at
-// 768 entries, 153.  The FP32 MFMA kernel of 128 x 128 tiles, filtered
-// through LDS, that this replaces took 605; at 70,000 x 784 bytes 6.7 ms where
-// the INT8 one took 46.6.
+// All tiles of 400,000 x 128, three FP16 products, are 123 TFLOP, 50 ms of the
+// matrix units; the kernel takes 144: 100 with the loads and the lists taken
+// away (barriers of the stages, LDS latency, the filter), the rest for loads
+// that come late and for the lists (3,000 entries a row on the way to the last
+// 182).  By the groups' lists (100 clusters of unequal size, k = 150) 130 of
+// the 1,563 tiles remain for a block on average: 24 ms, a third each for the
+// stages, for the lists as they fill and for cutting them, which a block does
+// all at once.  Tried: stages half as deep, three in flight, 165; lists cut
+// only at 768 entries, 153; the next list read while one is cut, no gain.  The
+// FP32 MFMA kernel of 128 x 128 tiles, filtered through LDS, that this replaces
+// took 605.  70,000 x 784 bytes: 4.2 ms by the lists, 10.7 with all tiles, 46.6
+// by the INT8 kernel of 128 x 128 tiles.
+// The order of the rows, or null pointers: the row at a place, the groups' lists,
+// rows per group, number of groups, and what an approximate distance may be off by.
+struct RowOrder {
+    const uint32_t* perm;
+    const GroupAt* order;
+    int64_t G;
+    int T;
+    float err;
+};
+
 typedef __attribute__((address_space(1))) const void GlobalPtr;
 typedef __attribute__((address_space(3))) void LdsPtr;
 
@@ -320,6 +716,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
                                                         int64_t n, int steps,
                                                         const typename F::Num* __restrict__ nrm,
                                                         float f, int64_t q_first, int kp,
+                                                        RowOrder ord,
                                                         uint64_t* __restrict__ cand,
                                                         uint32_t* __restrict__ cand_cnt,
                                                         uint32_t* __restrict__ cand_thr) {
@@ -347,7 +744,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
     const int64_t tiles = (n + kCB - 1) / kCB;
     if (t < kQB) {
         cnt[t] = 0;
-        thr[t] = kNoThr;
+        thr[t] = q0 + t < n ? kNoThr : 0u;
         nq[t] = q0 + t < n ? nrm[q0 + t] : Num(0);
         bnd[t] = q0 + t < n ? F::bound(kNoThr, Num(0)) : F::none();
     }
@@ -409,10 +806,28 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
                    Q + (rb * 8 * F::kParts + rest) * kFrag);
         }
     }
-    fetch(0, 0, 0);
+    // the tiles in turn, or by the list of the queries' group
+    const GroupAt* const list = ord.order ? ord.order + (q0 / ord.G) * ord.T : nullptr;
+    const int64_t sub = ord.order ? ord.G / kCB : 1;
+    const int64_t places = ord.order ? ord.T * sub : tiles;
+    uint32_t worst = kNoThr;               // the largest threshold of the block's rows
+    int64_t place = -1;
+    auto next_tile = [&]() -> int64_t {
+        while (++place < places) {
+            if (!list) return place;
+            const GroupAt g = list[place / sub];
+            if (worst != kNoThr && F::beyond(g.low2, ord.err, worst)) return -1;
+            const int64_t at = (int64_t)g.group * sub + place % sub;
+            if (at < tiles) return at;
+        }
+        return -1;
+    };
+    int64_t tile = next_tile(), next = -1;
+    fetch(tile, 0, 0);
     settle();
     int buf = 0;
-    for (int64_t tile = 0; tile < tiles; tile++) {
+    for (bool begun = false; tile >= 0; tile = next, begun = true) {
+        next = next_tile();
         typename F::Acc acc[2][2];
 #pragma unroll
         for (int a = 0; a < 2; a++)
@@ -424,7 +839,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
         const Num nc0 = c0 < n ? nrm[c0] : F::far(), nc1 = c0 + 32 < n ? nrm[c0 + 32] : F::far();
         auto stage = [&](int s) {
             if (s + 1 < nst) fetch(tile, s + 1, buf ^ 1);
-            else if (tile + 1 < tiles) fetch(tile + 1, 0, buf ^ 1);
+            else if (next >= 0) fetch(next, 0, buf ^ 1);
             const char* cs = C[buf] + 2 * wc * kPer * kFrag + lane * 16;
             const char* qs = HOLD ? Q + (2 * wr * 8 * F::kParts + s * kPer) * kFrag + lane * 16
                                   : Q + (buf * kStageQ + 2 * wr * kPer) * kFrag + lane * 16;
@@ -451,9 +866,13 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
         stage(0);
         // the previous tile's candidates are all in the lists now; the next
         // stage's barrier, or one more, shows the new bounds to everybody
-        if (tile > 0) {
+        if (begun) {
             cut();
-            if (nst == 1) __syncthreads();
+            if (nst == 1 || list) __syncthreads();
+            if (list) {
+                const uint32_t a = thr[lane], b = thr[lane + kWave];
+                worst = wave_max(a > b ? a : b);
+            }
         }
         for (int s = 1; s < nst; s++) stage(s);
         // filter: element v of tile (a, b) is row 8 (v / 4) + 4 (lane / 32) + v % 4,
@@ -470,7 +889,8 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
                 if (gc < n && gc != q0 + rl) {
                     const uint32_t pos = atomicAdd(&cnt[rl], 1u);
                     cand[(q0 - q_first + rl) * kCap + pos] =
-                        ((uint64_t)F::bits(h.part, nq[rl]) << 32) | (uint64_t)gc;
+                        ((uint64_t)F::bits(h.part, nq[rl]) << 32) |
+                        (uint64_t)(ord.perm ? ord.perm[gc] : (uint32_t)gc);
                 }
             }
             __builtin_amdgcn_wave_barrier();
@@ -548,15 +968,37 @@ __global__ __launch_bounds__(256) void k_knn_cut(uint64_t* __restrict__ cand, in
 // the first k.  flag[i] = 1 when the error bound of the pre-selection does not
 // prove that the k best are among the candidates.
 //
-// A wavefront takes 64 candidates at a time: their rows pass through LDS in
-// slices of kSlice dimensions, read along the rows, and each lane sums its
-// candidate's terms in order of the dimension.  (A lane reading its own row
-// touched 64 cache lines per load: 44 ms at 400,000 x 128.)
-constexpr int kSlice = 32;
+// A lane sums its candidate's terms in order of the dimension, its row read 16
+// bytes at a time at the rows' own alignment.  400,000 rows of 182 candidates of 128:
+// 4.7 ms, 10.7 with the candidates' rows staged through LDS.
+template <typename X>
+__device__ __forceinline__ double rerank_dist(const X* __restrict__ a, const X* __restrict__ b,
+                                              int D) {
+    constexpr int V = 16 / sizeof(X);
+    double acc = 0.0;
+    int d = 0;
+#pragma unroll 4
+    for (; d + V <= D; d += V) {
+        X u[V], v[V];
+        __builtin_memcpy(u, a + d, 16);
+        __builtin_memcpy(v, b + d, 16);
+#pragma unroll
+        for (int q = 0; q < V; q++) {
+            const double e = to_f64(u[q]) - to_f64(v[q]);
+            acc = fma(e, e, acc);
+        }
+    }
+    for (; d < D; d++) {
+        const double e = to_f64(a[d]) - to_f64(b[d]);
+        acc = fma(e, e, acc);
+    }
+    return acc;
+}
 
 template <typename X>
 __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, int64_t q_first,
                                                     int D, int k,
+                                                    const uint32_t* __restrict__ perm,
                                                     const uint64_t* __restrict__ cand,
                                                     const uint32_t* __restrict__ cand_cnt,
                                                     const uint32_t* __restrict__ cand_thr,
@@ -566,10 +1008,8 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
                                                     uint32_t* __restrict__ flag) {
     __shared__ double dv[512];
     __shared__ uint32_t jv[512];
-    __shared__ X rows[4][kWave][kSlice + 1];
-    __shared__ X own[4][kSlice];
-    const int64_t l = blockIdx.x, i = q_first + l;
-    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const int64_t l = blockIdx.x, i = perm ? (int64_t)perm[q_first + l] : q_first + l;
+    const int t = threadIdx.x;
     const int m = (int)cand_cnt[l];                 // at most 256 + kMargin
     const uint64_t* lst = cand + l * kCap;
     for (int e = t; e < 512; e += 256) {
@@ -577,31 +1017,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
         jv[e] = e < m ? (uint32_t)lst[e] : 0xFFFFFFFFu;
     }
     __syncthreads();
-    constexpr int kPass = kWave / kSlice;
-    const int col = lane % kSlice, r0 = lane / kSlice;
-    for (int g = w * kWave; g < m; g += 256) {      // wavefronts go their own ways here
-        double a = 0.0;
-        for (int d0 = 0; d0 < D; d0 += kSlice) {
-            const int wd = D - d0 < kSlice ? D - d0 : kSlice;
-            X v[kWave / kPass];
-            const X vx = lane < wd ? Xm[i * D + d0 + lane] : X(0);
-#pragma unroll
-            for (int q = 0; q < kWave / kPass; q++) {
-                const uint32_t c = jv[g + r0 + kPass * q];
-                v[q] = c != 0xFFFFFFFFu && col < wd ? Xm[(int64_t)c * D + d0 + col] : X(0);
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (lane < kSlice) own[w][lane] = vx;
-#pragma unroll
-            for (int q = 0; q < kWave / kPass; q++) rows[w][r0 + kPass * q][col] = v[q];
-            __builtin_amdgcn_wave_barrier();
-            for (int d = 0; d < wd; d++) {
-                const double e = to_f64(own[w][d]) - to_f64(rows[w][lane][d]);
-                a += e * e;
-            }
-        }
-        if (g + lane < m) dv[g + lane] = a;
-    }
+    for (int e = t; e < m; e += 256) dv[e] = rerank_dist(Xm + i * D, Xm + (int64_t)jv[e] * D, D);
     __syncthreads();
     for (int kk = 2; kk <= 512; kk <<= 1) {
         for (int j = kk >> 1; j > 0; j >>= 1) {
@@ -649,10 +1065,11 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
 __global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ cand,
                                                   const uint32_t* __restrict__ cand_cnt,
                                                   int64_t q_first, int k,
+                                                  const uint32_t* __restrict__ perm,
                                                   int32_t* __restrict__ idx,
                                                   double* __restrict__ d2) {
     __shared__ uint64_t key[512];
-    const int64_t l = blockIdx.x, i = q_first + l;
+    const int64_t l = blockIdx.x, i = perm ? (int64_t)perm[q_first + l] : q_first + l;
     const int t = threadIdx.x, m = (int)cand_cnt[l];
     for (int e = t; e < 512; e += 256) key[e] = e < m ? cand[l * kCap + e] : ~0ull;
     __syncthreads();
@@ -999,18 +1416,145 @@ hipError_t scan_i64_local(const int64_t* a, int64_t m, int64_t* out, int64_t* tm
 
 template <typename F>
 void launch_candidates(const char* packed, int64_t n, int steps, const typename F::Num* nrm,
-                       float f, int64_t first, int64_t rows, int kp, uint64_t* cand,
-                       uint32_t* ccnt, uint32_t* cthr, hipStream_t s) {
+                       float f, int64_t first, int64_t rows, int kp, const RowOrder& ord,
+                       uint64_t* cand, uint32_t* ccnt, uint32_t* cthr, hipStream_t s) {
     const dim3 g((unsigned)ceil_div(rows, kQB));
     // the queries' fragments stay in LDS while 8 steps of them fit beside two
     // stages (FP16: depth 128)
     if (steps <= 8)
-        k_knn_candidates<F, true><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, cand,
-                                                    ccnt, cthr);
+        k_knn_candidates<F, true><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, ord,
+                                                    cand, ccnt, cthr);
     else
-        k_knn_candidates<F, false><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, cand,
-                                                     ccnt, cthr);
+        k_knn_candidates<F, false><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, ord,
+                                                     cand, ccnt, cthr);
     k_knn_cut<<<dim3((unsigned)ceil_div(rows, 4)), 256, 0, s>>>(cand, rows, n, kp, ccnt, cthr);
+}
+
+// The order of the rows (see above): packs the rows in their own order, assigns
+// them to pivots, sorts them, packs them again and makes the groups' lists.
+// pack(perm) packs the rows; nrm_p: the norms in the order; *held: what was
+// allocated.  Two checks end it where it would not pay.  If the even pivots are
+// not much nearer to the rows than to each other, the rows keep their own order
+// (66,000 Gaussian rows of 50: 7.5 ms, 9.0 with all of the order made, 7.3 with
+// none).  If hardly any groups are apart, neither: a block whose own cluster
+// comes late keeps a loose threshold until then, and blocks that take the tiles
+// in turn share them in L2 (100,000 Gaussian rows of 8: 10.2 ms without an
+// order, 12.5 by the lists; with clusters 4 sigma apart, 7% of the pairs apart,
+// 10.0 and 8.8; 100,000 x 100 in such clusters 15.6 and 7.0).
+template <typename X, typename F, typename P, typename Pack>
+hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float scale, float err,
+                      const Num_t<F>* nrm, float norm_max, char* packed, Pack&& pack, void** held,
+                      hipStream_t s, RowOrder* ord, const Num_t<F>** nrm_p) {
+    using Num = typename F::Num;
+    const int64_t G = kCB * ceil_div(ceil_div(n, kCB), kMaxGroups);
+    const int T = (int)ceil_div(n, G), most = T > kPivots ? T : kPivots;
+    char* frag = nullptr;
+    float *ct = nullptr, *d2 = nullptr, *m = nullptr;
+    Num *cn = nullptr, *np = nullptr;
+    uint32_t *rank = nullptr, *key[2] = {nullptr, nullptr}, *idx[2] = {nullptr, nullptr},
+             *hist = nullptr, *dtot = nullptr, *rows = nullptr, *radius2 = nullptr;
+    GroupAt* order = nullptr;
+    int64_t *weight = nullptr, *sum = nullptr, *tmp = nullptr;
+    unsigned long long* apart = nullptr;
+    const size_t frags = (size_t)ceil_div(most, 32) * steps * 1024;
+    hipError_t e = hipSuccess;
+    size_t bytes = 0;
+    *nrm_p = nrm;
+    for (int go = 0; go < 2; go++) {            // sizes, then places
+        bytes = 0;
+        auto get = [&](auto** q, int64_t count) {
+            if (go) *q = reinterpret_cast<std::remove_reference_t<decltype(*q)>>((char*)*held + bytes);
+            bytes += ((size_t)count * sizeof(**q) + 255) / 256 * 256;
+        };
+        get(&frag, (int64_t)frags);
+        get(&ct, (int64_t)D * most);
+        get(&cn, most);
+        get(&d2, (int64_t)most * most);
+        get(&m, (int64_t)T * T);
+        get(&order, (int64_t)T * T);
+        get(&radius2, T);
+        get(&apart, 1);
+        get(&rank, kPivots);
+        get(&rows, kPivots);
+        for (int h = 0; h < 2; h++) {
+            get(&key[h], n);
+            get(&idx[h], n);
+        }
+        get(&np, n);
+        get(&weight, n + 1);
+        get(&sum, n + 1);
+        get(&tmp, scan_i64_tmp_len(n + 1));
+        get(&hist, sort_hist_words(n, 8));
+        get(&dtot, sort_digit_words());
+        if (!go && (e = hipMalloc(held, bytes)) != hipSuccess) {
+            // no room: the rows keep their order
+            (void)hipGetLastError();
+            if (e != hipErrorOutOfMemory) return e;
+            pack(nullptr);
+            return hipGetLastError();
+        }
+    }
+    const dim3 blocks((unsigned)(pad_rows(n) / 256));
+    pack(nullptr);
+    if ((e = hipMemsetAsync(frag, 0, frags, s)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(weight + n, 0, sizeof(int64_t), s)) != hipSuccess) return e;
+    const float unit = 0x1p28f / (norm_max > 0.f ? norm_max : 1.f);
+    k_even_rows<<<1, kRoundPivots, 0, s>>>(n, rows);
+    for (int r = 1; r <= kRounds; r++) {
+        const int count = r * kRoundPivots;
+        k_centers<X, F, P><<<count, 256, 0, s>>>(Xm, count, D, rows, 1, 1, steps, scale, frag, ct,
+                                                 cn);
+        if (r == kRounds) break;
+        k_center_dots<F, true><<<blocks, 512, 0, s>>>(packed, n, steps, frag, cn, count, f, G,
+                                                      nullptr, nullptr, nrm, unit, weight, nullptr,
+                                                      nullptr);
+        if ((e = scan_i64_local(weight, n + 1, sum, tmp, s)) != hipSuccess) return e;
+        if (r == 1) {
+            std::vector<float> between((size_t)count * count);
+            int64_t total = 0;
+            k_center_d2<<<count, 256, 0, s>>>(ct, D, count, d2);
+            e = hipMemcpyAsync(between.data(), d2, 4 * between.size(), hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(&total, sum + n, 8, hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) return e;
+            double all = 0.0;
+            for (float v : between) all += v;
+            all /= (double)count * (count - 1);
+            if (!((double)total / (double)n < kNearShare * all * unit)) return hipSuccess;
+        }
+        k_pick<<<1, kRoundPivots, 0, s>>>(sum, n, rows + count);
+    }
+    k_center_d2<<<kPivots, 256, 0, s>>>(ct, D, kPivots, d2);
+    k_chain<<<1, kWave, 0, s>>>(d2, rank);
+    k_center_dots<F, true><<<blocks, 512, 0, s>>>(packed, n, steps, frag, cn, kPivots, f, G, rank,
+                                                  key[0], nrm, 0.f, nullptr, nullptr, nullptr);
+    int at = 0;
+    if ((e = sort_pairs32(key, idx, n, 8, hist, dtot, s, &at)) != hipSuccess) return e;
+    const uint32_t* perm = idx[at];
+    pack(perm);
+    k_permuted<<<dim3((unsigned)ceil_div(n, 256)), 256, 0, s>>>(nrm, perm, n, np);
+    if ((e = hipMemsetAsync(frag, 0, frags, s)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(radius2, 0, sizeof(uint32_t) * T, s)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(apart, 0, sizeof(*apart), s)) != hipSuccess) return e;
+    k_centers<X, F, P><<<dim3((unsigned)T), 256, 0, s>>>(Xm, n, D, perm, G, G, steps, scale, frag, ct,
+                                                         cn);
+    k_center_d2<<<dim3((unsigned)T), 256, 0, s>>>(ct, D, T, d2);
+    k_fill_inf<<<dim3((unsigned)ceil_div((int64_t)T * T, 256)), 256, 0, s>>>(m, (int64_t)T * T);
+    k_center_dots<F, false><<<blocks, 512, 0, s>>>(packed, n, steps, frag, cn, T, f, G, nullptr,
+                                                   nullptr, np, 0.f, nullptr, m, radius2);
+    k_group_order<<<dim3((unsigned)T), 256, 0, s>>>(m, d2, T, 2.f * err, radius2, order, apart);
+    unsigned long long far = 0;
+    e = hipMemcpyAsync(&far, apart, sizeof(far), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    if ((double)far >= kApartShare * (double)T * (double)T) {
+        *ord = RowOrder{perm, order, G, T, err};
+        *nrm_p = np;
+    } else {
+        pack(nullptr);
+    }
+    return hipGetLastError();
 }
 
 template <typename X>
@@ -1028,9 +1572,11 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     uint32_t *ccnt = nullptr, *cthr = nullptr, *flag = nullptr;
     RowStats* st = nullptr;
     hipError_t e = hipSuccess;
+    void* held = nullptr;
+    RowOrder ord{};
     auto fail = [&](hipError_t x) {
         for (void* q : {(void*)nrm, (void*)nrm_i, (void*)packed, (void*)cand, (void*)ccnt,
-                        (void*)cthr, (void*)flag, (void*)st})
+                        (void*)cthr, (void*)flag, (void*)st, held})
             (void)hipFree(q);
         return x;
     };
@@ -1046,12 +1592,23 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
         if ((e = hipMalloc(&nrm_i, sizeof(int32_t) * n)) != hipSuccess) return fail(e);
         k_row_norms_i8<<<dim3((unsigned)ceil_div(n, 4)), 256, 0, s>>>((const uint8_t*)Xm, n, D,
                                                                      nrm_i);
-        k_pack_i8<<<gpack, 256, 0, s>>>((const uint8_t*)Xm, n, np, D, steps, (uint4*)packed);
+        auto pack = [&](const uint32_t* perm) {
+            k_pack_i8<<<gpack, 256, 0, s>>>((const uint8_t*)Xm, n, np, D, steps, perm,
+                                            (uint4*)packed);
+        };
+        // the distances' halves reach 2^30: as floats they are off by 2^7
+        const int32_t* nrm_p = nrm_i;
+        if (n >= kOrderFrom)
+            e = order_rows<X, PartsI8, CenterI8>(Xm, n, D, steps, 0.f, 1.f, 128.f, nrm_i,
+                                                 16384.f * D, packed, pack, &held, s, &ord, &nrm_p);
+        else
+            pack(nullptr);
+        if (e != hipSuccess) return fail(e);
         for (int64_t first = 0; first < n; first += kBatch) {
             const int64_t m = n - first < kBatch ? n - first : kBatch;
-            launch_candidates<PartsI8>(packed, n, steps, nrm_i, 0.f, first, m, kp, cand, ccnt,
-                                       cthr, s);
-            k_knn_emit<<<dim3((unsigned)m), 256, 0, s>>>(cand, ccnt, first, k, idx, d2);
+            launch_candidates<PartsI8>(packed, n, steps, nrm_p, 0.f, first, m, kp, ord, cand,
+                                       ccnt, cthr, s);
+            k_knn_emit<<<dim3((unsigned)m), 256, 0, s>>>(cand, ccnt, first, k, ord.perm, idx, d2);
         }
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);
         return fail(hipStreamSynchronize(s));
@@ -1079,12 +1636,29 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     if (entry_max > 0.f) (void)frexpf(entry_max, &ex);
     const int sh = 15 - ex < -60 ? -60 : (15 - ex > 60 ? 60 : 15 - ex);
     const float scale = ldexpf(1.f, sh), f = ldexpf(-2.f, -2 * sh);
-    k_pack_f16<X><<<gpack, 256, 0, s>>>(Xm, n, np, D, steps, scale, (_Float16*)packed);
+    auto pack = [&](const uint32_t* perm) {
+        k_pack_f16<X><<<gpack, 256, 0, s>>>(Xm, n, np, D, steps, scale, perm, (_Float16*)packed);
+    };
+    const float* nrm_p = nrm;
+    if (n >= kOrderFrom) {
+        // the error bound of k_knn_rerank for any two rows; a centre's norm is no
+        // larger than the largest row's, but for its rounding to 11 bits
+        const double sum = 2.0 * sqrt((double)norm_max) * (1.0 + 0x1.0p-10);
+        const double err = 1.01 * ((1.5 * D + 16.0) * 0x1.0p-24 * sum * sum +
+                                   2.0 * sqrt((double)D) * sum * (0x1.0p-14 / (double)scale));
+        e = order_rows<X, PartsF16, CenterF16>(Xm, n, D, steps, f, scale, (float)(1.001 * err), nrm,
+                                               norm_max, packed, pack, &held, s, &ord, &nrm_p);
+    } else {
+        pack(nullptr);
+    }
+    if (e != hipSuccess) return fail(e);
     for (int64_t first = 0; first < n; first += kBatch) {
         const int64_t m = n - first < kBatch ? n - first : kBatch;
-        launch_candidates<PartsF16>(packed, n, steps, nrm, f, first, m, kp, cand, ccnt, cthr, s);
-        k_knn_rerank<X><<<dim3((unsigned)m), 256, 0, s>>>(Xm, first, D, k, cand, ccnt, cthr, nrm,
-                                                          norm_max, scale, idx, d2, flag);
+        launch_candidates<PartsF16>(packed, n, steps, nrm_p, f, first, m, kp, ord, cand, ccnt,
+                                    cthr, s);
+        k_knn_rerank<X><<<dim3((unsigned)m), 256, 0, s>>>(Xm, first, D, k, ord.perm, cand, ccnt,
+                                                          cthr, nrm, norm_max, scale, idx, d2,
+                                                          flag);
     }
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     std::vector<uint32_t> hf(n);
