@@ -100,11 +100,26 @@ psne_status check_screen(int32_t w, int32_t h, int* L) {
 
 template <typename P>
 hipError_t dalloc(pixelsne_ctx* c, P** out, size_t bytes) {
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
-    if (e != hipSuccess) return e;
-    c->allocs.push_back(p);
-    *out = (P*)p;
+    // arrays of up to a quarter of a slab share slabs: some forty allocations
+    // become a few
+    const size_t slab = std::min(std::max((size_t)c->n * 64, (size_t)1 << 20), (size_t)32 << 20);
+    const size_t size = (std::max(bytes, (size_t)1) + 255) / 256 * 256;
+    const bool small = size <= slab / 4;
+    if (!small || size > c->slab_left) {
+        void* p = nullptr;
+        const hipError_t e = hipMalloc(&p, small ? slab : size);
+        if (e != hipSuccess) return e;
+        c->allocs.push_back(p);
+        if (!small) {
+            *out = (P*)p;
+            return hipSuccess;
+        }
+        c->slab = (char*)p;
+        c->slab_left = slab;
+    }
+    *out = (P*)c->slab;
+    c->slab += size;
+    c->slab_left -= size;
     return hipSuccess;
 }
 
@@ -272,7 +287,8 @@ pixelsne_ctx* new_ctx(int64_t n, int L, int32_t r, const pixelsne_params* p) {
 }
 
 // state buffers + initial embedding; P must already be in the context
-psne_status finish_init(pixelsne_ctx* c) {
+// (chunks: in the caller's order; not where a data order follows)
+psne_status finish_init(pixelsne_ctx* c, bool chunks) {
     hipError_t e = alloc_iteration_buffers(c);
     if (e == hipErrorNotSupported) return PSNE_E_UNSUPPORTED;
     if (e != hipSuccess) return device_error(c, e, "allocation");
@@ -285,7 +301,7 @@ psne_status finish_init(pixelsne_ctx* c) {
     e = kl_scratch_address(c->device, &kl_fixed);
     if (e != hipSuccess) return device_error(c, e, "resolving the fixed KL buffer");
     e = run_init_state(c, c->prm.Y_init, c->prm.seed, c->prm.init_sigma);
-    if (e == hipSuccess) e = run_identity_order(c);
+    if (e == hipSuccess) e = run_identity_order(c, chunks);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return device_error(c, e, "initial embedding");
     return PSNE_OK;
@@ -355,12 +371,15 @@ pixelsne_ctx* pixelsne_init_ex(const void* X, int64_t n, int32_t D, double perpl
     c->k = (int32_t)k;
     int32_t* idx = nullptr;
     double *d2 = nullptr, *Pc = nullptr, *val64 = nullptr;
+    Arena lists;
+    lists.add(&idx, n * k);
+    lists.add(&d2, n * k);
+    lists.add(&Pc, n * k);
     auto cleanup = [&]() {
-        (void)hipFree(idx); (void)hipFree(d2); (void)hipFree(Pc); (void)hipFree(val64);
+        lists.release();
+        (void)hipFree(val64);
     };
-    hipError_t e = hipMalloc(&idx, sizeof(int32_t) * n * k);
-    if (e == hipSuccess) e = hipMalloc(&d2, sizeof(double) * n * k);
-    if (e == hipSuccess) e = hipMalloc(&Pc, sizeof(double) * n * k);
+    hipError_t e = lists.make();
     std::string err;
     const int32_t leaf = p.knn_leaf > 0 ? p.knn_leaf : (int32_t)(2 * k + 2);
     if (p.knn_trees > 0 && leaf < 2 * k + 2) {
@@ -395,7 +414,7 @@ pixelsne_ctx* pixelsne_init_ex(const void* X, int64_t n, int32_t D, double perpl
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     cleanup();
     if (e != hipSuccess) { device_error(c, e, "storing P"); free_ctx(c); return nullptr; }
-    if (finish_init(c) != PSNE_OK) { free_ctx(c); return nullptr; }
+    if (finish_init(c, !p.data_order) != PSNE_OK) { free_ctx(c); return nullptr; }
     if (p.data_order) {
         e = run_data_order(c, X, D, p.x_dtype);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -445,7 +464,7 @@ pixelsne_ctx* pixelsne_init_with_P(int64_t n, int64_t nnz, const int64_t* row_pt
         free_ctx(c);
         return nullptr;
     }
-    if (finish_init(c) != PSNE_OK) { free_ctx(c); return nullptr; }
+    if (finish_init(c, true) != PSNE_OK) { free_ctx(c); return nullptr; }
     return c;
 }
 

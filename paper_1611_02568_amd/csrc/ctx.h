@@ -3,6 +3,7 @@
 #pragma once
 
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -114,6 +115,8 @@ struct pixelsne_ctx {
     bool graph_failed = false;
 
     std::vector<void*> allocs;
+    char* slab = nullptr;                    // room for small arrays, in allocs
+    size_t slab_left = 0;
 };
 
 namespace psne {
@@ -123,6 +126,34 @@ psne_status device_error(pixelsne_ctx* c, hipError_t e, const char* where);
 bool is_device_ptr(const void* p);
 
 // iteration passes (iter.hip); each enqueues on c->stream
+// Several arrays in one device allocation: add() them all, then make().  An
+// allocation and its release cost 30 to 250 us each whatever their size.
+class Arena {
+public:
+    template <typename P> void add(P** at, int64_t count) {
+        parts_.push_back({(void**)at, bytes_});
+        bytes_ += ((size_t)count * sizeof(P) + 255) / 256 * 256;
+    }
+    hipError_t make() {
+        const hipError_t e = hipMalloc(&base_, bytes_ ? bytes_ : 1);
+        if (e == hipSuccess)
+            for (const auto& p : parts_) *p.first = (char*)base_ + p.second;
+        return e;
+    }
+    void release() {
+        (void)hipFree(base_);
+        base_ = nullptr;
+    }
+    Arena() = default;
+    Arena(const Arena&) = delete;
+    Arena& operator=(const Arena&) = delete;
+
+private:
+    std::vector<std::pair<void**, size_t>> parts_;
+    size_t bytes_ = 0;
+    void* base_ = nullptr;
+};
+
 hipError_t run_snap(pixelsne_ctx* c);
 hipError_t run_sort(pixelsne_ctx* c);
 // the data-driven tree (dtree.hip): snap with 64-bit grid keys, their sort,
@@ -176,7 +207,7 @@ hipError_t run_reorder(pixelsne_ctx* c);
 hipError_t run_scheduled_reorder(pixelsne_ctx* c);
 // put the renumbering schedule where it stands after t iterations from the start
 void reset_reorder_schedule(pixelsne_ctx* c, int32_t t);
-hipError_t run_identity_order(pixelsne_ctx* c);
+hipError_t run_identity_order(pixelsne_ctx* c, bool chunks);
 // renumber by a Morton code of three random projections of X (rows of D
 // elements of x_dtype) and delay the first renumbering by the embedding to the
 // end of the early exaggeration

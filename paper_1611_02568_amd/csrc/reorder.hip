@@ -298,7 +298,7 @@ hipError_t build_chunks(pixelsne_ctx* c) {
 
 }  // namespace
 
-hipError_t run_identity_order(pixelsne_ctx* c) {
+hipError_t run_identity_order(pixelsne_ctx* c, bool chunks) {
     k_iota2<<<grid_for(c->n), kBlock, 0, c->stream>>>(c->orig, c->inv, c->n);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -306,7 +306,7 @@ hipError_t run_identity_order(pixelsne_ctx* c) {
     c->reorder_interval = c->prm.reorder_every;
     c->since_reorder = c->prm.reorder_every > 0 ? c->prm.reorder_every - 1 : 0;
     c->since_reorder0 = c->since_reorder;
-    return build_chunks(c);
+    return chunks ? build_chunks(c) : hipSuccess;
 }
 
 hipError_t run_data_order(pixelsne_ctx* c, const void* X, int32_t D, int32_t x_dtype) {

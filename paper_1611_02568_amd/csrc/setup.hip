@@ -1432,8 +1432,7 @@ void launch_candidates(const char* packed, int64_t n, int steps, const typename 
 
 // The order of the rows (see above): packs the rows in their own order, assigns
 // them to pivots, sorts them, packs them again and makes the groups' lists.
-// pack(perm) packs the rows; nrm_p: the norms in the order; *held: what was
-// allocated.  Two checks end it where it would not pay.  If the even pivots are
+// pack(perm) packs the rows; nrm_p: the norms in the order; held: the arrays.  Two checks end it where it would not pay.  If the even pivots are
 // not much nearer to the rows than to each other, the rows keep their own order
 // (66,000 Gaussian rows of 50: 7.5 ms, 9.0 with all of the order made, 7.3 with
 // none).  If hardly any groups are apart, neither: a block whose own cluster
@@ -1443,7 +1442,7 @@ void launch_candidates(const char* packed, int64_t n, int steps, const typename 
 // 10.0 and 8.8; 100,000 x 100 in such clusters 15.6 and 7.0).
 template <typename X, typename F, typename P, typename Pack>
 hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float scale, float err,
-                      const Num_t<F>* nrm, float norm_max, char* packed, Pack&& pack, void** held,
+                      const Num_t<F>* nrm, float norm_max, char* packed, Pack&& pack, Arena* held,
                       hipStream_t s, RowOrder* ord, const Num_t<F>** nrm_p) {
     using Num = typename F::Num;
     const int64_t G = kCB * ceil_div(ceil_div(n, kCB), kMaxGroups);
@@ -1458,41 +1457,33 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     unsigned long long* apart = nullptr;
     const size_t frags = (size_t)ceil_div(most, 32) * steps * 1024;
     hipError_t e = hipSuccess;
-    size_t bytes = 0;
     *nrm_p = nrm;
-    for (int go = 0; go < 2; go++) {            // sizes, then places
-        bytes = 0;
-        auto get = [&](auto** q, int64_t count) {
-            if (go) *q = reinterpret_cast<std::remove_reference_t<decltype(*q)>>((char*)*held + bytes);
-            bytes += ((size_t)count * sizeof(**q) + 255) / 256 * 256;
-        };
-        get(&frag, (int64_t)frags);
-        get(&ct, (int64_t)D * most);
-        get(&cn, most);
-        get(&d2, (int64_t)most * most);
-        get(&m, (int64_t)T * T);
-        get(&order, (int64_t)T * T);
-        get(&radius2, T);
-        get(&apart, 1);
-        get(&rank, kPivots);
-        get(&rows, kPivots);
-        for (int h = 0; h < 2; h++) {
-            get(&key[h], n);
-            get(&idx[h], n);
-        }
-        get(&np, n);
-        get(&weight, n + 1);
-        get(&sum, n + 1);
-        get(&tmp, scan_i64_tmp_len(n + 1));
-        get(&hist, sort_hist_words(n, 8));
-        get(&dtot, sort_digit_words());
-        if (!go && (e = hipMalloc(held, bytes)) != hipSuccess) {
-            // no room: the rows keep their order
-            (void)hipGetLastError();
-            if (e != hipErrorOutOfMemory) return e;
-            pack(nullptr);
-            return hipGetLastError();
-        }
+    held->add(&frag, (int64_t)frags);
+    held->add(&ct, (int64_t)D * most);
+    held->add(&cn, most);
+    held->add(&d2, (int64_t)most * most);
+    held->add(&m, (int64_t)T * T);
+    held->add(&order, (int64_t)T * T);
+    held->add(&radius2, T);
+    held->add(&apart, 1);
+    held->add(&rank, kPivots);
+    held->add(&rows, kPivots);
+    for (int h = 0; h < 2; h++) {
+        held->add(&key[h], n);
+        held->add(&idx[h], n);
+    }
+    held->add(&np, n);
+    held->add(&weight, n + 1);
+    held->add(&sum, n + 1);
+    held->add(&tmp, scan_i64_tmp_len(n + 1));
+    held->add(&hist, sort_hist_words(n, 8));
+    held->add(&dtot, sort_digit_words());
+    if ((e = held->make()) != hipSuccess) {
+        // no room: the rows keep their order
+        (void)hipGetLastError();
+        if (e != hipErrorOutOfMemory) return e;
+        pack(nullptr);
+        return hipGetLastError();
     }
     const dim3 blocks((unsigned)(pad_rows(n) / 256));
     pack(nullptr);
@@ -1572,24 +1563,29 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     uint32_t *ccnt = nullptr, *cthr = nullptr, *flag = nullptr;
     RowStats* st = nullptr;
     hipError_t e = hipSuccess;
-    void* held = nullptr;
     RowOrder ord{};
+    Arena own, held;
     auto fail = [&](hipError_t x) {
-        for (void* q : {(void*)nrm, (void*)nrm_i, (void*)packed, (void*)cand, (void*)ccnt,
-                        (void*)cthr, (void*)flag, (void*)st, held})
-            (void)hipFree(q);
+        own.release();
+        held.release();
         return x;
     };
-    if ((e = hipMalloc(&cand, sizeof(uint64_t) * kCap * rows)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&ccnt, sizeof(uint32_t) * rows)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&cthr, sizeof(uint32_t) * rows)) != hipSuccess) return fail(e);
-    const size_t bytes = exact ? packed_bytes<PartsI8>(n, D) : packed_bytes<PartsF16>(n, D);
-    if ((e = hipMalloc(&packed, bytes)) != hipSuccess) return fail(e);
+    own.add(&cand, (int64_t)kCap * rows);
+    own.add(&ccnt, rows);
+    own.add(&cthr, rows);
+    own.add(&packed, (int64_t)(exact ? packed_bytes<PartsI8>(n, D) : packed_bytes<PartsF16>(n, D)));
+    if (exact) {
+        own.add(&nrm_i, n);
+    } else {
+        own.add(&nrm, n);
+        own.add(&flag, n);
+        own.add(&st, 1);
+    }
+    if ((e = own.make()) != hipSuccess) return fail(e);
     const int64_t np = pad_rows(n);
     const dim3 gpack((unsigned)ceil_div(np * steps * 2, 256));
     if (exact) {
         // uint8 rows: exact integer distances from INT8 MFMA
-        if ((e = hipMalloc(&nrm_i, sizeof(int32_t) * n)) != hipSuccess) return fail(e);
         k_row_norms_i8<<<dim3((unsigned)ceil_div(n, 4)), 256, 0, s>>>((const uint8_t*)Xm, n, D,
                                                                      nrm_i);
         auto pack = [&](const uint32_t* perm) {
@@ -1613,9 +1609,6 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);
         return fail(hipStreamSynchronize(s));
     }
-    if ((e = hipMalloc(&nrm, sizeof(float) * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&flag, sizeof(uint32_t) * n)) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&st, sizeof(RowStats))) != hipSuccess) return fail(e);
     if ((e = hipMemsetAsync(st, 0, sizeof(RowStats), s)) != hipSuccess) return fail(e);
     const int64_t nblk = ceil_div(n, 4) < 2048 ? ceil_div(n, 4) : 2048;
     k_row_norms<X><<<dim3((unsigned)nblk), 256, 0, s>>>(Xm, n, D, nrm, st);
@@ -1837,27 +1830,24 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
     int64_t *start = nullptr, *tmp = nullptr, *ucnt = nullptr, *rp = nullptr;
     double* val = nullptr;
     hipError_t e = hipSuccess;
-    auto cleanup = [&]() {
-        for (void* q : {(void*)key[0], (void*)key[1], (void*)edge[0], (void*)edge[1], (void*)hist,
-                        (void*)dtot, (void*)start, (void*)tmp, (void*)ucnt})
-            (void)hipFree(q);
-    };
+    Arena own;
     auto fail = [&](hipError_t x) {
-        cleanup();
+        own.release();
         (void)hipFree(rp); (void)hipFree(col); (void)hipFree(val);
         return x;
     };
-    for (int h = 0; h < 2; h++) {
-        if ((e = hipMalloc(&key[h], 4 * m)) != hipSuccess) return fail(e);
-        if ((e = hipMalloc(&edge[h], 4 * m)) != hipSuccess) return fail(e);
-    }
     int bits = 1, at = 0;
     while (((int64_t)1 << bits) < n) bits++;
-    if ((e = hipMalloc(&hist, 4 * (size_t)sort_hist_words(m, bits))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&dtot, 4 * (size_t)sort_digit_words())) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&start, 8 * (n + 1))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&tmp, 8 * (size_t)scan_i64_tmp_len(n + 1))) != hipSuccess) return fail(e);
-    if ((e = hipMalloc(&ucnt, 8 * (n + 1))) != hipSuccess) return fail(e);
+    for (int h = 0; h < 2; h++) {
+        own.add(&key[h], m);
+        own.add(&edge[h], m);
+    }
+    own.add(&hist, sort_hist_words(m, bits));
+    own.add(&dtot, sort_digit_words());
+    own.add(&start, n + 1);
+    own.add(&tmp, scan_i64_tmp_len(n + 1));
+    own.add(&ucnt, n + 1);
+    if ((e = own.make()) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&rp, 8 * (n + 1))) != hipSuccess) return fail(e);
     if ((e = hipMemcpyAsync(key[0], idx, 4 * m, hipMemcpyDeviceToDevice, s)) != hipSuccess)
         return fail(e);
@@ -1874,7 +1864,7 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
                                                 1.0 / (2.0 * (double)n), col, val);
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
-    cleanup();
+    own.release();
     *row_ptr_out = rp;
     *col_out = col;
     *val_out = val;
