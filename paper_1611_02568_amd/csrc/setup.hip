@@ -110,8 +110,9 @@ constexpr uint32_t kNoThr = 0xFFFFFFFFu;
 // One wavefront cuts a list of m keys, kp <= m <= kCap, to its smallest, kp of
 // them or up to `slack` more (in no order), and returns their number;
 // thr: distance bits that none of the kp best exceeds.  The bits of the
-// kp-th distance are found from the top by counts over the wave, until a count
-// within the slack ends the search (about ten of the 32 for a slack of 32);
+// kp-th distance are found by bisection between the list's smallest and largest,
+// with counts over the wave, until a count within the slack ends the search
+// (CUTFIG);
 // among equal distances at the kp-th place the smallest columns are kept.
 __device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int kp, int slack,
                                         uint32_t& thr) {
@@ -132,17 +133,26 @@ __device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int k
         return c;
     };
     // the kept are d < end, or d == end and j <= last
-    uint32_t end = 0, last = 0xFFFFFFFEu;
+    uint32_t end = ~0u, top = 0, last = 0xFFFFFFFEu;
+#pragma unroll
+    for (int q = 0; q < kPer; q++) {
+        end = d[q] < end ? d[q] : end;
+        top = lane + q * kWave < m && d[q] > top ? d[q] : top;
+    }
+    end = wave_min(end);
+    top = wave_max(top);
     bool found = false;
-    for (int b = 31; b >= 0; b--) {
-        const uint32_t u = end | (1u << b);
+    while (end < top) {             // fewer than kp below end, at least kp up to top
+        const uint32_t u = end + (top - end + 1) / 2;
         const int c = count([&](int q) { return d[q] < u; });
         if (c < kp) {
-            end = u;                // the largest value with fewer than kp below it
+            end = u;
         } else if (c <= kp + slack) {
             end = u - 1;
             found = true;
             break;
+        } else {
+            top = u - 1;
         }
     }
     if (!found) {
