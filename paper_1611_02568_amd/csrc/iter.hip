@@ -1855,10 +1855,14 @@ void launch_traverse_shared(pixelsne_ctx* c, double th2, uint32_t* visits, uint3
 // 383 / 238 / 220 / 233; 50,000: 392 / 245 / 256 / 276; 200,000: 489 / 434 /
 // 470 / 608; 300,000: 553 / 533 / 573 / 809; 1,000,000: 1,208 / 1,374 / 1,619 /
 // 2,333; FP64 30,000: 489 / 282 / 238 / 254; 200,000: 642 / 543 / 579 / 743.
+// Since then, alone / 4: 400,000: 664 / 666; 421,161 early 708 / 683, late 667 /
+// 697; 500,000: 732 / 782.  FP64, twice the work for the same latency: 450,000:
+// 1,024 / 953; 700,000: 1,454 / 1,409; 800,000: 1,567 / 1,585; 1,000,000: 1,868 /
+// 1,945.
 // The data-driven tree's 33 levels do not fit the shared walk's stack.
 static int traverse_share(const pixelsne_ctx* c) {
     if (c->prm.tree == PSNE_TREE_DATA) return 0;
-    return c->n <= 40000 ? 8 : c->n <= 400000 ? 4 : 0;
+    return c->n <= 40000 ? 8 : c->n <= (fp64(c) ? 700000 : 400000) ? 4 : 0;
 }
 
 template <typename T, bool COUNT, bool F32T>
