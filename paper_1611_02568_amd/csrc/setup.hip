@@ -604,7 +604,7 @@ __global__ __launch_bounds__(512) void k_center_dots(const char* __restrict__ pa
 // Group q's (block) list of the groups by their bound on the squared distance,
 // rounded down; err: what a value of m may be off by.  apart counts the pairs of
 // groups further apart than the rows of the first typically are (for rows at r
-// from their mean 2 r^2, squared).
+// from their mean 2 r^2, squared), far_of those of each first group.
 struct GroupAt { float low2; uint32_t group; };
 
 __global__ __launch_bounds__(256) void k_group_order(const float* __restrict__ m,
@@ -612,6 +612,7 @@ __global__ __launch_bounds__(256) void k_group_order(const float* __restrict__ m
                                                      float err,
                                                      const uint32_t* __restrict__ radius2,
                                                      GroupAt* __restrict__ order,
+                                                     uint32_t* __restrict__ far_of,
                                                      unsigned long long* __restrict__ apart) {
     __shared__ uint64_t key[kMaxGroups];
     const int q = blockIdx.x, t = threadIdx.x;
@@ -636,7 +637,10 @@ __global__ __launch_bounds__(256) void k_group_order(const float* __restrict__ m
         key[g] = k;
     }
     for (int o = 32; o > 0; o >>= 1) far += __shfl_xor(far, o, kWave);
-    if (lane_id() == 0 && far) atomicAdd(apart, (unsigned long long)far);
+    if (lane_id() == 0 && far) {
+        atomicAdd(apart, (unsigned long long)far);
+        atomicAdd(&far_of[q], far);
+    }
     __syncthreads();
     for (int k = 2; k <= P; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -674,6 +678,31 @@ __global__ __launch_bounds__(kRoundPivots) void k_even_rows(int64_t n, uint32_t*
     row[threadIdx.x] = (uint32_t)(n / kRoundPivots * threadIdx.x);
 }
 
+// The groups by the number of others that are far, fewest first: those that
+// will meet the most tiles.
+__global__ __launch_bounds__(1024) void k_group_turns(const uint32_t* __restrict__ far_of, int T,
+                                                      uint32_t* __restrict__ turn) {
+    __shared__ uint64_t key[kMaxGroups];
+    const int t = threadIdx.x;
+    int P = 1;
+    while (P < T) P <<= 1;
+    for (int g = t; g < P; g += 1024) key[g] = g < T ? (uint64_t)far_of[g] << 32 | (uint32_t)g : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int x = t; x < P / 2; x += 1024) {
+                const int a = ((x & ~(j - 1)) << 1) | (x & (j - 1)), b = a | j;
+                const uint64_t u = key[a], v = key[b];
+                if ((u > v) == ((a & k) == 0)) {
+                    key[a] = v;
+                    key[b] = u;
+                }
+            }
+            __syncthreads();
+        }
+    for (int x = t; x < T; x += 1024) turn[x] = (uint32_t)key[x];
+}
+
 template <typename V>
 __global__ __launch_bounds__(256) void k_permuted(const V* __restrict__ a,
                                                   const uint32_t* __restrict__ perm, int64_t n,
@@ -702,18 +731,22 @@ __global__ __launch_bounds__(256) void k_fill_inf(float* __restrict__ a, int64_t
 // away (barriers of the stages, LDS latency, the filter), the rest for loads
 // that come late and for the lists (3,000 entries a row on the way to the last
 // 182).  By the groups' lists (100 clusters of unequal size, k = 150) 130 of
-// the 1,563 tiles remain for a block on average: 24 ms, a third each for the
+// the 1,563 tiles remain for a block on average: 22 ms, a third each for the
 // stages, for the lists as they fill and for cutting them, which a block does
 // all at once.  Tried: stages half as deep, three in flight, 165; lists cut
 // only at 768 entries, 153; the next list read while one is cut, no gain.  The
 // FP32 MFMA kernel of 128 x 128 tiles, filtered through LDS, that this replaces
-// took 605.  70,000 x 784 bytes: 4.2 ms by the lists, 10.7 with all tiles, 46.6
+// took 605.  70,000 x 784 bytes: 3.2 ms by the lists, 10.7 with all tiles, 46.6
 // by the INT8 kernel of 128 x 128 tiles.
 // The order of the rows, or null pointers: the row at a place, the groups' lists,
-// rows per group, number of groups, and what an approximate distance may be off by.
+// the groups' turns, rows per group, number of groups, and what an approximate
+// distance may be off by.  Blocks begin in the groups' turns, the longest first:
+// 547 blocks of unequal length on 256 CUs (70,000 x 784 bytes) take 3.2 ms, in
+// the order of the rows 4.2; 3,125 (400,000 x 128) 22.4 and 23.6.
 struct RowOrder {
     const uint32_t* perm;
     const GroupAt* order;
+    const uint32_t* turn;
     int64_t G;
     int T;
     float err;
@@ -750,7 +783,13 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
     const int t = threadIdx.x, lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wr = w >> 2, wc = w & 3;                      // 64 query rows, 64 columns
-    const int64_t q0 = q_first + (int64_t)blockIdx.x * kQB; // q0 - q_first indexes the lists
+    int64_t block = blockIdx.x;
+    if (ord.turn) {
+        const int64_t per = ord.G / kQB;
+        block = ord.turn[block / per] * per + block % per;
+    }
+    const int64_t q0 = q_first + block * kQB;               // q0 - q_first indexes the lists
+    if (q0 >= n) return;
     const int nst = steps / F::kSteps;
     const int64_t tiles = (n + kCB - 1) / kCB;
     if (t < kQB) {
@@ -1429,7 +1468,7 @@ template <typename F>
 void launch_candidates(const char* packed, int64_t n, int steps, const typename F::Num* nrm,
                        float f, int64_t first, int64_t rows, int kp, const RowOrder& ord,
                        uint64_t* cand, uint32_t* ccnt, uint32_t* cthr, hipStream_t s) {
-    const dim3 g((unsigned)ceil_div(rows, kQB));
+    const dim3 g((unsigned)(ord.turn ? ord.T * (ord.G / kQB) : ceil_div(rows, kQB)));
     // the queries' fragments stay in LDS while 8 steps of them fit beside two
     // stages (FP16: depth 128)
     if (steps <= 8)
@@ -1462,7 +1501,8 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     float *ct = nullptr, *d2 = nullptr, *m = nullptr;
     Num *cn = nullptr, *np = nullptr;
     uint32_t *rank = nullptr, *key[2] = {nullptr, nullptr}, *idx[2] = {nullptr, nullptr},
-             *hist = nullptr, *dtot = nullptr, *rows = nullptr, *radius2 = nullptr;
+             *hist = nullptr, *dtot = nullptr, *rows = nullptr, *radius2 = nullptr, *far_of = nullptr,
+             *turn = nullptr;
     GroupAt* order = nullptr;
     int64_t *weight = nullptr, *sum = nullptr, *tmp = nullptr;
     unsigned long long* apart = nullptr;
@@ -1476,6 +1516,8 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     held->add(&m, (int64_t)T * T);
     held->add(&order, (int64_t)T * T);
     held->add(&radius2, T);
+    held->add(&far_of, T);
+    held->add(&turn, T);
     held->add(&apart, 1);
     held->add(&rank, kPivots);
     held->add(&rows, kPivots);
@@ -1538,6 +1580,7 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     k_permuted<<<dim3((unsigned)ceil_div(n, 256)), 256, 0, s>>>(nrm, perm, n, np);
     if ((e = hipMemsetAsync(frag, 0, frags, s)) != hipSuccess) return e;
     if ((e = hipMemsetAsync(radius2, 0, sizeof(uint32_t) * T, s)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(far_of, 0, sizeof(uint32_t) * T, s)) != hipSuccess) return e;
     if ((e = hipMemsetAsync(apart, 0, sizeof(*apart), s)) != hipSuccess) return e;
     k_centers<X, F, P><<<dim3((unsigned)T), 256, 0, s>>>(Xm, n, D, perm, G, G, steps, scale, frag, ct,
                                                          cn);
@@ -1545,13 +1588,16 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     k_fill_inf<<<dim3((unsigned)ceil_div((int64_t)T * T, 256)), 256, 0, s>>>(m, (int64_t)T * T);
     k_center_dots<F, false><<<blocks, 512, 0, s>>>(packed, n, steps, frag, cn, T, f, G, nullptr,
                                                    nullptr, np, 0.f, nullptr, m, radius2);
-    k_group_order<<<dim3((unsigned)T), 256, 0, s>>>(m, d2, T, 2.f * err, radius2, order, apart);
+    k_group_order<<<dim3((unsigned)T), 256, 0, s>>>(m, d2, T, 2.f * err, radius2, order, far_of,
+                                                    apart);
+    k_group_turns<<<1, 1024, 0, s>>>(far_of, T, turn);
     unsigned long long far = 0;
     e = hipMemcpyAsync(&far, apart, sizeof(far), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     if ((double)far >= kApartShare * (double)T * (double)T) {
-        *ord = RowOrder{perm, order, G, T, err};
+        // (a batch of rows takes its own in order)
+        *ord = RowOrder{perm, order, n <= kBatch ? turn : nullptr, G, T, err};
         *nrm_p = np;
     } else {
         pack(nullptr);
