@@ -7,8 +7,9 @@
 //                x - 128; each row keeps a candidate list (global memory,
 //                threshold in LDS) that a wavefront cuts to the K' = k + 32
 //                best whenever it fills up.  Rows that fall into clusters are
-//                put in an order by which whole tiles can be left out.  The K' survivors are re-ranked
-//                with exact FP64 distances and ties go to the smaller index.
+//                put in an order by which whole tiles can be left out.
+//                The K' survivors are re-ranked with exact FP64 distances
+//                and ties go to the smaller index.
 //   perplexity   per-row bisection on the Gaussian precision (FP64)
 //   symmetrize   p_ij = (p_{j|i} + p_{i|j}) / 2n on the union pattern -> CSR
 #include <math.h>
@@ -36,7 +37,7 @@ constexpr int kCutSlack = 32;  // entries beyond the kp best that a cut may leav
 // Rows from which on an order is looked for: at 17,000 x 50 in 30 clusters the
 // search takes 1.5 ms without and 1.8 with it, at 33,000 3.3 and 2.1.
 constexpr int64_t kOrderFrom = 1 << 15;
-constexpr int kBatch = 1 << 19;   // query rows whose lists exist at a time (4 GB)
+constexpr int kBatch = 1 << 19;   // query rows whose candidates exist at a time
 static_assert(kBatch % kQB == 0, "batches are whole blocks");
 static_assert(kCutLow >= 256 + kMargin + kCutSlack && kCutAt + kCB <= kCap,
               "a cut list is shorter than kCutLow, and a tile's columns fit");
@@ -108,15 +109,16 @@ __device__ void bitonic512(uint64_t* s) {
 constexpr uint32_t kNoThr = 0xFFFFFFFFu;
 
 // One wavefront cuts a list of m keys, kp <= m <= kCap, to its smallest, kp of
-// them or up to `slack` more (in no order), and returns their number;
+// them or up to `slack` more (in no order, to `to`, which may be the list), and
+// returns their number;
 // thr: distance bits that none of the kp best exceeds.  The bits of the
 // kp-th distance are found by bisection from the list's smallest to its largest,
 // by counts over the wave, until a count within the slack ends the search
 // (some five steps; bit by bit from the top took ten, 10.8 ms for 100,000
 // Gaussian rows of 8 where this takes 10.1).  Among equal distances at the
 // kp-th place the smallest columns are kept.
-__device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int kp, int slack,
-                                        uint32_t& thr) {
+__device__ __forceinline__ int cut_list(const uint64_t* lst, int m, int kp, int slack,
+                                        uint64_t* to, uint32_t& thr) {
     constexpr int kPer = kCap / kWave;
     const int lane = lane_id();
     uint32_t d[kPer], j[kPer];
@@ -173,7 +175,7 @@ __device__ __forceinline__ int cut_list(uint64_t* __restrict__ lst, int m, int k
         const bool keep = d[q] < end || (d[q] == end && j[q] <= last);
         const uint64_t b = ballot64(keep);
         if (keep)
-            lst[at + __popcll(b & lanemask_lt())] = ((uint64_t)d[q] << 32) | (uint64_t)j[q];
+            to[at + __popcll(b & lanemask_lt())] = ((uint64_t)d[q] << 32) | (uint64_t)j[q];
         at += __popcll(b);
     }
     thr = end;
@@ -249,7 +251,8 @@ struct PartsI8 {
         return low2 > (float)thr * (1.f + 0x1p-20f);
     }
     static __device__ __forceinline__ int32_t none() { return -0x7FFFFFFF - 1; }
-    static __device__ __forceinline__ int32_t far() { return 0x7FFFFFFF; }   // a padding row's dot is 0
+    // a padding row's dot is 0
+    static __device__ __forceinline__ int32_t far() { return 0x7FFFFFFF; }
 };
 
 inline int64_t pad_rows(int64_t n) { return ceil_div(n, kCB) * kCB; }
@@ -460,7 +463,8 @@ __global__ __launch_bounds__(64) void k_chain(const float* __restrict__ d2,
 
 // All rows against all T centres: a wavefront takes 32 rows, a block one run of
 // 256, and four tiles of 32 centres at a time.  ASSIGN: key[row] = rank of the
-// nearest centre, or weight[row] its squared distance in units of 1 / unit.  Else m[group][t] (infinity to begin with) gets the smallest
+// nearest centre, or weight[row] its squared distance in units of 1 / unit.
+// Else m[group][t] (infinity to begin with) gets the smallest
 // |x - c_t|^2 - |x - c_group|^2 of the group's rows, and radius2[group] (bits,
 // zero to begin with) the largest |x - c_group|^2.
 __device__ __forceinline__ void atomic_min_float(float* at, float v) {
@@ -686,7 +690,8 @@ __global__ __launch_bounds__(1024) void k_group_turns(const uint32_t* __restrict
     const int t = threadIdx.x;
     int P = 1;
     while (P < T) P <<= 1;
-    for (int g = t; g < P; g += 1024) key[g] = g < T ? (uint64_t)far_of[g] << 32 | (uint32_t)g : ~0ull;
+    for (int g = t; g < P; g += 1024)
+        key[g] = g < T ? (uint64_t)far_of[g] << 32 | (uint32_t)g : ~0ull;
     __syncthreads();
     for (int k = 2; k <= P; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -716,9 +721,27 @@ __global__ __launch_bounds__(256) void k_fill_inf(float* __restrict__ a, int64_t
     if (i < n) a[i] = INFINITY;
 }
 
-// Candidate generation.  A block of eight wavefronts owns kQB query rows and
-// sweeps all candidates in tiles of kCB; each wavefront computes a 64 x 64
-// part as 2 x 2 MFMA tiles.  The depth runs in stages of F::kSteps
+// The order of the rows, or null pointers: the row at a place, the groups' lists,
+// the groups' turns, rows per group, number of groups, and what an approximate
+// distance may be off by.  Blocks begin in the groups' turns, the longest first:
+// 547 blocks of unequal length on 256 CUs (70,000 x 784 bytes) take 3.2 ms, in
+// the order of the rows 4.2; 3,125 (400,000 x 128) 22.4 and 23.6.
+struct RowOrder {
+    const uint32_t* perm;
+    const GroupAt* order;
+    const uint32_t* turn;
+    int64_t G;
+    int T;
+    float err;
+};
+
+// Candidate generation.  Blocks of eight wavefronts, one per CU, take turns of
+// kQB query rows; their working lists are a block's (268 MB in all) and each
+// row's kp best go to its own place: with working lists for every row, 3.3 GB at
+// 400,000, the allocation alone took up to 70 ms once that much memory had been
+// released before.  A block sweeps all candidates in tiles of kCB; each
+// wavefront computes a 64 x 64 part as 2 x 2 MFMA tiles.  The depth runs in
+// stages of F::kSteps
 // instructions, staged by loads straight into LDS, the next stage (of this
 // tile or of the next) in flight while one is multiplied; with HOLD the
 // queries' fragments stay in LDS (depth up to 128 for FP16), else they are
@@ -736,22 +759,8 @@ __global__ __launch_bounds__(256) void k_fill_inf(float* __restrict__ a, int64_t
 // all at once.  Tried: stages half as deep, three in flight, 165; lists cut
 // only at 768 entries, 153; the next list read while one is cut, no gain.  The
 // FP32 MFMA kernel of 128 x 128 tiles, filtered through LDS, that this replaces
-// took 605.  70,000 x 784 bytes: 3.2 ms by the lists, 10.7 with all tiles, 46.6
+// took 605.  70,000 x 784 bytes: 3.4 ms by the lists, 10.7 with all tiles, 46.6
 // by the INT8 kernel of 128 x 128 tiles.
-// The order of the rows, or null pointers: the row at a place, the groups' lists,
-// the groups' turns, rows per group, number of groups, and what an approximate
-// distance may be off by.  Blocks begin in the groups' turns, the longest first:
-// 547 blocks of unequal length on 256 CUs (70,000 x 784 bytes) take 3.2 ms, in
-// the order of the rows 4.2; 3,125 (400,000 x 128) 22.4 and 23.6.
-struct RowOrder {
-    const uint32_t* perm;
-    const GroupAt* order;
-    const uint32_t* turn;
-    int64_t G;
-    int T;
-    float err;
-};
-
 typedef __attribute__((address_space(1))) const void GlobalPtr;
 typedef __attribute__((address_space(3))) void LdsPtr;
 
@@ -760,7 +769,9 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
                                                         int64_t n, int steps,
                                                         const typename F::Num* __restrict__ nrm,
                                                         float f, int64_t q_first, int kp,
-                                                        RowOrder ord,
+                                                        RowOrder ord, uint32_t blocks,
+                                                        uint32_t* __restrict__ ticket,
+                                                        uint64_t* __restrict__ work,
                                                         uint64_t* __restrict__ cand,
                                                         uint32_t* __restrict__ cand_cnt,
                                                         uint32_t* __restrict__ cand_thr) {
@@ -783,234 +794,241 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
     const int t = threadIdx.x, lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wr = w >> 2, wc = w & 3;                      // 64 query rows, 64 columns
-    int64_t block = blockIdx.x;
-    if (ord.turn) {
-        const int64_t per = ord.G / kQB;
-        block = ord.turn[block / per] * per + block % per;
-    }
-    const int64_t q0 = q_first + block * kQB;               // q0 - q_first indexes the lists
-    if (q0 >= n) return;
-    const int nst = steps / F::kSteps;
-    const int64_t tiles = (n + kCB - 1) / kCB;
-    if (t < kQB) {
-        cnt[t] = 0;
-        thr[t] = q0 + t < n ? kNoThr : 0u;
-        nq[t] = q0 + t < n ? nrm[q0 + t] : Num(0);
-        bnd[t] = q0 + t < n ? F::bound(kNoThr, Num(0)) : F::none();
-    }
-    // A stage takes kPer = 4 fragments of each 32 rows.  Wavefront w loads the
-    // fragments w, w + 8, ... of a stage: fragment w % 4 of the rows w / 4,
-    // w / 4 + 2, ...
-    constexpr int kPer = F::kSteps * F::kParts;
-    static_assert(kPer == 4 && kStageC % 8 == 0 && kStageQ % 8 == 0, "whole rounds of loads");
-    const int64_t frag_row = (int64_t)steps * F::kParts * kFrag;   // bytes of 32 rows
-    const char* const mine = packed + (w >> 2) * frag_row + (w & 3) * kFrag + lane * 16;
-    auto to_lds = [&](const char* src, char* dst) {
-        __builtin_amdgcn_global_load_lds((GlobalPtr*)src, (LdsPtr*)dst, 16, 0, 0);
-    };
-    auto fetch = [&](int64_t tile, int s, int buf) {
-        const char* c = mine + tile * (kCF * frag_row) + s * (kPer * kFrag);
-#pragma unroll
-        for (int y = 0; y < kStageC / 8; y++)
-            to_lds(c + y * (2 * frag_row), C[buf] + (w + 8 * y) * kFrag);
-        if constexpr (!HOLD) {
-            const char* q = mine + (q0 / 32) * frag_row + s * (kPer * kFrag);
-#pragma unroll
-            for (int y = 0; y < kStageQ / 8; y++)
-                to_lds(q + y * (2 * frag_row), Q + (buf * kStageQ + w + 8 * y) * kFrag);
-        }
-    };
-    // every load and store of the block is done, in LDS and in the lists
-    auto settle = [&]() {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint64_t* const lists = work + (int64_t)blockIdx.x * (kQB * kCap);
+    __shared__ uint32_t s_block;
+    for (;;) {
         __syncthreads();
-    };
-    auto cut = [&]() {
-        // Lists that could overflow during the next tile are cut, 16 rows per
-        // wavefront.  The block waits for a wavefront that cuts, so once any
-        // list is that long every long one is cut.
-        const uint64_t full =
-            ballot64(cnt[lane] > (uint32_t)kCutAt || cnt[lane + kWave] > (uint32_t)kCutAt);
-        if (full == 0) return;
-        uint64_t todo = ballot64(lane < 16 && cnt[w * 16 + (lane & 15)] > (uint32_t)kCutLow);
-        while (todo) {
-            const int q = w * 16 + __ffsll((long long)todo) - 1;
-            todo &= todo - 1;
-            uint32_t end;
-            const int m = cut_list(cand + (q0 - q_first + q) * (int64_t)kCap, (int)cnt[q], kp,
-                                   kCutSlack, end);
+        if (t == 0) s_block = atomicAdd(ticket, 1u);
+        __syncthreads();
+        int64_t block = __builtin_amdgcn_readfirstlane(s_block);
+        if (block >= blocks) return;
+        if (ord.turn) {
+            const int64_t per = ord.G / kQB;
+            block = ord.turn[block / per] * per + block % per;
+        }
+        const int64_t q0 = q_first + block * kQB;
+        if (q0 >= n) continue;
+        const int nst = steps / F::kSteps;
+        const int64_t tiles = (n + kCB - 1) / kCB;
+        if (t < kQB) {
+            cnt[t] = 0;
+            thr[t] = q0 + t < n ? kNoThr : 0u;
+            nq[t] = q0 + t < n ? nrm[q0 + t] : Num(0);
+            bnd[t] = q0 + t < n ? F::bound(kNoThr, Num(0)) : F::none();
+        }
+        // A stage takes kPer = 4 fragments of each 32 rows.  Wavefront w loads the
+        // fragments w, w + 8, ... of a stage: fragment w % 4 of the rows w / 4,
+        // w / 4 + 2, ...
+        constexpr int kPer = F::kSteps * F::kParts;
+        static_assert(kPer == 4 && kStageC % 8 == 0 && kStageQ % 8 == 0, "whole rounds of loads");
+        const int64_t frag_row = (int64_t)steps * F::kParts * kFrag;   // bytes of 32 rows
+        const char* const mine = packed + (w >> 2) * frag_row + (w & 3) * kFrag + lane * 16;
+        auto to_lds = [&](const char* src, char* dst) {
+            __builtin_amdgcn_global_load_lds((GlobalPtr*)src, (LdsPtr*)dst, 16, 0, 0);
+        };
+        auto fetch = [&](int64_t tile, int s, int buf) {
+            const char* c = mine + tile * (kCF * frag_row) + s * (kPer * kFrag);
+#pragma unroll
+            for (int y = 0; y < kStageC / 8; y++)
+                to_lds(c + y * (2 * frag_row), C[buf] + (w + 8 * y) * kFrag);
+            if constexpr (!HOLD) {
+                const char* q = mine + (q0 / 32) * frag_row + s * (kPer * kFrag);
+#pragma unroll
+                for (int y = 0; y < kStageQ / 8; y++)
+                    to_lds(q + y * (2 * frag_row), Q + (buf * kStageQ + w + 8 * y) * kFrag);
+            }
+        };
+        // every load and store of the block is done, in LDS and in the lists
+        auto settle = [&]() {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        };
+        auto cut = [&]() {
+            // Lists that could overflow during the next tile are cut, 16 rows per
+            // wavefront.  The block waits for a wavefront that cuts, so once any
+            // list is that long every long one is cut.
+            const uint64_t full =
+                ballot64(cnt[lane] > (uint32_t)kCutAt || cnt[lane + kWave] > (uint32_t)kCutAt);
+            if (full == 0) return;
+            uint64_t todo = ballot64(lane < 16 && cnt[w * 16 + (lane & 15)] > (uint32_t)kCutLow);
+            while (todo) {
+                const int q = w * 16 + __ffsll((long long)todo) - 1;
+                todo &= todo - 1;
+                uint32_t end;
+                uint64_t* const lst = lists + q * kCap;
+                const int m = cut_list(lst, (int)cnt[q], kp, kCutSlack, lst, end);
+                if (lane == 0) {
+                    end = end < thr[q] ? end : thr[q];
+                    cnt[q] = (uint32_t)m;
+                    thr[q] = end;
+                    bnd[q] = F::bound(end, nq[q]);
+                }
+            }
+        };
+
+        if constexpr (HOLD) {
+            // all steps of the queries, by [32 rows][8 steps][part]
+            for (int x = w; x < kQF * steps * F::kParts; x += 8) {
+                const int rb = x / (steps * F::kParts), rest = x % (steps * F::kParts);
+                to_lds(packed + (q0 / 32 + rb) * frag_row + rest * kFrag + lane * 16,
+                       Q + (rb * 8 * F::kParts + rest) * kFrag);
+            }
+        }
+        // the tiles in turn, or by the list of the queries' group
+        const GroupAt* const list = ord.order ? ord.order + (q0 / ord.G) * ord.T : nullptr;
+        const int64_t sub = ord.order ? ord.G / kCB : 1;
+        const int64_t places = ord.order ? ord.T * sub : tiles;
+        uint32_t worst = kNoThr;               // the largest threshold of the block's rows
+        int64_t place = -1;
+        auto next_tile = [&]() -> int64_t {
+            while (++place < places) {
+                if (!list) return place;
+                const GroupAt g = list[place / sub];
+                if (worst != kNoThr && F::beyond(g.low2, ord.err, worst)) return -1;
+                const int64_t at = (int64_t)g.group * sub + place % sub;
+                if (at < tiles) return at;
+            }
+            return -1;
+        };
+        int64_t tile = next_tile(), next = -1;
+        fetch(tile, 0, 0);
+        settle();
+        int buf = 0;
+        for (bool begun = false; tile >= 0; tile = next, begun = true) {
+            next = next_tile();
+            typename F::Acc acc[2][2];
+#pragma unroll
+            for (int a = 0; a < 2; a++)
+#pragma unroll
+                for (int b = 0; b < 2; b++)
+#pragma unroll
+                    for (int v = 0; v < 16; v++) acc[a][b][v] = 0;
+            const int64_t c0 = tile * kCB + 64 * wc + (lane & 31);
+            const Num nc0 = c0 < n ? nrm[c0] : F::far();
+            const Num nc1 = c0 + 32 < n ? nrm[c0 + 32] : F::far();
+            auto stage = [&](int s) {
+                if (s + 1 < nst) fetch(tile, s + 1, buf ^ 1);
+                else if (next >= 0) fetch(next, 0, buf ^ 1);
+                const char* cs = C[buf] + 2 * wc * kPer * kFrag + lane * 16;
+                const char* qs = HOLD ? Q + (2 * wr * 8 * F::kParts + s * kPer) * kFrag + lane * 16
+                                      : Q + (buf * kStageQ + 2 * wr * kPer) * kFrag + lane * 16;
+                constexpr int kQRow = HOLD ? 8 * F::kParts : kPer;     // fragments of 32 queries
+#pragma unroll
+                for (int k = 0; k < F::kSteps; k++) {
+                    Vec av[2][F::kParts], bv[2][F::kParts];
+#pragma unroll
+                    for (int p = 0; p < F::kParts; p++)
+#pragma unroll
+                        for (int h = 0; h < 2; h++) {
+                            const int x = k * F::kParts + p;
+                            av[h][p] = *reinterpret_cast<const Vec*>(qs + (h * kQRow + x) * kFrag);
+                            bv[h][p] = *reinterpret_cast<const Vec*>(cs + (h * kPer + x) * kFrag);
+                        }
+#pragma unroll
+                    for (int a = 0; a < 2; a++)
+#pragma unroll
+                        for (int b = 0; b < 2; b++) F::product(av[a], bv[b], acc[a][b]);
+                }
+                settle();
+                buf ^= 1;
+            };
+            stage(0);
+            // the previous tile's candidates are all in the lists now; the next
+            // stage's barrier, or one more, shows the new bounds to everybody
+            if (begun) {
+                cut();
+                if (nst == 1 || list) __syncthreads();
+                if (list) {
+                    const uint32_t a = thr[lane], b = thr[lane + kWave];
+                    worst = wave_max(a > b ? a : b);
+                }
+            }
+            for (int s = 1; s < nst; s++) stage(s);
+            // filter: element v of tile (a, b) is row 8 (v / 4) + 4 (lane / 32) + v % 4,
+            // column lane % 32.  Each lane collects a bit per element that passes;
+            // those few are picked out lane by lane, gather in LDS and go to the
+            // lists together.
+            int qn = 0;
+            auto drain = [&]() {
+                __builtin_amdgcn_wave_barrier();
+                for (int x = lane; x < qn; x += kWave) {
+                    const Hit h = hits[w][x];
+                    const uint32_t rl = h.at >> 8;
+                    const int64_t gc = tile * kCB + (h.at & 255u);
+                    if (gc < n && gc != q0 + rl) {
+                        const uint32_t pos = atomicAdd(&cnt[rl], 1u);
+                        lists[rl * kCap + pos] =
+                            ((uint64_t)F::bits(h.part, nq[rl]) << 32) |
+                            (uint64_t)(ord.perm ? ord.perm[gc] : (uint32_t)gc);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                qn = 0;
+            };
+#pragma unroll
+            for (int a = 0; a < 2; a++) {
+                Num g[16];
+#pragma unroll
+                for (int v = 0; v < 16; v++)
+                    g[v] = bnd[64 * wr + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)];
+#pragma unroll
+                for (int b = 0; b < 2; b++) {
+                    const Num ncv = b ? nc1 : nc0;
+                    uint32_t pass = 0;
+#pragma unroll
+                    for (int v = 15; v >= 0; v--)
+                        pass = pass + pass + (F::part_dist(acc[a][b][v], f, ncv) <= g[v] ? 1u : 0u);
+                    uint64_t m;
+                    while ((m = ballot64(pass != 0u)) != 0) {
+                        const int c = __popcll(m);
+                        if (qn + c > kHits) drain();
+                        const uint32_t v = (uint32_t)__ffs((int)pass) - 1u;
+                        // acc[a][b][v], by a tree of selects between values
+                        auto pick = [](bool c, Num hi, Num lo) { return c ? hi : lo; };
+                        const bool v0 = (v & 1u) != 0, v1 = (v & 2u) != 0, v2 = (v & 4u) != 0,
+                                   v3 = (v & 8u) != 0;
+                        auto of4 = [&](int q) {
+                            return pick(v1, pick(v0, acc[a][b][q + 3], acc[a][b][q + 2]),
+                                        pick(v0, acc[a][b][q + 1], acc[a][b][q]));
+                        };
+                        const Num x = pick(v3, pick(v2, of4(12), of4(8)), pick(v2, of4(4), of4(0)));
+                        if (pass != 0u) {
+                            const uint32_t rl = (uint32_t)(64 * wr + 32 * a + 4 * (lane >> 5)) +
+                                                8u * (v >> 2) + (v & 3u);
+                            const uint32_t cl = (uint32_t)(64 * wc + 32 * b + (lane & 31));
+                            hits[w][qn + __builtin_amdgcn_mbcnt_hi(
+                                             (uint32_t)(m >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
+                                Hit{F::part_dist(x, f, ncv), rl << 8 | cl};
+                            pass &= pass - 1u;
+                        }
+                        qn += c;
+                    }
+                }
+            }
+            if (qn > 0) drain();
+        }
+        settle();
+        // the kp best of each row
+        for (int q = 16 * w; q < 16 * w + 16; q++) {
+            if (q0 + q >= n) break;
+            const int64_t r = q0 - q_first + q;
+            const uint64_t* const lst = lists + q * kCap;
+            int m = __builtin_amdgcn_readfirstlane((int)cnt[q]);
+            uint32_t end = thr[q];
+            if (m < kp) {
+                for (int e = lane; e < m; e += kWave) cand[r * kp + e] = lst[e];
+            } else {
+                uint32_t last;
+                m = cut_list(lst, m, kp, 0, cand + r * kp, last);
+                // kNoThr: all are in the list
+                end = kp == n - 1 ? kNoThr : last < end ? last : end;
+            }
             if (lane == 0) {
-                end = end < thr[q] ? end : thr[q];
-                cnt[q] = (uint32_t)m;
-                thr[q] = end;
-                bnd[q] = F::bound(end, nq[q]);
+                cand_cnt[r] = (uint32_t)m;
+                cand_thr[r] = end;
             }
         }
-    };
-
-    if constexpr (HOLD) {
-        // all steps of the queries, by [32 rows][8 steps][part]
-        for (int x = w; x < kQF * steps * F::kParts; x += 8) {
-            const int rb = x / (steps * F::kParts), rest = x % (steps * F::kParts);
-            to_lds(packed + (q0 / 32 + rb) * frag_row + rest * kFrag + lane * 16,
-                   Q + (rb * 8 * F::kParts + rest) * kFrag);
-        }
-    }
-    // the tiles in turn, or by the list of the queries' group
-    const GroupAt* const list = ord.order ? ord.order + (q0 / ord.G) * ord.T : nullptr;
-    const int64_t sub = ord.order ? ord.G / kCB : 1;
-    const int64_t places = ord.order ? ord.T * sub : tiles;
-    uint32_t worst = kNoThr;               // the largest threshold of the block's rows
-    int64_t place = -1;
-    auto next_tile = [&]() -> int64_t {
-        while (++place < places) {
-            if (!list) return place;
-            const GroupAt g = list[place / sub];
-            if (worst != kNoThr && F::beyond(g.low2, ord.err, worst)) return -1;
-            const int64_t at = (int64_t)g.group * sub + place % sub;
-            if (at < tiles) return at;
-        }
-        return -1;
-    };
-    int64_t tile = next_tile(), next = -1;
-    fetch(tile, 0, 0);
-    settle();
-    int buf = 0;
-    for (bool begun = false; tile >= 0; tile = next, begun = true) {
-        next = next_tile();
-        typename F::Acc acc[2][2];
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-#pragma unroll
-            for (int b = 0; b < 2; b++)
-#pragma unroll
-                for (int v = 0; v < 16; v++) acc[a][b][v] = 0;
-        const int64_t c0 = tile * kCB + 64 * wc + (lane & 31);
-        const Num nc0 = c0 < n ? nrm[c0] : F::far(), nc1 = c0 + 32 < n ? nrm[c0 + 32] : F::far();
-        auto stage = [&](int s) {
-            if (s + 1 < nst) fetch(tile, s + 1, buf ^ 1);
-            else if (next >= 0) fetch(next, 0, buf ^ 1);
-            const char* cs = C[buf] + 2 * wc * kPer * kFrag + lane * 16;
-            const char* qs = HOLD ? Q + (2 * wr * 8 * F::kParts + s * kPer) * kFrag + lane * 16
-                                  : Q + (buf * kStageQ + 2 * wr * kPer) * kFrag + lane * 16;
-            constexpr int kQRow = HOLD ? 8 * F::kParts : kPer;     // fragments of 32 queries
-#pragma unroll
-            for (int k = 0; k < F::kSteps; k++) {
-                Vec av[2][F::kParts], bv[2][F::kParts];
-#pragma unroll
-                for (int p = 0; p < F::kParts; p++)
-#pragma unroll
-                    for (int h = 0; h < 2; h++) {
-                        const int x = k * F::kParts + p;
-                        av[h][p] = *reinterpret_cast<const Vec*>(qs + (h * kQRow + x) * kFrag);
-                        bv[h][p] = *reinterpret_cast<const Vec*>(cs + (h * kPer + x) * kFrag);
-                    }
-#pragma unroll
-                for (int a = 0; a < 2; a++)
-#pragma unroll
-                    for (int b = 0; b < 2; b++) F::product(av[a], bv[b], acc[a][b]);
-            }
-            settle();
-            buf ^= 1;
-        };
-        stage(0);
-        // the previous tile's candidates are all in the lists now; the next
-        // stage's barrier, or one more, shows the new bounds to everybody
-        if (begun) {
-            cut();
-            if (nst == 1 || list) __syncthreads();
-            if (list) {
-                const uint32_t a = thr[lane], b = thr[lane + kWave];
-                worst = wave_max(a > b ? a : b);
-            }
-        }
-        for (int s = 1; s < nst; s++) stage(s);
-        // filter: element v of tile (a, b) is row 8 (v / 4) + 4 (lane / 32) + v % 4,
-        // column lane % 32.  Each lane collects a bit per element that passes;
-        // those few are picked out lane by lane, gather in LDS and go to the
-        // lists together.
-        int qn = 0;
-        auto drain = [&]() {
-            __builtin_amdgcn_wave_barrier();
-            for (int x = lane; x < qn; x += kWave) {
-                const Hit h = hits[w][x];
-                const uint32_t rl = h.at >> 8;
-                const int64_t gc = tile * kCB + (h.at & 255u);
-                if (gc < n && gc != q0 + rl) {
-                    const uint32_t pos = atomicAdd(&cnt[rl], 1u);
-                    cand[(q0 - q_first + rl) * kCap + pos] =
-                        ((uint64_t)F::bits(h.part, nq[rl]) << 32) |
-                        (uint64_t)(ord.perm ? ord.perm[gc] : (uint32_t)gc);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            qn = 0;
-        };
-#pragma unroll
-        for (int a = 0; a < 2; a++) {
-            Num g[16];
-#pragma unroll
-            for (int v = 0; v < 16; v++)
-                g[v] = bnd[64 * wr + 32 * a + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)];
-#pragma unroll
-            for (int b = 0; b < 2; b++) {
-                const Num ncv = b ? nc1 : nc0;
-                uint32_t pass = 0;
-#pragma unroll
-                for (int v = 15; v >= 0; v--)
-                    pass = pass + pass + (F::part_dist(acc[a][b][v], f, ncv) <= g[v] ? 1u : 0u);
-                uint64_t m;
-                while ((m = ballot64(pass != 0u)) != 0) {
-                    const int c = __popcll(m);
-                    if (qn + c > kHits) drain();
-                    const uint32_t v = (uint32_t)__ffs((int)pass) - 1u;
-                    // acc[a][b][v], by a tree of selects between values
-                    auto pick = [](bool c, Num hi, Num lo) { return c ? hi : lo; };
-                    const bool v0 = (v & 1u) != 0, v1 = (v & 2u) != 0, v2 = (v & 4u) != 0,
-                               v3 = (v & 8u) != 0;
-                    auto of4 = [&](int q) {
-                        return pick(v1, pick(v0, acc[a][b][q + 3], acc[a][b][q + 2]),
-                                    pick(v0, acc[a][b][q + 1], acc[a][b][q]));
-                    };
-                    const Num x = pick(v3, pick(v2, of4(12), of4(8)), pick(v2, of4(4), of4(0)));
-                    if (pass != 0u) {
-                        const uint32_t rl = (uint32_t)(64 * wr + 32 * a + 4 * (lane >> 5)) +
-                                            8u * (v >> 2) + (v & 3u);
-                        const uint32_t cl = (uint32_t)(64 * wc + 32 * b + (lane & 31));
-                        hits[w][qn + __builtin_amdgcn_mbcnt_hi(
-                                         (uint32_t)(m >> 32),
-                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
-                            Hit{F::part_dist(x, f, ncv), rl << 8 | cl};
-                        pass &= pass - 1u;
-                    }
-                    qn += c;
-                }
-            }
-        }
-        if (qn > 0) drain();
-    }
-    __syncthreads();
-    if (t < kQB && q0 + t < n) {
-        cand_cnt[q0 - q_first + t] = cnt[t];
-        cand_thr[q0 - q_first + t] = thr[t];
-    }
-}
-
-// Cuts every list to its kp best (one wavefront per row).
-__global__ __launch_bounds__(256) void k_knn_cut(uint64_t* __restrict__ cand, int64_t rows,
-                                                 int64_t n, int kp,
-                                                 uint32_t* __restrict__ cand_cnt,
-                                                 uint32_t* __restrict__ cand_thr) {
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= rows) return;
-    const int m = __builtin_amdgcn_readfirstlane((int)cand_cnt[i]);
-    if (m < kp) return;
-    uint32_t end;
-    const int kept = cut_list(cand + i * kCap, m, kp, 0, end);
-    if (lane_id() == 0) {
-        end = end < cand_thr[i] ? end : cand_thr[i];
-        cand_cnt[i] = (uint32_t)kept;
-        cand_thr[i] = kp == n - 1 ? kNoThr : end;      // all of them are in the list
     }
 }
 
@@ -1049,7 +1067,7 @@ template <typename X>
 __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, int64_t q_first,
                                                     int D, int k,
                                                     const uint32_t* __restrict__ perm,
-                                                    const uint64_t* __restrict__ cand,
+                                                    const uint64_t* __restrict__ cand, int kp,
                                                     const uint32_t* __restrict__ cand_cnt,
                                                     const uint32_t* __restrict__ cand_thr,
                                                     const float* __restrict__ nrm, float nrm_max,
@@ -1061,7 +1079,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
     const int64_t l = blockIdx.x, i = perm ? (int64_t)perm[q_first + l] : q_first + l;
     const int t = threadIdx.x;
     const int m = (int)cand_cnt[l];                 // at most 256 + kMargin
-    const uint64_t* lst = cand + l * kCap;
+    const uint64_t* lst = cand + l * kp;
     for (int e = t; e < 512; e += 256) {
         dv[e] = INFINITY;
         jv[e] = e < m ? (uint32_t)lst[e] : 0xFFFFFFFFu;
@@ -1112,7 +1130,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const X* __restrict__ Xm, in
 // uint8 rows: the kept keys are exact integer distances and a candidate equal
 // to the threshold is always kept, so the first k of the sorted list are the
 // answer.
-__global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ cand,
+__global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ cand, int kp,
                                                   const uint32_t* __restrict__ cand_cnt,
                                                   int64_t q_first, int k,
                                                   const uint32_t* __restrict__ perm,
@@ -1121,7 +1139,7 @@ __global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ c
     __shared__ uint64_t key[512];
     const int64_t l = blockIdx.x, i = perm ? (int64_t)perm[q_first + l] : q_first + l;
     const int t = threadIdx.x, m = (int)cand_cnt[l];
-    for (int e = t; e < 512; e += 256) key[e] = e < m ? cand[l * kCap + e] : ~0ull;
+    for (int e = t; e < 512; e += 256) key[e] = e < m ? cand[l * kp + e] : ~0ull;
     __syncthreads();
     bitonic512(key);
     for (int e = t; e < k; e += 256) {
@@ -1464,20 +1482,41 @@ hipError_t scan_i64_local(const int64_t* a, int64_t m, int64_t* out, int64_t* tm
     return hipGetLastError();
 }
 
+// Working lists of the blocks that run at a time, one per CU (as LDS allows).
+inline int64_t resident_blocks(int64_t rows) {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 0;
+    const int64_t most = ceil_div(rows, kQB);
+    return cus < 1 ? 1 : (cus < most ? cus : most);
+}
+
+struct Lists {
+    uint32_t* ticket;
+    uint64_t *work, *cand;              // [resident blocks][kQB][kCap]; [rows][kp]
+    uint32_t *cnt, *thr;
+};
+
 template <typename F>
-void launch_candidates(const char* packed, int64_t n, int steps, const typename F::Num* nrm,
-                       float f, int64_t first, int64_t rows, int kp, const RowOrder& ord,
-                       uint64_t* cand, uint32_t* ccnt, uint32_t* cthr, hipStream_t s) {
-    const dim3 g((unsigned)(ord.turn ? ord.T * (ord.G / kQB) : ceil_div(rows, kQB)));
+hipError_t launch_candidates(const char* packed, int64_t n, int steps, const typename F::Num* nrm,
+                             float f, int64_t first, int64_t rows, int kp, const RowOrder& ord,
+                             const Lists& l, hipStream_t s) {
+    const int64_t blocks = ord.turn ? ord.T * (ord.G / kQB) : ceil_div(rows, kQB);
+    const dim3 g((unsigned)resident_blocks(rows));
+    const hipError_t e = hipMemsetAsync(l.ticket, 0, sizeof(uint32_t), s);
+    if (e != hipSuccess) return e;
     // the queries' fragments stay in LDS while 8 steps of them fit beside two
     // stages (FP16: depth 128)
     if (steps <= 8)
         k_knn_candidates<F, true><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, ord,
-                                                    cand, ccnt, cthr);
+                                                    (uint32_t)blocks, l.ticket, l.work, l.cand,
+                                                    l.cnt, l.thr);
     else
         k_knn_candidates<F, false><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, ord,
-                                                     cand, ccnt, cthr);
-    k_knn_cut<<<dim3((unsigned)ceil_div(rows, 4)), 256, 0, s>>>(cand, rows, n, kp, ccnt, cthr);
+                                                     (uint32_t)blocks, l.ticket, l.work, l.cand,
+                                                     l.cnt, l.thr);
+    return hipGetLastError();
 }
 
 // The order of the rows (see above): packs the rows in their own order, assigns
@@ -1616,8 +1655,8 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     float* nrm = nullptr;
     int32_t* nrm_i = nullptr;
     char* packed = nullptr;
-    uint64_t* cand = nullptr;
-    uint32_t *ccnt = nullptr, *cthr = nullptr, *flag = nullptr;
+    Lists lists{};
+    uint32_t* flag = nullptr;
     RowStats* st = nullptr;
     hipError_t e = hipSuccess;
     RowOrder ord{};
@@ -1627,9 +1666,11 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
         held.release();
         return x;
     };
-    own.add(&cand, (int64_t)kCap * rows);
-    own.add(&ccnt, rows);
-    own.add(&cthr, rows);
+    own.add(&lists.ticket, 1);
+    own.add(&lists.work, resident_blocks(rows) * (kQB * kCap));
+    own.add(&lists.cand, rows * kp);
+    own.add(&lists.cnt, rows);
+    own.add(&lists.thr, rows);
     own.add(&packed, (int64_t)(exact ? packed_bytes<PartsI8>(n, D) : packed_bytes<PartsF16>(n, D)));
     if (exact) {
         own.add(&nrm_i, n);
@@ -1659,9 +1700,10 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
         if (e != hipSuccess) return fail(e);
         for (int64_t first = 0; first < n; first += kBatch) {
             const int64_t m = n - first < kBatch ? n - first : kBatch;
-            launch_candidates<PartsI8>(packed, n, steps, nrm_p, 0.f, first, m, kp, ord, cand,
-                                       ccnt, cthr, s);
-            k_knn_emit<<<dim3((unsigned)m), 256, 0, s>>>(cand, ccnt, first, k, ord.perm, idx, d2);
+            e = launch_candidates<PartsI8>(packed, n, steps, nrm_p, 0.f, first, m, kp, ord, lists, s);
+            if (e != hipSuccess) return fail(e);
+            k_knn_emit<<<dim3((unsigned)m), 256, 0, s>>>(lists.cand, kp, lists.cnt, first, k,
+                                                         ord.perm, idx, d2);
         }
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);
         return fail(hipStreamSynchronize(s));
@@ -1704,11 +1746,11 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     if (e != hipSuccess) return fail(e);
     for (int64_t first = 0; first < n; first += kBatch) {
         const int64_t m = n - first < kBatch ? n - first : kBatch;
-        launch_candidates<PartsF16>(packed, n, steps, nrm_p, f, first, m, kp, ord, cand, ccnt,
-                                    cthr, s);
-        k_knn_rerank<X><<<dim3((unsigned)m), 256, 0, s>>>(Xm, first, D, k, ord.perm, cand, ccnt,
-                                                          cthr, nrm, norm_max, scale, idx, d2,
-                                                          flag);
+        e = launch_candidates<PartsF16>(packed, n, steps, nrm_p, f, first, m, kp, ord, lists, s);
+        if (e != hipSuccess) return fail(e);
+        k_knn_rerank<X><<<dim3((unsigned)m), 256, 0, s>>>(Xm, first, D, k, ord.perm, lists.cand, kp,
+                                                          lists.cnt, lists.thr, nrm, norm_max,
+                                                          scale, idx, d2, flag);
     }
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     std::vector<uint32_t> hf(n);
