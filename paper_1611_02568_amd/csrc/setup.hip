@@ -15,6 +15,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -1148,7 +1149,72 @@ __global__ __launch_bounds__(256) void k_knn_emit(const uint64_t* __restrict__ c
     }
 }
 
-// Exact fallback for rows the bound could not certify: block per row,
+// Rows the bound could not certify.  The k-th distance that the re-ranking
+// found bounds the true one from above, so one FP64 pass over all rows collects
+// what is not further (k and a few), and a block sorts it.  A single such row at
+// 41,273 x 474 took 1.8 s by k passes, 1 ms by this.
+constexpr int kMissCap = 2048;     // collected per row
+constexpr int kMissRows = 1024;    // rows at a time
+
+template <typename X>
+__global__ __launch_bounds__(256) void k_miss_scan(const X* __restrict__ Xm, int64_t n, int D, int k,
+                                                   const uint32_t* __restrict__ rows,
+                                                   const double* __restrict__ d2,
+                                                   uint32_t* __restrict__ cnt,
+                                                   double* __restrict__ md,
+                                                   uint32_t* __restrict__ mj) {
+    const int64_t r = blockIdx.y, i = rows[r];
+    const double bound = d2[i * k + k - 1];
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (int64_t)gridDim.x * 256) {
+        if (j == i) continue;
+        const double d = rerank_dist(Xm + i * D, Xm + j * D, D);
+        if (d <= bound) {
+            const uint32_t at = atomicAdd(&cnt[r], 1u);
+            if (at < (uint32_t)kMissCap) {
+                md[r * kMissCap + at] = d;
+                mj[r * kMissCap + at] = (uint32_t)j;
+            }
+        }
+    }
+}
+
+// (a row with more than kMissCap is left as it is)
+__global__ __launch_bounds__(256) void k_miss_sort(const uint32_t* __restrict__ rows, int k,
+                                                   const uint32_t* __restrict__ cnt,
+                                                   const double* __restrict__ md,
+                                                   const uint32_t* __restrict__ mj,
+                                                   int32_t* __restrict__ idx,
+                                                   double* __restrict__ d2) {
+    __shared__ double dv[kMissCap];
+    __shared__ uint32_t jv[kMissCap];
+    const int64_t r = blockIdx.x, i = rows[r];
+    const int t = threadIdx.x, m = cnt[r] <= (uint32_t)kMissCap ? (int)cnt[r] : 0;
+    if (m < k) return;
+    for (int e = t; e < kMissCap; e += 256) {
+        dv[e] = e < m ? md[r * kMissCap + e] : INFINITY;
+        jv[e] = e < m ? mj[r * kMissCap + e] : 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    for (int kk = 2; kk <= kMissCap; kk <<= 1)
+        for (int j = kk >> 1; j > 0; j >>= 1) {
+            for (int x = t; x < kMissCap / 2; x += 256) {
+                const int a = ((x & ~(j - 1)) << 1) | (x & (j - 1)), b = a | j;
+                const double da = dv[a], db = dv[b];
+                const uint32_t ja = jv[a], jb = jv[b];
+                if ((da > db || (da == db && ja > jb)) == ((a & kk) == 0)) {
+                    dv[a] = db; dv[b] = da;
+                    jv[a] = jb; jv[b] = ja;
+                }
+            }
+            __syncthreads();
+        }
+    for (int e = t; e < k; e += 256) {
+        idx[i * k + e] = (int32_t)jv[e];
+        d2[i * k + e] = dv[e];
+    }
+}
+
+// Rows with more than kMissCap others at the bound (ties): block per row,
 // FP64 over all n, keeps a sorted top-k in LDS by repeated block passes.
 template <typename X>
 __global__ __launch_bounds__(256) void k_knn_exact_row(const X* __restrict__ Xm, int64_t n, int D,
@@ -1761,13 +1827,47 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     for (int64_t i = 0; i < n; i++)
         if (hf[i]) miss.push_back((uint32_t)i);
     if (!miss.empty()) {
-        // exact FP64 fallback for rows the bound did not certify
         if ((e = hipMemcpyAsync(flag, miss.data(), sizeof(uint32_t) * miss.size(),
                                 hipMemcpyHostToDevice, s)) != hipSuccess)
             return fail(e);
-        k_knn_exact_row<X><<<dim3((unsigned)miss.size()), 256, 0, s>>>(Xm, n, D, k, flag, idx, d2);
-        if ((e = hipGetLastError()) != hipSuccess) return fail(e);
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
+        uint32_t *cnt = nullptr, *mj = nullptr;
+        double* md = nullptr;
+        const int64_t at_once = std::min((int64_t)miss.size(), (int64_t)kMissRows);
+        Arena found;
+        found.add(&cnt, (int64_t)miss.size());
+        found.add(&md, at_once * kMissCap);
+        found.add(&mj, at_once * kMissCap);
+        if ((e = found.make()) != hipSuccess) return fail(e);
+        auto stop = [&](hipError_t x) {
+            found.release();
+            return fail(x);
+        };
+        if ((e = hipMemsetAsync(cnt, 0, sizeof(uint32_t) * miss.size(), s)) != hipSuccess)
+            return stop(e);
+        const int64_t chunks = std::min(ceil_div(n, 256), (int64_t)1024);
+        for (int64_t r = 0; r < (int64_t)miss.size(); r += kMissRows) {
+            const int64_t m = std::min((int64_t)miss.size() - r, (int64_t)kMissRows);
+            k_miss_scan<X><<<dim3((unsigned)chunks, (unsigned)m), 256, 0, s>>>(
+                Xm, n, D, k, flag + r, d2, cnt + r, md, mj);
+            k_miss_sort<<<dim3((unsigned)m), 256, 0, s>>>(flag + r, k, cnt + r, md, mj, idx, d2);
+        }
+        std::vector<uint32_t> hc(miss.size());
+        if ((e = hipMemcpyAsync(hc.data(), cnt, sizeof(uint32_t) * hc.size(), hipMemcpyDeviceToHost,
+                                s)) != hipSuccess)
+            return stop(e);
+        if ((e = hipStreamSynchronize(s)) != hipSuccess) return stop(e);
+        size_t left = 0;
+        for (size_t r = 0; r < miss.size(); r++)
+            if (hc[r] > (uint32_t)kMissCap) miss[left++] = miss[r];
+        if (left > 0) {
+            if ((e = hipMemcpyAsync(flag, miss.data(), sizeof(uint32_t) * left,
+                                    hipMemcpyHostToDevice, s)) != hipSuccess)
+                return stop(e);
+            k_knn_exact_row<X><<<dim3((unsigned)left), 256, 0, s>>>(Xm, n, D, k, flag, idx, d2);
+            if ((e = hipGetLastError()) != hipSuccess) return stop(e);
+            if ((e = hipStreamSynchronize(s)) != hipSuccess) return stop(e);
+        }
+        found.release();
     }
     return fail(hipSuccess);
 }
