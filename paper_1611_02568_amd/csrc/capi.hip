@@ -223,8 +223,9 @@ void free_ctx(pixelsne_ctx* c) {
     // the second stream's work is joined into the context's stream, except
     // after an error between the fork and the join
     if (c->side) (void)hipStreamSynchronize(c->side);
-    for (hipGraphExec_t& g : c->gexec)
-        if (g) (void)hipGraphExecDestroy(g);
+    for (auto& parity : c->gexec)
+        for (hipGraphExec_t& g : parity)
+            if (g) (void)hipGraphExecDestroy(g);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
@@ -234,8 +235,8 @@ void free_ctx(pixelsne_ctx* c) {
     delete c;
 }
 
-// The iteration's passes captured once per state-buffer parity on a private
-// stream (nothing runs during the capture) and replayed on the caller's stream.
+// The iteration's passes captured once per state-buffer parity and walk on a
+// private stream (nothing runs during the capture) and replayed on the caller's stream.
 hipError_t capture_iteration(pixelsne_ctx* c, hipGraphExec_t* out) {
     hipError_t e = hipSuccess;
     if (!c->cap_stream) e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
@@ -257,7 +258,7 @@ hipError_t step_one(pixelsne_ctx* c) {
     hipError_t e = hipSuccess;
     bool done = false;
     if (c->prm.graphs && !c->graph_failed) {
-        hipGraphExec_t& ge = c->gexec[c->parity];
+        hipGraphExec_t& ge = c->gexec[c->parity][traverse_share(c) != 0];
         if (!ge && capture_iteration(c, &ge) != hipSuccess) {
             // capture unavailable: launch the kernels directly from now on
             (void)hipGetLastError();
@@ -271,6 +272,7 @@ hipError_t step_one(pixelsne_ctx* c) {
         }
     }
     if (!done) e = run_iteration_passes(c);
+    if (e == hipSuccess) c->t++;
     if (e == hipSuccess) e = run_scheduled_reorder(c);
     return e;
 }
@@ -505,8 +507,10 @@ psne_status pixelsne_step_profiled(pixelsne_ctx* c, int32_t n_iter, pixelsne_pas
     size_t made = 0;
     for (; made < ev.size() && e == hipSuccess; made++) e = hipEventCreate(&ev[made]);
     if (e != hipSuccess) made--;
-    for (int32_t it = 0; it < n_iter && e == hipSuccess; it++)
+    for (int32_t it = 0; it < n_iter && e == hipSuccess; it++) {
         e = run_iteration_timed(c, &ev[(size_t)kEv * it]);
+        c->t++;
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     double* acc[8] = {&out->snap_ms, &out->sort_ms, &out->tree_ms, &out->traverse_ms,
                       &out->zsum_ms, &out->attract_ms, &out->finalize_ms, &out->reorder_ms};
@@ -593,7 +597,7 @@ psne_status pixelsne_set_state(pixelsne_ctx* c, const void* z, const void* u, co
     h.zmin[0] = h.zmin[1] = 0.0;
     h.scale[0] = h.scale[1] = 1.0;
     h.uscale[0] = h.uscale[1] = 1.0;
-    h.t = iteration;
+    h.t = c->t = iteration;
     h.nonfinite = 0;
     reset_fork_tuner(h, c->prm.attract_fork);
     e = hipMemcpyAsync(c->sc, &h, sizeof(h), hipMemcpyHostToDevice, c->stream);

@@ -96,7 +96,8 @@ struct pixelsne_ctx {
     void* vch = nullptr;                     // FP64: [nnz] values
 
     // one iteration captured as a HIP graph, one per state-buffer parity
-    // (renumbering swaps the state buffers with their spares)
+    // (renumbering swaps the state buffers with their spares) and walk (alone
+    // or shared)
     hipStream_t cap_stream = nullptr;
 
     // The attraction's row sums (A, internal order, state type [n][2]) run on
@@ -110,8 +111,9 @@ struct pixelsne_ctx {
     hipEvent_t ev_fork = nullptr, ev_cells = nullptr, ev_join = nullptr;
     int64_t side_blocks = 0;
     int64_t help_blocks = 0;
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};
+    hipGraphExec_t gexec[2][2] = {};
     int32_t parity = 0;
+    int32_t t = 0;                           // iterations enqueued: DevScalars::t once they ran
     bool graph_failed = false;
 
     std::vector<void*> allocs;
@@ -177,6 +179,7 @@ hipError_t sort_pairs32(uint32_t* const key[2], uint32_t* const idx[2], int64_t 
 hipError_t run_tree(pixelsne_ctx* c);
 hipError_t run_traverse(pixelsne_ctx* c, uint32_t* visits, uint32_t* used, double* Zi);
 hipError_t run_zsum(pixelsne_ctx* c);
+int traverse_share(const pixelsne_ctx* c);
 // mode 0: gradient step; mode 1: write A and B only (no update)
 hipError_t run_attract(pixelsne_ctx* c, double alpha, void* A, void* B);
 hipError_t run_finalize(pixelsne_ctx* c, int advance);

@@ -1,8 +1,9 @@
 """The Barnes-Hut walk at the point counts where its work split changes.
 
 Up to 40,000 points eight wavefronts share the walk of 64 points, up to
-400,000 four do, above that one walks alone; theta = 0 opens every cell, which
-overflows the shared walk's lists.  The octree's walk is shared by eight at
+400,000 four do, above that one walks alone; FP32 walks alone at every size
+while the early exaggeration lasts (iteration 0 here); theta = 0 opens every
+cell, which overflows the shared walk's lists.  The octree's walk is shared by eight at
 every size.  Against the CPU oracle: visits exact; R and Z within the bars of
 the gradient parity tests.
 """
@@ -36,15 +37,31 @@ def test_walk_at_the_split_points(n, r, theta, prec):
     s = np.array([0.05, 0.06])
     P = _ring_P(n)
     ctx = pixelsne.Context.from_P(*P, screen=r, precision=prec, theta=theta)
-    ctx.set_state(torch.as_tensor(z), s)
-    g = ctx.gradient(1.0)
     og = oracle.gradient(z.astype(np.float64), r, s, P, theta=theta, predicate=0 if prec else 1)
-    assert np.array_equal(g["visits"].cpu().numpy(), og["visits"])
-    R = g["R"].double().cpu().numpy()
-    assert np.linalg.norm(R - og["R"]) <= TOL_R[prec] * np.linalg.norm(og["R"])
-    assert abs(g["Z"] - og["Z"]) <= TOL_Z[prec] * og["Z"]
-    again = ctx.gradient(1.0)
-    assert torch.equal(g["R"], again["R"]) and torch.equal(g["Zi"], again["Zi"])
+    for iteration in (0, 250):
+        ctx.set_state(torch.as_tensor(z), s, iteration=iteration)
+        g = ctx.gradient(1.0)
+        assert np.array_equal(g["visits"].cpu().numpy(), og["visits"])
+        R = g["R"].double().cpu().numpy()
+        assert np.linalg.norm(R - og["R"]) <= TOL_R[prec] * np.linalg.norm(og["R"])
+        assert abs(g["Z"] - og["Z"]) <= TOL_Z[prec] * og["Z"]
+        again = ctx.gradient(1.0)
+        assert torch.equal(g["R"], again["R"]) and torch.equal(g["Zi"], again["Zi"])
+
+
+@pytest.mark.parametrize("n", [65, 4001, 50003])
+def test_walk_changes_where_the_exaggeration_ends(n):
+    from paper_1611_02568_amd import pixelsne
+    P = _ring_P(n)
+    out = []
+    for graphs in (0, 1):
+        ctx = pixelsne.Context.from_P(*P, screen=256, precision=0, seed=3, exag_iters=3,
+                                      graphs=graphs)
+        ctx.step(2)
+        ctx.step(4)                      # two walks in one call
+        out.append(ctx.get_Y())
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(out[0], out[1])
 
 
 @pytest.mark.parametrize("n,r,theta", [(3, 2, 0.5), (65, 16, 0.5), (4001, 64, 0.0),
