@@ -1547,7 +1547,7 @@ __global__ __launch_bounds__(kBlock) void k_cast_val(const double* __restrict__ 
 // copies of its 256 lanes and takes every fourth tile: n / 256 blocks of four
 // wavefronts left a SIMD of the chip one wavefront at 60,000 points.  FP32
 // issue bounds it: about 11 slots per pair, the reciprocal four of them.
-// 60,000 points: 0.6 ms where every ordered pair took 1.77.
+// 60,000 points: 0.5 ms where every ordered pair took 1.77.
 constexpr int kKlCopies = 4;
 
 template <typename T>
