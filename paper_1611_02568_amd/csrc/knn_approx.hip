@@ -158,7 +158,8 @@ __global__ __launch_bounds__(kBlock) void k_rp_scatter(
 // k-th entry, and the rest are merged into the list by groups of 64 with their
 // distance in FP64, terms in order of d.  The resulting list, the best k of the
 // old list and the candidates by (d^2, index), does not depend on the order of
-// insertion.
+// insertion.  Distances are compared as keys (dist_key): of a row that holds NaN
+// they come after all others, by index, and enter a list only while it is short.
 //
 // A round of exploring at 100,000 x 100 (FP32, k = 90: 8,100 candidates per
 // point, 2,700 distinct) is bound by the latency of its row gathers, so what
@@ -178,13 +179,13 @@ template <typename X> struct Near { using type = X; };
 template <> struct Near<uint8_t> { using type = double; };
 
 struct ListLds {
-    double ld[kMaxK];
+    uint64_t ld[kMaxK];
     int32_t lj[kMaxK];
-    double ld2[kMaxK];                       // the merged list before it is copied back
+    uint64_t ld2[kMaxK];                     // the merged list before it is copied back
     int32_t lj2[kMaxK];
     int32_t gj[kBlock + kFlush];             // candidates that may enter
-    double gd[kBlock + kFlush];
-    double sd[kWave];                        // a group of them, sorted
+    uint64_t gd[kBlock + kFlush];
+    uint64_t sd[kWave];                      // a group of them, sorted
     int32_t sj[kWave];
     int32_t oj[kMaxK], om[kMaxK];            // exploring: the old list and its entries' lengths
     int32_t pend[kBlock + kPer * kBlock];
@@ -192,7 +193,7 @@ struct ListLds {
 };
 
 // number of entries of a sorted list (ascending (d, j)) below (d, j)
-__device__ __forceinline__ int rank_in(const double* ld, const int32_t* lj, int m, double d,
+__device__ __forceinline__ int rank_in(const uint64_t* ld, const int32_t* lj, int m, uint64_t d,
                                        int32_t j) {
     int lo = 0, hi = m;
     while (lo < hi) {
@@ -353,18 +354,18 @@ __device__ __forceinline__ void merge(const X* __restrict__ Xm, int32_t D, int64
                                       ListLds& s, int ng) {
     const int t = threadIdx.x, lane = lane_id();
     for (int q = t; q < ng; q += kBlock)
-        s.gd[q] = row_sqdist(Xm + i * D, Xm + (int64_t)s.gj[q] * D, D);
+        s.gd[q] = dist_key(row_sqdist(Xm + i * D, Xm + (int64_t)s.gj[q] * D, D));
     __syncthreads();
     for (int g0 = 0; g0 < ng; g0 += kWave) {
         const int m0 = s.m;
         if (t < kWave) {
-            double d = g0 + lane < ng ? s.gd[g0 + lane] : __builtin_inf();
+            uint64_t d = g0 + lane < ng ? s.gd[g0 + lane] : ~0ull;
             int32_t j = g0 + lane < ng ? s.gj[g0 + lane] : 0x7FFFFFFF;
             // sort the group, drop repeats (equal pairs: the same index has the
             // same distance), and place every entry of list and group by its
             // rank in the other; the first k form the new list
             wave_sort(d, j);
-            const double pd = __shfl_up(d, 1, kWave);
+            const uint64_t pd = __shfl_up(d, 1, kWave);
             const int32_t pj = __shfl_up(j, 1, kWave);
             bool valid = j != 0x7FFFFFFF && !(lane > 0 && pd == d && pj == j);
             const int r_list = valid ? rank_in(s.ld, s.lj, m0, d, j) : 0;
@@ -409,7 +410,7 @@ __device__ __forceinline__ void process(const X* __restrict__ Xm, int32_t D, int
     bool may = cand >= 0;
     if (s.m == k) {
         const auto near = near_sqdist(Xm, D, i, cand);
-        may = may && !beyond(near, D, s.ld[k - 1]);
+        may = may && !beyond(near, D, key_dist(s.ld[k - 1]));
     }
     const uint64_t mb = ballot64(may);
     int base = 0;
@@ -437,8 +438,8 @@ template <typename X, int MODE>
 __global__ __launch_bounds__(kBlock, 5) void k_lists(
     const X* __restrict__ Xm, int32_t D, int64_t b0, int64_t b1, int32_t k, int bits,
     int words, const uint32_t* __restrict__ perm, const uint32_t* __restrict__ sa,
-    const uint32_t* __restrict__ sb, const double* __restrict__ ld,
-    const int32_t* __restrict__ lj, const int32_t* __restrict__ lm, double* __restrict__ nd,
+    const uint32_t* __restrict__ sb, const uint64_t* __restrict__ ld,
+    const int32_t* __restrict__ lj, const int32_t* __restrict__ lm, uint64_t* __restrict__ nd,
     int32_t* __restrict__ nj, int32_t* __restrict__ nm) {
     __shared__ ListLds s;
     extern __shared__ __attribute__((aligned(16))) int32_t set[];
@@ -520,7 +521,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_lists(
         if (t == 0) s.npend = np;
         __syncthreads();
     }
-    double* od = MODE == 0 ? const_cast<double*>(ld) : nd;
+    uint64_t* od = MODE == 0 ? const_cast<uint64_t*>(ld) : nd;
     int32_t* oj = MODE == 0 ? const_cast<int32_t*>(lj) : nj;
     int32_t* om = MODE == 0 ? const_cast<int32_t*>(lm) : nm;
     if (t < s.m) {
@@ -547,8 +548,8 @@ constexpr int64_t kRun = (int64_t)1 << 22;
 
 template <typename X, int MODE>
 hipError_t lists(const X* Xm, int32_t D, int64_t n, int32_t k, int64_t candidates,
-                 const uint32_t* perm, const uint32_t* sa, const uint32_t* sb, const double* ld,
-                 const int32_t* lj, const int32_t* lm, double* nd, int32_t* nj, int32_t* nm,
+                 const uint32_t* perm, const uint32_t* sa, const uint32_t* sb, const uint64_t* ld,
+                 const int32_t* lj, const int32_t* lm, uint64_t* nd, int32_t* nj, int32_t* nm,
                  hipStream_t s) {
     int bits = set_bits(candidates);
     int words = 1 << bits;
@@ -565,7 +566,7 @@ hipError_t lists(const X* Xm, int32_t D, int64_t n, int32_t k, int64_t candidate
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(kBlock) void k_lists_out(const double* __restrict__ ld,
+__global__ __launch_bounds__(kBlock) void k_lists_out(const uint64_t* __restrict__ ld,
                                                       const int32_t* __restrict__ lj,
                                                       const int32_t* __restrict__ lm, int64_t n,
                                                       int32_t k, int32_t* __restrict__ idx,
@@ -576,7 +577,7 @@ __global__ __launch_bounds__(kBlock) void k_lists_out(const double* __restrict__
     const int64_t i = e / k;
     if (e % k == 0 && lm[i] < k) atomicAdd(short_rows, 1u);
     idx[e] = lj[e];
-    d2[e] = ld[e];
+    d2[e] = key_dist(ld[e]);
 }
 
 template <typename X>
@@ -586,7 +587,7 @@ hipError_t knn_approx_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_
     uint32_t *perm[2] = {nullptr, nullptr}, *sa[2] = {nullptr, nullptr},
              *sb[2] = {nullptr, nullptr}, *flag = nullptr;
     int64_t *side = nullptr, *ones = nullptr, *tmp = nullptr;
-    double* ld[2] = {nullptr, nullptr};
+    uint64_t* ld[2] = {nullptr, nullptr};
     int32_t* lj[2] = {nullptr, nullptr};
     int32_t* lm[2] = {nullptr, nullptr};
     hipError_t e = hipSuccess;
