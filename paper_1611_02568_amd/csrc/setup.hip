@@ -2008,12 +2008,19 @@ hipError_t knn(const void* X, int64_t n, int32_t D, int32_t x_dtype, int32_t k, 
 
 hipError_t perplexity(const double* d2, int64_t n, int32_t k, double u, double* P, double* beta,
                       hipStream_t s) {
-    const dim3 g((unsigned)ceil_div(n, 4));
     const double target = log(u);
-    if (k <= 64) k_perplexity<1><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
-    else if (k <= 128) k_perplexity<2><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
-    else if (k <= 256) k_perplexity<4><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
-    else k_perplexity<0><<<g, 256, 0, s>>>(d2, n, k, target, 1e-5, 200, P, beta);
+    // a grid holds fewer than 2^32 threads, 64 of them to a row
+    constexpr int64_t kRun = (int64_t)1 << 22;
+    for (int64_t r0 = 0; r0 < n; r0 += kRun) {
+        const int64_t m = n - r0 < kRun ? n - r0 : kRun;
+        const dim3 g((unsigned)ceil_div(m, 4));
+        const double* d = d2 + r0 * k;
+        double *p = P + r0 * k, *b = beta ? beta + r0 : nullptr;
+        if (k <= 64) k_perplexity<1><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
+        else if (k <= 128) k_perplexity<2><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
+        else if (k <= 256) k_perplexity<4><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
+        else k_perplexity<0><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
+    }
     return hipGetLastError();
 }
 
