@@ -1262,38 +1262,47 @@ __global__ __launch_bounds__(256) void k_knn_exact_row(const X* __restrict__ Xm,
 }
 
 // ---------------------------------------------------------------------------
-// perplexity calibration, one wavefront per row (FP64)
+// perplexity calibration (FP64)
 // ---------------------------------------------------------------------------
-// Lane l holds the row's entries l, l + 64, ...: in registers up to 64 * HELD
-// entries, read again for every evaluation beyond (HELD = 0).  Bound by the
-// FP64 exponentials, about 20 evaluations of k of them per row; a thread per
-// row also read and wrote its row, 8 k bytes from its neighbour's, at every
-// evaluation.  70,000 rows of 150: 1.1 ms where that took 4.8.
-template <int HELD>
+// W lanes (a power of two) share a row, lane l of them holds its entries l, l + W,
+// ...: up to HELD in registers, and for longer rows all are read again for every
+// evaluation (HELD = 0).  Bound by the FP64 exponentials, about 20 evaluations of
+// k of them per row, so with four entries a lane W is the smallest that holds the
+// row.  100,000 rows of 3, 15, 30, 60, 90 and 150: 29, 84, 140, 260, 430 and
+// 810 us; with a wavefront per row whatever its length 156, 545, 556, 570, 686 and
+// 817; with a thread per row, which read and wrote its row, 8 k bytes from its
+// neighbour's, at every evaluation, 34, 273, 664, 1,259, 2,464 and 3,718.
+template <int W, int HELD>
 __global__ __launch_bounds__(256) void k_perplexity(const double* __restrict__ d2, int64_t n,
                                                     int k, double target, double tol,
                                                     int max_iter, double* __restrict__ P,
                                                     double* __restrict__ beta_out) {
-    const int lane = lane_id();
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & (W - 1);
+    const int64_t i = (int64_t)blockIdx.x * (256 / W) + threadIdx.x / W;
     if (i >= n) return;
     const double* d = d2 + i * k;
     double* p = P + i * k;
     constexpr int kH = HELD > 0 ? HELD : 1;
+    // over the lanes of the row, which leave the loop together
+    auto row_sum = [](double v) {
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, W);
+        return v;
+    };
     double dh[kH], eh[kH];
     double dmin = INFINITY;
     if constexpr (HELD > 0) {
 #pragma unroll
         for (int q = 0; q < HELD; q++) {
-            const int j = lane + q * kWave;
+            const int j = lane + q * W;
             dh[q] = j < k ? d[j] : INFINITY;
             dmin = fmin(dmin, dh[q]);
         }
     } else {
-        for (int j = lane; j < k; j += kWave) dmin = fmin(dmin, d[j]);
+        for (int j = lane; j < k; j += W) dmin = fmin(dmin, d[j]);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dmin = fmin(dmin, __shfl_xor(dmin, o, kWave));
+    for (int o = W / 2; o > 0; o >>= 1) dmin = fmin(dmin, __shfl_xor(dmin, o, W));
     double b = 1.0, lo = 0.0, hi = 0.0, S = 0.0;
     bool have_lo = false, have_hi = false;
     for (int it = 0; it < max_iter; it++) {
@@ -1303,7 +1312,7 @@ __global__ __launch_bounds__(256) void k_perplexity(const double* __restrict__ d
 #pragma unroll
             for (int q = 0; q < HELD; q++) {
                 eh[q] = 0.0;
-                if (lane + q * kWave < k) {
+                if (lane + q * W < k) {
                     const double dj = dh[q] - dmin;
                     eh[q] = exp(-b * dj);
                     S += eh[q];
@@ -1311,15 +1320,15 @@ __global__ __launch_bounds__(256) void k_perplexity(const double* __restrict__ d
                 }
             }
         } else {
-            for (int j = lane; j < k; j += kWave) {
+            for (int j = lane; j < k; j += W) {
                 const double dj = d[j] - dmin;
                 const double e = exp(-b * dj);
                 S += e;
                 SD += dj * e;
             }
         }
-        S = wave_sum(S);
-        SD = wave_sum(SD);
+        S = row_sum(S);
+        SD = row_sum(SD);
         const double H = log(S) + b * SD / S;
         if (fabs(H - target) < tol || it == max_iter - 1) break;
         if (H > target) {
@@ -1333,9 +1342,9 @@ __global__ __launch_bounds__(256) void k_perplexity(const double* __restrict__ d
     if constexpr (HELD > 0) {
 #pragma unroll
         for (int q = 0; q < HELD; q++)
-            if (lane + q * kWave < k) p[lane + q * kWave] = eh[q] / S;
+            if (lane + q * W < k) p[lane + q * W] = eh[q] / S;
     } else {
-        for (int j = lane; j < k; j += kWave) p[j] = exp(-b * (d[j] - dmin)) / S;
+        for (int j = lane; j < k; j += W) p[j] = exp(-b * (d[j] - dmin)) / S;
     }
     if (beta_out && lane == 0) beta_out[i] = b;
 }
@@ -2009,17 +2018,26 @@ hipError_t knn(const void* X, int64_t n, int32_t D, int32_t x_dtype, int32_t k, 
 hipError_t perplexity(const double* d2, int64_t n, int32_t k, double u, double* P, double* beta,
                       hipStream_t s) {
     const double target = log(u);
-    // a grid holds fewer than 2^32 threads, 64 of them to a row
+    // a grid holds fewer than 2^32 threads, up to 64 of them to a row
     constexpr int64_t kRun = (int64_t)1 << 22;
     for (int64_t r0 = 0; r0 < n; r0 += kRun) {
         const int64_t m = n - r0 < kRun ? n - r0 : kRun;
-        const dim3 g((unsigned)ceil_div(m, 4));
         const double* d = d2 + r0 * k;
         double *p = P + r0 * k, *b = beta ? beta + r0 : nullptr;
-        if (k <= 64) k_perplexity<1><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
-        else if (k <= 128) k_perplexity<2><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
-        else if (k <= 256) k_perplexity<4><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
-        else k_perplexity<0><<<g, 256, 0, s>>>(d, m, k, target, 1e-5, 200, p, b);
+        auto run = [&](auto w, auto held) {
+            constexpr int W = decltype(w)::value, HELD = decltype(held)::value;
+            k_perplexity<W, HELD><<<dim3((unsigned)ceil_div(m, 256 / W)), 256, 0, s>>>(
+                d, m, k, target, 1e-5, 200, p, b);
+        };
+        auto by4 = [&](auto w) { run(w, std::integral_constant<int, 4>()); };
+        if (k <= 4) by4(std::integral_constant<int, 1>());
+        else if (k <= 8) by4(std::integral_constant<int, 2>());
+        else if (k <= 16) by4(std::integral_constant<int, 4>());
+        else if (k <= 32) by4(std::integral_constant<int, 8>());
+        else if (k <= 64) by4(std::integral_constant<int, 16>());
+        else if (k <= 128) by4(std::integral_constant<int, 32>());
+        else if (k <= 256) by4(std::integral_constant<int, 64>());
+        else run(std::integral_constant<int, 64>(), std::integral_constant<int, 0>());
     }
     return hipGetLastError();
 }
