@@ -124,12 +124,13 @@ __global__ __launch_bounds__(kB) void k_knn2d(const T* __restrict__ zs,
                                               const uint32_t* __restrict__ us,
                                               const T* __restrict__ box,
                                               const T* __restrict__ group,
-                                              const DevScalars* __restrict__ sc, int64_t n,
-                                              int32_t* __restrict__ out) {
+                                              const DevScalars* __restrict__ sc, int64_t first,
+                                              int64_t n, int32_t* __restrict__ out) {
     __shared__ double pend_d[kB / kWave][kWave];
     __shared__ int32_t pend_j[kB / kWave][kWave];
     const int lane = lane_id(), w = threadIdx.x >> 6;
-    const int64_t s = (int64_t)blockIdx.x * (kB / kWave) + __builtin_amdgcn_readfirstlane(w);
+    const int64_t s =
+        first + (int64_t)blockIdx.x * (kB / kWave) + __builtin_amdgcn_readfirstlane(w);
     if (s >= n) return;                         // no barrier below
     const double s0 = sc->s[0], s1 = sc->s[1];
     const double b1 = s0 * s0, b2 = s1 * s1;
@@ -267,8 +268,11 @@ hipError_t knn2d_typed(const pixelsne_ctx* c, int32_t* out) {
     k_near_tiles<T><<<g, kB, 0, c->stream>>>(idx[sorted], (const T*)c->zh, c->sc, c->orig, n, c->r,
                                              zs, us, box);
     k_near_groups<T><<<dim3((unsigned)groups), kWave, 0, c->stream>>>(box, tiles, group);
-    k_knn2d<T><<<dim3((unsigned)ceil_div(n, kB / kWave)), kB, 0, c->stream>>>(zs, us, box, group,
-                                                                            c->sc, n, out);
+    // a grid holds fewer than 2^32 threads, 64 of them to a point
+    constexpr int64_t kRun = (int64_t)1 << 20;
+    for (int64_t s0 = 0; s0 < n; s0 += kRun)
+        k_knn2d<T><<<dim3((unsigned)ceil_div(n - s0 < kRun ? n - s0 : kRun, kB / kWave)), kB, 0,
+                     c->stream>>>(zs, us, box, group, c->sc, s0, n, out);
     return hipGetLastError();
 }
 
