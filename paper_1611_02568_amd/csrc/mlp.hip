@@ -568,6 +568,9 @@ __device__ __forceinline__ void column_sums(const float* __restrict__ a, int row
 // take sixteen wavefronts, as in the small layers.
 constexpr int kGradT = 1024, kGradSlices = kGradT / 256;   // row slices of a block of sums
 constexpr int kSliceBlocks = kSlices / kGradSlices;
+// blocks of a launch: a grid holds fewer than 2^32 threads, which networks of a
+// billion weights would pass
+constexpr int64_t kGradBlocks = 1 << 15;
 struct GradArgs {
     const uint16_t *h1q, *da2q, *xq, *da1q, *h2b;
     const float *da1, *da2, *dout;
@@ -577,6 +580,7 @@ struct GradArgs {
     int slice_steps, slices;                // split-K
     int g2, g1;                             // blocks of dW2 and dW1
     int c1, c2;                             // groups of 64 columns of the sums (the head's last)
+    int first;                              // the launch's first block
 };
 
 __global__ __launch_bounds__(kGradT) void k_grads(GradArgs g) {
@@ -587,7 +591,7 @@ __global__ __launch_bounds__(kGradT) void k_grads(GradArgs g) {
         __device__ Room() {}
     };
     __shared__ __attribute__((aligned(16))) Room room;
-    int b = blockIdx.x;
+    int b = g.first + (int)blockIdx.x;
     if (b < g.g2 + g.g1) {
         const bool two = b < g.g2;
         if (!two) b -= g.g2;
@@ -913,7 +917,11 @@ hipError_t grad_batch(pixelsne_mlp* m, int Bn, double* lossp, FinishArgs& fin) {
     g.g1 = (int)g1;
     g.c1 = (int)t1;
     g.c2 = (int)t2;
-    k_grads<<<dim3((unsigned)total), kGradT, 0, m->stream>>>(g);
+    for (int64_t b = 0; b < total; b += kGradBlocks) {
+        g.first = (int)b;
+        k_grads<<<dim3((unsigned)(total - b < kGradBlocks ? total - b : kGradBlocks)), kGradT, 0,
+                  m->stream>>>(g);
+    }
     fin = finish_args(m);
     fin.pw2 = g.pw2;
     fin.pw1 = g.pw1;
