@@ -400,6 +400,9 @@ psne_status pixelsne_neighborhood_precision(const pixelsne_ctx* c, const int32_t
  *   X device [n][D] of x_dtype; idx device int32 [n][k], d2 device float64
  *   [n][k] ascending (exact distances recomputed in FP64).  Requires
  *   1 <= k <= min(n - 1, 256).  Synchronises (returns after completion).
+ *   Allocates scratch for the call: 16 bytes a row and, with enough memory
+ *   free, a packed copy of X (4 bytes an element, 1 for bytes) and lists;
+ *   with less it takes the rows in runs.
  */
 psne_status pixelsne_knn(const void* X, int64_t n, int32_t D, int32_t x_dtype, int32_t k,
                          int32_t* idx, double* d2, void* stream);

@@ -146,6 +146,12 @@ public:
         (void)hipFree(base_);
         base_ = nullptr;
     }
+    // empty again, for another make()
+    void reset() {
+        release();
+        parts_.clear();
+        bytes_ = 0;
+    }
     Arena() = default;
     Arena(const Arena&) = delete;
     Arena& operator=(const Arena&) = delete;

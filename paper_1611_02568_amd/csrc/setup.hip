@@ -765,9 +765,14 @@ struct RowOrder {
 typedef __attribute__((address_space(1))) const void GlobalPtr;
 typedef __attribute__((address_space(3))) void LdsPtr;
 
+//
+// queries: the packed rows q_first .. of the batch; packed: the candidates, rows
+// c_first .. c_first + cols (all of them, or as many as there is room for).
 template <typename F, bool HOLD>
-__global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__ packed,
-                                                        int64_t n, int steps,
+__global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__ queries,
+                                                        const char* __restrict__ packed,
+                                                        int64_t n, int64_t c_first, int64_t cols,
+                                                        int steps,
                                                         const typename F::Num* __restrict__ nrm,
                                                         float f, int64_t q_first, int kp,
                                                         RowOrder ord, uint32_t blocks,
@@ -810,7 +815,8 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
         const int64_t q0 = q_first + block * kQB;
         if (q0 >= n) continue;
         const int nst = steps / F::kSteps;
-        const int64_t tiles = (n + kCB - 1) / kCB;
+        const int64_t tiles = (cols + kCB - 1) / kCB;
+        const int64_t q32 = (q0 - q_first) / 32;           // the queries' first fragment
         if (t < kQB) {
             cnt[t] = 0;
             thr[t] = q0 + t < n ? kNoThr : 0u;
@@ -823,7 +829,8 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
         constexpr int kPer = F::kSteps * F::kParts;
         static_assert(kPer == 4 && kStageC % 8 == 0 && kStageQ % 8 == 0, "whole rounds of loads");
         const int64_t frag_row = (int64_t)steps * F::kParts * kFrag;   // bytes of 32 rows
-        const char* const mine = packed + (w >> 2) * frag_row + (w & 3) * kFrag + lane * 16;
+        const int64_t piece = (w >> 2) * frag_row + (w & 3) * kFrag + lane * 16;
+        const char* const mine = packed + piece;
         auto to_lds = [&](const char* src, char* dst) {
             __builtin_amdgcn_global_load_lds((GlobalPtr*)src, (LdsPtr*)dst, 16, 0, 0);
         };
@@ -833,7 +840,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
             for (int y = 0; y < kStageC / 8; y++)
                 to_lds(c + y * (2 * frag_row), C[buf] + (w + 8 * y) * kFrag);
             if constexpr (!HOLD) {
-                const char* q = mine + (q0 / 32) * frag_row + s * (kPer * kFrag);
+                const char* q = queries + piece + q32 * frag_row + s * (kPer * kFrag);
 #pragma unroll
                 for (int y = 0; y < kStageQ / 8; y++)
                     to_lds(q + y * (2 * frag_row), Q + (buf * kStageQ + w + 8 * y) * kFrag);
@@ -871,7 +878,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
             // all steps of the queries, by [32 rows][8 steps][part]
             for (int x = w; x < kQF * steps * F::kParts; x += 8) {
                 const int rb = x / (steps * F::kParts), rest = x % (steps * F::kParts);
-                to_lds(packed + (q0 / 32 + rb) * frag_row + rest * kFrag + lane * 16,
+                to_lds(queries + (q32 + rb) * frag_row + rest * kFrag + lane * 16,
                        Q + (rb * 8 * F::kParts + rest) * kFrag);
             }
         }
@@ -905,8 +912,8 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
 #pragma unroll
                     for (int v = 0; v < 16; v++) acc[a][b][v] = 0;
             const int64_t c0 = tile * kCB + 64 * wc + (lane & 31);
-            const Num nc0 = c0 < n ? nrm[c0] : F::far();
-            const Num nc1 = c0 + 32 < n ? nrm[c0 + 32] : F::far();
+            const Num nc0 = c0 < cols ? nrm[c_first + c0] : F::far();
+            const Num nc1 = c0 + 32 < cols ? nrm[c_first + c0 + 32] : F::far();
             auto stage = [&](int s) {
                 if (s + 1 < nst) fetch(tile, s + 1, buf ^ 1);
                 else if (next >= 0) fetch(next, 0, buf ^ 1);
@@ -955,8 +962,8 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
                 for (int x = lane; x < qn; x += kWave) {
                     const Hit h = hits[w][x];
                     const uint32_t rl = h.at >> 8;
-                    const int64_t gc = tile * kCB + (h.at & 255u);
-                    if (gc < n && gc != q0 + rl) {
+                    const int64_t lc = tile * kCB + (h.at & 255u), gc = c_first + lc;
+                    if (lc < cols && gc != q0 + rl) {
                         const uint32_t pos = atomicAdd(&cnt[rl], 1u);
                         lists[rl * kCap + pos] =
                             ((uint64_t)F::bits(h.part, nq[rl]) << 32) |
@@ -1568,30 +1575,65 @@ inline int64_t resident_blocks(int64_t rows) {
 }
 
 struct Lists {
+    int64_t resident;                   // blocks that run at a time
     uint32_t* ticket;
-    uint64_t *work, *cand;              // [resident blocks][kQB][kCap]; [rows][kp]
+    uint64_t *work, *cand;              // [resident][kQB][kCap]; [rows][kp]
     uint32_t *cnt, *thr;
 };
 
+// rows first .. of the batch against the candidates c_first .. c_first + cols
 template <typename F>
-hipError_t launch_candidates(const char* packed, int64_t n, int steps, const typename F::Num* nrm,
-                             float f, int64_t first, int64_t rows, int kp, const RowOrder& ord,
+hipError_t launch_candidates(const char* queries, const char* packed, int64_t n, int64_t c_first,
+                             int64_t cols, int steps, const typename F::Num* nrm, float f,
+                             int64_t first, int64_t rows, int kp, const RowOrder& ord,
                              const Lists& l, hipStream_t s) {
     const int64_t blocks = ord.turn ? ord.T * (ord.G / kQB) : ceil_div(rows, kQB);
-    const dim3 g((unsigned)resident_blocks(rows));
+    const dim3 g((unsigned)std::min(l.resident, blocks));
     const hipError_t e = hipMemsetAsync(l.ticket, 0, sizeof(uint32_t), s);
     if (e != hipSuccess) return e;
     // the queries' fragments stay in LDS while 8 steps of them fit beside two
     // stages (FP16: depth 128)
     if (steps <= 8)
-        k_knn_candidates<F, true><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, ord,
-                                                    (uint32_t)blocks, l.ticket, l.work, l.cand,
-                                                    l.cnt, l.thr);
+        k_knn_candidates<F, true><<<g, 512, 0, s>>>(queries, packed, n, c_first, cols, steps, nrm,
+                                                    f, first, kp, ord, (uint32_t)blocks, l.ticket,
+                                                    l.work, l.cand, l.cnt, l.thr);
     else
-        k_knn_candidates<F, false><<<g, 512, 0, s>>>(packed, n, steps, nrm, f, first, kp, ord,
-                                                     (uint32_t)blocks, l.ticket, l.work, l.cand,
-                                                     l.cnt, l.thr);
+        k_knn_candidates<F, false><<<g, 512, 0, s>>>(queries, packed, n, c_first, cols, steps, nrm,
+                                                     f, first, kp, ord, (uint32_t)blocks, l.ticket,
+                                                     l.work, l.cand, l.cnt, l.thr);
     return hipGetLastError();
+}
+
+// The kp best of a row's list and of its list from further candidates, one
+// wavefront per row: to `best`, with the number kept and the bits of a distance
+// that no row left out is nearer than.
+__global__ __launch_bounds__(256) void k_join_lists(int64_t rows, int kp,
+                                                    const uint64_t* __restrict__ more,
+                                                    const uint32_t* __restrict__ more_cnt,
+                                                    const uint32_t* __restrict__ more_thr,
+                                                    uint64_t* best, uint32_t* __restrict__ cnt,
+                                                    uint32_t* __restrict__ thr) {
+    __shared__ uint64_t both[256 / kWave][kCap];
+    const int lane = lane_id(), w = threadIdx.x >> 6;
+    const int64_t r = (int64_t)blockIdx.x * (256 / kWave) + w;
+    if (r >= rows) return;
+    const int a = (int)cnt[r], b = (int)more_cnt[r];        // at most kp each
+    for (int e = lane; e < a; e += kWave) both[w][e] = best[r * kp + e];
+    for (int e = lane; e < b; e += kWave) both[w][a + e] = more[r * kp + e];
+    __builtin_amdgcn_wave_barrier();
+    uint32_t end = thr[r] < more_thr[r] ? thr[r] : more_thr[r];
+    int m = a + b;
+    if (m < kp) {
+        for (int e = a + lane; e < m; e += kWave) best[r * kp + e] = both[w][e];
+    } else {
+        uint32_t last;
+        m = cut_list(both[w], m, kp, 0, best + r * kp, last);
+        end = last < end ? last : end;
+    }
+    if (lane == 0) {
+        cnt[r] = (uint32_t)m;
+        thr[r] = end;
+    }
 }
 
 // The order of the rows (see above): packs the rows in their own order, assigns
@@ -1719,18 +1761,34 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     return hipGetLastError();
 }
 
+// What a search holds at a time: the lists of `rows` queries, `cols` candidates
+// packed, working lists of `resident` blocks.
+struct Room {
+    int64_t rows, cols, resident;
+    // half of everything; false once there is nothing to halve
+    bool shrink() {
+        if (rows <= kQB && cols <= kCB && resident <= 1) return false;
+        rows = ceil_div(ceil_div(rows, 2), kQB) * kQB;
+        cols = ceil_div(ceil_div(cols, 2), kCB) * kCB;
+        resident = ceil_div(resident, 2);
+        return true;
+    }
+};
+
 template <typename X>
 hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx, double* d2,
                      hipStream_t s, std::string* err) {
     const int kp = (int)((int64_t)(k + kMargin) < n - 1 ? (k + kMargin) : (n - 1));
     // exact while 256^2 D fits an int32
     const bool exact = std::is_same<X, uint8_t>::value && D <= 32768;
-    const int64_t rows = n < kBatch ? n : kBatch;
     const int steps = exact ? pad_steps<PartsI8>(D) : pad_steps<PartsF16>(D);
+    auto bytes = [&](int64_t rows) {
+        return (int64_t)(exact ? packed_bytes<PartsI8>(rows, D) : packed_bytes<PartsF16>(rows, D));
+    };
     float* nrm = nullptr;
     int32_t* nrm_i = nullptr;
-    char* packed = nullptr;
-    Lists lists{};
+    char *packed = nullptr, *queries = nullptr;
+    Lists lists{}, more{};
     uint32_t* flag = nullptr;
     RowStats* st = nullptr;
     hipError_t e = hipSuccess;
@@ -1741,42 +1799,81 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
         held.release();
         return x;
     };
-    own.add(&lists.ticket, 1);
-    own.add(&lists.work, resident_blocks(rows) * (kQB * kCap));
-    own.add(&lists.cand, rows * kp);
-    own.add(&lists.cnt, rows);
-    own.add(&lists.thr, rows);
-    own.add(&packed, (int64_t)(exact ? packed_bytes<PartsI8>(n, D) : packed_bytes<PartsF16>(n, D)));
-    if (exact) {
-        own.add(&nrm_i, n);
-    } else {
-        own.add(&nrm, n);
-        own.add(&flag, n);
-        own.add(&st, 1);
+    // All rows are packed at once, 4 bytes an element (1 for bytes) of padded depth.
+    // Where there is no room for that, runs of candidates are packed in turn for
+    // each batch of queries and their lists joined; the rows keep their order then.
+    Room room{n < kBatch ? n : kBatch, n, 0};
+    room.resident = resident_blocks(room.rows);
+    for (;;) {
+        const bool whole = room.cols >= n;
+        own.add(&lists.ticket, 1);
+        own.add(&lists.work, room.resident * (kQB * kCap));
+        for (Lists* l : {&lists, &more}) {
+            if (l == &more && whole) break;
+            own.add(&l->cand, room.rows * kp);
+            own.add(&l->cnt, room.rows);
+            own.add(&l->thr, room.rows);
+        }
+        own.add(&packed, bytes(room.cols));
+        if (!whole) own.add(&queries, bytes(room.rows));
+        if (exact) {
+            own.add(&nrm_i, n);
+        } else {
+            own.add(&nrm, n);
+            own.add(&flag, n);
+            own.add(&st, 1);
+        }
+        if ((e = own.make()) == hipSuccess) break;
+        if (e != hipErrorOutOfMemory || !room.shrink()) return fail(e);
+        (void)hipGetLastError();
+        own.reset();
     }
-    if ((e = own.make()) != hipSuccess) return fail(e);
-    const int64_t np = pad_rows(n);
-    const dim3 gpack((unsigned)ceil_div(np * steps * 2, 256));
+    lists.resident = more.resident = room.resident;
+    more.ticket = lists.ticket;
+    more.work = lists.work;
+    const bool whole = room.cols >= n;
+    // the candidates of queries first .. first + m, by pack(rows, count, perm, to)
+    auto search = [&](auto parts, const auto* nrm_p, float f, int64_t first, int64_t m,
+                      auto&& pack) {
+        using F = decltype(parts);
+        if (whole)
+            return launch_candidates<F>(packed + bytes(kCB) / kCB * first, packed, n, 0, n, steps,
+                                        nrm_p, f, first, m, kp, ord, lists, s);
+        pack(first, m, nullptr, queries);
+        for (int64_t c = 0; c < n; c += room.cols) {
+            const int64_t cols = std::min(room.cols, n - c);
+            pack(c, cols, nullptr, packed);
+            const hipError_t x = launch_candidates<F>(queries, packed, n, c, cols, steps, nrm_p, f,
+                                                      first, m, kp, ord, c ? more : lists, s);
+            if (x != hipSuccess) return x;
+            if (c)
+                k_join_lists<<<dim3((unsigned)ceil_div(m, 256 / kWave)), 256, 0, s>>>(
+                    m, kp, more.cand, more.cnt, more.thr, lists.cand, lists.cnt, lists.thr);
+        }
+        return hipGetLastError();
+    };
     if (exact) {
         // uint8 rows: exact integer distances from INT8 MFMA
         k_row_norms_i8<<<dim3((unsigned)ceil_div(n, 4)), 256, 0, s>>>((const uint8_t*)Xm, n, D,
                                                                      nrm_i);
-        auto pack = [&](const uint32_t* perm) {
-            k_pack_i8<<<gpack, 256, 0, s>>>((const uint8_t*)Xm, n, np, D, steps, perm,
-                                            (uint4*)packed);
+        auto pack = [&](int64_t first, int64_t count, const uint32_t* perm, char* to) {
+            const int64_t np = pad_rows(count);
+            k_pack_i8<<<dim3((unsigned)ceil_div(np * steps * 2, 256)), 256, 0, s>>>(
+                (const uint8_t*)Xm + first * D, count, np, D, steps, perm, (uint4*)to);
         };
+        auto pack_all = [&](const uint32_t* perm) { pack(0, n, perm, packed); };
         // the distances' halves reach 2^30: as floats they are off by 2^7
         const int32_t* nrm_p = nrm_i;
-        if (n >= kOrderFrom)
+        if (whole && n >= kOrderFrom)
             e = order_rows<X, PartsI8, CenterI8>(Xm, n, D, steps, 0.f, 1.f, 128.f, nrm_i,
-                                                 16384.f * D, packed, pack, &held, s, &ord, &nrm_p);
-        else
-            pack(nullptr);
+                                                 16384.f * D, packed, pack_all, &held, s, &ord,
+                                                 &nrm_p);
+        else if (whole)
+            pack_all(nullptr);
         if (e != hipSuccess) return fail(e);
-        for (int64_t first = 0; first < n; first += kBatch) {
-            const int64_t m = n - first < kBatch ? n - first : kBatch;
-            e = launch_candidates<PartsI8>(packed, n, steps, nrm_p, 0.f, first, m, kp, ord, lists, s);
-            if (e != hipSuccess) return fail(e);
+        for (int64_t first = 0; first < n; first += room.rows) {
+            const int64_t m = std::min(room.rows, n - first);
+            if ((e = search(PartsI8{}, nrm_p, 0.f, first, m, pack)) != hipSuccess) return fail(e);
             k_knn_emit<<<dim3((unsigned)m), 256, 0, s>>>(lists.cand, kp, lists.cnt, first, k,
                                                          ord.perm, idx, d2);
         }
@@ -1803,26 +1900,28 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     if (entry_max > 0.f) (void)frexpf(entry_max, &ex);
     const int sh = 15 - ex < -60 ? -60 : (15 - ex > 60 ? 60 : 15 - ex);
     const float scale = ldexpf(1.f, sh), f = ldexpf(-2.f, -2 * sh);
-    auto pack = [&](const uint32_t* perm) {
-        k_pack_f16<X><<<gpack, 256, 0, s>>>(Xm, n, np, D, steps, scale, perm, (_Float16*)packed);
+    auto pack = [&](int64_t first, int64_t count, const uint32_t* perm, char* to) {
+        const int64_t np = pad_rows(count);
+        k_pack_f16<X><<<dim3((unsigned)ceil_div(np * steps * 2, 256)), 256, 0, s>>>(
+            Xm + first * D, count, np, D, steps, scale, perm, (_Float16*)to);
     };
+    auto pack_all = [&](const uint32_t* perm) { pack(0, n, perm, packed); };
     const float* nrm_p = nrm;
-    if (n >= kOrderFrom) {
+    if (whole && n >= kOrderFrom) {
         // the error bound of k_knn_rerank for any two rows; a centre's norm is no
         // larger than the largest row's, but for its rounding to 11 bits
         const double sum = 2.0 * sqrt((double)norm_max) * (1.0 + 0x1.0p-10);
         const double err = 1.01 * ((1.5 * D + 16.0) * 0x1.0p-24 * sum * sum +
                                    2.0 * sqrt((double)D) * sum * (0x1.0p-14 / (double)scale));
         e = order_rows<X, PartsF16, CenterF16>(Xm, n, D, steps, f, scale, (float)(1.001 * err), nrm,
-                                               norm_max, packed, pack, &held, s, &ord, &nrm_p);
-    } else {
-        pack(nullptr);
+                                               norm_max, packed, pack_all, &held, s, &ord, &nrm_p);
+    } else if (whole) {
+        pack_all(nullptr);
     }
     if (e != hipSuccess) return fail(e);
-    for (int64_t first = 0; first < n; first += kBatch) {
-        const int64_t m = n - first < kBatch ? n - first : kBatch;
-        e = launch_candidates<PartsF16>(packed, n, steps, nrm_p, f, first, m, kp, ord, lists, s);
-        if (e != hipSuccess) return fail(e);
+    for (int64_t first = 0; first < n; first += room.rows) {
+        const int64_t m = std::min(room.rows, n - first);
+        if ((e = search(PartsF16{}, nrm_p, f, first, m, pack)) != hipSuccess) return fail(e);
         k_knn_rerank<X><<<dim3((unsigned)m), 256, 0, s>>>(Xm, first, D, k, ord.perm, lists.cand, kp,
                                                           lists.cnt, lists.thr, nrm, norm_max,
                                                           scale, idx, d2, flag);
