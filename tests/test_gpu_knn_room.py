@@ -10,6 +10,18 @@ pytestmark = pytest.mark.gpu
 MB = 1 << 20
 
 
+@pytest.fixture(scope="module", autouse=True)
+def most_memory_taken():
+    """All but 4 GB of the device's memory held, in pieces, while the module runs."""
+    torch.cuda.empty_cache()
+    hold = []
+    while (left := torch.cuda.mem_get_info()[0] - 4096 * MB) > 2 * MB:
+        hold.append(torch.empty(min(left, 1 << 34), dtype=torch.uint8, device="cuda"))
+    yield
+    del hold
+    torch.cuda.empty_cache()
+
+
 def _rows(n, D, x, g):
     lab = torch.randint(0, 9, (n,), device="cuda", generator=g)
     if x == "u8":
@@ -31,19 +43,16 @@ def test_short_of_memory(x, n, D, k, free):
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     idx, d2 = torch.empty_like(want), torch.empty_like(wd)
-    hold = []
+    torch.cuda.empty_cache()
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - free * MB, dtype=torch.uint8, device="cuda")
     try:
-        left = torch.cuda.mem_get_info()[0] - free * MB
-        while left > 2 * MB:
-            hold.append(torch.empty(min(left, 1 << 34), dtype=torch.uint8, device="cuda"))
-            left = torch.cuda.mem_get_info()[0] - free * MB
         L = pixelsne.load()
         rc = L.pixelsne_knn(pixelsne._ptr(X), n, D, pixelsne._X_TYPES[X.dtype], k,
                             pixelsne._ptr(idx), pixelsne._ptr(d2), pixelsne._stream())
         print("free MB", torch.cuda.mem_get_info()[0] // MB, "packed MB",
               n * D * (1 if x == "u8" and D <= 32768 else 4) // MB, flush=True)
     finally:
-        del hold
+        del rest
         torch.cuda.empty_cache()
     assert rc == 0, L.pixelsne_last_error()
     assert torch.equal(idx, want) and torch.equal(d2, wd)
