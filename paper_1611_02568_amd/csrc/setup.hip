@@ -1940,33 +1940,44 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
             return fail(e);
         uint32_t *cnt = nullptr, *mj = nullptr;
         double* md = nullptr;
-        const int64_t at_once = std::min((int64_t)miss.size(), (int64_t)kMissRows);
+        // the order's scratch is done with; short of memory fewer rows go at a time, and
+        // where not one has room all take the passes below
+        held.release();
+        int64_t at_once = std::min((int64_t)miss.size(), (int64_t)kMissRows);
         Arena found;
-        found.add(&cnt, (int64_t)miss.size());
-        found.add(&md, at_once * kMissCap);
-        found.add(&mj, at_once * kMissCap);
-        if ((e = found.make()) != hipSuccess) return fail(e);
         auto stop = [&](hipError_t x) {
             found.release();
             return fail(x);
         };
-        if ((e = hipMemsetAsync(cnt, 0, sizeof(uint32_t) * miss.size(), s)) != hipSuccess)
-            return stop(e);
-        const int64_t chunks = std::min(ceil_div(n, 256), (int64_t)1024);
-        for (int64_t r = 0; r < (int64_t)miss.size(); r += kMissRows) {
-            const int64_t m = std::min((int64_t)miss.size() - r, (int64_t)kMissRows);
-            k_miss_scan<X><<<dim3((unsigned)chunks, (unsigned)m), 256, 0, s>>>(
-                Xm, n, D, k, flag + r, d2, cnt + r, md, mj);
-            k_miss_sort<<<dim3((unsigned)m), 256, 0, s>>>(flag + r, k, cnt + r, md, mj, idx, d2);
+        for (; at_once > 0; at_once /= 2) {
+            found.add(&cnt, (int64_t)miss.size());
+            found.add(&md, at_once * kMissCap);
+            found.add(&mj, at_once * kMissCap);
+            if ((e = found.make()) == hipSuccess) break;
+            if (e != hipErrorOutOfMemory) return stop(e);
+            (void)hipGetLastError();
+            found.reset();
         }
-        std::vector<uint32_t> hc(miss.size());
-        if ((e = hipMemcpyAsync(hc.data(), cnt, sizeof(uint32_t) * hc.size(), hipMemcpyDeviceToHost,
-                                s)) != hipSuccess)
-            return stop(e);
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return stop(e);
-        size_t left = 0;
-        for (size_t r = 0; r < miss.size(); r++)
-            if (hc[r] > (uint32_t)kMissCap) miss[left++] = miss[r];
+        size_t left = miss.size();
+        if (at_once > 0) {
+            if ((e = hipMemsetAsync(cnt, 0, sizeof(uint32_t) * miss.size(), s)) != hipSuccess)
+                return stop(e);
+            const int64_t chunks = std::min(ceil_div(n, 256), (int64_t)1024);
+            for (int64_t r = 0; r < (int64_t)miss.size(); r += at_once) {
+                const int64_t m = std::min((int64_t)miss.size() - r, at_once);
+                k_miss_scan<X><<<dim3((unsigned)chunks, (unsigned)m), 256, 0, s>>>(
+                    Xm, n, D, k, flag + r, d2, cnt + r, md, mj);
+                k_miss_sort<<<dim3((unsigned)m), 256, 0, s>>>(flag + r, k, cnt + r, md, mj, idx, d2);
+            }
+            std::vector<uint32_t> hc(miss.size());
+            if ((e = hipMemcpyAsync(hc.data(), cnt, sizeof(uint32_t) * hc.size(), hipMemcpyDeviceToHost,
+                                    s)) != hipSuccess)
+                return stop(e);
+            if ((e = hipStreamSynchronize(s)) != hipSuccess) return stop(e);
+            left = 0;
+            for (size_t r = 0; r < miss.size(); r++)
+                if (hc[r] > (uint32_t)kMissCap) miss[left++] = miss[r];
+        }
         if (left > 0) {
             if ((e = hipMemcpyAsync(flag, miss.data(), sizeof(uint32_t) * left,
                                     hipMemcpyHostToDevice, s)) != hipSuccess)
