@@ -753,13 +753,21 @@ hipError_t mal_frags(pixelsne_mlp* m, uint16_t** p, int64_t rows, int64_t k) {
     return e == hipSuccess ? hipMemsetAsync(*p, 0, bytes, m->stream) : e;
 }
 
-// buffers of a forward pass over B rows
+// buffers of a forward pass over B rows: all of them, or those that were there
 hipError_t ensure_forward(pixelsne_mlp* m, int64_t B) {
     if (B <= m->cap_batch) return hipSuccess;
-    hipError_t e;
-    if ((e = mal_frags(m, &m->xp, B, m->d)) != hipSuccess) return e;
-    if ((e = mal_frags(m, &m->h1p, B, m->h1)) != hipSuccess) return e;
-    if ((e = mal(m, &m->h2b, 2 * (size_t)B * m->h2)) != hipSuccess) return e;
+    const size_t had = m->allocs.size();
+    uint16_t *xp = nullptr, *h1p = nullptr, *h2b = nullptr;
+    hipError_t e = mal_frags(m, &xp, B, m->d);
+    if (e == hipSuccess) e = mal_frags(m, &h1p, B, m->h1);
+    if (e == hipSuccess) e = mal(m, &h2b, 2 * (size_t)B * m->h2);
+    if (e != hipSuccess) {
+        for (; m->allocs.size() > had; m->allocs.pop_back()) (void)hipFree(m->allocs.back());
+        return e;
+    }
+    m->xp = xp;
+    m->h1p = h1p;
+    m->h2b = h2b;
     m->cap_batch = B;
     return hipSuccess;
 }
@@ -1206,9 +1214,14 @@ psne_status pixelsne_mlp_forward(pixelsne_mlp* m, const float* X, int64_t n, flo
         return PSNE_E_INVAL;
     }
     // rows per pass: whole rounds of 128 x 128 tiles, 140 MB of activations at
-    // 1,024 wide
-    const int64_t B = n < kForwardRows ? n : kForwardRows;
+    // 1,024 wide; fewer where there is no room for as many
+    int64_t B = n < kForwardRows ? n : kForwardRows;
     hipError_t e = ensure_forward(m, B);
+    while (e == hipErrorOutOfMemory && B > kTileRows) {
+        (void)hipGetLastError();
+        B = ceil_div(B, 2);
+        e = ensure_forward(m, B);
+    }
     const int steps = depth_steps(m->d);
     for (int64_t b0 = 0; b0 < n && e == hipSuccess; b0 += B) {
         const int Bn = (int)(n - b0 < B ? n - b0 : B);
