@@ -973,12 +973,26 @@ psne_status mlp_error(hipError_t e, const char* where) {
     return e == hipErrorOutOfMemory ? PSNE_E_NOMEM : PSNE_E_DEVICE;
 }
 
-// He-normal weights of the three layers.  Flattened: with the generator out of
-// line 1.15 million weights take 78 ms, inline 46.
-__attribute__((flatten)) void initial_weights(float* th, uint64_t seed, const int64_t* off,
-                                              const int64_t* rows, const int64_t* cols) {
-    std::mt19937_64 rng(seed);
+// The generator of the initial weights.  Its steps are inlined, and as a type of this
+// file's own it has the distribution's code inlined beside them: 1.15 million weights
+// take 12 ms.  As shared functions of the C++ library they took 45 ms or 78, which of
+// the two hung on where the linker put them.
+struct WeightRng {
+    using result_type = std::mt19937_64::result_type;
+    std::mt19937_64 rng;
+    static constexpr result_type min() { return std::mt19937_64::min(); }
+    static constexpr result_type max() { return std::mt19937_64::max(); }
+    __attribute__((always_inline)) result_type operator()() {
+        [[clang::always_inline]] return rng();
+    }
+};
+
+// He-normal weights of the three layers
+__attribute__((noinline)) void initial_weights(float* th, uint64_t seed, const int64_t* off,
+                                               const int64_t* rows, const int64_t* cols) {
+    WeightRng rng{std::mt19937_64(seed)};
     std::normal_distribution<float> nd(0.f, 1.f);
+#pragma clang loop unroll(disable)
     for (int l = 0; l < 3; l++) {
         const float sc = sqrtf(2.f / (float)rows[l]);
         float* w = th + off[l];
