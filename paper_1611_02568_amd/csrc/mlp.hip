@@ -18,6 +18,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <random>
 #include <string>
 #include <vector>
@@ -777,6 +778,11 @@ int splits_for(int64_t K) {
     return s < 1 ? 1 : (s > 16 ? 16 : s);
 }
 
+// weight-gradient elements of one batch slice
+int64_t slice_len(const pixelsne_mlp* m) {
+    return (int64_t)m->h1 * m->h2 + (int64_t)m->d * m->h1;
+}
+
 // and of a training batch of B rows; the orders by columns are laid out for
 // their batch, so another size starts from zeroed ones
 hipError_t ensure_train(pixelsne_mlp* m, int64_t B) {
@@ -806,10 +812,16 @@ hipError_t ensure_train(pixelsne_mlp* m, int64_t B) {
                 return e;
         m->train_steps = depth_steps(B);
     }
-    const int64_t need = splits_for(B) * ((int64_t)m->h1 * m->h2 + (int64_t)m->d * m->h1);
-    if (need > m->splitk_len) {
-        if ((e = mal(m, &m->splitk, 4 * (size_t)need)) != hipSuccess) return e;
-        m->splitk_len = need;
+    // partials for as many batch slices as there is room for, at least one
+    const int64_t slice = slice_len(m);
+    for (int64_t splits = splits_for(B); splits * slice > m->splitk_len; splits /= 2) {
+        e = mal(m, &m->splitk, 4 * (size_t)(splits * slice));
+        if (e == hipSuccess) {
+            m->splitk_len = splits * slice;
+            break;
+        }
+        if (e != hipErrorOutOfMemory || splits == 1) return e;
+        (void)hipGetLastError();
     }
     if (!m->part &&
         (e = mal(m, &m->part, 4 * (size_t)kSlices * (m->h1 + 3 * (int64_t)m->h2 + 2))) != hipSuccess)
@@ -910,7 +922,8 @@ hipError_t grad_batch(pixelsne_mlp* m, int Bn, double* lossp, FinishArgs& fin) {
     g.h2 = m->h2;
     g.Bn = Bn;
     g.sq = sq;
-    g.slice_steps = (int)ceil_div(ceil_div(Bn, splits_for(Bn)), 32);
+    const int64_t splits = std::min((int64_t)splits_for(Bn), m->splitk_len / slice_len(m));
+    g.slice_steps = (int)ceil_div(ceil_div(Bn, splits), 32);
     g.slices = (int)ceil_div(Bn, 32 * (int64_t)g.slice_steps);
     g.pw2 = m->splitk;
     g.pw1 = m->splitk + (int64_t)g.slices * m->h1 * m->h2;
