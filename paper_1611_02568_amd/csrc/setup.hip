@@ -777,6 +777,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
                                                         float f, int64_t q_first, int kp,
                                                         RowOrder ord, uint32_t blocks,
                                                         uint32_t* __restrict__ ticket,
+                                                        unsigned long long* __restrict__ met,
                                                         uint64_t* __restrict__ work,
                                                         uint64_t* __restrict__ cand,
                                                         uint32_t* __restrict__ cand_cnt,
@@ -902,8 +903,10 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
         fetch(tile, 0, 0);
         settle();
         int buf = 0;
+        uint32_t swept = 0;
         for (bool begun = false; tile >= 0; tile = next, begun = true) {
             next = next_tile();
+            swept++;
             typename F::Acc acc[2][2];
 #pragma unroll
             for (int a = 0; a < 2; a++)
@@ -1017,6 +1020,7 @@ __global__ __launch_bounds__(512) void k_knn_candidates(const char* __restrict__
             if (qn > 0) drain();
         }
         settle();
+        if (list && t == 0) atomicAdd(met, (unsigned long long)swept);
         // the kp best of each row
         for (int q = 16 * w; q < 16 * w + 16; q++) {
             if (q0 + q >= n) break;
@@ -1577,6 +1581,7 @@ inline int64_t resident_blocks(int64_t rows) {
 struct Lists {
     int64_t resident;                   // blocks that run at a time
     uint32_t* ticket;
+    unsigned long long* met;            // tiles that blocks with an order met
     uint64_t *work, *cand;              // [resident][kQB][kCap]; [rows][kp]
     uint32_t *cnt, *thr;
 };
@@ -1596,11 +1601,11 @@ hipError_t launch_candidates(const char* queries, const char* packed, int64_t n,
     if (steps <= 8)
         k_knn_candidates<F, true><<<g, 512, 0, s>>>(queries, packed, n, c_first, cols, steps, nrm,
                                                     f, first, kp, ord, (uint32_t)blocks, l.ticket,
-                                                    l.work, l.cand, l.cnt, l.thr);
+                                                    l.met, l.work, l.cand, l.cnt, l.thr);
     else
         k_knn_candidates<F, false><<<g, 512, 0, s>>>(queries, packed, n, c_first, cols, steps, nrm,
                                                      f, first, kp, ord, (uint32_t)blocks, l.ticket,
-                                                     l.work, l.cand, l.cnt, l.thr);
+                                                     l.met, l.work, l.cand, l.cnt, l.thr);
     return hipGetLastError();
 }
 
@@ -1761,6 +1766,11 @@ hipError_t order_rows(const X* Xm, int64_t n, int D, int steps, float f, float s
     return hipGetLastError();
 }
 
+// What the thread's last exact search did: groups of the rows' order (0: none was
+// taken), tiles of kQB x kCB met by it, and tiles of all pairs.
+struct SearchTrace { int64_t groups, met, all; };
+thread_local SearchTrace g_trace;
+
 // What a search holds at a time: the lists of `rows` queries, `cols` candidates
 // packed, working lists of `resident` blocks.
 struct Room {
@@ -1807,6 +1817,7 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     for (;;) {
         const bool whole = room.cols >= n;
         own.add(&lists.ticket, 1);
+        own.add(&lists.met, 1);
         own.add(&lists.work, room.resident * (kQB * kCap));
         for (Lists* l : {&lists, &more}) {
             if (l == &more && whole) break;
@@ -1830,8 +1841,16 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     }
     lists.resident = more.resident = room.resident;
     more.ticket = lists.ticket;
+    more.met = lists.met;
     more.work = lists.work;
     const bool whole = room.cols >= n;
+    g_trace = SearchTrace{0, 0, ceil_div(n, kQB) * ceil_div(n, kCB)};
+    auto trace = [&]() {         // after the launches, before a synchronisation
+        g_trace.groups = ord.order ? ord.T : 0;
+        return ord.order ? hipMemcpyAsync(&g_trace.met, lists.met, sizeof(*lists.met),
+                                          hipMemcpyDeviceToHost, s)
+                         : hipSuccess;
+    };
     // the candidates of queries first .. first + m, by pack(rows, count, perm, to)
     auto search = [&](auto parts, const auto* nrm_p, float f, int64_t first, int64_t m,
                       auto&& pack) {
@@ -1870,6 +1889,7 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
                                                  &nrm_p);
         else if (whole)
             pack_all(nullptr);
+        if (e == hipSuccess && ord.order) e = hipMemsetAsync(lists.met, 0, sizeof(*lists.met), s);
         if (e != hipSuccess) return fail(e);
         for (int64_t first = 0; first < n; first += room.rows) {
             const int64_t m = std::min(room.rows, n - first);
@@ -1878,6 +1898,7 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
                                                          ord.perm, idx, d2);
         }
         if ((e = hipGetLastError()) != hipSuccess) return fail(e);
+        if ((e = trace()) != hipSuccess) return fail(e);
         return fail(hipStreamSynchronize(s));
     }
     if ((e = hipMemsetAsync(st, 0, sizeof(RowStats), s)) != hipSuccess) return fail(e);
@@ -1918,6 +1939,7 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     } else if (whole) {
         pack_all(nullptr);
     }
+    if (e == hipSuccess && ord.order) e = hipMemsetAsync(lists.met, 0, sizeof(*lists.met), s);
     if (e != hipSuccess) return fail(e);
     for (int64_t first = 0; first < n; first += room.rows) {
         const int64_t m = std::min(room.rows, n - first);
@@ -1927,6 +1949,7 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
                                                           scale, idx, d2, flag);
     }
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
+    if ((e = trace()) != hipSuccess) return fail(e);
     std::vector<uint32_t> hf(n);
     if ((e = hipMemcpyAsync(hf.data(), flag, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, s)) != hipSuccess)
         return fail(e);
@@ -2207,3 +2230,10 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
 }
 
 }  // namespace psne
+
+// For the tests, which cannot see from the lists whether tiles were left out.
+extern "C" void psne_knn_trace(int64_t* groups, int64_t* met, int64_t* all) {
+    *groups = psne::g_trace.groups;
+    *met = psne::g_trace.met;
+    *all = psne::g_trace.all;
+}
