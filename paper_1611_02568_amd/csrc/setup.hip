@@ -264,13 +264,13 @@ template <typename F> inline size_t packed_bytes(int64_t n, int D) {
     return (size_t)(pad_rows(n) / 32) * pad_steps<F>(D) * F::kParts * 1024;
 }
 
-// One thread per 16-byte piece of the hi (and lo) fragments.
+// One thread per 16-byte piece of the hi (and lo) fragments, from piece `first` on.
 template <typename X>
 __global__ __launch_bounds__(256) void k_pack_f16(const X* __restrict__ Xm, int64_t n, int64_t np,
                                                   int D, int steps, float scale,
-                                                  const uint32_t* __restrict__ perm,
+                                                  const uint32_t* __restrict__ perm, int64_t first,
                                                   _Float16* __restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t e = first + (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= np * steps * 2) return;
     const int lane = (int)(e & 63);
     const int64_t f = e >> 6;                               // [32 rows][step]
@@ -291,9 +291,9 @@ __global__ __launch_bounds__(256) void k_pack_f16(const X* __restrict__ Xm, int6
 
 __global__ __launch_bounds__(256) void k_pack_i8(const uint8_t* __restrict__ Xm, int64_t n,
                                                  int64_t np, int D, int steps,
-                                                 const uint32_t* __restrict__ perm,
+                                                 const uint32_t* __restrict__ perm, int64_t first,
                                                  uint4* __restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t e = first + (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= np * steps * 2) return;
     const int lane = (int)(e & 63);
     const int64_t f = e >> 6;
@@ -1851,6 +1851,14 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
                                           hipMemcpyDeviceToHost, s)
                          : hipSuccess;
     };
+    // launch(first, blocks) over the pieces of np packed rows; a grid holds fewer than
+    // 2^32 threads, which a packed copy of 64 GB would pass
+    auto by_pieces = [&](int64_t np, auto&& launch) {
+        constexpr int64_t kRun = (int64_t)1 << 26;
+        const int64_t all = np * steps * 2;
+        for (int64_t e0 = 0; e0 < all; e0 += kRun)
+            launch(e0, dim3((unsigned)ceil_div(std::min(kRun, all - e0), 256)));
+    };
     // the candidates of queries first .. first + m, by pack(rows, count, perm, to)
     auto search = [&](auto parts, const auto* nrm_p, float f, int64_t first, int64_t m,
                       auto&& pack) {
@@ -1877,8 +1885,10 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
                                                                      nrm_i);
         auto pack = [&](int64_t first, int64_t count, const uint32_t* perm, char* to) {
             const int64_t np = pad_rows(count);
-            k_pack_i8<<<dim3((unsigned)ceil_div(np * steps * 2, 256)), 256, 0, s>>>(
-                (const uint8_t*)Xm + first * D, count, np, D, steps, perm, (uint4*)to);
+            by_pieces(np, [&](int64_t e0, dim3 g) {
+                k_pack_i8<<<g, 256, 0, s>>>((const uint8_t*)Xm + first * D, count, np, D, steps,
+                                            perm, e0, (uint4*)to);
+            });
         };
         auto pack_all = [&](const uint32_t* perm) { pack(0, n, perm, packed); };
         // the distances' halves reach 2^30: as floats they are off by 2^7
@@ -1923,8 +1933,10 @@ hipError_t knn_typed(const X* Xm, int64_t n, int32_t D, int32_t k, int32_t* idx,
     const float scale = ldexpf(1.f, sh), f = ldexpf(-2.f, -2 * sh);
     auto pack = [&](int64_t first, int64_t count, const uint32_t* perm, char* to) {
         const int64_t np = pad_rows(count);
-        k_pack_f16<X><<<dim3((unsigned)ceil_div(np * steps * 2, 256)), 256, 0, s>>>(
-            Xm + first * D, count, np, D, steps, scale, perm, (_Float16*)to);
+        by_pieces(np, [&](int64_t e0, dim3 g) {
+            k_pack_f16<X><<<g, 256, 0, s>>>(Xm + first * D, count, np, D, steps, scale, perm, e0,
+                                            (_Float16*)to);
+        });
     };
     auto pack_all = [&](const uint32_t* perm) { pack(0, n, perm, packed); };
     const float* nrm_p = nrm;
