@@ -1491,8 +1491,8 @@ __global__ __launch_bounds__(256) void k_sym_count(const int32_t* __restrict__ i
     if (lane == 0) ucnt[i] = (int64_t)k + (b - a) - both;
 }
 
-// One row per block: k <= 256 out-edges, any number of in-edges.
-__global__ __launch_bounds__(256) void k_sym_row(const int32_t* __restrict__ idx,
+// One row per block, from row `first` on: k <= 256 out-edges, any number of in-edges.
+__global__ __launch_bounds__(256) void k_sym_row(int64_t first, const int32_t* __restrict__ idx,
                                                  const double* __restrict__ Pc,
                                                  const int64_t* __restrict__ start,
                                                  const uint32_t* __restrict__ edge, int k,
@@ -1503,7 +1503,7 @@ __global__ __launch_bounds__(256) void k_sym_row(const int32_t* __restrict__ idx
     __shared__ uint32_t sorted[256];
     __shared__ uint32_t both[257];          // sorted targets that are in-edges too, before each
     __shared__ uint32_t wsum[4];
-    const int64_t i = blockIdx.x;
+    const int64_t i = first + blockIdx.x;
     const int t = threadIdx.x, w = t >> 6, lane = lane_id();
     const int64_t a = start[i], b = start[i + 1], o = rp[i];
     const uint32_t uk = (uint32_t)k;
@@ -2229,8 +2229,11 @@ hipError_t symmetrize(const int32_t* idx, const double* Pc, int64_t n, int32_t k
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&col, 4 * (nnz > 0 ? nnz : 1))) != hipSuccess) return fail(e);
     if ((e = hipMalloc(&val, 8 * (nnz > 0 ? nnz : 1))) != hipSuccess) return fail(e);
-    k_sym_row<<<dim3((unsigned)n), 256, 0, s>>>(idx, Pc, start, edge[at], k, rp,
-                                                1.0 / (2.0 * (double)n), col, val);
+    // a grid holds fewer than 2^32 threads
+    constexpr int64_t kRun = (int64_t)1 << 22;
+    for (int64_t i = 0; i < n; i += kRun)
+        k_sym_row<<<dim3((unsigned)std::min(kRun, n - i)), 256, 0, s>>>(
+            i, idx, Pc, start, edge[at], k, rp, 1.0 / (2.0 * (double)n), col, val);
     if ((e = hipGetLastError()) != hipSuccess) return fail(e);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e);
     own.release();
