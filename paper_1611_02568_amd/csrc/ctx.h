@@ -127,7 +127,6 @@ void set_error(const std::string& msg);
 psne_status device_error(pixelsne_ctx* c, hipError_t e, const char* where);
 bool is_device_ptr(const void* p);
 
-// iteration passes (iter.hip); each enqueues on c->stream
 // Several arrays in one device allocation: add() them all, then make().  An
 // allocation and its release cost 30 to 250 us each whatever their size.
 class Arena {
@@ -162,6 +161,7 @@ private:
     void* base_ = nullptr;
 };
 
+// iteration passes (iter.hip); each enqueues on c->stream
 hipError_t run_snap(pixelsne_ctx* c);
 hipError_t run_sort(pixelsne_ctx* c);
 // the data-driven tree (dtree.hip): snap with 64-bit grid keys, their sort,

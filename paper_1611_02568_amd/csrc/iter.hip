@@ -1,13 +1,16 @@
 // Per-iteration passes of PixelSNE on gfx950 (wave64).
 //
-//   snap        pending screen scaling (Section 4.2) + pixel (Eq. 1-2) + Morton key
-//   sort        stable LSD radix sort of (key, index), 8-bit digits, LDS ranking
+//   snap        pending screen scaling (Section 4.2) + pixel (Eq. 1-2) + Morton key,
+//               and the first digit's counts for the sort
+//   sort        stable LSD radix sort of (key, index), digits of up to 11 bits, LDS
+//               ranking
 //   tree        P-Quadtree (Section 4.1) as a linear tree: one node per occupied
 //               (level, Morton prefix); counts and FP64 coordinate sums (Eq. 8)
 //               reduced bottom-up, up to five levels per launch
 //   traverse    Barnes-Hut repulsion (Eq. 5, 11, 12): one wavefront walks the
 //               union of the interaction lists of 64 Morton-consecutive points,
-//               each stack entry carrying the mask of lanes still descending
+//               each stack entry carrying the mask of lanes still descending; or,
+//               for fewer points, four or eight wavefronts share that walk
 //   zsum        Z = sum_i Z_i in FP64, fixed order
 //   attract     row sums of the sparse attraction over CSR P (Eq. 5), on a
 //               second stream beside the traversal and Z (and beside sort and
@@ -1703,10 +1706,11 @@ StepParams step_params(const pixelsne_ctx* c, double alpha) {
 
 int64_t point_block_count(int64_t n) { return point_blocks(n); }
 
-// Blocks of 512 threads give 70,000 points 35 tiles, of 1,024 only 18: an
-// iteration takes 235 us with the former and 242 with the latter.  At a million
-// points the halves of a larger tile's scan rows count for more: 1,207 us with
-// 1,024 threads, 1,224 with 512.
+// Blocks of 512 threads give 70,000 points 35 tiles, of 1,024 only 18, whose scan
+// rows are half as long.  An iteration (late, FP32 / FP64) with 512 and with 1,024:
+// 30,000 points 171 and 178 / 188 and 193 us, 70,000 222 and 227 / 264 and 269,
+// 200,000 355 and 369 / 456 and 467, 262,144 418 and 420 / 544 and 547; from there
+// on they differ by less than 0.5%, the larger ahead at a million (1,017 and 1,014).
 static SortPlan sort_plan(int64_t n, int bits) {
     SortPlan p;
     p.passes = (int)ceil_div(bits, kRsMaxBits);
@@ -1860,12 +1864,14 @@ void launch_traverse_shared(pixelsne_ctx* c, double th2, uint32_t* visits, uint3
 // 1,024 / 953; 700,000: 1,454 / 1,409; 800,000: 1,567 / 1,585; 1,000,000: 1,868 /
 // 1,945.
 // The data-driven tree's 33 levels do not fit the shared walk's stack.
-// FP32 walks alone while the early exaggeration lasts: sharing adds the terms
-// in another order, and the first iterations, in which the embedding spreads
-// from a point and the gains turn on signs, make of those last bits up to 6e-4
-// of the positions and 0.09 of a coordinate after ten of them (900 drawn
-// problems of up to 60,000 points, 43 past 8e-4); of 600 drawn after it none
-// passed 1.5e-6 and 1.3e-4.  It costs these iterations 0.1 ms each (30,000
+// FP32 walks alone while the early exaggeration lasts, so that its iterations keep
+// the bits that one order of the sums gives whatever n is: sharing adds the terms in
+// another order, and the first iterations, in which the embedding spreads from a
+// point and the gains turn on signs, make of those last bits up to 6e-4 of the
+// positions' norm after ten of them, and 0.09 of a coordinate (of the coordinates'
+// root mean square, if that is larger), the largest of 900 drawn problems of up to
+// 60,000 points.  Once it has ended the largest of 860 problems are 1.5e-5 and 8.0e-4,
+// of all but one 8.2e-6 and 5.1e-4.  It costs these iterations 0.1 ms each (30,000
 // points: 0.27 ms).
 int traverse_share(const pixelsne_ctx* c) {
     if (c->prm.tree == PSNE_TREE_DATA) return 0;

@@ -192,7 +192,11 @@ __device__ __forceinline__ int cut_list(const uint64_t* lst, int m, int kp, int 
 //
 // FP16: a row times the power of two `scale` is split into two halves of 11
 // bits each, x = hi + lo, and x.y = hi.hi + hi.lo + lo.hi up to 2^-22 per
-// product.
+// product.  The sums have fewer roundings than FP32 MFMA's, one depth of 2 after
+// another, so the distances are nearer to 64 bits than those: of all pairs of 2,048
+// rows of the mixture of 16 / 128 / 784 dimensions the errors' root mean squares are
+// 3.8e-5 / 4.3e-4 / 6.3e-3, of the FP32 unit 4.5e-5 / 6.9e-4 / 1.0e-2 (a fourth
+// product, lo.lo: 3.6e-5 / 4.3e-4 / 6.3e-3).
 struct PartsF16 {
     using Vec = _Float16 __attribute__((ext_vector_type(8)));
     using Acc = float __attribute__((ext_vector_type(16)));
