@@ -19,6 +19,7 @@ void set_error(const std::string& msg) { g_err = msg; }
 
 psne_status device_error(pixelsne_ctx* c, hipError_t e, const char* where) {
     if (c) c->poisoned = true;
+    (void)hipGetLastError();     // the status reports it: nobody else's next call should
     set_error(std::string(where) + ": " + hipGetErrorString(e));
     return e == hipErrorOutOfMemory ? PSNE_E_NOMEM : PSNE_E_DEVICE;
 }

@@ -982,6 +982,7 @@ hipError_t adam_update(pixelsne_mlp* m, FinishArgs a, float lr) {
 }
 
 psne_status mlp_error(hipError_t e, const char* where) {
+    (void)hipGetLastError();     // the status reports it: nobody else's next call should
     set_error(std::string(where) + ": " + hipGetErrorString(e));
     return e == hipErrorOutOfMemory ? PSNE_E_NOMEM : PSNE_E_DEVICE;
 }

@@ -871,6 +871,7 @@ psne_status invalid3(const std::string& m) {
 
 psne_status dev_error3(pixelsne3_ctx* c, hipError_t e, const char* where) {
     if (c) c->poisoned = true;
+    (void)hipGetLastError();     // the status reports it: nobody else's next call should
     set_error(std::string(where) + ": " + hipGetErrorString(e));
     return e == hipErrorOutOfMemory ? PSNE_E_NOMEM : PSNE_E_DEVICE;
 }
