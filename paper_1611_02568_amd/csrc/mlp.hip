@@ -1170,7 +1170,7 @@ psne_status pixelsne_mlp_train(pixelsne_mlp* m, const float* X, const float* Y01
     if (e == hipSuccess) e = ensure_loss(m, nbatch * nl);
     if (e == hipSuccess && m->order_len < n) {
         e = mal(m, &m->order, 4 * (size_t)n);
-        m->order_len = n;
+        if (e == hipSuccess) m->order_len = n;
     }
     if (e != hipSuccess) return mlp_error(e, "mlp_train");
     std::vector<uint32_t> ord(n);
