@@ -1177,7 +1177,7 @@ psne_status pixelsne_mlp_train(pixelsne_mlp* m, const float* X, const float* Y01
     for (int64_t i = 0; i < n; i++) ord[i] = (uint32_t)i;
     std::mt19937_64 rng(m->seed ^ 0x5DEECE66DULL);
     double epoch_loss = 0.0;
-    for (int32_t ep = 0; ep < epochs; ep++) {
+    for (int32_t ep = 0; ep < epochs && e == hipSuccess; ep++) {
         std::shuffle(ord.begin(), ord.end(), rng);
         e = hipMemcpyAsync(m->order, ord.data(), 4 * (size_t)n, hipMemcpyHostToDevice, m->stream);
         if (e != hipSuccess) return mlp_error(e, "mlp_train");
